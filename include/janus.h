@@ -156,11 +156,13 @@ janus_status janus_lstm_state_carry(const janus_lstm_desc* d, int32_t B_prev,
  *  timed_out         1 if any wait of the step ran out (forward or
  *                    backward: the backward keeps the forward's flag, and
  *                    its kernels then drain at once).
- *  bwd_groups        backward unit groups launched by the last backward
- *                    call, summed over layers (0 when the per-step kernels
- *                    ran, or before a backward).
+ *  bwd_groups        backward workgroup groups launched by the last backward
+ *                    call, summed over layers: unit groups of the kernels
+ *                    that slice the contraction, row groups of the kernels
+ *                    that give each group of rows to one XCD (0 when the
+ *                    per-step kernels ran, or before a backward).
  *  bwd_local_groups  of those, groups whose workgroups all ran on one XCD
- *                    and kept their partial sums in its L2.
+ *                    and exchanged their values through its L2.
  *  fwd_groups, fwd_local_groups  the same for the forward recurrence when
  *                    its contraction is split over the columns of Wh (0
  *                    otherwise).

@@ -36,6 +36,7 @@
 
 #include "device.hpp"
 #include "lstm_persist.hpp"
+#include "lstm_xcd.hpp"
 #include "ops.hpp"
 
 namespace janus {
@@ -69,6 +70,8 @@ struct LstmWs {
     int64_t ldht = 0;
     bf16_t* Hf = nullptr;               // [T + 1] slots of h in fragment layout (persistent forward)
     int64_t hf_slot = 0;                // elements per slot
+    void* ring = nullptr;               // operand slots of the row-group recurrence (lstm_xcd.hpp)
+    float* dbp = nullptr;               // its bias gradient sums, [row groups][4H]
     void* gs = nullptr;                 // contraction scratch (transposed operands, split-K partials)
     size_t gs_bytes = 0;
     int64_t ldh = 0, ldg = 0, ldk = 0;
@@ -128,6 +131,45 @@ int64_t persist_fwd_part_floats(const janus_lstm_desc& d, int ns) {
     if (ns <= 1) return 0;
     return persist_fwd_part_local(d, ns) +
            int64_t(d.T) * persist_straddle_slots() * ns * ns * ((d.B + 31) / 32) * 1024;
+}
+
+// ------------------------------------------ recurrence in row groups per XCD
+// Widest H whose weights (4H x H) fit the VGPRs of one XCD's workgroups: Q =
+// ceil(H / 256) up to 4 (bf16) and 2 (float32) units-of-8 per workgroup.
+int xcd_max_h(janus_dtype dt) { return dt == JANUS_BF16 ? 1024 : 512; }
+
+struct XcdPlan {
+    int Q = 0, RT = 0, nu = 0, blocks = 0;   // Q == 0: does not fit
+};
+
+// One launch works `rows` rows (at most 256) in groups of 16 RT.  A group is
+// nu = ceil(H / 8Q) workgroups on one XCD; one row tile per group while the
+// groups fit the chip (more XCDs share the work), else two.
+XcdPlan xcd_plan(const janus_lstm_desc& d, int rows) {
+    XcdPlan p;
+    const DeviceInfo info = device_info();
+    const int xccs = info.xccs > 0 && info.xccs <= persist::kMaxXcds ? info.xccs : 1;
+    const int per_xcd = info.cus / xccs;
+    if (d.H > xcd_max_h(d.dtype) || (d.dtype == JANUS_BF16 && d.H % 8 != 0)) return p;
+    const int Q = (d.H + 255) / 256;
+    p.nu = (d.H + 8 * Q - 1) / (8 * Q);
+    if (per_xcd < p.nu) return p;
+    const int room = xccs * (per_xcd / p.nu);
+    const int tiles = (rows + 15) / 16;
+    for (int rt : {1, 2}) {
+        const int groups = (tiles + rt - 1) / rt;
+        if (groups > room || groups > xcd::kMaxGroups) continue;
+        p.RT = rt;
+        p.blocks = xccs * p.nu * ((groups + xccs - 1) / xccs);
+        p.Q = Q;
+        return p;
+    }
+    return p;
+}
+
+bool env_is(const char* name, char v) {
+    const char* e = getenv(name);
+    return e && e[0] == v;
 }
 
 // Contraction scratch for every contraction of the forward and backward
@@ -194,6 +236,12 @@ size_t carve(const janus_lstm_desc& d, void* base, LstmWs& w) {
     w.act_dev = c.take<int32_t>(int64_t(d.T) + 1);
     w.off_dev = c.take<int32_t>(int64_t(d.T) + 2);
     w.sync = c.take<persist::Sync>(1);
+    if (d.H <= xcd_max_h(d.dtype)) {
+        // rows of the largest launch, rounded up to two 16-row tiles
+        const int64_t tiles = round_up((std::min(d.B, persist::kMaxB) + 15) / 16, 2);
+        w.ring = c.take<char>(xcd::kSlots * tiles * 16 * round_up(int64_t(4) * d.H, 32) * es);
+        w.dbp = c.take<float>(int64_t((d.B + 15) / 16) * 4 * d.H);
+    }
     if (d.dtype == JANUS_BF16) {
         // partial sums of the persistent backward, and of the forward (the two
         // never run at the same time)
@@ -285,17 +333,39 @@ int persist_bwd_slices(const janus_lstm_desc& d) {
     return 0;
 }
 
-// The persistent path needs bf16, H a multiple of 8, one co-resident
-// workgroup per slice and the weight slice in LDS; a batch of more than 256
-// rows runs in parts of 256 sorted rows, one launch each.  It can be
-// switched off with JANUS_PERSIST=0 (the per-step kernels then run).
+// The persistent path: for bf16, H a multiple of 8, one co-resident workgroup
+// per slice and the weight slice in LDS; for float32, what runs in row groups
+// per XCD and is not small enough for the one-workgroup kernels.  A batch of
+// more than 256 rows runs in parts of 256 sorted rows, one launch each.  It
+// can be switched off with JANUS_PERSIST=0 (the per-step kernels then run).
+bool use_small(const janus_lstm_desc& d);
 bool use_persistent(const janus_lstm_desc& d) {
-    const char* e = getenv("JANUS_PERSIST");
-    const bool env = !(e && e[0] == '0');
-    if (!env || d.dtype != JANUS_BF16 || d.H % 8 != 0) return false;
+    if (env_is("JANUS_PERSIST", '0')) return false;
     const DeviceInfo info = device_info();
     if (info.cus <= 0) return false;
+    if (d.dtype == JANUS_F32) return !use_small(d) && xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
+    if (d.dtype != JANUS_BF16 || d.H % 8 != 0) return false;
     return persist_fwd_slices(d) > 0 && persist_bwd_slices(d) > 0;
+}
+
+// Whether the forward / backward recurrence of the persistent path runs in
+// row groups per XCD: wherever it fits, since a step then waits on one L2
+// round trip instead of a device-wide barrier (H 1024, B 128: 1.25 against
+// 2.73 ms for both directions; H 512, B 33 forward: 0.24 against 0.52).  The
+// backward keeps the sliced kernels where the dG slot (B x 4H bf16) is 2 MB
+// and more, which among these sizes is H = 1024 with a full 256 rows.  Asking
+// for a slice count (JANUS_FWD_SLICES, JANUS_BWD_SLICES) asks for the sliced
+// kernels, and so does JANUS_XCD=0.
+bool use_xcd_fwd(const janus_lstm_desc& d) {
+    if (d.dtype == JANUS_F32) return true;
+    if (env_is("JANUS_XCD", '0') || getenv("JANUS_FWD_SLICES")) return false;
+    return xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
+}
+bool use_xcd_bwd(const janus_lstm_desc& d) {
+    if (d.dtype == JANUS_F32) return true;
+    if (env_is("JANUS_XCD", '0') || getenv("JANUS_BWD_SLICES")) return false;
+    if (int64_t(d.B) * 4 * d.H * 2 >= (int64_t(2) << 20)) return false;
+    return xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
 }
 
 __global__ void perm4_kernel(int H, int32_t* perm4) {
@@ -821,8 +891,7 @@ size_t small_bwd_lds(const janus_lstm_desc& d) {
 // slot and Wh (float32), the state and dG fit one workgroup's LDS.
 // JANUS_SMALL=0 switches it off.
 bool use_small(const janus_lstm_desc& d) {
-    const char* e = getenv("JANUS_SMALL");
-    if (e && e[0] == '0') return false;
+    if (env_is("JANUS_SMALL", '0')) return false;
     if (int64_t(d.B) * d.H > int64_t(kSmallThreads) * kSmallCells) return false;
     const size_t cap = device_lds(device_info());
     return small_fwd_lds(d) <= cap && small_bwd_lds(d) <= cap;
@@ -979,27 +1048,20 @@ double part_rows(const SeqSchedule& s, int rb) {
     return rows;
 }
 
-// Algorithmic bytes of one persistent launch over `rows` active rows: every
-// value the recurrence must read or write, counted once, plus the recurrent
-// weight (4H x H bf16) read once.
-//   forward, per row:  XG (4H bf16), h_{t-1} (H bf16), c_t (H fp32), the
-//                      gates (4H bf16), h_t for the next step (H bf16), and
-//                      the optional copies (h row-major, h transposed, y)
-//   backward, per row: the saved gates (4H bf16), c_{t-1} (H fp32), dy
-//                      (H bf16), dG_{t+1} (4H bf16), dG_t for the next step
-//                      (4H bf16), and the optional dG copies (transposed,
-//                      row-major)
-double fwd_persistent_bytes(const persist::FwdArgs& a, double rows) {
-    const double H = a.H;
-    const double per_row = (8.0 + 2.0 + 4.0 + 8.0 + 2.0) * H + (a.Hs ? 2.0 * H : 0.0) + (a.HT ? 2.0 * H : 0.0) +
-                           (a.y ? 2.0 * H : 0.0);
-    return rows * per_row + 8.0 * H * H;
+// Algorithmic bytes of one recurrence launch over `rows` active rows (es
+// bytes per element): every value the recurrence must read or write, counted
+// once, plus the recurrent weight (4H x H) read once.
+//   forward, per row:  XG (4H), h_{t-1} (H), c_t (H fp32), the gates (4H),
+//                      h_t for the next step (H), and the optional copies
+//                      (h row-major, h transposed, y)
+//   backward, per row: the saved gates (4H), c_{t-1} (H fp32), dy (H),
+//                      dG_{t+1} (4H), dG_t for the next step (4H), and the
+//                      optional dG copies (transposed, row-major)
+double fwd_recurrence_bytes(double H, double es, const void* Hs, const void* HT, const void* y, double rows) {
+    return rows * H * (4.0 + es * (10.0 + (Hs ? 1.0 : 0.0) + (HT ? 1.0 : 0.0) + (y ? 1.0 : 0.0))) + 4.0 * es * H * H;
 }
-double bwd_persistent_bytes(const persist::BwdArgs& a, double rows) {
-    const double H = a.H;
-    const double per_row = (8.0 + 4.0 + 8.0 + 8.0) * H + (a.dy ? 2.0 * H : 0.0) + (a.GT ? 8.0 * H : 0.0) +
-                           (a.G ? 8.0 * H : 0.0);
-    return rows * per_row + 8.0 * H * H;
+double bwd_recurrence_bytes(double H, double es, const void* dy, const void* GT, const void* G, double rows) {
+    return rows * H * (4.0 + es * (12.0 + (dy ? 1.0 : 0.0) + (GT ? 4.0 : 0.0) + (G ? 4.0 : 0.0))) + 4.0 * es * H * H;
 }
 
 // With equal lengths the persistent forward also writes h transposed (HT,
@@ -1007,31 +1069,98 @@ double bwd_persistent_bytes(const persist::BwdArgs& a, double rows) {
 // packed row (the dWh operand) and HT + B is the layer output transposed
 // (the next layer's dWx operand), both read in place (K = T B a multiple of 8).
 bool use_ht(const janus_lstm_desc& d, const SeqSchedule& s, bool persistent) {
-    return persistent && s.fixed && (int64_t(d.T) * d.B) % 8 == 0;
+    return persistent && d.dtype == JANUS_BF16 && s.fixed && (int64_t(d.T) * d.B) % 8 == 0;
 }
 
 // The persistent backward writes dG transposed itself when the padded tail of
 // each row (past the packed count, to a multiple of 8) needs no zeros.
-bool gt_by_kernel(const SeqSchedule& s, bool persistent) { return persistent && s.packed % 8 == 0; }
+bool gt_by_kernel(const janus_lstm_desc& d, const SeqSchedule& s, bool persistent) {
+    return persistent && d.dtype == JANUS_BF16 && s.packed % 8 == 0;
+}
 
-// One layer of the forward pass on the persistent path (bf16 only).
+// Launches of the row-group recurrence: kernel by (Q, RT), with its LDS limit.
+template <typename T, int Q, int RT>
+janus_status launch_fwd_xcd_as(const XcdPlan& p, const xcd::FwdArgs<T>& a, hipStream_t st) {
+    static size_t attr = 0;
+    return persistent_launch(xcd::lstm_fwd_xcd<T, Q, RT>, p.blocks, xcd::FwdCfg<Q, RT>::SMEM, a, st, attr);
+}
+template <typename T, int Q, int RT>
+janus_status launch_bwd_xcd_as(const XcdPlan& p, const xcd::BwdArgs<T>& a, hipStream_t st) {
+    static size_t attr = 0;
+    return persistent_launch(xcd::lstm_bwd_xcd<T, Q, RT>, p.blocks, xcd::BwdCfg<Q, RT>::SMEM, a, st, attr);
+}
+#define JANUS_XCD_CASES(T, FN)                                                     \
+    if (p.Q == 1) return p.RT == 1 ? FN<T, 1, 1>(p, a, st) : FN<T, 1, 2>(p, a, st); \
+    if (p.Q == 2) return p.RT == 1 ? FN<T, 2, 1>(p, a, st) : FN<T, 2, 2>(p, a, st);
+template <typename T>
+janus_status launch_fwd_xcd(const XcdPlan& p, const xcd::FwdArgs<T>& a, hipStream_t st) {
+    JANUS_XCD_CASES(T, launch_fwd_xcd_as)
+    if constexpr (sizeof(T) == 2) {
+        if (p.Q == 3) return p.RT == 1 ? launch_fwd_xcd_as<T, 3, 1>(p, a, st) : launch_fwd_xcd_as<T, 3, 2>(p, a, st);
+        if (p.Q == 4) return p.RT == 1 ? launch_fwd_xcd_as<T, 4, 1>(p, a, st) : launch_fwd_xcd_as<T, 4, 2>(p, a, st);
+    }
+    return JANUS_ERR_UNSUPPORTED;
+}
+template <typename T>
+janus_status launch_bwd_xcd(const XcdPlan& p, const xcd::BwdArgs<T>& a, hipStream_t st) {
+    JANUS_XCD_CASES(T, launch_bwd_xcd_as)
+    if constexpr (sizeof(T) == 2) {
+        if (p.Q == 3) return p.RT == 1 ? launch_bwd_xcd_as<T, 3, 1>(p, a, st) : launch_bwd_xcd_as<T, 3, 2>(p, a, st);
+        if (p.Q == 4) return p.RT == 1 ? launch_bwd_xcd_as<T, 4, 1>(p, a, st) : launch_bwd_xcd_as<T, 4, 2>(p, a, st);
+    }
+    return JANUS_ERR_UNSUPPORTED;
+}
+#undef JANUS_XCD_CASES
+
+// Steps each row group runs: those at which its first row is active.
+void xcd_steps(const SeqSchedule& s, int rbase, int rt, int groups, int32_t* steps) {
+    for (int g = 0; g < groups; ++g) {
+        const int row0 = rbase + 16 * rt * g;
+        // active[] does not increase: the first t with active[t] <= row0
+        const auto b = s.active.begin(), e = b + s.t_eff;
+        steps[g] = int32_t(std::partition_point(b, e, [&](int32_t v) { return v > row0; }) - b);
+    }
+}
+int xcd_groups(int rows, int rt) { return (rows + 16 * rt - 1) / (16 * rt); }
+
+// Initial state and operand slots of the row-group forward for rows rb + [0, kMaxB).
+template <typename T>
+janus_status fwd_init_xcd(const janus_lstm_desc& d, const SeqSchedule& s, const LstmWs& w, int l, int rb,
+                          const int32_t* perm, const float* h0, const float* c0, float* hT, float* cT, hipStream_t st) {
+    const int rows = std::min(d.B - rb, persist::kMaxB);
+    const XcdPlan p = xcd_plan(d, rows);
+    const int tiles = p.RT * xcd_groups(rows, p.RT);
+    const int nkg = int((d.H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
+    const int64_t n = int64_t(tiles) * 16 * nkg * xcd::Lay<T>::KG;
+    TraceScope trace("lstm_fwd_init", 0.0, double(rows) * d.H * (8.0 + 4.0 + sizeof(T)), st);
+    hipLaunchKernelGGL(xcd::fwd_init_kernel<T>, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 1024))), dim3(256), 0,
+                       st, d.B, d.H, w.ldh, rb, tiles, nkg, perm, h0, c0, static_cast<T*>(w.Hs[l]), w.Cs[l],
+                       s.active[0], hT, cT, use_ht(d, s, true) ? reinterpret_cast<T*>(w.HT[l]) : nullptr, w.ldht,
+                       static_cast<T*>(w.ring), w.sync);
+    JANUS_LAUNCH_CHECK();
+    return JANUS_OK;
+}
+
+// One layer of the forward pass on the persistent path.
+template <typename T>
 janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s, const LstmWs& w, int l,
                                   const void* x, const int32_t* xrow, const void* Wx, const void* Wh, const void* b,
-                                  const int32_t* perm, void* y, float* hT, float* cT, hipStream_t st) {
+                                  const int32_t* perm, const float* h0, const float* c0, void* y, float* hT, float* cT,
+                                  hipStream_t st) {
     const int H = d.H, B = d.B;
     const int Il = l == 0 ? d.I : H;
     const int64_t rows4 = int64_t(4) * H * Il;
     {
-        TraceScope trace("interleave_weights", 0.0, 4.0 * double(rows4 + 4 * H), st);
-        hipLaunchKernelGGL(interleave_rows_kernel<bf16_t>, dim3(unsigned((rows4 + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const bf16_t*>(Wx), static_cast<bf16_t*>(w.Wxi[l]), H, Il);
+        TraceScope trace("interleave_weights", 0.0, 2.0 * sizeof(T) * double(rows4 + 4 * H), st);
+        hipLaunchKernelGGL(interleave_rows_kernel<T>, dim3(unsigned((rows4 + 255) / 256)), dim3(256), 0, st,
+                           static_cast<const T*>(Wx), static_cast<T*>(w.Wxi[l]), H, Il);
         JANUS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(interleave_rows_kernel<bf16_t>, dim3(unsigned((4 * H + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const bf16_t*>(b), static_cast<bf16_t*>(w.bi[l]), H, 1);
+        hipLaunchKernelGGL(interleave_rows_kernel<T>, dim3(unsigned((4 * H + 255) / 256)), dim3(256), 0, st,
+                           static_cast<const T*>(b), static_cast<T*>(w.bi[l]), H, 1);
         JANUS_LAUNCH_CHECK();
     }
     GemmDesc g;
-    g.dtype = JANUS_BF16;
+    g.dtype = d.dtype;
     g.M = int(s.packed);
     g.N = 4 * H;
     g.K = Il;
@@ -1040,7 +1169,7 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
         g.lda = d.I;
         g.a_idx = xrow;
     } else {
-        g.A = static_cast<const bf16_t*>(w.Hs[l - 1]) + int64_t(B) * w.ldh;
+        g.A = static_cast<const T*>(w.Hs[l - 1]) + int64_t(B) * w.ldh;
         g.lda = w.ldh;
     }
     g.a_src_rows = int64_t(d.T) * B;
@@ -1054,6 +1183,48 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
     g.scratch_bytes = w.gs_bytes;
     janus_status e = gemm(g, st);
     if (e != JANUS_OK) return e;
+    if (use_xcd_fwd(d)) {
+        xcd::FwdArgs<T> a = {};
+        a.H = H;
+        a.B = B;
+        a.t_eff = s.t_eff;
+        a.fixed = s.fixed ? 1 : 0;
+        a.nkg = int((H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
+        a.force_remote = env_is("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+        a.active = w.act_dev;
+        a.offsets = w.off_dev;
+        a.perm = perm;
+        a.Wh = static_cast<const T*>(Wh);
+        a.Hs = static_cast<T*>(w.Hs[l]);
+        a.Cs = w.Cs[l];
+        a.XG = static_cast<const T*>(w.XG);
+        a.Gs = static_cast<T*>(w.Gs[l]);
+        a.y = static_cast<T*>(y);
+        a.hT = hT;
+        a.cT = cT;
+        a.ldh = w.ldh;
+        a.ldg = w.ldg;
+        a.HT = use_ht(d, s, true) ? reinterpret_cast<T*>(w.HT[l]) : nullptr;
+        if (l == d.L - 1 && a.HT) a.Hs = nullptr;   // as below
+        a.ldht = w.ldht;
+        a.ring = static_cast<T*>(w.ring);
+        a.sync = w.sync;
+        for (int rb = 0; rb < B; rb += persist::kMaxB) {
+            if (rb > 0 && (e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0, c0, hT, cT, st)) != JANUS_OK) return e;
+            const int rows = std::min(B - rb, persist::kMaxB);
+            const XcdPlan p = xcd_plan(d, rows);
+            a.rbase = rb;
+            a.nu = p.nu;
+            a.groups = xcd_groups(rows, p.RT);
+            xcd_steps(s, rb, p.RT, a.groups, a.steps);
+            const double work = part_rows(s, rb);
+            TraceScope trace("lstm_fwd_persistent", 2.0 * 4.0 * H * double(H) * work,
+                             fwd_recurrence_bytes(H, sizeof(T), a.Hs, a.HT, a.y, work), st);
+            if ((e = launch_fwd_xcd<T>(p, a, st)) != JANUS_OK) return e;
+        }
+        return JANUS_OK;
+    }
+    if constexpr (sizeof(T) == 2) {
     if ((e = zero_fill(w.sync, persist::kSyncCounterBytes, st)) != JANUS_OK) return e;
     persist::FwdArgs a = {};
     a.H = H;
@@ -1094,10 +1265,12 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
         if (rb > 0 && (e = zero_fill(w.sync, persist::kSyncCounterBytes, st)) != JANUS_OK) return e;
         a.rbase = rb;
         const double rows = part_rows(s, rb);
-        e = launch_fwd_persistent(d, ns, a, 2.0 * 4.0 * H * double(H) * rows, fwd_persistent_bytes(a, rows), st);
+        e = launch_fwd_persistent(d, ns, a, 2.0 * 4.0 * H * double(H) * rows, fwd_recurrence_bytes(H, 2, a.Hs, a.HT, a.y, rows), st);
         if (e != JANUS_OK) return e;
     }
     return JANUS_OK;
+    }
+    return JANUS_ERR_UNSUPPORTED;
 }
 
 template <typename T, class Cfg>
@@ -1114,7 +1287,8 @@ janus_status lstm_fwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     }
     const bool al = weight_aligned(d);
     const bool persistent = use_persistent(d);
-    if (persistent && H % 64 != 0) {
+    const bool in_xcds = persistent && use_xcd_fwd(d);
+    if (persistent && !in_xcds && H % 64 != 0) {
         // columns [H, Kp) of the fragment-layout copy are never written and
         // take part in the contraction against zero weights: make them 0
         janus_status e = zero_fill(w.Hf, size_t(d.T + 1) * size_t(w.hf_slot) * 2, st);
@@ -1122,21 +1296,26 @@ janus_status lstm_fwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     }
     for (int l = 0; l < d.L; ++l) {
         const int64_t bh = int64_t(B) * H;
-        {
+        const float *h0l = h0 ? h0 + l * bh : nullptr, *c0l = c0 ? c0 + l * bh : nullptr;
+        float *hTl = hT ? hT + l * bh : nullptr, *cTl = cT ? cT + l * bh : nullptr;
+        if (in_xcds) {
+            // (with nothing to run, the later parts' rows are set here too)
+            for (int rb = 0; rb < (s.packed == 0 ? B : 1); rb += persist::kMaxB) {
+                janus_status e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0l, c0l, hTl, cTl, st);
+                if (e != JANUS_OK) return e;
+            }
+        } else {
             TraceScope trace("lstm_fwd_init", 0.0, double(bh) * (8.0 + 4.0 + sizeof(T)), st);
             hipLaunchKernelGGL(fwd_init_kernel<T>, dim3(unsigned((bh + 255) / 256)), dim3(256), 0, st, B, H, w.ldh,
-                               perm, h0 ? h0 + l * bh : nullptr, c0 ? c0 + l * bh : nullptr,
-                               static_cast<T*>(w.Hs[l]), w.Cs[l], s.active[0], hT ? hT + l * bh : nullptr,
-                               cT ? cT + l * bh : nullptr, persistent ? reinterpret_cast<T*>(w.Hf) : nullptr,
+                               perm, h0l, c0l, static_cast<T*>(w.Hs[l]), w.Cs[l], s.active[0], hTl, cTl, persistent ? reinterpret_cast<T*>(w.Hf) : nullptr,
                                int(round_up(H, 64)), use_ht(d, s, persistent) ? reinterpret_cast<T*>(w.HT[l]) : nullptr,
                                w.ldht);
             JANUS_LAUNCH_CHECK();
         }
         if (s.packed == 0) continue;
         if (persistent) {
-            janus_status e = fwd_layer_persistent(d, s, w, l, x, xrow, Wx[l], Wh[l], b[l], perm,
-                                                  l == d.L - 1 ? y : nullptr, hT ? hT + l * bh : nullptr,
-                                                  cT ? cT + l * bh : nullptr, st);
+            janus_status e = fwd_layer_persistent<T>(d, s, w, l, x, xrow, Wx[l], Wh[l], b[l], perm, h0l, c0l,
+                                                     l == d.L - 1 ? y : nullptr, hTl, cTl, st);
             if (e != JANUS_OK) return e;
             continue;
         }
@@ -1240,7 +1419,62 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     }
     for (int l = d.L - 1; l >= 0; --l) {
         const bool top = l == d.L - 1;
-        if (persistent) {
+        if (persistent && use_xcd_bwd(d)) {
+            xcd::BwdArgs<T> a = {};
+            a.H = H;
+            a.B = B;
+            a.t_eff = s.t_eff;
+            a.fixed = s.fixed ? 1 : 0;
+            a.nkg = int((4 * H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
+            a.force_remote = env_is("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+            a.active = w.act_dev;
+            a.offsets = w.off_dev;
+            a.perm = perm;
+            a.Wh = static_cast<const T*>(Wh[l]);
+            a.Gs = static_cast<const T*>(w.Gs[l]);
+            a.Cs = w.Cs[l];
+            a.dy = static_cast<const T*>(top ? dy : w.dY);
+            a.dy_ld = top ? H : w.ldh;
+            a.dy_time = top ? 1 : 0;
+            a.dhT = dhT ? dhT + l * bh : nullptr;
+            a.dcT = dcT ? dcT + l * bh : nullptr;
+            a.dh0 = dh0 ? dh0 + l * bh : nullptr;
+            a.dc0 = dc0 ? dc0 + l * bh : nullptr;
+            a.db_part = w.dbp;
+            a.GT = gt_by_kernel(d, s, true) ? static_cast<T*>(w.GT) : nullptr;
+            // row-major dG where something reads it (as below)
+            a.G = l == 0 && !dx && a.GT ? nullptr : static_cast<T*>(w.XG);
+            a.ldk = w.ldk;
+            a.ldh = w.ldh;
+            a.ldg = w.ldg;
+            a.ring = static_cast<T*>(w.ring);
+            a.sync = w.sync;
+            for (int rb = 0; rb < B; rb += persist::kMaxB) {
+                const int rows = std::min(B - rb, persist::kMaxB);
+                const XcdPlan p = xcd_plan(d, rows);
+                a.rbase = rb;
+                a.nu = p.nu;
+                a.groups = xcd_groups(rows, p.RT);
+                xcd_steps(s, rb, p.RT, a.groups, a.steps);
+                {
+                    const int64_t n16 = int64_t(xcd::kSlots) * a.groups * p.RT * a.nkg * 64;
+                    TraceScope trace("lstm_bwd_init", 0.0, 16.0 * double(n16), st);
+                    hipLaunchKernelGGL(xcd::bwd_init_kernel, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 1024))),
+                                       dim3(256), 0, st, reinterpret_cast<uint4*>(w.ring), n16, w.sync);
+                    JANUS_LAUNCH_CHECK();
+                }
+                const double work = part_rows(s, rb);
+                TraceScope trace("lstm_bwd_persistent", 2.0 * 4.0 * H * double(H) * work,
+                                 bwd_recurrence_bytes(H, sizeof(T), a.dy, a.GT, a.G, work), st);
+                janus_status e = launch_bwd_xcd<T>(p, a, st);
+                if (e != JANUS_OK) return e;
+                a.gbase += a.groups;
+            }
+            TraceScope trace("lstm_db_reduce", 0.0, 16.0 * double(a.gbase + 1) * H, st);
+            hipLaunchKernelGGL(xcd::db_reduce_kernel, dim3(unsigned((4 * H + 255) / 256)), dim3(256), 0, st, w.dbp,
+                               a.gbase, H, db[l]);
+            JANUS_LAUNCH_CHECK();
+        } else if (persistent) {
             janus_status e = zero_fill(w.sync, persist::kSyncCounterBytes, st);
             if (e != JANUS_OK) return e;
             persist::BwdArgs a = {};
@@ -1275,7 +1509,7 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
             a.dc0 = dc0 ? dc0 + l * bh : nullptr;
             a.part = w.dpart;
             a.db = db[l];
-            a.GT = gt_by_kernel(s, persistent) ? static_cast<bf16_t*>(w.GT) : nullptr;
+            a.GT = gt_by_kernel(d, s, persistent) ? static_cast<bf16_t*>(w.GT) : nullptr;
             // row-major dG only where something reads it: dX (the layer below,
             // or dx asked for), or the weight gradients when dG^T is not here
             if (l == 0 && !dx && a.GT) a.G = nullptr;
@@ -1291,7 +1525,7 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
                 a.rbase = rb;
                 a.db_add = rb > 0 ? 1 : 0;
                 const double rows = part_rows(s, rb);
-                e = launch_bwd_persistent(d, ns, a, 2.0 * 4.0 * H * double(H) * rows, bwd_persistent_bytes(a, rows), st);
+                e = launch_bwd_persistent(d, ns, a, 2.0 * 4.0 * H * double(H) * rows, bwd_recurrence_bytes(H, 2, a.dy, a.GT, a.G, rows), st);
                 if (e != JANUS_OK) return e;
             }
         } else {
@@ -1379,7 +1613,7 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
         // dG^T once for both weight gradients, so that they read it in place
         // (written by the persistent backward itself when it can)
         const bool gt = w.GT && (4 * H) % 8 == 0;
-        if (gt && !gt_by_kernel(s, persistent)) {
+        if (gt && !gt_by_kernel(d, s, persistent)) {
             janus_status e = transpose_bf16(w.XG, w.ldg, nullptr, s.packed, 4 * H, w.GT, w.ldk,
                                             round_up(s.packed, 64), st);
             if (e != JANUS_OK) return e;
