@@ -124,6 +124,66 @@ janus_status upload_pieces(const UploadPiece* pieces, int n, hipStream_t stream)
     return upload(base, image.data(), span, stream);
 }
 
+// ------------------------------------------------- kernels that need the chip
+namespace {
+
+struct Turn {
+    std::mutex mu;               // held from the wait to the record
+    bool used = false;           // `last` is set
+    bool shared = false;         // more than one stream has been seen
+    hipStream_t last = nullptr;
+    hipEvent_t ev = nullptr;     // after the last launch (once shared)
+};
+
+constexpr int kMaxDevices = 64;
+Turn& turn(int dev) {
+    static Turn t[kMaxDevices];
+    return t[dev];
+}
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+}  // namespace
+
+ResidentTurn::ResidentTurn(hipStream_t stream) : stream_(stream) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices || capturing(stream)) {
+        (void)hipGetLastError();
+        return;
+    }
+    Turn& t = turn(dev);
+    t.mu.lock();
+    dev_ = dev;
+    bool ok = true;
+    if (t.used && t.last != stream) {
+        if (!t.shared) {
+            // first sight of a second stream: mark the end of the first one's work
+            ok = hipEventCreateWithFlags(&t.ev, hipEventDisableTiming) == hipSuccess;
+            t.shared = ok;
+            if (ok && !capturing(t.last)) ok = hipEventRecord(t.ev, t.last) == hipSuccess;
+        }
+        if (ok) ok = hipStreamWaitEvent(stream, t.ev, 0) == hipSuccess;
+    }
+    // a stream that is gone has nothing left to wait for
+    if (!ok) (void)hipGetLastError();
+    t.used = true;
+    t.last = stream;
+}
+
+ResidentTurn::~ResidentTurn() {
+    if (dev_ < 0) return;
+    Turn& t = turn(dev_);
+    if (t.shared && hipEventRecord(t.ev, stream_) != hipSuccess) (void)hipGetLastError();
+    t.mu.unlock();
+}
+
 // ------------------------------------------------------------------ tracing
 namespace {
 

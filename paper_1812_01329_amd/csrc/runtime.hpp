@@ -102,6 +102,26 @@ class TraceScope {
     hipStream_t stream_ = nullptr;
 };
 
+// Held around the launch of a kernel whose workgroups must all be resident at
+// once (they wait for each other on the device).  Two such kernels on
+// different streams could each hold part of the chip and wait for the rest of
+// it, so on one device they take turns: the launch waits, on its stream, for
+// the last such kernel of any other stream.  A program that uses one stream
+// pays a comparison; from the first call on a second stream each of these
+// launches records an event (one per device).  Launches under stream capture
+// are left alone.
+class ResidentTurn {
+  public:
+    explicit ResidentTurn(hipStream_t stream);
+    ~ResidentTurn();
+    ResidentTurn(const ResidentTurn&) = delete;
+    ResidentTurn& operator=(const ResidentTurn&) = delete;
+
+  private:
+    int dev_ = -1;
+    hipStream_t stream_ = nullptr;
+};
+
 // Records which HIP call failed, with its error, for janus_last_error on
 // this thread, and returns JANUS_ERR_DEVICE.
 janus_status device_error(hipError_t e, const char* what, const char* file, int line);

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 from oracle import steps as oracle_steps
+from paper_1812_01329_amd import workloads as wl
 from tests.parity import compare_lstm
 from tests.test_gpu_parity import _lstm, _run
 
@@ -79,3 +80,40 @@ def test_nan_rows_do_not_stall(dtype):
     assert np.isnan(g["hT"][0, 3]).all()
     rest = [b for b in range(B) if b != 3]
     assert np.array_equal(g["y"][:, rest], clean["y"][:, rest])
+
+
+def test_two_threads_on_two_streams():
+    """Kernels whose workgroups wait for each other take turns across
+    streams: two host threads, each on its own stream, give the bits of the
+    same steps run one after another."""
+    import threading
+
+    import torch
+    from paper_1812_01329_amd.train_step import make_step
+    ws = [_lstm("mse", "f32", L=1, I=24, H=400, B=40, T=12, seed=21, P=16),
+          _lstm("mse", "bf16", L=2, I=24, H=1024, B=64, T=12, seed=22, P=16),
+          wl.sst_treelstm(n_trees=9, E=64, H=96, V=200, seed=23)]
+    steps = [make_step(w) for w in ws]
+    keys = ["y", "y", "h_root"]
+    for s in steps:
+        s.run()
+    want = [s.results()[k] for s, k in zip(steps, keys)]
+    torch.cuda.synchronize()
+    print("[xcd-threads]", flush=True)
+
+    def work(step):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                step.run()
+        st.synchronize()
+
+    th = [threading.Thread(target=work, args=(s,)) for s in steps]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for s, k, a in zip(steps, keys, want):
+        assert np.array_equal(s.results()[k], a), k
+    for s in steps[:2]:
+        assert _report(s)["timed_out"] == 0
