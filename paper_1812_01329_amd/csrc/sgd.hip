@@ -8,12 +8,12 @@
 // state changes all-or-nothing (Section 4.2.3): a non-finite norm leaves
 // every parameter as it was.
 //
-// Three launches, each bound by HBM traffic:
+// Two launches, each bound by HBM traffic:
 //   sgd_sumsq_kernel   block b of kSgdBlocks sums g^2 (in float64) over its
 //                      range of the concatenation of the tensors;
-//   sgd_scale_kernel   one block adds the block sums in block order and forms
-//                      the norm, lr s and the skip flag;
-//   sgd_update_kernel  p <- p - (lr s) g over the same ranges.
+//   sgd_update_kernel  forms the norm from the block sums, lr s and whether
+//                      anything may change, then p <- p - (lr s) g over the
+//                      same ranges.
 // Every sum runs in a fixed order, so the norm does not depend on timing.
 #include <algorithm>
 #include <cmath>
@@ -35,12 +35,6 @@ struct SgdTable {
     int64_t off[kSgdTable + 1];   // element offsets of the tensors in their concatenation
     const float* g[kSgdTable];
     void* p[kSgdTable];
-};
-
-struct SgdCtrl {
-    float ls;        // lr * s (0 when skipped)
-    int skip;        // 1: the norm is not finite, nothing changes
-    int pad[62];
 };
 
 // [lo, hi) of the concatenation for block b of nb
@@ -98,39 +92,72 @@ __global__ __launch_bounds__(kSgdThreads) void sgd_sumsq_kernel(SgdTable t, doub
     if (tid == 0) partial[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(kSgdThreads) void sgd_scale_kernel(const double* partial, int n, float lr,
-                                                                float max_norm, const uint32_t* hold, SgdCtrl* ctrl,
-                                                                float* stats) {
+// The step from the norm's n block sums: every thread of the block gets lr s,
+// or false where nothing may change (the norm is not finite, or the update is
+// held because the step that produced the gradients failed).
+struct SgdStep {
+    float lr, max_norm;
+    const double* partial;
+    int n;
+    const uint32_t* hold;
+    float* stats;
+};
+__device__ bool sgd_step(const SgdStep& a, bool report, float& ls) {
     __shared__ double red[kSgdThreads / 64];
+    __shared__ float out[2];
     double acc = 0.0;
-    for (int k = threadIdx.x; k < n; k += kSgdThreads) acc += partial[k];
+    for (int k = threadIdx.x; k < a.n; k += kSgdThreads) acc += a.partial[k];
     const double total = block_sum(acc, red);
     if (threadIdx.x == 0) {
         const double norm = sqrt(total);
         const bool finite = isfinite(norm);
-        // a held update (the step that produced the gradients failed) writes
-        // nothing, as for a non-finite norm
-        const bool held = hold != nullptr && *hold != 0u;
+        const bool held = a.hold != nullptr && *a.hold != 0u;
         double s = 1.0;
         if (!finite || held) s = 0.0;
-        else if (max_norm > 0.f && isfinite(max_norm)) s = fmin(1.0, double(max_norm) / (norm + 1e-6));
-        ctrl->ls = float(double(lr) * s);
-        ctrl->skip = (finite && !held) ? 0 : 1;
-        if (stats) {
-            stats[0] = float(norm);
-            stats[1] = float(s);
+        else if (a.max_norm > 0.f && isfinite(a.max_norm)) s = fmin(1.0, double(a.max_norm) / (norm + 1e-6));
+        out[0] = float(double(a.lr) * s);
+        out[1] = (finite && !held) ? 1.f : 0.f;
+        if (report && a.stats) {
+            a.stats[0] = float(norm);
+            a.stats[1] = float(s);
         }
+    }
+    __syncthreads();
+    ls = out[0];
+    return out[1] != 0.f;
+}
+
+// One vector of four parameters: p - ls g.
+template <typename T>
+__device__ __forceinline__ void sgd_apply4(T* q, float4 v, float ls) {
+    if constexpr (sizeof(T) == 4) {
+        float4 w = *reinterpret_cast<const float4*>(q);
+        w.x -= ls * v.x;
+        w.y -= ls * v.y;
+        w.z -= ls * v.z;
+        w.w -= ls * v.w;
+        *reinterpret_cast<float4*>(q) = w;
+    } else {
+        const uint2 w = *reinterpret_cast<const uint2*>(q);
+        const float a = bf2f(bf16_t(w.x & 0xffffu)) - ls * v.x, b = bf2f(bf16_t(w.x >> 16)) - ls * v.y;
+        const float c = bf2f(bf16_t(w.y & 0xffffu)) - ls * v.z, d = bf2f(bf16_t(w.y >> 16)) - ls * v.w;
+        *reinterpret_cast<uint2*>(q) = make_uint2(uint32_t(f2bf(a)) | (uint32_t(f2bf(b)) << 16),
+                                                  uint32_t(f2bf(c)) | (uint32_t(f2bf(d)) << 16));
     }
 }
 
+// Every block forms the step from the block sums itself (8 KB from the L2,
+// one launch less), then walks its range backwards: the pass over the
+// gradients just before read it forwards, so their last part is still in the
+// 256 MB cache in front of the HBM.
 template <typename T>
-__global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, const SgdCtrl* ctrl) {
-    if (ctrl->skip) return;
-    const float ls = ctrl->ls;
+__global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, SgdStep st) {
+    float ls = 0.f;
+    if (!sgd_step(st, blockIdx.x == 0, ls)) return;
     const int tid = threadIdx.x;
     int64_t lo, hi;
     block_range(t.off[t.n], blockIdx.x, gridDim.x, lo, hi);
-    for (int i = 0; i < t.n; ++i) {
+    for (int i = t.n - 1; i >= 0; --i) {
         const int64_t s0 = lo > t.off[i] ? lo : t.off[i];
         const int64_t s1 = hi < t.off[i + 1] ? hi : t.off[i + 1];
         if (s0 >= s1) continue;
@@ -143,28 +170,11 @@ __global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, con
         const bool vec = (reinterpret_cast<uintptr_t>(p + head) % (4 * sizeof(T))) == 0;
         const int64_t n4 = vec ? (len - head) / 4 : 0;
         if (!vec) head = 0;
-        if (tid < head) p[tid] = from_f<T>(to_f<T>(p[tid]) - ls * g[tid]);
+        for (int64_t k = head + 4 * n4 + tid; k < len; k += kSgdThreads) p[k] = from_f<T>(to_f<T>(p[k]) - ls * g[k]);
         const float4* g4 = reinterpret_cast<const float4*>(g + head);
 #pragma unroll 4
-        for (int64_t k = tid; k < n4; k += kSgdThreads) {
-            const float4 v = g4[k];
-            T* q = p + head + 4 * k;
-            if constexpr (sizeof(T) == 4) {
-                float4 w = *reinterpret_cast<const float4*>(q);
-                w.x -= ls * v.x;
-                w.y -= ls * v.y;
-                w.z -= ls * v.z;
-                w.w -= ls * v.w;
-                *reinterpret_cast<float4*>(q) = w;
-            } else {
-                const uint2 w = *reinterpret_cast<const uint2*>(q);
-                const float a = bf2f(bf16_t(w.x & 0xffffu)) - ls * v.x, b = bf2f(bf16_t(w.x >> 16)) - ls * v.y;
-                const float c = bf2f(bf16_t(w.y & 0xffffu)) - ls * v.z, d = bf2f(bf16_t(w.y >> 16)) - ls * v.w;
-                *reinterpret_cast<uint2*>(q) = make_uint2(uint32_t(f2bf(a)) | (uint32_t(f2bf(b)) << 16),
-                                                          uint32_t(f2bf(c)) | (uint32_t(f2bf(d)) << 16));
-            }
-        }
-        for (int64_t k = head + 4 * n4 + tid; k < len; k += kSgdThreads) p[k] = from_f<T>(to_f<T>(p[k]) - ls * g[k]);
+        for (int64_t k = n4 - 1 - tid; k >= 0; k -= kSgdThreads) sgd_apply4<T>(p + head + 4 * k, g4[k], ls);
+        if (tid < head) p[tid] = from_f<T>(to_f<T>(p[tid]) - ls * g[tid]);
     }
 }
 
@@ -174,11 +184,10 @@ constexpr size_t sgd_ws_bytes(int n) {
     return ((size_t(sgd_chunks(n)) * kSgdBlocks * sizeof(double) + 255) / 256) * 256 + 256;
 }
 
-// The allocation-free update keeps its block sums and control word in this
-// file-scope array (one copy per device, alive until the process ends)
-// instead of a caller workspace: room for kNoAllocMaxTensors tensors.  Every
-// call writes all of it that it reads (each block its sum, the scale kernel
-// the control word), so nothing is cleared between calls.
+// The allocation-free update keeps its block sums in this file-scope array
+// (one copy per device, alive until the process ends) instead of a caller
+// workspace: room for kNoAllocMaxTensors tensors.  Every call writes all of
+// it that it reads (each block its sum), so nothing is cleared between calls.
 constexpr int kNoAllocMaxTensors = JANUS_SGD_NOALLOC_MAX_TENSORS;
 constexpr size_t kNoAllocScratchBytes = sgd_ws_bytes(kNoAllocMaxTensors);
 static_assert(kNoAllocScratchBytes <= 64 * 1024, "a modest fixed array");
@@ -247,15 +256,13 @@ janus_status sgd_check(const janus_sgd_desc* d, void* const* params, const float
     return JANUS_OK;
 }
 
-// The three launches of the update on `ws` (sgd_ws_bytes(d->n) bytes, block
-// sums then the control word in its last 256 bytes).  `traced`: record the
+// The launches of the update on `ws` (the norm's block sums).  `traced`: record the
 // launches for janus_trace_end (which creates events, so the
 // allocation-free entry point passes false).
 janus_status sgd_run(const janus_sgd_desc* d, void* const* params, const float* const* grads, const int64_t* sizes,
                      float* stats, const uint32_t* hold, void* ws, hipStream_t st, bool traced) {
     const int nc = sgd_chunks(d->n);
     double* partial = static_cast<double*>(ws);
-    SgdCtrl* ctrl = reinterpret_cast<SgdCtrl*>(static_cast<char*>(ws) + sgd_ws_bytes(d->n) - 256);
     const char* no_label = nullptr;
     for (int c = 0; c < nc; ++c) {
         const SgdTable t = sgd_table(c, d->n, params, grads, sizes);
@@ -264,22 +271,18 @@ janus_status sgd_run(const janus_sgd_desc* d, void* const* params, const float* 
                            partial + int64_t(c) * kSgdBlocks);
         JANUS_LAUNCH_CHECK();
     }
-    {
-        TraceScope trace(traced ? "sgd_scale" : no_label, 0.0, 8.0 * nc * kSgdBlocks, st);
-        hipLaunchKernelGGL(sgd_scale_kernel, dim3(1), dim3(kSgdThreads), 0, st, partial, nc * kSgdBlocks, d->lr,
-                           d->max_norm, hold, ctrl, stats);
-        JANUS_LAUNCH_CHECK();
-    }
+    SgdStep step{d->lr, d->max_norm, partial, nc * kSgdBlocks, hold, stats};
     const size_t es = dtype_size(d->dtype);
     for (int c = 0; c < nc; ++c) {
         const SgdTable t = sgd_table(c, d->n, params, grads, sizes);
         TraceScope trace(traced ? "sgd_update" : no_label, 2.0 * double(t.off[t.n]),
                          (4.0 + 2.0 * es) * double(t.off[t.n]), st);
         if (d->dtype == JANUS_BF16)
-            hipLaunchKernelGGL(sgd_update_kernel<bf16_t>, dim3(kSgdBlocks), dim3(kSgdThreads), 0, st, t, ctrl);
+            hipLaunchKernelGGL(sgd_update_kernel<bf16_t>, dim3(kSgdBlocks), dim3(kSgdThreads), 0, st, t, step);
         else
-            hipLaunchKernelGGL(sgd_update_kernel<float>, dim3(kSgdBlocks), dim3(kSgdThreads), 0, st, t, ctrl);
+            hipLaunchKernelGGL(sgd_update_kernel<float>, dim3(kSgdBlocks), dim3(kSgdThreads), 0, st, t, step);
         JANUS_LAUNCH_CHECK();
+        step.stats = nullptr;   // written by the first launch
     }
     return JANUS_OK;
 }
