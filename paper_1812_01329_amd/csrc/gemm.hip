@@ -879,13 +879,35 @@ janus_status gemm_fast(const GemmDesc& g, const NtPlan& p, hipStream_t s) {
 
 }  // namespace
 
-// out[c] = sum over k < n of part[k * C + c], in order k = 0, 1, ...
-__global__ __launch_bounds__(256) void colpart_reduce_kernel(const float* part, int n, int C, float* out) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
+// out[c] = sum over k < n of part[k * C + c].  A block sums 64 columns: wave
+// w takes every 16th row from row w, eight in flight, and the waves' sums are
+// added in wave order.  (One thread per column walking all rows kept 8 blocks
+// busy for 85 us at n = 256, C = 2048.)
+constexpr int kPartWaves = 16;
+__global__ __launch_bounds__(64 * kPartWaves) void colpart_reduce_kernel(const float* part, int n, int C, float* out) {
+    __shared__ float red[kPartWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane;
     float s = 0.f;
-    for (int k = 0; k < n; ++k) s += part[int64_t(k) * C + c];
-    out[c] = s;
+    if (c < C) {
+        int k = wave;
+        for (; k + 7 * kPartWaves < n; k += 8 * kPartWaves) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = part[int64_t(k + e * kPartWaves) * C + c];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += v[e];
+        }
+        for (; k < n; k += kPartWaves) s += part[int64_t(k) * C + c];
+    }
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && c < C) {
+        s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kPartWaves; ++w) s += red[w][lane];
+        out[c] = s;
+    }
 }
 
 size_t gemm_mse_partials(int M, int N) {
@@ -941,8 +963,8 @@ janus_status gemm_mse(int M, int N, int K, const void* h, const void* W, const v
     janus_status e = launch_nt<float, false, kEpiMse>(a, g, s);
     if (e != JANUS_OK) return e;
     TraceScope trace("colpart_reduce", 0.0, 4.0 * double(a.mt) * N + 4.0 * N, s);
-    hipLaunchKernelGGL(colpart_reduce_kernel, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, a.part_col, a.mt, N,
-                       db);
+    hipLaunchKernelGGL(colpart_reduce_kernel, dim3(unsigned((N + 63) / 64)), dim3(64 * kPartWaves), 0, s, a.part_col,
+                       a.mt, N, db);
     JANUS_LAUNCH_CHECK();
     return JANUS_OK;
 }
