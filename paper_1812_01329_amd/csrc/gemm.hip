@@ -712,9 +712,34 @@ struct NtPlan {
 
 bool rows16(const void* p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 8 == 0; }
 
+// K splits of a contraction of `tiles` tiles and `ktiles` K blocks: the count
+// with the least expected time, a K block taking about 1.5 us and the
+// partials going to memory and back at 4 TB/s plus the launch that sums them.
+// A grid of 160 tiles and more fills the chip without.
+// (700 x 650 outputs over K = 10000: 35 us in 8 splits, 29 in 16.)
+constexpr int kMaxSplits = 32;
+int nt_max_splits(int tiles) { return tiles >= 160 ? 1 : std::min(kMaxSplits, std::max(1, 256 / tiles)); }
+int nt_splits(int tiles, int ktiles, int M, int N) {
+    int best = 1;
+    double least = 1.5 * ktiles;
+    for (int n = 2; n <= std::min(nt_max_splits(tiles), ktiles / 4); ++n) {
+        const double us = 1.5 * ((ktiles + n - 1) / n) + 5.0 + 8e-6 / 4.0 * n * double(M) * N;
+        if (us < least) {
+            least = us;
+            best = n;
+        }
+    }
+    return best;
+}
+
+// The fast path takes every bf16 contraction with at least 16 rows and
+// columns and K of 64 and more.  Below 128 rows or columns most of a 256-wide
+// tile is padding, but such a contraction has few tiles and its K, when long,
+// is then split over the chip, which the general kernel's serial walk of K
+// cannot do (96 x 300 outputs over K = 15000: 3430 us there).
 NtPlan plan_nt(const GemmDesc& g) {
     NtPlan p;
-    if (g.dtype != JANUS_BF16 || g.M < 128 || g.N < 128 || g.K < 64) return p;
+    if (g.dtype != JANUS_BF16 || g.M < 16 || g.N < 16 || g.K < 64) return p;
     constexpr int64_t kMaxOff = int64_t(1) << 31;
     // an operand read in place: 16-byte chunks along K (K a multiple of 8, or
     // rows zero-padded past K), byte offsets in 31 bits
@@ -731,8 +756,7 @@ NtPlan plan_nt(const GemmDesc& g) {
     if (int64_t(NtCfg::BM) * p.ldt * 2 >= kMaxOff) return p;
     const int tiles = ((g.M + NtCfg::BM - 1) / NtCfg::BM) * ((g.N + NtCfg::BN - 1) / NtCfg::BN);
     const int ktiles = (g.K + NtCfg::BK - 1) / NtCfg::BK;
-    int splits = 1;
-    if (tiles < 160 && ktiles >= 32) splits = std::max(1, std::min({8, 256 / tiles, ktiles / 16}));
+    const int splits = nt_splits(tiles, ktiles, g.M, g.N);
     p.ktiles_per_split = (ktiles + splits - 1) / splits;
     p.splits = (ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split;
     size_t off = 0;
@@ -986,7 +1010,7 @@ size_t gemm_scratch_bound(const GemmDesc& g) {
     size_t b = 0;
     if (p.amode != kInPlace) b += (size_t(g.M) * p.ldt * 2 + 255) / 256 * 256;
     if (p.bmode != kInPlace) b += (size_t(g.N) * p.ldt * 2 + 255) / 256 * 256;
-    if (tiles < 160) b += (size_t(8) * g.M * g.N * 4 + 255) / 256 * 256;
+    if (nt_max_splits(tiles) > 1) b += (size_t(nt_max_splits(tiles)) * g.M * g.N * 4 + 255) / 256 * 256;
     return b;
 }
 

@@ -245,8 +245,10 @@ size_t head_gemm_scratch(janus_dtype dt, int rows, int H, int V) {
     GemmDesc g;
     g.dtype = dt;
     g.M = rows; g.N = V; g.K = H;
+    g.lda = g.ldb = H;           // rows of no whole 16-byte chunks are copied
     size_t m = gemm_scratch_bound(g);
     g.N = H; g.K = V; g.b_t = true;
+    g.lda = V; g.ldb = H;
     m = std::max(m, gemm_scratch_bound(g));
     g.M = V; g.N = H; g.K = rows; g.a_t = true;
     return std::max(m, gemm_scratch_bound(g));
