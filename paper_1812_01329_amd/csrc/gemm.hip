@@ -7,6 +7,7 @@
 #include <cstdlib>
 
 #include "device.hpp"
+#include "gemm_f32.hpp"
 #include "ops.hpp"
 
 namespace janus {
@@ -94,6 +95,37 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(GemmDesc g) {
     mma_mainloop<Cfg>(acc, la, lb, g.K, sA, sB, tid);
 
     store_tile<T, Cfg>(g, acc, m0, n0, tid);
+}
+
+// K range of split blockIdx.z: whole chunks of 64
+__device__ __forceinline__ void f32_split(int K, int per, int& k0, int& k1) {
+    k0 = int(blockIdx.z) * per;
+    k1 = min(K, k0 + per);
+}
+
+template <bool AT, bool BT, bool PARTIAL>
+__global__ __launch_bounds__(F32Cfg::NT) void gemm_f32_kernel(GemmDesc g, int per, float* partial) {
+    __shared__ __align__(16) float smem[F32Cfg::SMEM / 4];
+    const int m0 = blockIdx.y * F32Cfg::BM, n0 = blockIdx.x * F32Cfg::BN;
+    int k0, k1;
+    f32_split(g.K, per, k0, k1);
+    f32x16_t acc;
+    f32_tile<AT, BT>(g, m0, n0, k0, k1, smem, acc);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = n0 + 32 * (wave & 1) + acc_col(lane);
+    if (col >= g.N) return;
+    const float bv = !PARTIAL && g.bias ? static_cast<const float*>(g.bias)[col] : 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int row = m0 + 32 * (wave >> 1) + acc_row(v, lane);
+        if (row >= g.M) continue;
+        if constexpr (PARTIAL) {
+            partial[(int64_t(blockIdx.z) * g.M + row) * g.N + col] = acc[v];
+        } else {
+            const int64_t crow = g.c_idx ? int64_t(g.c_idx[row]) : int64_t(row);
+            static_cast<float*>(g.C)[crow * g.ldc + col] = g.alpha * acc[v] + bv;
+        }
+    }
 }
 
 // ------------------------------------------------------------ fast NT path
@@ -540,7 +572,7 @@ void gemm_nt_fast_kernel(NtArgs p, GemmDesc g) {
 }
 
 // C = alpha * (sum over splits of the partials, in split order) + bias
-template <typename OutT>
+template <typename OutT, typename BiasT = bf16_t>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* partial, int splits, int M, int N,
                                                             GemmDesc g) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -548,7 +580,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* partial
     const int row = int(i / N), col = int(i % N);
     float s = 0.f;
     for (int k = 0; k < splits; ++k) s += partial[int64_t(k) * M * N + i];
-    const float bv = g.bias ? to_f(static_cast<const bf16_t*>(g.bias)[col]) : 0.f;
+    const float bv = g.bias ? to_f(static_cast<const BiasT*>(g.bias)[col]) : 0.f;
     const int64_t crow = g.c_idx ? int64_t(g.c_idx[row]) : int64_t(row);
     static_cast<OutT*>(g.C)[crow * g.ldc + col] = from_f<OutT>(g.alpha * s + bv);
 }
@@ -689,9 +721,8 @@ __global__ void zero_kernel(unsigned char* p, size_t head, uint4* mid, size_t n1
 
 }  // namespace
 
-// bf16: 128x128 tiles, 4 waves of 64x64; fp32: 64x64 tiles, 4 waves of 32x32
+// the general bf16 path: 128x128 tiles, 4 waves of 64x64
 using CfgBF16 = TileCfg<bf16_t, 128, 128, 32, 2, 2>;
-using CfgF32 = TileCfg<float, 64, 64, 32, 2, 2>;
 
 namespace {
 
@@ -718,12 +749,12 @@ bool rows16(const void* p, int64_t ld) { return reinterpret_cast<uintptr_t>(p) %
 // A grid of 160 tiles and more fills the chip without.
 // (700 x 650 outputs over K = 10000: 35 us in 8 splits, 29 in 16.)
 constexpr int kMaxSplits = 32;
-int nt_max_splits(int tiles) { return tiles >= 160 ? 1 : std::min(kMaxSplits, std::max(1, 256 / tiles)); }
 int nt_splits(int tiles, int ktiles, int M, int N) {
+    if (tiles >= 160) return 1;
     int best = 1;
     double least = 1.5 * ktiles;
-    for (int n = 2; n <= std::min(nt_max_splits(tiles), ktiles / 4); ++n) {
-        const double us = 1.5 * ((ktiles + n - 1) / n) + 5.0 + 8e-6 / 4.0 * n * double(M) * N;
+    for (int n = 2; n <= std::min({kMaxSplits, 256 / tiles, ktiles / 4}); ++n) {
+        const double us = 1.5 * ktiles / n + 5.0 + 2e-6 * n * double(M) * N;
         if (us < least) {
             least = us;
             best = n;
@@ -993,12 +1024,72 @@ janus_status gemm_mse(int M, int N, int K, const void* h, const void* W, const v
     return JANUS_OK;
 }
 
-size_t gemm_scratch_bytes(const GemmDesc& g) {
-    const NtPlan p = plan_nt(g);
-    return p.fast ? p.bytes : 0;
+namespace {
+
+// K splits of a float32 contraction: the count with the least expected time.
+// Up to four workgroups share a CU (1024 on the chip); a chunk of 64 k takes
+// a workgroup about 1.6 us with one per CU and 3.4 us with four (the MFMA
+// rate), a split's partials go out and back at 4 TB/s, and the sum is a
+// launch.  (1024 x 300 outputs over K = 800: 88 us in one piece.)
+constexpr size_t kF32Scratch = size_t(16) << 20;   // partials of a contraction at most: 1024 tiles
+int f32_splits(const GemmDesc& g) {
+    const int64_t tiles = int64_t((g.M + F32Cfg::BM - 1) / F32Cfg::BM) * ((g.N + F32Cfg::BN - 1) / F32Cfg::BN);
+    const int chunks = (g.K + F32Cfg::BK - 1) / F32Cfg::BK;
+    auto us = [&](int n) {
+        const int64_t wgs = tiles * n;
+        const double waves = double((wgs + 1023) / 1024), per_cu = std::min(4.0, double(wgs) / 256.0);
+        const double t = waves * chunks / n * std::max(1.6, 0.85 * per_cu);
+        return n == 1 ? t : t + 5.0 + 2e-6 * n * double(g.M) * g.N;
+    };
+    int best = 1;
+    for (int n = 2; n <= std::min(kMaxSplits, chunks) && size_t(n) * g.M * g.N * 4 <= kF32Scratch; ++n)
+        if (us(n) < us(best)) best = n;
+    return best;
 }
 
-size_t gemm_scratch_bound(const GemmDesc& g) {
+template <bool AT, bool BT>
+janus_status launch_f32(const GemmDesc& g, hipStream_t s) {
+    const int chunks = (g.K + F32Cfg::BK - 1) / F32Cfg::BK;
+    int splits = f32_splits(g);
+    if (splits > 1 && (!g.scratch || g.scratch_bytes < size_t(splits) * g.M * g.N * 4)) splits = 1;
+    const int per = std::max(1, (chunks + splits - 1) / splits) * F32Cfg::BK;
+    splits = std::max(1, (g.K + per - 1) / per);
+    const dim3 grid((g.N + F32Cfg::BN - 1) / F32Cfg::BN, (g.M + F32Cfg::BM - 1) / F32Cfg::BM, splits);
+    {
+        TraceScope trace(gemm_label(AT, BT, false), 2.0 * g.M * g.N * double(g.K),
+                         4.0 * (double(g.M) * g.K + double(g.N) * g.K + double(g.M) * g.N), s);
+        if (splits > 1)
+            hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, true>), grid, dim3(F32Cfg::NT), 0, s, g, per,
+                               static_cast<float*>(g.scratch));
+        else
+            hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, false>), grid, dim3(F32Cfg::NT), 0, s, g, per,
+                               static_cast<float*>(nullptr));
+        JANUS_LAUNCH_CHECK();
+    }
+    if (splits == 1) return JANUS_OK;
+    const int64_t n = int64_t(g.M) * g.N;
+    TraceScope trace("splitk_reduce", 0.0, 4.0 * n * (splits + 1), s);
+    hipLaunchKernelGGL((splitk_reduce_kernel<float, float>), dim3(unsigned((n + 255) / 256)), dim3(256), 0, s,
+                       static_cast<const float*>(g.scratch), splits, g.M, g.N, g);
+    JANUS_LAUNCH_CHECK();
+    return JANUS_OK;
+}
+
+janus_status gemm_f32(const GemmDesc& g, hipStream_t s) {
+    if (!g.a_t) return g.b_t ? launch_f32<false, true>(g, s) : launch_f32<false, false>(g, s);
+    return g.b_t ? launch_f32<true, true>(g, s) : JANUS_ERR_UNSUPPORTED;
+}
+
+}  // namespace
+
+
+size_t gemm_scratch_bound(const GemmDesc& g, bool fewer_rows) {
+    auto round = [](size_t b) { return (b + 255) / 256 * 256; };
+    if (g.dtype == JANUS_F32) {
+        if (fewer_rows) return g.K > F32Cfg::BK ? std::min(kF32Scratch, size_t(kMaxSplits) * g.M * g.N * 4) : 0;
+        const int n = f32_splits(g);
+        return n > 1 ? size_t(n) * g.M * g.N * 4 : 0;
+    }
     GemmDesc q = g;
     q.A = q.B = nullptr;            // 16-byte aligned stand-ins (unaligned caller tensors may need more;
                                     // gemm() then takes the slower path that needs none)
@@ -1006,11 +1097,13 @@ size_t gemm_scratch_bound(const GemmDesc& g) {
     q.b_src_rows = q.b_idx ? int64_t(1) : 0;
     const NtPlan p = plan_nt(q);
     if (!p.fast) return 0;
-    const int tiles = ((g.M + NtCfg::BM - 1) / NtCfg::BM) * ((g.N + NtCfg::BN - 1) / NtCfg::BN);
     size_t b = 0;
-    if (p.amode != kInPlace) b += (size_t(g.M) * p.ldt * 2 + 255) / 256 * 256;
-    if (p.bmode != kInPlace) b += (size_t(g.N) * p.ldt * 2 + 255) / 256 * 256;
-    if (nt_max_splits(tiles) > 1) b += (size_t(nt_max_splits(tiles)) * g.M * g.N * 4 + 255) / 256 * 256;
+    if (p.amode != kInPlace) b += round(size_t(g.M) * p.ldt * 2);
+    if (p.bmode != kInPlace) b += round(size_t(g.N) * p.ldt * 2);
+    // the split count grows with K; fewer rows may split more, up to 256 tiles in all
+    constexpr size_t kTileBytes = size_t(NtCfg::BM) * NtCfg::BN * 4;
+    if (fewer_rows && g.K >= 8 * NtCfg::BK) b += round(std::min(256 * kTileBytes, size_t(kMaxSplits) * g.M * g.N * 4));
+    else if (p.splits > 1) b += round(size_t(p.splits) * g.M * g.N * 4);
     return b;
 }
 
@@ -1023,7 +1116,7 @@ janus_status gemm(const GemmDesc& g, hipStream_t stream) {
         if (p.fast && (p.bytes == 0 || (g.scratch && g.scratch_bytes >= p.bytes))) return gemm_fast(g, p, stream);
         return dispatch<bf16_t, CfgBF16>(g, aligned, stream);
     }
-    if (g.dtype == JANUS_F32) return dispatch<float, CfgF32>(g, aligned, stream);
+    if (g.dtype == JANUS_F32) return gemm_f32(g, stream);
     return JANUS_ERR_UNSUPPORTED;
 }
 

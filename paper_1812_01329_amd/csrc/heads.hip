@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "device.hpp"
+#include "gemm_f32.hpp"
 #include "ops.hpp"
 
 namespace janus {
@@ -188,6 +189,33 @@ __global__ __launch_bounds__(Cfg::NT) void mse_gemm_kernel(int M, int N, int K, 
     if (tid == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = sq;
 }
 
+// The same in float32 (64 x 64 tiles).
+__global__ __launch_bounds__(F32Cfg::NT) void mse_f32_kernel(GemmDesc g, const float* tgt, float* dY, float scale,
+                                                             float* part) {
+    __shared__ __align__(16) float smem[F32Cfg::SMEM / 4];
+    __shared__ float red[16];
+    const int m0 = blockIdx.y * F32Cfg::BM, n0 = blockIdx.x * F32Cfg::BN;
+    f32x16_t acc;
+    f32_tile<false, false>(g, m0, n0, 0, g.K, smem, acc);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = n0 + 32 * (wave & 1) + acc_col(lane);
+    float sq = 0.f;
+    if (col < g.N) {
+        const float bv = static_cast<const float*>(g.bias)[col];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = m0 + 32 * (wave >> 1) + acc_row(v, lane);
+            if (row >= g.M) continue;
+            const int64_t o = int64_t(row) * g.N + col;
+            const float d = acc[v] + bv - tgt[o];
+            sq += d * d;
+            dY[o] = scale * d;
+        }
+    }
+    sq = block_sum(sq, red);
+    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = sq;
+}
+
 // --------------------------------------------------------------- scalar losses
 // One workgroup: 16-byte loads, eight in flight per thread (the loop is
 // unrolled), four running sums per thread added in a fixed order, then the
@@ -225,7 +253,7 @@ __global__ void loss_grad_kernel(int kind, const float* h, int64_t n, float* dh)
 }
 
 using HeadBF16 = TileCfg<bf16_t, 128, 128, 32, 2, 2>;
-using HeadF32 = TileCfg<float, 64, 64, 32, 2, 2>;
+using HeadF32 = F32Cfg;
 
 struct XentWs {
     int32_t* seg = nullptr;      // EMBED_BWD: the rows grouped by id
@@ -241,7 +269,6 @@ struct XentWs {
 // scratch bound of the head's contractions: logits = h Wout^T, dh = dz Wout,
 // dWout = dz^T h (run one after another, so one buffer serves all)
 size_t head_gemm_scratch(janus_dtype dt, int rows, int H, int V) {
-    if (dt != JANUS_BF16) return 0;
     GemmDesc g;
     g.dtype = dt;
     g.M = rows; g.N = V; g.K = H;
@@ -316,18 +343,33 @@ janus_status mse_impl(const janus_mse_desc& d, const void* h, const void* W, con
             TraceScope trace("mse_gemm", 2.0 * d.rows * double(d.P) * d.H,
                              double(sizeof(T)) * (double(d.rows) * d.H + double(d.P) * d.H + 2.0 * d.rows * double(d.P)),
                              st);
-            const bool al = (int64_t(d.H) * int64_t(sizeof(T))) % 16 == 0 &&
-                            reinterpret_cast<uintptr_t>(h) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
-            if (al)
-                hipLaunchKernelGGL((mse_gemm_kernel<T, Cfg, true>), grid, dim3(Cfg::NT), Cfg::SMEM_BYTES, st, d.rows,
-                                   d.P, d.H, static_cast<const T*>(h), static_cast<const T*>(W),
-                                   static_cast<const T*>(b), static_cast<const T*>(tgt), static_cast<T*>(w.dY),
-                                   2.f / count, w.part);
-            else
-                hipLaunchKernelGGL((mse_gemm_kernel<T, Cfg, false>), grid, dim3(Cfg::NT), Cfg::SMEM_BYTES, st, d.rows,
-                                   d.P, d.H, static_cast<const T*>(h), static_cast<const T*>(W),
-                                   static_cast<const T*>(b), static_cast<const T*>(tgt), static_cast<T*>(w.dY),
-                                   2.f / count, w.part);
+            if constexpr (sizeof(T) == 4) {
+                GemmDesc g;
+                g.dtype = JANUS_F32;
+                g.M = d.rows;
+                g.N = d.P;
+                g.K = d.H;
+                g.A = h;
+                g.lda = d.H;
+                g.B = W;
+                g.ldb = d.H;
+                g.bias = b;
+                hipLaunchKernelGGL(mse_f32_kernel, grid, dim3(F32Cfg::NT), 0, st, g, static_cast<const float*>(tgt),
+                                   static_cast<float*>(w.dY), 2.f / count, w.part);
+            } else {
+                const bool al = (int64_t(d.H) * int64_t(sizeof(T))) % 16 == 0 &&
+                                reinterpret_cast<uintptr_t>(h) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
+                if (al)
+                    hipLaunchKernelGGL((mse_gemm_kernel<T, Cfg, true>), grid, dim3(Cfg::NT), Cfg::SMEM_BYTES, st, d.rows,
+                                       d.P, d.H, static_cast<const T*>(h), static_cast<const T*>(W),
+                                       static_cast<const T*>(b), static_cast<const T*>(tgt), static_cast<T*>(w.dY),
+                                       2.f / count, w.part);
+                else
+                    hipLaunchKernelGGL((mse_gemm_kernel<T, Cfg, false>), grid, dim3(Cfg::NT), Cfg::SMEM_BYTES, st, d.rows,
+                                       d.P, d.H, static_cast<const T*>(h), static_cast<const T*>(W),
+                                       static_cast<const T*>(b), static_cast<const T*>(tgt), static_cast<T*>(w.dY),
+                                       2.f / count, w.part);
+            }
             JANUS_LAUNCH_CHECK();
         }
         TraceScope trace("finish_sum", 0.0, 4.0 * w.nparts, st);

@@ -176,7 +176,7 @@ bool env_is(const char* name, char v) {
 // passes (they run one after another on one stream, so one buffer serves all).
 size_t lstm_gemm_scratch(const janus_lstm_desc& d) {
     const int64_t TB = int64_t(d.T) * d.B;
-    if (d.dtype != JANUS_BF16 || TB > INT32_MAX) return 0;
+    if (TB > INT32_MAX) return 0;
     size_t m = 0;
     for (int l = 0; l < d.L; ++l) {
         const int Il = l == 0 ? d.I : d.H;
@@ -184,7 +184,7 @@ size_t lstm_gemm_scratch(const janus_lstm_desc& d) {
         g.dtype = d.dtype;
         g.M = int(TB); g.N = 4 * d.H; g.K = Il;            // input projection
         g.a_idx = reinterpret_cast<const int32_t*>(16);
-        m = std::max(m, gemm_scratch_bound(g));
+        m = std::max(m, gemm_scratch_bound(g, true));
         g = GemmDesc();
         g.dtype = d.dtype;
         g.M = 4 * d.H; g.N = Il; g.K = int(TB);             // dWx, dWh (dG^T in place, rows transposed)
@@ -197,7 +197,7 @@ size_t lstm_gemm_scratch(const janus_lstm_desc& d) {
         g.dtype = d.dtype;
         g.M = int(TB); g.N = Il; g.K = 4 * d.H;             // dX = dG Wx
         g.b_t = true;
-        m = std::max(m, gemm_scratch_bound(g));
+        m = std::max(m, gemm_scratch_bound(g, true));
     }
     return m;
 }
@@ -256,9 +256,9 @@ size_t carve(const janus_lstm_desc& d, void* base, LstmWs& w) {
         w.Hf = c.take<bf16_t>((int64_t(d.T) + 1) * w.hf_slot);
         w.ldk = round_up(TB, 64);
         w.GT = c.take<char>(int64_t(4) * d.H * w.ldk * es);
-        w.gs_bytes = lstm_gemm_scratch(d);
-        w.gs = c.take<char>(int64_t(w.gs_bytes));
     }
+    w.gs_bytes = lstm_gemm_scratch(d);
+    w.gs = c.take<char>(int64_t(w.gs_bytes));
     return c.off + 256;
 }
 

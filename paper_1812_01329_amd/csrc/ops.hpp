@@ -47,9 +47,10 @@ struct GemmDesc {
 
 janus_status gemm(const GemmDesc& g, hipStream_t stream);
 size_t gemm_scratch_bytes(const GemmDesc& g);
-// scratch enough for the contraction with any K up to g.K, any operand
-// alignment and any gathered-row count (for sizing workspaces in advance)
-size_t gemm_scratch_bound(const GemmDesc& g);
+// scratch enough for the contraction with any K up to g.K and any
+// gathered-row count (for sizing workspaces in advance); `fewer_rows`: also
+// with any M up to g.M
+size_t gemm_scratch_bound(const GemmDesc& g, bool fewer_rows = false);
 
 // Projection + MSE in one pass (bf16, K-contiguous h [M, K] and W [N, K]):
 // d = h W^T + bias - tgt, dY = scale d (bf16, [M, N]), part[0, mt * nt) =

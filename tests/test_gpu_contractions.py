@@ -19,3 +19,14 @@ def test_thin_bf16(rows, H, P):
 @pytest.mark.parametrize("V,H,rows", [(15000, 300, 96), (3001, 40, 20), (1000, 130, 1)])
 def test_thin_bf16_softmax(V, H, rows, monkeypatch):
     _softmax("bf16", V, H, rows, "1", "random", monkeypatch)
+
+
+@pytest.mark.parametrize("rows,H,P", [(1, 1, 1), (3, 7, 2), (64, 64, 64), (65, 63, 66), (63, 129, 65), (7, 1000, 5),
+                                      (2000, 33, 31), (700, 130, 257)])
+def test_float32(rows, H, P):
+    _linear_mse("f32", rows, H, P)
+
+
+@pytest.mark.parametrize("V,H,rows", [(3001, 37, 20), (130, 1, 9)])
+def test_float32_softmax(V, H, rows, monkeypatch):
+    _softmax("f32", V, H, rows, "1", "random", monkeypatch)
