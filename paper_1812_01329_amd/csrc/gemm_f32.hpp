@@ -158,7 +158,12 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& g, int m0, int n0, int 
             a.index(k + 2 * C::BK, k1, tid);
             b.index(k + 2 * C::BK, k1, tid);
         }
+        // a chunk's products start from zero and are added to the total at its
+        // end: the sum over a long K then rounds like one of K / 64 terms
         const int steps = (min(C::BK, k1 - k) + 15) / 16;
+        f32x16_t part;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[v] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < C::BK / 16; ++ks) {
             if (ks >= steps) break;
@@ -166,8 +171,10 @@ __device__ __forceinline__ void f32_tile(const GemmDesc& g, int m0, int n0, int 
             F32Operand<AT>::frag(sA, ar, ks, lane, fa);
             F32Operand<BT>::frag(sB, br, ks, lane, fb);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j], fb[j], acc, 0, 0, 0);
+            for (int j = 0; j < 8; ++j) part = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j], fb[j], part, 0, 0, 0);
         }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] += part[v];
     }
 }
 
