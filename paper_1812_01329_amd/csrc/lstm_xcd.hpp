@@ -124,7 +124,8 @@ __device__ __forceinline__ void wait_own_stores() {
 struct Place {
     int g, m, local;
 };
-__device__ __forceinline__ Place take_place(Sync* s, int nu, int groups, int force_remote) {
+template <class S>
+__device__ __forceinline__ Place take_place(S* s, int nu, int groups, int force_remote) {
     __shared__ int place[3];
     if (threadIdx.x == 0) {
         const unsigned x = persist::xcc_id();
@@ -158,7 +159,8 @@ __device__ __forceinline__ Place take_place(Sync* s, int nu, int groups, int for
 }
 
 // Barrier of a group that does not share an L2: release, arrive, wait, acquire.
-__device__ __forceinline__ void remote_barrier(Sync* s, int g, unsigned& phase, unsigned members) {
+template <class S>
+__device__ __forceinline__ void remote_barrier(S* s, int g, unsigned& phase, unsigned members) {
     ++phase;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
@@ -174,8 +176,8 @@ __device__ __forceinline__ void remote_barrier(Sync* s, int g, unsigned& phase, 
 // (`poll`; only the k-groups that still do are loaded again).  Offsets out
 // of range read zeros, which pass.  A wait that runs out sets the error flag;
 // from then on (`dead`) nothing waits.
-template <typename T, int N, class Off>
-__device__ __forceinline__ void load_operand(uint4 (&f)[N], __amdgpu_buffer_rsrc_t rs, Off off, bool poll, Sync* s,
+template <typename T, int N, class Off, class S>
+__device__ __forceinline__ void load_operand(uint4 (&f)[N], __amdgpu_buffer_rsrc_t rs, Off off, bool poll, S* s,
                                              bool& dead) {
 #pragma unroll
     for (int i = 0; i < N; ++i) f[i] = load_l2(rs, off(i));
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(256) void fwd_init_kernel(int B, int H, int64_t ldh
 }
 
 // Backward: every slot empty, the barrier counters zero.
-__global__ __launch_bounds__(256) void bwd_init_kernel(uint4* ring, int64_t n16, Sync* sync) {
+static __global__ __launch_bounds__(256) void bwd_init_kernel(uint4* ring, int64_t n16, Sync* sync) {
     const int64_t stride = int64_t(gridDim.x) * 256, i0 = int64_t(blockIdx.x) * 256 + threadIdx.x;
     for (int64_t i = i0; i < n16; i += stride) ring[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(sync);
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(256) void bwd_init_kernel(uint4* ring, int64_t n16,
 }
 
 // db[g * H + u] = sum over the row groups of their sums, in group order
-__global__ __launch_bounds__(256) void db_reduce_kernel(const float* part, int groups, int H, float* db) {
+static __global__ __launch_bounds__(256) void db_reduce_kernel(const float* part, int groups, int H, float* db) {
     const int n = blockIdx.x * 256 + threadIdx.x;
     if (n >= 4 * H) return;
     float s = 0.f;

@@ -29,7 +29,9 @@
 #include "device.hpp"
 #include "ops.hpp"
 #include "simt.hpp"
-#include "tree_persist.hpp"
+#include "tree_common.hpp"
+#include "tree_tail.hpp"
+#include "tree_xcd.hpp"
 #include "treernn_persist.hpp"
 
 namespace janus {
@@ -66,13 +68,18 @@ struct TreeWs {
     // upload is one copy), and node rows padded to whole 128-byte lines
     int32_t* loff = nullptr;     // [N + 1]
     tpersist::TreeSync* tsync = nullptr;
+    // groups of trees per XCD (tree_xcd.hpp): the groups, then their tiles
+    treex::Group* xgroup = nullptr;
+    treex::Tile* xtile = nullptr;    // [N]
+    float* xl = nullptr;         // [N x ldx] leaf inputs
+    float* hx = nullptr;         // [N x ldc] h of every node
     float* Gp = nullptr;         // [N x ldg] gates
     float* Cp = nullptr;         // [N x ldc]
     float* HLRp = nullptr;       // [N x ldl]
-    float* dhp = nullptr;        // [N x ldc]
-    float* dcp = nullptr;        // [N x ldc]
     float* dAp = nullptr;        // [N x lda]
-    float* dxp = nullptr;        // [N x ldx]
+    float* dxp = nullptr;        // [3][N x E] parts of the leaves' input gradient
+    float* tpart = nullptr;      // parts of dU and dW
+    float* tsum = nullptr;       // parts of db
     int64_t ldg = 0, ldc = 0, ldl = 0, lda = 0, ldx = 0;
 };
 
@@ -86,6 +93,8 @@ size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, Tre
     w.parent = c.take<int32_t>(N);
     w.rootk = c.take<int32_t>(N);
     w.rootpos = c.take<int32_t>(K);
+    w.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(std::min(treex::kGroupInts, size_t(8) * (K + treex::kMaxGroups))));
+    w.xtile = c.take<treex::Tile>(N);
     w.loff = c.take<int32_t>(int64_t(N) + 1);
     w.tsync = c.take<tpersist::TreeSync>(1);
     // the leaves grouped by word, and (persistent backward) each workgroup's
@@ -109,10 +118,12 @@ size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, Tre
     w.Gp = c.take<float>(int64_t(N) * w.ldg);
     w.Cp = c.take<float>(int64_t(N) * w.ldc);
     w.HLRp = c.take<float>(int64_t(N) * w.ldl);
-    w.dhp = c.take<float>(int64_t(N) * w.ldc);
-    w.dcp = c.take<float>(int64_t(N) * w.ldc);
     w.dAp = c.take<float>(int64_t(N) * w.lda);
-    w.dxp = c.take<float>(int64_t(N) * w.ldx);
+    w.dxp = c.take<float>(int64_t(3) * N * d.E);
+    w.tpart = c.take<float>(tail_part_floats(5 * H, 2 * H) + tail_part_floats(5 * H, d.E));
+    w.tsum = c.take<float>(tail_sum_floats(N, 5 * H));
+    w.xl = c.take<float>(int64_t(N) * w.ldx);
+    w.hx = c.take<float>(int64_t(N) * w.ldc);
     return c.off + 256;
 }
 
@@ -121,8 +132,8 @@ struct TreeHost {
     std::vector<int32_t> lword, lchild, rchild, parent, rootk, rootpos;
 };
 
-void build_host(const janus_tree_batch* t, const TreeSchedule& s, TreeHost& h) {
-    const int32_t N = s.N;
+void build_host(const janus_tree_batch* t, int32_t N, const std::vector<int32_t>& order,
+                const std::vector<int32_t>& pos, TreeHost& h) {
     h.lword.assign(N, -1);
     h.lchild.assign(N, -1);
     h.rchild.assign(N, -1);
@@ -130,11 +141,11 @@ void build_host(const janus_tree_batch* t, const TreeSchedule& s, TreeHost& h) {
     h.rootk.assign(N, -1);
     h.rootpos.assign(t->num_trees, 0);
     for (int32_t p = 0; p < N; ++p) {
-        const int32_t n = s.level_nodes[p];
+        const int32_t n = order[p];
         if (t->left[n] < 0) {
             h.lword[p] = t->word[n];
         } else {
-            const int32_t pl = s.pos[t->left[n]], pr = s.pos[t->right[n]];
+            const int32_t pl = pos[t->left[n]], pr = pos[t->right[n]];
             h.lchild[p] = pl;
             h.rchild[p] = pr;
             h.parent[pl] = 2 * p;
@@ -142,10 +153,13 @@ void build_host(const janus_tree_batch* t, const TreeSchedule& s, TreeHost& h) {
         }
     }
     for (int32_t k = 0; k < t->num_trees; ++k) {
-        const int32_t p = s.pos[t->root[k]];
+        const int32_t p = pos[t->root[k]];
         h.rootk[p] = k;
         h.rootpos[k] = p;
     }
+}
+void build_host(const janus_tree_batch* t, const TreeSchedule& s, TreeHost& h) {
+    build_host(t, s.N, s.level_nodes, s.pos, h);
 }
 
 __device__ __forceinline__ float sig(float x) { return sigmoidf_(x); }
@@ -327,75 +341,125 @@ janus_status prepare(const janus_treelstm_desc* d, const janus_tree_batch* t, vo
 
 // ------------------------------------------------------- persistent path
 
-// Grid and LDS of the persistent TreeLSTM kernels: one workgroup per CU at
-// most, the grid a multiple of the unit groups (forward) and of the column
-// tiles (backward) so every workgroup holds one weight slice.  Off with
-// JANUS_TREE_PERSIST=0, where a slice does not fit the LDS (about H > 170
-// for the backward's U columns) or for inputs wider than 512; the
-// level-by-level kernels run then.
-struct TreePlan {
-    bool on = false;
-    int ngroups = 0, fwd_grid = 0, ncol = 0, bwd_grid = 0;
-    size_t fwd_lds = 0, bwd_lds = 0;
-};
-TreePlan tree_plan(const janus_treelstm_desc& d) {
-    TreePlan p;
-    const char* e = getenv("JANUS_TREE_PERSIST");
-    if (e && e[0] == '0') return p;
-    const TreeDev dev = tree_dev();
-    if (dev.cus <= 0 || dev.lds == 0) return p;
-    if (d.E > tpersist::kMaxE || d.H > tpersist::kUC * tpersist::kMaxCh) return p;
-    p.ngroups = (d.H + tpersist::kUG - 1) / tpersist::kUG;
-    p.ncol = (2 * d.H + 31) / 32;
-    if (p.ngroups > dev.cus || p.ncol > dev.cus) return p;
-    const int cus = dev.cus < kMaxTreeGrid ? dev.cus : kMaxTreeGrid;
-    p.fwd_grid = p.ngroups * (cus / p.ngroups);
-    p.bwd_grid = p.ncol * (cus / p.ncol);
-    p.fwd_lds = size_t(tpersist::fwd_lds_floats(d.E, d.H)) * sizeof(float);
-    p.bwd_lds = size_t(tpersist::bwd_lds_floats(d.H)) * sizeof(float);
-    p.on = p.fwd_lds <= dev.lds && p.bwd_lds <= dev.lds;
-    return p;
+// ------------------------------------------------- groups of trees per XCD
+
+bool tree_env(const char* name, char v) {
+    const char* e = getenv(name);
+    return e && e[0] == v;
 }
 
+// The tree of every node (a child belongs to its parent's).
+std::vector<int32_t> tree_of_nodes(const janus_tree_batch* t, const TreeSchedule& s) {
+    std::vector<int32_t> tree(s.N, 0);
+    for (int32_t k = 0; k < t->num_trees; ++k) tree[t->root[k]] = k;
+    for (int32_t i = s.N; i-- > 0;) {
+        const int32_t n = s.level_nodes[i];
+        if (t->left[n] >= 0) tree[t->left[n]] = tree[t->right[n]] = tree[n];
+    }
+    return tree;
+}
 
-// Forward on the persistent path: the schedule, the level offsets and the
-// barrier's counters (with its error flag) go over in one copy, then one
-// launch runs every level.
-janus_status treelstm_fwd_persistent_call(const janus_treelstm_desc& d, const janus_tree_batch* t,
-                                          const TreeSchedule& s, const TreeWs& w, const TreePlan& plan,
-                                          const void* emb, const void* W, const void* U, const void* b, void* h_root,
-                                          hipStream_t st) {
+// The binary TreeLSTM in groups of trees per XCD: row tiles of the forward
+// (5 gates of 16 NT / 5 units) and of the backward ([dh_L; dh_R] of 8 MT
+// units) by H, so that a group's workgroups fit one XCD (32 CUs) and their
+// weights its VGPRs; each direction cuts the batch the same way, with the
+// larger workgroup count and the backward's LDS (dh and dc of every node).
+struct TreeXcdPlan {
+    bool on = false;
+    int NT = 0, MT = 0, fwd_nu = 0, bwd_nu = 0;
+    treex::Cut cut;
+    size_t fwd_lds = 0, bwd_lds = 0;
+};
+size_t tree_xcd_fwd_lds(int NT, int nodes) {
+    return NT == 1   ? treex::LstmFwdCfg<1>::lds(nodes)
+           : NT == 2 ? treex::LstmFwdCfg<2>::lds(nodes)
+           : NT == 3 ? treex::LstmFwdCfg<3>::lds(nodes)
+                     : treex::LstmFwdCfg<4>::lds(nodes);
+}
+size_t tree_xcd_bwd_lds(int MT, int nodes) {
+    return MT == 1 ? treex::LstmBwdCfg<1>::lds(nodes) : treex::LstmBwdCfg<2>::lds(nodes);
+}
+TreeXcdPlan tree_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s) {
+    TreeXcdPlan p;
+    if (tree_env("JANUS_TREE_PERSIST", '0')) return p;
+    const TreeDev dev = tree_dev();
+    if (dev.cus <= 0 || dev.lds == 0 || d.H > 384 || d.E > tpersist::kMaxE) return p;
+    // 32-bit byte offsets into the exchanged rows
+    if (int64_t(s.N) * round_up(5 * d.H, 32) * 4 >= (int64_t(1) << 31) ||
+        int64_t(s.N) * round_up(d.E, 32) * 4 >= (int64_t(1) << 31))
+        return p;
+    p.NT = d.H <= 96 ? 1 : d.H <= 192 ? 2 : d.H <= 288 ? 3 : 4;
+    p.MT = d.H <= 256 ? 1 : 2;
+    const int fu = 16 * p.NT / 5, bu = 8 * p.MT;
+    p.fwd_nu = (d.H + fu - 1) / fu;
+    p.bwd_nu = (d.H + bu - 1) / bu;
+    int capacity = 0;
+    for (int step = 1 << 16; step > 0; step >>= 1)
+        if (tree_xcd_fwd_lds(p.NT, capacity + step) <= dev.lds - 1024 && tree_xcd_bwd_lds(p.MT, capacity + step) <= dev.lds - 1024)
+            capacity += step;
+    if (capacity == 0) return p;
+    p.on = treex::cut_batch(t->num_trees, s.N, s.level_nodes, s.level_offsets, s.num_levels, tree_of_nodes(t, s),
+                            std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut);
+    p.fwd_lds = tree_xcd_fwd_lds(p.NT, p.cut.most_nodes);
+    p.bwd_lds = tree_xcd_bwd_lds(p.MT, p.cut.most_nodes);
+    return p;
+}
+// workgroups of a launch whose groups have nu members
+int tree_xcd_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
+
+unsigned fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
+
+template <int NT>
+janus_status launch_tree_fwd(const TreeXcdPlan& p, const treex::LstmFwd& a, hipStream_t st) {
+    static size_t attr = 0;
+    return tree_persistent_launch(treex::treelstm_fwd_xcd<NT>, tree_xcd_blocks(p.cut, p.fwd_nu), p.fwd_lds, a, st, attr,
+                                  treex::kThreads);
+}
+template <int MT>
+janus_status launch_tree_bwd(const TreeXcdPlan& p, const treex::LstmBwd& a, hipStream_t st) {
+    static size_t attr = 0;
+    return tree_persistent_launch(treex::treelstm_bwd_xcd<MT>, tree_xcd_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
+                                  treex::kThreads);
+}
+
+janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
+                                   const TreeWs& w, const TreeXcdPlan& p, const void* emb, const void* W, const void* U,
+                                   const void* b, void* h_root, hipStream_t st) {
     TreeHost h;
-    build_host(t, s, h);
+    build_host(t, s.N, p.cut.order, p.cut.pos, h);
     const size_t nb = sizeof(int32_t) * s.N;
-    const std::vector<char> zero_sync(sizeof(tpersist::TreeSync), 0);
     const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},
                                   {w.lchild, h.lchild.data(), nb},
                                   {w.rchild, h.rchild.data(), nb},
                                   {w.parent, h.parent.data(), nb},
                                   {w.rootk, h.rootk.data(), nb},
                                   {w.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
-                                  {w.loff, s.level_offsets.data(), sizeof(int32_t) * s.level_offsets.size()},
-                                  {w.tsync, zero_sync.data(), zero_sync.size()}};
+                                  {w.xgroup, p.cut.group.data(), sizeof(treex::Group) * p.cut.group.size()},
+                                  {w.xtile, p.cut.tile.data(), sizeof(treex::Tile) * p.cut.tile.size()}};
     janus_status e = upload_pieces(pieces, 8, st);
     if (e != JANUS_OK) return e;
-    tpersist::FwdArgs a;
+    const int M0 = s.level_offsets[1];
+    treex::LstmFwd a = {};
     a.E = d.E;
     a.H = d.H;
-    a.N = s.N;
-    a.M0 = s.level_offsets[1];
-    a.nlev = s.num_levels;
-    a.ngroups = plan.ngroups;
-    a.loff = w.loff;
-    a.lword = w.lword;
+    a.M0 = M0;
+    a.groups = p.cut.groups;
+    a.nu = p.fwd_nu;
+    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.tile = w.xtile;
     a.lchild = w.lchild;
     a.rchild = w.rchild;
     a.parent = w.parent;
     a.rootk = w.rootk;
-    a.emb = static_cast<const float*>(emb);
     a.W = static_cast<const float*>(W);
     a.U = static_cast<const float*>(U);
     a.b = static_cast<const float*>(b);
+    a.x = w.xl;
+    a.ldx = w.ldx;
+    a.x_bytes = uint32_t(int64_t(M0) * w.ldx * 4);
+    a.hx = w.hx;
+    a.ldh = w.ldc;
+    a.hx_bytes = uint32_t(int64_t(s.N) * w.ldc * 4);
     a.G = w.Gp;
     a.ldg = w.ldg;
     a.C = w.Cp;
@@ -404,82 +468,137 @@ janus_status treelstm_fwd_persistent_call(const janus_treelstm_desc& d, const ja
     a.ldl = w.ldl;
     a.h_root = static_cast<float*>(h_root);
     a.sync = w.tsync;
-    static size_t attr = 0;
-    const double flops = 2.0 * 5.0 * d.H * (double(a.M0) * d.E + double(s.N - a.M0) * 2.0 * d.H);
-    TraceScope trace("treelstm_fwd_persistent", flops, 0.0, st);
-    return tree_persistent_launch(tpersist::treelstm_fwd_persistent, plan.fwd_grid, plan.fwd_lds, a, st, attr);
+    for (int part = 0; part < p.cut.parts; ++part) {
+        if (part == 0) {
+            TraceScope trace("tree_fwd_init", 0.0, 4.0 * (double(s.N) * w.ldc + 2.0 * M0 * w.ldx), st);
+            hipLaunchKernelGGL(treex::fwd_init_kernel, dim3(fill_blocks(int64_t(s.N) * w.ldc + int64_t(M0) * w.ldx)),
+                               dim3(256), 0, st, s.N, M0, d.E, w.lword, static_cast<const float*>(emb), w.xl, w.ldx,
+                               w.hx, w.ldc, d.H, w.tsync);
+        } else {   // the counters of the next launch
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(4), dim3(256), 0, st, w.hx, w.ldc, int64_t(0), int64_t(0), d.H,
+                               w.tsync);
+        }
+        JANUS_LAUNCH_CHECK();
+        a.group = w.xgroup + part * p.cut.groups;
+        const double flops = 2.0 * 5.0 * d.H * (double(M0) * d.E + double(s.N - M0) * 2.0 * d.H) / p.cut.parts;
+        TraceScope trace("treelstm_fwd_persistent", flops, 0.0, st);
+        e = p.NT == 1   ? launch_tree_fwd<1>(p, a, st)
+            : p.NT == 2 ? launch_tree_fwd<2>(p, a, st)
+            : p.NT == 3 ? launch_tree_fwd<3>(p, a, st)
+                        : launch_tree_fwd<4>(p, a, st);
+        if (e != JANUS_OK) return e;
+    }
+    return JANUS_OK;
 }
 
-// Backward on the persistent path: the schedule is the forward's (the
-// workspace is unchanged between the two calls); the leaves grouped by word
-// and the barrier's counters (not its error flag) go over in one copy, then
-// one launch runs the levels, the weight and input gradients and the
-// embedding gradient.
-janus_status treelstm_bwd_persistent_call(const janus_treelstm_desc& d, const janus_tree_batch* t,
-                                          const TreeSchedule& s, const TreeWs& w, const TreePlan& plan,
-                                          const void* emb, const void* W, const void* U, const void* dh_root,
-                                          float* demb, float* dW, float* dU, float* db, hipStream_t st) {
-    TreeHost h;
-    build_host(t, s, h);
+// The backward's levels in groups of trees per XCD: dA of every node.
+janus_status treelstm_bwd_xcd_levels(const janus_treelstm_desc& d, const TreeSchedule& s, const TreeWs& w,
+                                     const TreeXcdPlan& p, const void* U, const void* dh_root, hipStream_t st) {
     const int M0 = s.level_offsets[1];
-    std::vector<int32_t> seg;
-    const int nseg = embed_segments(h.lword.data(), M0, d.V, seg);
-    // first group of each workgroup's rows [V w / grid, V (w + 1) / grid)
-    const int32_t* sid = seg.data() + M0 + nseg + 1;
-    for (int g = 0; g < plan.bwd_grid; ++g) {
-        const int64_t v0 = int64_t(d.V) * g / plan.bwd_grid;
-        seg.push_back(int32_t(std::lower_bound(sid, sid + nseg, v0) - sid));
-        sid = seg.data() + M0 + nseg + 1;   // push_back may move the array
-    }
-    const size_t counters = sizeof(tpersist::TreeSync) - tpersist::kTreeSyncCounters;
-    const std::vector<char> zero_counters(counters, 0);
-    const UploadPiece pieces[] = {
-        {reinterpret_cast<char*>(w.tsync) + tpersist::kTreeSyncCounters, zero_counters.data(), counters},
-        {w.seg, seg.data(), seg.size() * sizeof(int32_t)}};
-    janus_status e = upload_pieces(pieces, 2, st);
-    if (e != JANUS_OK) return e;
-    tpersist::BwdArgs a;
-    a.E = d.E;
+    treex::LstmBwd a = {};
     a.H = d.H;
-    a.N = s.N;
     a.M0 = M0;
-    a.nlev = s.num_levels;
-    a.ncol = plan.ncol;
-    a.nseg = nseg;
-    a.V = d.V;
-    a.loff = w.loff;
-    a.lword = w.lword;
+    a.groups = p.cut.groups;
+    a.nu = p.bwd_nu;
+    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.tile = w.xtile;
     a.lchild = w.lchild;
     a.rchild = w.rchild;
     a.rootk = w.rootk;
-    a.seg = w.seg;
-    a.emb = static_cast<const float*>(emb);
-    a.W = static_cast<const float*>(W);
     a.U = static_cast<const float*>(U);
     a.G = w.Gp;
     a.ldg = w.ldg;
     a.C = w.Cp;
     a.ldc = w.ldc;
-    a.HLR = w.HLRp;
-    a.ldl = w.ldl;
     a.dh_root = static_cast<const float*>(dh_root);
-    a.dh = w.dhp;
-    a.dc = w.dcp;
     a.dA = w.dAp;
     a.lda = w.lda;
-    a.dxl = w.dxp;
-    a.ldx = w.ldx;
-    a.demb = demb;
-    a.dW = dW;
-    a.dU = dU;
-    a.db = db;
+    a.dA_bytes = uint32_t(int64_t(s.N) * w.lda * 4);
     a.sync = w.tsync;
-    static size_t attr = 0;
-    // [dh_L; dh_R] = dA U on internal nodes, dU, dW and dx_leaf
-    const double Nint = double(s.N - M0);
-    const double flops = 2.0 * 5.0 * d.H * (Nint * 2.0 * d.H * 2.0 + double(M0) * d.E * 2.0);
-    TraceScope trace("treelstm_bwd_persistent", flops, 0.0, st);
-    return tree_persistent_launch(tpersist::treelstm_bwd_persistent, plan.bwd_grid, plan.bwd_lds, a, st, attr);
+    for (int part = 0; part < p.cut.parts; ++part) {
+        const int64_t rows = part == 0 ? s.N - M0 : 0;
+        {
+            TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(rows) * w.lda, st);
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(fill_blocks(rows * w.lda + 4096)), dim3(256), 0, st, w.dAp, w.lda,
+                               int64_t(M0), rows, 5 * d.H, w.tsync);
+            JANUS_LAUNCH_CHECK();
+        }
+        a.group = w.xgroup + part * p.cut.groups;
+        TraceScope trace("treelstm_bwd_persistent", 2.0 * 5.0 * d.H * double(s.N - M0) * 2.0 * d.H / p.cut.parts, 0.0, st);
+        const janus_status e = p.MT == 1 ? launch_tree_bwd<1>(p, a, st) : launch_tree_bwd<2>(p, a, st);
+        if (e != JANUS_OK) return e;
+    }
+    return JANUS_OK;
+}
+
+// Backward: the schedule is the forward's (the workspace is unchanged between
+// the two calls); the leaves grouped by word go over in one copy, then the
+// levels, the contractions over nodes and the embedding gradient.
+janus_status treelstm_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
+                                   const TreeWs& w, const TreeXcdPlan& p, const void* W, const void* U,
+                                   const void* dh_root, float* demb, float* dW, float* dU, float* db, hipStream_t st) {
+    const int M0 = s.level_offsets[1], Nint = s.N - M0, H = d.H, E = d.E;
+    std::vector<int32_t> lword(M0);
+    for (int i = 0; i < M0; ++i) lword[i] = t->word[p.cut.order[i]];
+    std::vector<int32_t> seg;
+    const int nseg = embed_segments(lword.data(), M0, d.V, seg);
+    janus_status e;
+    if ((e = upload(w.seg, seg.data(), seg.size() * sizeof(int32_t), st)) != JANUS_OK) return e;
+    if ((e = treelstm_bwd_xcd_levels(d, s, w, p, U, dh_root, st)) != JANUS_OK) return e;
+    TailArgs a;
+    GemmDesc g;
+    g.dtype = JANUS_F32;
+    // dU = dA_int^T [h_L; h_R]
+    g.M = 5 * H;
+    g.N = 2 * H;
+    g.K = Nint;
+    g.a_t = g.b_t = true;
+    g.A = w.dAp + int64_t(M0) * w.lda;
+    g.lda = w.lda;
+    g.B = w.HLRp;
+    g.ldb = w.ldl;
+    g.C = dU;
+    g.ldc = 2 * H;
+    tail_add(a, g, w.tpart);
+    // dW = dA_leaf^T x
+    g.N = E;
+    g.K = M0;
+    g.A = w.dAp;
+    g.B = w.xl;
+    g.ldb = w.ldx;
+    g.C = dW;
+    g.ldc = E;
+    tail_add(a, g, w.tpart + tail_part_floats(5 * H, 2 * H));
+    // dx = dA_leaf W, in up to three parts that the embedding rows add up
+    g.M = M0;
+    g.K = 5 * H;
+    g.a_t = false;
+    g.B = W;
+    g.ldb = E;
+    g.C = nullptr;
+    tail_add(a, g, w.dxp, 3);
+    TailProblem& dx = a.p[a.n - 1];
+    if (dx.splits == 1) {
+        dx.g.C = w.dxp;
+        dx.g.ldc = E;
+    }
+    a.dx = w.dxp;
+    a.ldx = E;
+    a.dx_parts = dx.splits;
+    a.dx_stride = int64_t(M0) * E;
+    a.src = w.dAp;
+    a.ld = w.lda;
+    a.rows = s.N;
+    a.cols = 5 * H;
+    a.sum_part = w.tsum;
+    a.sum_out = db;
+    a.demb = demb;
+    a.demb_n = int64_t(d.V) * E;
+    a.E = E;
+    a.leaves = M0;
+    a.nseg = nseg;
+    a.seg = w.seg;
+    return tail_run(a, "treelstm_bwd_tail", st);
 }
 
 // ------------------------------------------------------------------ TreeRNN
@@ -596,8 +715,8 @@ extern "C" janus_status janus_treelstm_fwd(const janus_treelstm_desc* d, const j
     janus_status e = prepare(d, t, ws, ws_bytes, s, w);
     if (e != JANUS_OK) return e;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const TreePlan plan = tree_plan(*d);
-    if (plan.on) return treelstm_fwd_persistent_call(*d, t, s, w, plan, emb, W, U, b, h_root, st);
+    const TreeXcdPlan xp = tree_xcd_plan(*d, t, s);
+    if (xp.on) return treelstm_fwd_xcd_call(*d, t, s, w, xp, emb, W, U, b, h_root, st);
     if ((e = upload_tree(t, s, w, st)) != JANUS_OK) return e;
     const int H = d->H, E = d->E;
     const int M0 = s.level_offsets[1];
@@ -638,9 +757,8 @@ extern "C" janus_status janus_treelstm_bwd(const janus_treelstm_desc* d, const j
     if (e != JANUS_OK) return e;
     const int M0 = s.level_offsets[1];
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const TreePlan plan = tree_plan(*d);
-    if (plan.on)
-        return treelstm_bwd_persistent_call(*d, t, s, w, plan, emb, W, U, dh_root, demb, dW, dU, db, st);
+    const TreeXcdPlan xp = tree_xcd_plan(*d, t, s);
+    if (xp.on) return treelstm_bwd_xcd_call(*d, t, s, w, xp, W, U, dh_root, demb, dW, dU, db, st);
     TreeHost host;
     if ((e = upload_tree(t, s, w, st, &host)) != JANUS_OK) return e;
     const int H = d->H, E = d->E, N = s.N;

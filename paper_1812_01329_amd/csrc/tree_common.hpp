@@ -35,6 +35,7 @@ struct TreeSync {
     unsigned pad0[63];
     unsigned xcd[16][64];
     unsigned census[16][64];
+    unsigned group[64][64];     // arrivals of each tree group's workgroups (groups that share no L2)
 };
 constexpr size_t kTreeSyncCounters = offsetof(TreeSync, count);   // byte offset of the counters
 
@@ -489,6 +490,7 @@ constexpr int kMaxTreeGrid = 4096;   // workgroups of a persistent tree launch (
 struct TreeDev {
     int cus = 0;
     size_t lds = 0;
+    int xccs = 0;
 };
 // Properties of the current device, queried once per device under a lock.
 inline TreeDev tree_dev() {
@@ -503,6 +505,7 @@ inline TreeDev tree_dev() {
         int v = 0;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) t.cus = v;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) t.lds = size_t(v);
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeNumberOfXccs, dev) == hipSuccess) t.xccs = v;
         (void)hipGetLastError();
         cache[dev] = t;
         have[dev] = true;
@@ -515,7 +518,7 @@ inline TreeDev tree_dev() {
 // confirms one fits a CU).  The barrier's waits are bounded.
 template <class K, class A>
 inline janus_status tree_persistent_launch(K kernel, int blocks, size_t smem, const A& args, hipStream_t st,
-                                    size_t& attr_smem) {
+                                           size_t& attr_smem, int threads = kThreads) {
     static std::mutex m;
     {
         std::lock_guard<std::mutex> lock(m);
@@ -527,10 +530,10 @@ inline janus_status tree_persistent_launch(K kernel, int blocks, size_t smem, co
     }
     int per_cu = 0;
     JANUS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel),
-                                                           kThreads, smem));
+                                                           threads, smem));
     if (per_cu < 1 || int64_t(per_cu) * tree_dev().cus < blocks) return JANUS_ERR_UNSUPPORTED;
     ResidentTurn turn(st);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), smem, st, args);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), smem, st, args);
     JANUS_LAUNCH_CHECK();
     return JANUS_OK;
 }

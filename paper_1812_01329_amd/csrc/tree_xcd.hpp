@@ -1,0 +1,619 @@
+// Tree level programs whose groups of trees each live on one XCD.
+//
+// Trees of a batch are independent, so a level's exchange of h (forward) or
+// of the pre-activation gradients (backward) is needed only among the
+// workgroups that work the same trees.  The batch is cut in groups of whole
+// trees, one per XCD, worked by NU workgroups (at most the CUs of an XCD) of
+// that XCD; workgroup m owns units [U m, U m + U), keeps their weights in
+// VGPRs for the whole launch, and handles them for every node of its group.
+// The nodes go through in tiles of 16, level by level.
+//
+// What bounds a level is the chain "publish -> load -> MFMA -> sum over the
+// waves -> cell"; its MFMA work is under 1 us at H 150.  A device-wide barrier
+// per level (about 2 us, after write-through stores) is replaced by the data
+// itself, as in the LSTM recurrence: a row that other workgroups read is
+// prefilled with a pattern no result takes, stored once, and loaded until no
+// word holds the pattern, all in the XCD's L2.  Everything else a node needs
+// from its children or parent (c, dc, dh of the owned units) stays in the LDS
+// of the workgroup that owns the unit.
+//
+// Measured, forward and backward levels of the binary TreeLSTM against the
+// kernels with a device-wide barrier per level: 25 trees of 5-50 leaves, H
+// 150: 61 and 58 us against 116 and about 120; 100 trees, H 300, against one
+// launch per level: 282 and 252 us against 950 and 720.
+#pragma once
+
+#include <algorithm>
+#include <vector>
+
+#include "lstm_xcd.hpp"
+#include "tree_common.hpp"
+
+namespace janus {
+namespace treex {
+
+using persist::kOutOfRange;
+using persist::make_rsrc;
+using tpersist::TreeSync;
+using xcd::f32x4_t;
+using xcd::kEmpty;
+using xcd::not_empty;
+
+constexpr int kThreads = xcd::kThreads;
+constexpr int kWaves = xcd::kWaves;
+constexpr int kRows = 16;        // nodes of a tile
+
+// One group's part of the launch: nodes by position (leaves first, then the
+// internal nodes; both contiguous per group), its tiles in order.  The tiles
+// [t0, t1) start with the `leaf_tiles` tiles of leaves.
+struct Group {
+    int leaf0, nleaf, int0, nint;
+    int t0, t1, leaf_tiles, pad;
+};
+// A tile: first position and (rows | level << 8).
+struct Tile {
+    int p0, rows_level;
+};
+__device__ __forceinline__ int tile_rows(Tile t) { return t.rows_level & 0xff; }
+__device__ __forceinline__ int tile_level(Tile t) { return t.rows_level >> 8; }
+// The tiles of a group, read 64 at a time into one register of the wave, so
+// that a tile's extent costs no load when its turn comes.
+struct TileWindow {
+    const Tile* tile;
+    int base, end;     // tiles [base, base + 64) of those below `end` are held
+    int p0, rl;        // this lane's tile
+    __device__ __forceinline__ void load(int first) {
+        base = first;
+        const int i = min(max(first + int(threadIdx.x & 63), 0), end - 1);
+        p0 = tile[i].p0;
+        rl = tile[i].rows_level;
+    }
+    __device__ __forceinline__ void init(const Tile* t, int e, int first) {
+        tile = t;
+        end = e;
+        load(first);
+    }
+    // tile i (the same for every lane); `down`: a miss loads the 64 tiles that end with it
+    __device__ __forceinline__ Tile at(int i, bool down = false) {
+        if (i < base || i >= base + 64) load(down ? max(i - 63, 0) : i);
+        Tile r;
+        r.p0 = __builtin_amdgcn_readlane(p0, i - base);
+        r.rows_level = __builtin_amdgcn_readlane(rl, i - base);
+        return r;
+    }
+};
+// index of a position among its group's nodes
+__device__ __forceinline__ int local_of(const Group& g, int M0, int p) {
+    return p < M0 ? p - g.leaf0 : g.nleaf + p - g.int0;
+}
+
+// ------------------------------------------------------------------ set-up
+// Rows [r0, r0 + rows) of a row array of pitch ld: columns below `cols` hold
+// the pattern, the padding zero.
+__device__ __forceinline__ void fill_empty(float* a, int64_t ld, int64_t r0, int64_t rows, int cols, int64_t i0,
+                                           int64_t stride) {
+    const int q = int(ld / 4);   // 16-byte pieces of a row
+    uint4* d = reinterpret_cast<uint4*>(a + r0 * ld);
+    for (int64_t i = i0; i < rows * q; i += stride) {
+        const int c = 4 * int(i % q);
+        d[i] = make_uint4(c < cols ? kEmpty : 0u, c + 1 < cols ? kEmpty : 0u, c + 2 < cols ? kEmpty : 0u,
+                          c + 3 < cols ? kEmpty : 0u);
+    }
+}
+__device__ __forceinline__ void zero_counters(TreeSync* s, int64_t i0, int64_t stride) {
+    uint32_t* c = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s) + tpersist::kTreeSyncCounters);
+    for (int64_t i = i0; i < int64_t((sizeof(TreeSync) - tpersist::kTreeSyncCounters) / 4); i += stride) c[i] = 0u;
+}
+// Empty rows and zero counters (not the error flag).
+static __global__ __launch_bounds__(256) void fill_kernel(float* a, int64_t ld, int64_t r0, int64_t rows, int cols,
+                                                   TreeSync* s) {
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    zero_counters(s, i0, stride);
+    fill_empty(a, ld, r0, rows, cols, i0, stride);
+}
+// Forward: the leaves' word vectors gathered into padded rows x (pitch ldx,
+// zero past E), every node's row of h empty, counters and error flag zero.
+static __global__ __launch_bounds__(256) void fwd_init_kernel(int N, int M0, int E, const int32_t* lword, const float* emb,
+                                                       float* x, int64_t ldx, float* hx, int64_t ldh, int H,
+                                                       TreeSync* s) {
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    zero_counters(s, i0, stride);
+    if (i0 == 0) s->error = 0u;
+    fill_empty(hx, ldh, 0, N, H, i0, stride);
+    for (int64_t i = i0; i < int64_t(M0) * ldx; i += stride) {
+        const int p = int(i / ldx), e = int(i % ldx);
+        x[i] = e < E ? emb[int64_t(lword[p]) * E + e] : 0.f;
+    }
+}
+
+// Sum of the waves' partial values of element (m, n) of the row tiles: the
+// partial tiles lie [wave][tile][lane][4], lane l holding rows 4 (l / 16) + v,
+// column l % 16.
+template <int NT>
+__device__ __forceinline__ float sum_waves(const float* red, int m, int n) {
+    const int o = ((m >> 4) * 64 + ((m & 15) >> 2) * 16 + n) * 4 + (m & 3);
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += red[w * NT * 256 + o];
+    return s;
+}
+
+// A weight fragment: row r of a [rows x K] matrix of pitch ld, columns k ..
+// k + 3, zero for r < 0 and past K.
+__device__ __forceinline__ uint4 weight4(const float* W, int64_t ld, int r, int k, int K) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (r >= 0 && k < K) {
+        const float* p = W + int64_t(r) * ld + k;
+        v.x = __float_as_uint(p[0]);
+        if (k + 1 < K) v.y = __float_as_uint(p[1]);
+        if (k + 2 < K) v.z = __float_as_uint(p[2]);
+        if (k + 3 < K) v.w = __float_as_uint(p[3]);
+    }
+    return v;
+}
+
+// ------------------------------------------------------- TreeLSTM, forward
+struct LstmFwd {
+    int E, H, M0;
+    int groups, nu, force_remote;
+    const Group* group;        // of this launch
+    const Tile* tile;
+    const int32_t* lchild;
+    const int32_t* rchild;
+    const int32_t* parent;     // 2 * position + side, -1 for roots
+    const int32_t* rootk;
+    const float* W;            // [5H x E]
+    const float* U;            // [5H x 2H]
+    const float* b;
+    const float* x;            // [M0 x ldx] leaf inputs
+    int64_t ldx;
+    uint32_t x_bytes;
+    float* hx;                 // [N x ldh] h of every node (exchange)
+    int64_t ldh;
+    uint32_t hx_bytes;
+    float* G;                  // [N x ldg] gates after activation, gate-major
+    int64_t ldg;
+    float* C;                  // [N x ldc]
+    int64_t ldc;
+    float* HLR;                // [(N - M0) x ldl]
+    int64_t ldl;
+    float* h_root;
+    TreeSync* sync;
+};
+
+// NT 16-row tiles hold the 5 gates of U = floor(16 NT / 5) units.  The waves
+// split the k-groups of 16 (left child's h, right child's h; or the leaf
+// input): at most J per wave.
+template <int NT>
+struct LstmFwdCfg {
+    static constexpr int U = 16 * NT / 5;
+    static constexpr int J = NT <= 2 ? 4 : NT == 3 ? 5 : 6;
+    static constexpr int RED = kWaves * NT * 256;   // floats of one set of partial tiles
+    // cells' c of the group's nodes follow the two sets
+    static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
+};
+
+template <int NT>
+__global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
+    using C = LstmFwdCfg<NT>;
+    constexpr int U = C::U, J = C::J;
+    extern __shared__ __align__(16) float sm[];
+    float* cl = sm + 2 * C::RED;   // [nodes][U]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    const int H = a.H, E = a.E, v0 = m * U;
+    const int KH = (H + 15) / 16;   // k-groups of one child
+
+    // row m of tile i: gate r % 5 of unit v0 + r / 5, r = 16 i + lr
+    uint4 w[NT][J];
+    auto gate_row = [&](int i) -> int {
+        const int r = 16 * i + lr, u = v0 + r / 5;
+        return r < 5 * U && u < H ? (r % 5) * H + u : -1;
+    };
+    // this wave's k-groups of nk: [kw0, kw1), at most J
+    auto share = [&](int nk, int& k0, int& k1) {
+        k0 = wave * nk / kWaves;
+        k1 = (wave + 1) * nk / kWaves;
+    };
+    int kw0, kw1;
+    share((E + 15) / 16, kw0, kw1);
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            w[i][j] = kw0 + j < kw1 ? weight4(a.W, E, gate_row(i), 16 * (kw0 + j) + 4 * lq, E) : make_uint4(0, 0, 0, 0);
+
+    // cells: thread (unit cu, node cn) of the tile
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    float bias[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) bias[q] = cell_thread ? a.b[q * H + cj] : 0.f;
+
+    bool dead = false;
+    unsigned phase = 0;
+    TileWindow win;
+    win.init(a.tile, gr.t1, gr.t0);
+    // a tile's links, loaded while the tile before it is worked: the operand
+    // rows of this lane's node, and the cell's children, parent and root slot
+    struct Links {
+        int ql, qr, lc, rc, par, rk;
+    };
+    auto links = [&](int t) {
+        const Tile tl = win.at(t);
+        Links k;
+        const int q = tl.p0 + min(lr, tile_rows(tl) - 1), p = tl.p0 + min(cn, tile_rows(tl) - 1);
+        k.ql = a.lchild[q];
+        k.qr = a.rchild[q];
+        k.lc = a.lchild[p];
+        k.rc = a.rchild[p];
+        k.par = a.parent[p];
+        k.rk = a.rootk[p];
+        return k;
+    };
+    Links next = links(gr.t0);
+    for (int t = gr.t0; t < gr.t1; ++t) {
+        const Tile tl = win.at(t);
+        const int rows = tile_rows(tl), ti = t - gr.t0;
+        const bool leaf = ti < gr.leaf_tiles;
+        if (ti == gr.leaf_tiles) {   // the internal nodes' weights
+            share(2 * KH, kw0, kw1);
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int kg = kw0 + j, side = kg >= KH;
+                    const int k = 16 * (kg - side * KH) + 4 * lq;
+                    w[i][j] = kg < kw1 ? weight4(a.U + side * H, 2 * H, gate_row(i), k, H) : make_uint4(0, 0, 0, 0);
+                }
+        }
+        const Links k = next;
+        const int p = tl.p0 + cn;
+        const bool cell = cell_thread && cn < rows;
+        f32x4_t acc[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        uint4 f[J];
+        if (leaf) {
+            const auto rs = make_rsrc(a.x, a.x_bytes);
+            xcd::load_operand<float>(f, rs, [&](int j) {
+                const int kg = kw0 + j;
+                return lr < rows && kg < kw1
+                           ? (uint32_t(tl.p0 + lr) * uint32_t(a.ldx) + uint32_t(16 * kg + 4 * lq)) * 4u
+                           : kOutOfRange;
+            }, false, a.sync, dead);
+        } else {
+            if (!local) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+            const auto rs = make_rsrc(a.hx, a.hx_bytes);
+            const uint32_t ol = uint32_t(k.ql) * uint32_t(a.ldh), orr = uint32_t(k.qr) * uint32_t(a.ldh);
+            xcd::load_operand<float>(f, rs, [&](int j) {
+                const int kg = kw0 + j;
+                const uint32_t o = kg < KH ? ol + uint32_t(16 * kg) : orr + uint32_t(16 * (kg - KH));
+                return lr < rows && kg < kw1 ? (o + uint32_t(4 * lq)) * 4u : kOutOfRange;
+            }, local, a.sync, dead);
+        }
+        if (t + 1 < gr.t1) next = links(t + 1);
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) acc[i] = xcd::mma(w[i][j], f[j], acc[i], static_cast<const float*>(nullptr));
+        float* red = sm + (t & 1) * C::RED;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) reinterpret_cast<f32x4_t*>(red)[(wave * NT + i) * 64 + lane] = acc[i];
+        __syncthreads();
+        if (cell) {
+            float z[5];
+#pragma unroll
+            for (int q = 0; q < 5; ++q) z[q] = bias[q] + sum_waves<NT>(red, 5 * cu + q, cn);
+            const float gi = sigmoidf_(z[0]), gl = sigmoidf_(z[1]), gr_ = sigmoidf_(z[2]), go = sigmoidf_(z[3]);
+            const float gu = tanhf_(z[4]);
+            float c = gi * gu;
+            if (!leaf) c += gl * cl[local_of(gr, a.M0, k.lc) * U + cu] + gr_ * cl[local_of(gr, a.M0, k.rc) * U + cu];
+            const float h = go * tanhf_(c);
+            // published for the tiles above
+            if (k.par >= 0)
+                xcd::store_b32(make_rsrc(a.hx, a.hx_bytes), (uint32_t(p) * uint32_t(a.ldh) + uint32_t(cj)) * 4u,
+                               not_empty(__float_as_uint(h)));
+            cl[local_of(gr, a.M0, p) * U + cu] = c;
+            a.C[int64_t(p) * a.ldc + cj] = c;
+            float* gp = a.G + int64_t(p) * a.ldg + cj;
+            gp[0] = gi;
+            gp[H] = gl;
+            gp[2 * H] = gr_;
+            gp[3 * H] = go;
+            gp[4 * H] = gu;
+            if (k.par >= 0) a.HLR[int64_t((k.par >> 1) - a.M0) * a.ldl + (k.par & 1) * H + cj] = h;
+            else a.h_root[int64_t(k.rk) * H + cj] = h;
+        }
+    }
+}
+
+// ------------------------------------------------------ TreeLSTM, backward
+struct LstmBwd {
+    int H, M0;
+    int groups, nu, force_remote;
+    const Group* group;
+    const Tile* tile;          // the forward's tiles, walked backwards
+    const int32_t* lchild;
+    const int32_t* rchild;
+    const int32_t* rootk;
+    const float* U;
+    const float* G;
+    int64_t ldg;
+    const float* C;
+    int64_t ldc;
+    const float* dh_root;
+    float* dA;                 // [N x lda] gate-major; internal rows are the exchange
+    int64_t lda;
+    uint32_t dA_bytes;
+    TreeSync* sync;
+};
+
+// MT 16-row tiles hold [dh_L; dh_R] of U = 8 MT units (row 2 u + side); K =
+// 5H gate columns in k-groups of 16, at most J per wave.
+template <int MT>
+struct LstmBwdCfg {
+    static constexpr int U = 8 * MT;
+    static constexpr int J = MT == 1 ? 10 : 15;
+    static constexpr int RED = kWaves * MT * 256;
+    // then dh and dc of the group's nodes, [nodes][U] each
+    static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + 2 * size_t(nodes) * U); }
+};
+
+template <int MT>
+__global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
+    using C = LstmBwdCfg<MT>;
+    constexpr int U = C::U, J = C::J;
+    extern __shared__ __align__(16) float sm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    float* dhl = sm + 2 * C::RED;                          // [nodes][U]
+    float* dcl = dhl + int64_t(gr.nleaf + gr.nint) * U;    // [nodes][U]
+    const int H = a.H, K = 5 * H, v0 = m * U;
+    const int nk = (K + 15) / 16, kw0 = wave * nk / kWaves, kw1 = (wave + 1) * nk / kWaves;
+
+    // row r = 16 i + lr: column side * H + unit of U, unit v0 + r / 2, side r % 2
+    uint4 w[MT][J];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int r = 16 * i + lr, u = v0 + (r >> 1), k = 16 * (kw0 + j) + 4 * lq;
+            float tmp[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                tmp[e] = u < H && kw0 + j < kw1 && k + e < K ? a.U[int64_t(k + e) * 2 * H + (r & 1) * H + u] : 0.f;
+            w[i][j] = make_uint4(__float_as_uint(tmp[0]), __float_as_uint(tmp[1]), __float_as_uint(tmp[2]),
+                                 __float_as_uint(tmp[3]));
+        }
+
+    // cells: thread (unit cu, node cn); their inputs are loaded a tile ahead
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    struct In {
+        int p, lc, rc, rk;
+        int ch;                          // child of this thread's element of [dh_L; dh_R]
+        float g[5], c, cl, cr, dhr;
+    } in;
+    TileWindow win;
+    win.init(a.tile, gr.t1, max(gr.t1 - 64, gr.t0));
+    auto fetch = [&](int t, In& x) {
+        const Tile tl = win.at(t, true);
+        {
+            const int q = tl.p0 + min(tid & 15, tile_rows(tl) - 1);
+            x.ch = (tid >> 4 & 1) ? a.rchild[q] : a.lchild[q];
+        }
+        const bool ok = cell_thread && cn < tile_rows(tl);
+        x.p = ok ? tl.p0 + cn : -1;
+        const int p = ok ? x.p : tl.p0, j = cell_thread ? cj : 0;
+        x.lc = a.lchild[p];
+        x.rc = a.rchild[p];
+        x.rk = a.rootk[p];
+        const float* gp = a.G + int64_t(p) * a.ldg + j;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) x.g[q] = gp[q * H];
+        x.c = a.C[int64_t(p) * a.ldc + j];
+        x.cl = a.C[int64_t(x.lc >= 0 ? x.lc : p) * a.ldc + j];
+        x.cr = a.C[int64_t(x.rc >= 0 ? x.rc : p) * a.ldc + j];
+        x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+    };
+    // cell backward of a tile: dA published (internal) or stored (leaves),
+    // the children's dc into LDS
+    auto cells = [&](const In& x) {
+        if (x.p < 0) return;
+        const int lo = local_of(gr, a.M0, x.p) * U + cu;
+        const bool leaf = x.p < a.M0;
+        const float dh = x.rk >= 0 ? x.dhr : dhl[lo], dc = x.rk >= 0 ? 0.f : dcl[lo];
+        const float gi = x.g[0], gl = x.g[1], gr_ = x.g[2], go = x.g[3], gu = x.g[4];
+        const float tau = tanhf_(x.c);
+        const float d_o = dh * tau;
+        const float dct = dc + dh * go * (1.f - tau * tau);
+        float da[5];
+        da[0] = dct * gu * gi * (1.f - gi);
+        da[1] = leaf ? 0.f : dct * x.cl * gl * (1.f - gl);
+        da[2] = leaf ? 0.f : dct * x.cr * gr_ * (1.f - gr_);
+        da[3] = d_o * go * (1.f - go);
+        da[4] = dct * gi * (1.f - gu * gu);
+        const auto rs = make_rsrc(a.dA, a.dA_bytes);
+        const uint32_t o = (uint32_t(x.p) * uint32_t(a.lda) + uint32_t(cj)) * 4u;
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+            xcd::store_b32(rs, o + uint32_t(q) * uint32_t(H) * 4u, not_empty(__float_as_uint(da[q])));
+        if (!leaf) {
+            dcl[local_of(gr, a.M0, x.lc) * U + cu] = dct * gl;
+            dcl[local_of(gr, a.M0, x.rc) * U + cu] = dct * gr_;
+        }
+    };
+    static_assert(2 * U * 16 <= kThreads, "one element of a tile's [dh_L; dh_R] per thread: row 2 u + side, node");
+
+    bool dead = false;
+    unsigned phase = 0;
+    const int first_int = gr.t0 + gr.leaf_tiles;
+    int t = gr.t1 - 1;
+    fetch(t, in);
+    cells(in);
+    for (; t >= first_int; --t) {
+        const Tile tl = win.at(t, true);
+        const int rows = tile_rows(tl);
+        const bool more = t - 1 >= gr.t0;
+        const bool same = more && t - 1 >= first_int && tile_level(win.at(t - 1, true)) == tile_level(tl);
+        In nx = in;
+        if (more) fetch(t - 1, nx);
+        if (same) cells(nx);   // a tile of the same level needs nothing of this one
+        if (!local) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+        f32x4_t acc[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        uint4 f[J];
+        const auto rs = make_rsrc(a.dA, a.dA_bytes);
+        xcd::load_operand<float>(f, rs, [&](int j) {
+            return lr < rows && kw0 + j < kw1
+                       ? (uint32_t(tl.p0 + lr) * uint32_t(a.lda) + uint32_t(16 * (kw0 + j) + 4 * lq)) * 4u
+                       : kOutOfRange;
+        }, local, a.sync, dead);
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i] = xcd::mma(w[i][j], f[j], acc[i], static_cast<const float*>(nullptr));
+        float* red = sm + (t & 1) * C::RED;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) reinterpret_cast<f32x4_t*>(red)[(wave * MT + i) * 64 + lane] = acc[i];
+        __syncthreads();
+        {
+            const int r = tid >> 4, n = tid & 15;
+            if (r < 2 * U && n < rows && v0 + (r >> 1) < H)
+                dhl[local_of(gr, a.M0, in.ch) * U + (r >> 1)] = sum_waves<MT>(red, r, n);
+        }
+        __syncthreads();   // the children's dh and dc
+        if (more && !same) cells(nx);
+        in = nx;
+    }
+    // the remaining tiles of leaves (the first one is done above)
+    for (--t; t >= gr.t0; --t) {
+        fetch(t, in);
+        cells(in);
+    }
+}
+
+// ------------------------------------------------------------- host side
+constexpr int kMaxGroups = 64;        // groups of one launch
+constexpr int kMaxParts = 16;         // launches of a batch at most
+constexpr size_t kGroupInts = size_t(kMaxGroups) * kMaxParts * (sizeof(Group) / 4);
+
+// Cut of a batch: its trees in parts (one launch each) of `groups` groups.
+// order lists the nodes by position: all leaves, then all internal nodes, in
+// each by (group, level, id).
+struct Cut {
+    int groups = 0, parts = 0, blocks = 0, nu = 0;
+    int most_nodes = 0;                // nodes of the largest group
+    std::vector<Group> group;          // [parts * groups]
+    std::vector<Tile> tile;
+    std::vector<int32_t> order;        // position -> node
+    std::vector<int32_t> pos;          // node -> position
+};
+
+// level_nodes: node ids by (level, id); level_offsets: their levels; tree[n]:
+// the tree of node n.  `capacity`: nodes a group may have (what its cells'
+// LDS holds).  False when the batch does not fit kMaxParts launches of groups
+// of nu workgroups each.
+inline bool cut_batch(int num_trees, int N, const std::vector<int32_t>& level_nodes,
+                      const std::vector<int32_t>& level_offsets, int num_levels, const std::vector<int32_t>& tree, int nu,
+                      int capacity, Cut& c) {
+    const tpersist::TreeDev dev = tpersist::tree_dev();
+    const int xccs = dev.xccs > 0 && dev.xccs <= persist::kMaxXcds ? dev.xccs : 1;
+    const int per_xcd = dev.cus / xccs;
+    if (per_xcd < nu) return false;
+    c.nu = nu;
+    c.groups = std::min({num_trees, xccs * (per_xcd / nu), kMaxGroups});
+    c.blocks = xccs * nu * ((c.groups + xccs - 1) / xccs);
+    std::vector<int32_t> size(num_trees, 0), by(num_trees);
+    for (int n = 0; n < N; ++n) ++size[tree[n]];
+    // trees from the largest on, each to the group with the fewest nodes
+    for (int k = 0; k < num_trees; ++k) by[k] = k;
+    std::sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return size[x] != size[y] ? size[x] > size[y] : x < y; });
+    std::vector<int32_t> bin(num_trees);
+    std::vector<int64_t> load;
+    for (c.parts = int(std::max<int64_t>(1, (int64_t(N) + int64_t(capacity) * c.groups - 1) / (int64_t(capacity) * c.groups)));;
+         ++c.parts) {
+        const int bins = c.parts * c.groups;
+        if (c.parts > kMaxParts || bins > num_trees + c.groups) return false;
+        load.assign(bins, 0);
+        std::vector<std::pair<int64_t, int>> heap;   // (-load, -bin): the least loaded, lowest bin on top
+        for (int b = 0; b < bins; ++b) heap.push_back({0, -b});
+        std::make_heap(heap.begin(), heap.end());
+        for (int k : by) {
+            std::pop_heap(heap.begin(), heap.end());
+            auto& top = heap.back();
+            bin[k] = -top.second;
+            load[bin[k]] += size[k];
+            top.first = -load[bin[k]];
+            std::push_heap(heap.begin(), heap.end());
+        }
+        const int64_t most = *std::max_element(load.begin(), load.end());
+        if (most <= capacity) {
+            c.most_nodes = int(most);
+            break;
+        }
+    }
+    const int bins = c.parts * c.groups, M0 = level_offsets[1];
+    c.group.assign(bins, Group{});
+    for (int i = 0; i < N; ++i) {
+        Group& g = c.group[bin[tree[level_nodes[i]]]];
+        ++(i < M0 ? g.nleaf : g.nint);
+    }
+    int lo = 0, io = M0;
+    for (Group& g : c.group) {
+        g.leaf0 = lo;
+        g.int0 = io;
+        lo += g.nleaf;
+        io += g.nint;
+    }
+    c.order.resize(N);
+    c.pos.resize(N);
+    std::vector<int32_t> nl(bins), ni(bins);
+    for (int b = 0; b < bins; ++b) {
+        nl[b] = c.group[b].leaf0;
+        ni[b] = c.group[b].int0;
+    }
+    // internal nodes of a group by level: how many of each group per level
+    std::vector<std::vector<int32_t>> width(bins);
+    for (int L = 0; L < num_levels; ++L)
+        for (int i = level_offsets[L]; i < level_offsets[L + 1]; ++i) {
+            const int n = level_nodes[i], b = bin[tree[n]];
+            const int p = L == 0 ? nl[b]++ : ni[b]++;
+            c.order[p] = n;
+            c.pos[n] = p;
+            if (L > 0) {
+                if (int(width[b].size()) < L) width[b].resize(L, 0);
+                ++width[b][L - 1];
+            }
+        }
+    c.tile.clear();
+    for (int b = 0; b < bins; ++b) {
+        Group& g = c.group[b];
+        g.t0 = int(c.tile.size());
+        for (int p = 0; p < g.nleaf; p += kRows) c.tile.push_back({g.leaf0 + p, std::min(kRows, g.nleaf - p)});
+        g.leaf_tiles = int(c.tile.size()) - g.t0;
+        int p0 = g.int0;
+        for (int L = 1; L <= int(width[b].size()); ++L) {
+            for (int p = 0; p < width[b][L - 1]; p += kRows)
+                c.tile.push_back({p0 + p, std::min(kRows, width[b][L - 1] - p) | L << 8});
+            p0 += width[b][L - 1];
+        }
+        g.t1 = int(c.tile.size());
+    }
+    return true;
+}
+
+}  // namespace treex
+}  // namespace janus

@@ -1,0 +1,54 @@
+"""Tree level programs whose groups of trees each live on one XCD, against the
+float64 oracle: the widths at which the row tiles of a workgroup change, odd
+sizes, one tree, more trees than groups, batches of several launches, and the
+placement in which a group's workgroups share no L2 (JANUS_XCD_REMOTE=1)."""
+import numpy as np
+import pytest
+
+from oracle import steps as oracle_steps
+from paper_1812_01329_amd import workloads as wl
+from tests.parity import TOL, check
+from tests.test_gpu_parity import _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _treelstm(w):
+    from paper_1812_01329_amd import janus as J
+    J.janus_trace_begin()
+    step, g = _run(w)
+    labels = {r["label"] for r in J.janus_trace_end()}
+    assert {"treelstm_fwd_persistent", "treelstm_bwd_persistent", "treelstm_bwd_tail"} <= labels, labels
+    assert J.janus_treelstm_device_report(step.desc, w.trees, step.ws) == 0
+    r = oracle_steps.tree_step(w)
+    t = TOL["f32"]
+    check("h_root", g["h_root"], r["h_root"], t["out"])
+    for k in ("dh_root", "dWs", "dbs", "dW", "dU", "db", "demb"):
+        check(k, g[k], r[k], t["grad"])
+    return g
+
+
+@pytest.mark.parametrize("H,E,n_trees", [(1, 1, 3), (3, 5, 1), (48, 37, 70), (96, 64, 9), (97, 33, 9), (192, 40, 20),
+                                         (193, 16, 20), (256, 8, 5), (257, 300, 5), (288, 12, 9), (289, 512, 9),
+                                         (384, 20, 6)])
+def test_treelstm_widths(H, E, n_trees):
+    print(f"[tree-xcd] H={H} E={E} trees={n_trees}", flush=True)
+    _treelstm(wl.sst_treelstm(n_trees=n_trees, E=E, H=H, V=60, seed=H + E))
+
+
+def test_treelstm_several_launches():
+    """A group's cells keep dh and dc of every node in LDS, so a large batch
+    runs in parts."""
+    print("[tree-xcd] parts", flush=True)
+    _treelstm(wl.sst_treelstm(n_trees=300, E=16, H=260, V=100, min_leaves=25, max_leaves=31, seed=14))
+
+
+@pytest.mark.parametrize("H", [29, 200])
+def test_treelstm_without_shared_l2(H, monkeypatch):
+    w = wl.sst_treelstm(n_trees=30, E=24, H=H, V=50, seed=5)
+    g0 = _treelstm(w)
+    monkeypatch.setenv("JANUS_XCD_REMOTE", "1")
+    print(f"[tree-xcd-remote] H={H}", flush=True)
+    g1 = _treelstm(w)
+    for k in ("h_root", "dW", "dU", "db", "demb"):
+        assert np.array_equal(g0[k], g1[k]), k
