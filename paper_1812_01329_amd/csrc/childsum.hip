@@ -205,7 +205,7 @@ janus_status prepare_cs(const janus_treelstm_desc* d, const janus_nary_tree_batc
     const size_t nb = sizeof(int32_t) * s.N;
     // the barrier block is zeroed too, so the device report of a call on
     // this path reads no stale flag
-    const std::vector<char> zero_sync(sizeof(tpersist::TreeSync), 0);
+    const std::vector<char> zero_sync(offsetof(tpersist::TreeSync, group), 0);
     const UploadPiece pieces[] = {{w.pword, s.pword.data(), nb},
                                   {w.pcoff, s.pcoff.data(), nb + sizeof(int32_t)},
                                   {w.pkids, s.pkids.data(), sizeof(int32_t) * s.pkids.size()},
@@ -250,7 +250,7 @@ janus_status cs_fwd_persistent_call(const janus_treelstm_desc& d, const NarySche
                                     const CsPlan& plan, const void* emb, const void* W, const void* U, const void* b,
                                     void* h_root, hipStream_t st) {
     const size_t nb = sizeof(int32_t) * s.N;
-    const std::vector<char> zero_sync(sizeof(tpersist::TreeSync), 0);
+    const std::vector<char> zero_sync(offsetof(tpersist::TreeSync, group), 0);
     const UploadPiece pieces[] = {{w.pword, s.pword.data(), nb},
                                   {w.pcoff, s.pcoff.data(), nb + sizeof(int32_t)},
                                   {w.pkids, s.pkids.data(), sizeof(int32_t) * s.pkids.size()},
@@ -308,7 +308,7 @@ janus_status cs_bwd_persistent_call(const janus_treelstm_desc& d, const NarySche
         const int32_t first = int32_t(std::lower_bound(sid, sid + nseg, v0) - sid);
         seg.push_back(first);
     }
-    const size_t counters = sizeof(tpersist::TreeSync) - tpersist::kTreeSyncCounters;
+    const size_t counters = offsetof(tpersist::TreeSync, group) - tpersist::kTreeSyncCounters;
     const std::vector<char> zero_counters(counters, 0);
     const UploadPiece pieces[] = {
         {reinterpret_cast<char*>(w.tsync) + tpersist::kTreeSyncCounters, zero_counters.data(), counters},

@@ -32,7 +32,6 @@
 #include "tree_common.hpp"
 #include "tree_tail.hpp"
 #include "tree_xcd.hpp"
-#include "treernn_persist.hpp"
 
 namespace janus {
 
@@ -63,12 +62,10 @@ struct TreeWs {
     float* part = nullptr;
     int32_t* seg = nullptr;      // the leaves grouped by word, for the embedding gradient
     int64_t ld5 = 0;
-    // persistent path: level offsets and the barrier's counters (carved right
-    // after the schedule arrays and before `seg`, so that each direction's
-    // upload is one copy), and node rows padded to whole 128-byte lines
-    int32_t* loff = nullptr;     // [N + 1]
+    // groups of trees per XCD (tree_xcd.hpp): the groups and their tiles (carved
+    // after the schedule arrays, so that one copy uploads both), the counters,
+    // and node rows padded to whole 128-byte lines
     tpersist::TreeSync* tsync = nullptr;
-    // groups of trees per XCD (tree_xcd.hpp): the groups, then their tiles
     treex::Group* xgroup = nullptr;
     treex::Tile* xtile = nullptr;    // [N]
     float* xl = nullptr;         // [N x ldx] leaf inputs
@@ -83,6 +80,11 @@ struct TreeWs {
     int64_t ldg = 0, ldc = 0, ldl = 0, lda = 0, ldx = 0;
 };
 
+// room for the groups of every launch of a batch of K trees
+size_t xgroup_ints(int32_t K) {
+    return std::min(treex::kGroupInts, sizeof(treex::Group) / 4 * (size_t(K) + treex::kMaxGroups));
+}
+
 size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, TreeWs& w) {
     Carver c(base);
     const int H = d.H;
@@ -93,14 +95,10 @@ size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, Tre
     w.parent = c.take<int32_t>(N);
     w.rootk = c.take<int32_t>(N);
     w.rootpos = c.take<int32_t>(K);
-    w.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(std::min(treex::kGroupInts, size_t(8) * (K + treex::kMaxGroups))));
+    w.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(xgroup_ints(K)));
     w.xtile = c.take<treex::Tile>(N);
-    w.loff = c.take<int32_t>(int64_t(N) + 1);
     w.tsync = c.take<tpersist::TreeSync>(1);
-    // the leaves grouped by word, and (persistent backward) each workgroup's
-    // first group of the embedding rows: one entry per workgroup, at most one
-    // per CU of the devices the library plans for
-    w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)) + kMaxTreeGrid);
+    w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));   // the leaves grouped by word
     w.A = c.take<float>(int64_t(N) * w.ld5);
     w.G = c.take<float>(int64_t(N) * w.ld5);
     w.C = c.take<float>(int64_t(N) * H);
@@ -315,10 +313,9 @@ janus_status upload_tree(const janus_tree_batch* t, const TreeSchedule& s, const
     TreeHost& h = keep ? *keep : local;
     build_host(t, s, h);
     const size_t nb = sizeof(int32_t) * s.N;
-    // carved one after another (only the level offsets between them): one
-    // copy.  The barrier block is zeroed too, so the device report of a call
-    // on this path reads no stale flag.
-    const std::vector<char> zero_sync(sizeof(tpersist::TreeSync), 0);
+    // The error flag is zeroed too, so the device report of a call on this
+    // path reads no stale one.
+    const std::vector<char> zero_sync(tpersist::kTreeSyncCounters, 0);
     const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},   {w.lchild, h.lchild.data(), nb},
                                   {w.rchild, h.rchild.data(), nb}, {w.parent, h.parent.data(), nb},
                                   {w.rootk, h.rootk.data(), nb},
@@ -393,11 +390,8 @@ TreeXcdPlan tree_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* 
     const int fu = 16 * p.NT / 5, bu = 8 * p.MT;
     p.fwd_nu = (d.H + fu - 1) / fu;
     p.bwd_nu = (d.H + bu - 1) / bu;
-    int capacity = 0;
-    for (int step = 1 << 16; step > 0; step >>= 1)
-        if (tree_xcd_fwd_lds(p.NT, capacity + step) <= dev.lds - 1024 && tree_xcd_bwd_lds(p.MT, capacity + step) <= dev.lds - 1024)
-            capacity += step;
-    if (capacity == 0) return p;
+    const int capacity = treex::node_capacity(
+        dev.lds, [&](int n) { return std::max(tree_xcd_fwd_lds(p.NT, n), tree_xcd_bwd_lds(p.MT, n)); });
     p.on = treex::cut_batch(t->num_trees, s.N, s.level_nodes, s.level_offsets, s.num_levels, tree_of_nodes(t, s),
                             std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut);
     p.fwd_lds = tree_xcd_fwd_lds(p.NT, p.cut.most_nodes);
@@ -406,6 +400,28 @@ TreeXcdPlan tree_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* 
 }
 // workgroups of a launch whose groups have nu members
 int tree_xcd_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
+
+// The schedule in the order of a cut, with its groups and tiles: one copy.
+janus_status upload_cut(const janus_tree_batch* t, int32_t N, const TreeWs& w, const treex::Cut& c, hipStream_t st) {
+    TreeHost h;
+    build_host(t, N, c.order, c.pos, h);
+    const size_t nb = sizeof(int32_t) * N;
+    const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},
+                                  {w.lchild, h.lchild.data(), nb},
+                                  {w.rchild, h.rchild.data(), nb},
+                                  {w.parent, h.parent.data(), nb},
+                                  {w.rootk, h.rootk.data(), nb},
+                                  {w.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
+                                  {w.xgroup, c.group.data(), sizeof(treex::Group) * c.group.size()},
+                                  {w.xtile, c.tile.data(), sizeof(treex::Tile) * c.tile.size()}};
+    return upload_pieces(pieces, 8, st);
+}
+// The leaves grouped by word, in the order of a cut.
+int leaf_segments(const janus_tree_batch* t, int32_t M0, int32_t V, const treex::Cut& c, std::vector<int32_t>& seg) {
+    std::vector<int32_t> word(M0);
+    for (int32_t i = 0; i < M0; ++i) word[i] = t->word[c.order[i]];
+    return embed_segments(word.data(), M0, V, seg);
+}
 
 unsigned fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
 
@@ -425,18 +441,7 @@ janus_status launch_tree_bwd(const TreeXcdPlan& p, const treex::LstmBwd& a, hipS
 janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
                                    const TreeWs& w, const TreeXcdPlan& p, const void* emb, const void* W, const void* U,
                                    const void* b, void* h_root, hipStream_t st) {
-    TreeHost h;
-    build_host(t, s.N, p.cut.order, p.cut.pos, h);
-    const size_t nb = sizeof(int32_t) * s.N;
-    const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},
-                                  {w.lchild, h.lchild.data(), nb},
-                                  {w.rchild, h.rchild.data(), nb},
-                                  {w.parent, h.parent.data(), nb},
-                                  {w.rootk, h.rootk.data(), nb},
-                                  {w.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
-                                  {w.xgroup, p.cut.group.data(), sizeof(treex::Group) * p.cut.group.size()},
-                                  {w.xtile, p.cut.tile.data(), sizeof(treex::Tile) * p.cut.tile.size()}};
-    janus_status e = upload_pieces(pieces, 8, st);
+    janus_status e = upload_cut(t, s.N, w, p.cut, st);
     if (e != JANUS_OK) return e;
     const int M0 = s.level_offsets[1];
     treex::LstmFwd a = {};
@@ -538,10 +543,8 @@ janus_status treelstm_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
                                    const TreeWs& w, const TreeXcdPlan& p, const void* W, const void* U,
                                    const void* dh_root, float* demb, float* dW, float* dU, float* db, hipStream_t st) {
     const int M0 = s.level_offsets[1], Nint = s.N - M0, H = d.H, E = d.E;
-    std::vector<int32_t> lword(M0);
-    for (int i = 0; i < M0; ++i) lword[i] = t->word[p.cut.order[i]];
     std::vector<int32_t> seg;
-    const int nseg = embed_segments(lword.data(), M0, d.V, seg);
+    const int nseg = leaf_segments(t, M0, d.V, p.cut, seg);
     janus_status e;
     if ((e = upload(w.seg, seg.data(), seg.size() * sizeof(int32_t), st)) != JANUS_OK) return e;
     if ((e = treelstm_bwd_xcd_levels(d, s, w, p, U, dh_root, st)) != JANUS_OK) return e;
@@ -613,19 +616,20 @@ janus_status treelstm_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
 // db = column sums of da over the internal nodes, and the leaves' dh is the
 // gradient of their word vectors.
 struct TreeRnnWs {
-    TreeWs s;                    // schedule arrays (lword .. rootpos, loff, tsync, seg) only
+    TreeWs s;                    // schedule arrays (lword .. rootpos, xgroup, xtile, tsync, seg) only
     float* A = nullptr;          // [N x H] pre-activations (forward), da (backward)
     float* Hn = nullptr;         // [N x H] h of every node
     float* HLR = nullptr;        // [N - M0 x 2H] children's h of internal nodes
     float* dh = nullptr;         // [N x H]
     float* Wt = nullptr;         // [2H x H] W transposed
     float* part = nullptr;
-    // persistent path: node rows padded to whole 128-byte lines
-    float* Hnp = nullptr;        // [N x ldh]
-    float* HLRp = nullptr;       // [N x ldl]
-    float* dhp = nullptr;        // [N x ldh]
+    // groups of trees per XCD: node rows padded to whole 128-byte lines
+    float* hx = nullptr;         // [N x ldh] h of every node
     float* dAp = nullptr;        // [N x ldh]
-    int64_t ldh = 0, ldl = 0;
+    float* dx = nullptr;         // [N x H] gradient of the leaves' word vectors
+    float* tpart = nullptr;      // parts of the two halves of dW
+    float* tsum = nullptr;       // parts of db
+    int64_t ldh = 0;
 };
 
 size_t carve_rnn(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, TreeRnnWs& w) {
@@ -637,11 +641,10 @@ size_t carve_rnn(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base,
     w.s.parent = c.take<int32_t>(N);
     w.s.rootk = c.take<int32_t>(N);
     w.s.rootpos = c.take<int32_t>(K);
-    // the persistent path's level offsets, barrier counters and leaf groups
-    // follow the schedule arrays, so each direction's upload is one copy
-    w.s.loff = c.take<int32_t>(int64_t(N) + 1);
+    w.s.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(xgroup_ints(K)));
+    w.s.xtile = c.take<treex::Tile>(N);
     w.s.tsync = c.take<tpersist::TreeSync>(1);
-    w.s.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)) + kMaxTreeGrid);
+    w.s.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));
     w.A = c.take<float>(int64_t(N) * H);
     w.Hn = c.take<float>(int64_t(N) * H);
     w.HLR = c.take<float>(int64_t(N) * 2 * H);
@@ -649,11 +652,11 @@ size_t carve_rnn(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base,
     w.Wt = c.take<float>(int64_t(2) * H * H);
     w.part = c.take<float>(colsum_partial_floats(H));
     w.ldh = round_up(H, 32);
-    w.ldl = round_up(int64_t(2) * H, 32);
-    w.Hnp = c.take<float>(int64_t(N) * w.ldh);
-    w.HLRp = c.take<float>(int64_t(N) * w.ldl);
-    w.dhp = c.take<float>(int64_t(N) * w.ldh);
+    w.hx = c.take<float>(int64_t(N) * w.ldh);
     w.dAp = c.take<float>(int64_t(N) * w.ldh);
+    w.dx = c.take<float>(int64_t(N) * H);
+    w.tpart = c.take<float>(2 * tail_part_floats(H, H));
+    w.tsum = c.take<float>(tail_sum_floats(N, H));
     return c.off + 256;
 }
 
@@ -835,146 +838,160 @@ extern "C" janus_status janus_treelstm_device_report(const janus_treelstm_desc* 
 namespace janus {
 namespace {
 
-// Grid and LDS of the persistent TreeRNN kernels: one workgroup per CU at
-// most, the grid a multiple of the column tiles of W (forward: H / 32 output
-// units; backward: 2H / 32 columns of [dh_L; dh_R]).  Off with
-// JANUS_TREE_PERSIST=0, for H above 512 (the embedding gradient's two
-// columns per thread), or where the forward's operand slabs do not fit the
-// LDS (about H > 312); the level-by-level kernels run then.
-struct RnnPlan {
+// The TreeRNN in groups of trees per XCD: 16 units per forward workgroup (H up
+// to 512 in the 32 workgroups of an XCD), [dh_L; dh_R] of 8 or 16 in the
+// backward.  Off with JANUS_TREE_PERSIST=0; wider models run level by level.
+struct RnnXcdPlan {
     bool on = false;
-    int ncol = 0, fwd_grid = 0, ncol2 = 0, bwd_grid = 0;
-    size_t fwd_lds = 0, bwd_lds = 0;
+    int MT = 0, fwd_nu = 0, bwd_nu = 0;
+    treex::Cut cut;
+    size_t bwd_lds = 0;
 };
-RnnPlan rnn_plan(const janus_treelstm_desc& d) {
-    RnnPlan p;
-    const char* e = getenv("JANUS_TREE_PERSIST");
-    if (e && e[0] == '0') return p;
+size_t rnn_bwd_lds(int MT, int nodes) {
+    return MT == 1 ? treex::RnnBwdCfg<1>::lds(nodes) : treex::RnnBwdCfg<2>::lds(nodes);
+}
+RnnXcdPlan rnn_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s) {
+    RnnXcdPlan p;
+    if (tree_env("JANUS_TREE_PERSIST", '0')) return p;
     const TreeDev dev = tree_dev();
-    if (dev.cus <= 0 || dev.lds == 0 || d.H > tpersist::kMaxE) return p;
-    p.ncol = (d.H + 31) / 32;
-    p.ncol2 = (2 * d.H + 31) / 32;
-    if (p.ncol2 > dev.cus) return p;
-    const int cus = dev.cus < kMaxTreeGrid ? dev.cus : kMaxTreeGrid;
-    p.fwd_grid = p.ncol * (cus / p.ncol);
-    p.bwd_grid = p.ncol2 * (cus / p.ncol2);
-    p.fwd_lds = size_t(tpersist::rnn_fwd_lds_floats(d.H)) * sizeof(float);
-    p.bwd_lds = size_t(tpersist::rnn_bwd_lds_floats(d.H)) * sizeof(float);
-    p.on = p.fwd_lds <= dev.lds && p.bwd_lds <= dev.lds;
+    if (dev.cus <= 0 || dev.lds == 0 || d.H > 512) return p;
+    if (int64_t(s.N) * round_up(d.H, 32) * 4 >= (int64_t(1) << 31)) return p;   // 32-bit byte offsets
+    p.MT = d.H <= 256 ? 1 : 2;
+    p.fwd_nu = (d.H + treex::kRnnU - 1) / treex::kRnnU;
+    p.bwd_nu = (d.H + 8 * p.MT - 1) / (8 * p.MT);
+    const int capacity = treex::node_capacity(dev.lds, [&](int n) { return rnn_bwd_lds(p.MT, n); });
+    p.on = treex::cut_batch(t->num_trees, s.N, s.level_nodes, s.level_offsets, s.num_levels, tree_of_nodes(t, s),
+                            std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut);
+    p.bwd_lds = rnn_bwd_lds(p.MT, p.cut.most_nodes);
     return p;
 }
-// The backward addresses dA through one buffer descriptor (byte offsets
-// below 2^31); larger batches run the level-by-level kernels.
-bool rnn_persist_fits(const RnnPlan& p, const janus_treelstm_desc& d, int32_t N) {
-    return p.on && int64_t(N) * round_up(d.H, 32) * 4 < (int64_t(1) << 31);
-}
 
-// Forward: schedule, level offsets and the zeroed barrier block (error flag
-// included) in one copy, then one launch for every level.
-janus_status treernn_fwd_persistent_call(const janus_treelstm_desc& d, const janus_tree_batch* t,
-                                         const TreeSchedule& s, const TreeRnnWs& w, const RnnPlan& plan,
-                                         const void* emb, const void* W, const void* b, void* h_root,
-                                         hipStream_t st) {
-    TreeHost h;
-    build_host(t, s, h);
-    const size_t nb = sizeof(int32_t) * s.N;
-    const std::vector<char> zero_sync(sizeof(tpersist::TreeSync), 0);
-    const UploadPiece pieces[] = {{w.s.lword, h.lword.data(), nb},
-                                  {w.s.lchild, h.lchild.data(), nb},
-                                  {w.s.rchild, h.rchild.data(), nb},
-                                  {w.s.parent, h.parent.data(), nb},
-                                  {w.s.rootk, h.rootk.data(), nb},
-                                  {w.s.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
-                                  {w.s.loff, s.level_offsets.data(), sizeof(int32_t) * s.level_offsets.size()},
-                                  {w.s.tsync, zero_sync.data(), zero_sync.size()}};
-    janus_status e = upload_pieces(pieces, 8, st);
+janus_status treernn_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
+                                  const TreeRnnWs& w, const RnnXcdPlan& p, const void* emb, const void* W,
+                                  const void* b, void* h_root, hipStream_t st) {
+    janus_status e = upload_cut(t, s.N, w.s, p.cut, st);
     if (e != JANUS_OK) return e;
-    tpersist::RnnFwdArgs a;
-    a.H = d.H;
-    a.N = s.N;
-    a.M0 = s.level_offsets[1];
-    a.nlev = s.num_levels;
-    a.ncol = plan.ncol;
-    a.loff = w.s.loff;
-    a.lword = w.s.lword;
-    a.parent = w.s.parent;
-    a.rootk = w.s.rootk;
-    a.emb = static_cast<const float*>(emb);
-    a.W = static_cast<const float*>(W);
-    a.b = static_cast<const float*>(b);
-    a.Hn = w.Hnp;
-    a.ldh = w.ldh;
-    a.HLR = w.HLRp;
-    a.ldl = w.ldl;
-    a.h_root = static_cast<float*>(h_root);
-    a.sync = w.s.tsync;
-    static size_t attr = 0;
-    const double flops = 2.0 * d.H * 2.0 * d.H * double(s.N - a.M0);
-    TraceScope trace("treernn_fwd_persistent", flops, 0.0, st);
-    return tree_persistent_launch(tpersist::treernn_fwd_persistent, plan.fwd_grid, plan.fwd_lds, a, st, attr);
-}
-
-// Backward: the forward's schedule (the workspace is unchanged between the
-// calls); the leaves grouped by word and the barrier's counters (not its
-// error flag) in one copy, then one launch for the levels, dW, db and the
-// embedding gradient.
-janus_status treernn_bwd_persistent_call(const janus_treelstm_desc& d, const janus_tree_batch* t,
-                                         const TreeSchedule& s, const TreeRnnWs& w, const RnnPlan& plan,
-                                         const void* W, const void* dh_root, float* demb, float* dW, float* db,
-                                         hipStream_t st) {
-    TreeHost h;
-    build_host(t, s, h);
     const int M0 = s.level_offsets[1];
-    std::vector<int32_t> seg;
-    const int nseg = embed_segments(h.lword.data(), M0, d.V, seg);
-    // first group of each workgroup's rows [V w / grid, V (w + 1) / grid)
-    for (int g = 0; g < plan.bwd_grid; ++g) {
-        const int32_t* sid = seg.data() + M0 + nseg + 1;
-        const int64_t v0 = int64_t(d.V) * g / plan.bwd_grid;
-        const int32_t first = int32_t(std::lower_bound(sid, sid + nseg, v0) - sid);
-        seg.push_back(first);
-    }
-    const size_t counters = sizeof(tpersist::TreeSync) - tpersist::kTreeSyncCounters;
-    const std::vector<char> zero_counters(counters, 0);
-    const UploadPiece pieces[] = {
-        {reinterpret_cast<char*>(w.s.tsync) + tpersist::kTreeSyncCounters, zero_counters.data(), counters},
-        {w.s.seg, seg.data(), seg.size() * sizeof(int32_t)}};
-    janus_status e = upload_pieces(pieces, 2, st);
-    if (e != JANUS_OK) return e;
-    tpersist::RnnBwdArgs a;
+    treex::RnnFwd a = {};
     a.H = d.H;
-    a.N = s.N;
     a.M0 = M0;
-    a.nlev = s.num_levels;
-    a.ncol = plan.ncol2;
-    a.nseg = nseg;
-    a.V = d.V;
-    a.ntrees = t->num_trees;
-    a.loff = w.s.loff;
-    a.lword = w.s.lword;
+    a.groups = p.cut.groups;
+    a.nu = p.fwd_nu;
+    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.tile = w.s.xtile;
     a.lchild = w.s.lchild;
     a.rchild = w.s.rchild;
     a.rootk = w.s.rootk;
-    a.rootpos = w.s.rootpos;
-    a.seg = w.s.seg;
     a.W = static_cast<const float*>(W);
-    a.Hn = w.Hnp;
+    a.b = static_cast<const float*>(b);
+    a.hx = w.hx;
     a.ldh = w.ldh;
-    a.HLR = w.HLRp;
-    a.ldl = w.ldl;
-    a.dh_root = static_cast<const float*>(dh_root);
-    a.dh = w.dhp;
-    a.dA = w.dAp;
-    a.lda = w.ldh;
-    a.demb = demb;
-    a.dW = dW;
-    a.db = db;
+    a.hx_bytes = uint32_t(int64_t(s.N) * w.ldh * 4);
+    a.h_root = static_cast<float*>(h_root);
     a.sync = w.s.tsync;
+    for (int part = 0; part < p.cut.parts; ++part) {
+        if (part == 0) {
+            TraceScope trace("tree_fwd_init", 0.0, 4.0 * double(s.N + M0) * w.ldh, st);
+            hipLaunchKernelGGL(treex::rnn_fwd_init_kernel, dim3(fill_blocks(int64_t(s.N) * w.ldh)), dim3(256), 0, st,
+                               s.N, M0, d.H, w.s.lword, w.s.rootk, static_cast<const float*>(emb), w.hx, w.ldh,
+                               static_cast<float*>(h_root), w.s.tsync);
+        } else {
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(4), dim3(256), 0, st, w.hx, w.ldh, int64_t(0), int64_t(0), d.H,
+                               w.s.tsync);
+        }
+        JANUS_LAUNCH_CHECK();
+        a.group = w.s.xgroup + part * p.cut.groups;
+        static size_t attr = 0;
+        TraceScope trace("treernn_fwd_persistent", 2.0 * d.H * 2.0 * d.H * double(s.N - M0) / p.cut.parts, 0.0, st);
+        e = tree_persistent_launch(treex::treernn_fwd_xcd, tree_xcd_blocks(p.cut, p.fwd_nu), treex::kRnnFwdLds, a, st,
+                                   attr, treex::kThreads);
+        if (e != JANUS_OK) return e;
+    }
+    return JANUS_OK;
+}
+
+template <int MT>
+janus_status launch_rnn_bwd(const RnnXcdPlan& p, const treex::RnnBwd& a, hipStream_t st) {
     static size_t attr = 0;
-    // [dh_L; dh_R] = da W and dW, both 2 H 2H per internal node
-    const double flops = 2.0 * 2.0 * d.H * 2.0 * d.H * double(s.N - M0);
-    TraceScope trace("treernn_bwd_persistent", flops, 0.0, st);
-    return tree_persistent_launch(tpersist::treernn_bwd_persistent, plan.bwd_grid, plan.bwd_lds, a, st, attr);
+    return tree_persistent_launch(treex::treernn_bwd_xcd<MT>, tree_xcd_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
+                                  treex::kThreads);
+}
+
+// The schedule is the forward's (the workspace is unchanged between the calls).
+janus_status treernn_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
+                                  const TreeRnnWs& w, const RnnXcdPlan& p, const void* W, const void* dh_root,
+                                  float* demb, float* dW, float* db, hipStream_t st) {
+    const int M0 = s.level_offsets[1], Nint = s.N - M0, H = d.H;
+    std::vector<int32_t> seg;
+    const int nseg = leaf_segments(t, M0, d.V, p.cut, seg);
+    janus_status e = upload(w.s.seg, seg.data(), seg.size() * sizeof(int32_t), st);
+    if (e != JANUS_OK) return e;
+    treex::RnnBwd a = {};
+    a.H = H;
+    a.M0 = M0;
+    a.groups = p.cut.groups;
+    a.nu = p.bwd_nu;
+    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.tile = w.s.xtile;
+    a.lchild = w.s.lchild;
+    a.rchild = w.s.rchild;
+    a.rootk = w.s.rootk;
+    a.W = static_cast<const float*>(W);
+    a.hx = w.hx;
+    a.ldh = w.ldh;
+    a.dh_root = static_cast<const float*>(dh_root);
+    a.dA = w.dAp;
+    a.dA_bytes = uint32_t(int64_t(s.N) * w.ldh * 4);
+    a.dx = w.dx;
+    a.sync = w.s.tsync;
+    for (int part = 0; part < p.cut.parts; ++part) {
+        if (part == 0) {
+            TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(Nint) * w.ldh, st);
+            hipLaunchKernelGGL(treex::rnn_bwd_init_kernel, dim3(fill_blocks(int64_t(Nint) * w.ldh + 4096)), dim3(256), 0,
+                               st, s.N, M0, H, w.s.rootpos, t->num_trees, a.dh_root, w.dAp, w.ldh, w.dx, w.s.tsync);
+        } else {
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(4), dim3(256), 0, st, w.dAp, w.ldh, int64_t(0), int64_t(0), H,
+                               w.s.tsync);
+        }
+        JANUS_LAUNCH_CHECK();
+        a.group = w.s.xgroup + part * p.cut.groups;
+        TraceScope trace("treernn_bwd_persistent", 2.0 * H * 2.0 * H * double(Nint) / p.cut.parts, 0.0, st);
+        e = p.MT == 1 ? launch_rnn_bwd<1>(p, a, st) : launch_rnn_bwd<2>(p, a, st);
+        if (e != JANUS_OK) return e;
+    }
+    // dW = dA_int^T [h_L; h_R], the children's rows gathered; db; demb
+    TailArgs q;
+    GemmDesc g;
+    g.dtype = JANUS_F32;
+    g.M = g.N = H;
+    g.K = Nint;
+    g.a_t = g.b_t = true;
+    g.A = w.dAp + int64_t(M0) * w.ldh;
+    g.lda = w.ldh;
+    g.B = w.hx;
+    g.ldb = w.ldh;
+    g.b_idx = w.s.lchild + M0;
+    g.C = dW;
+    g.ldc = 2 * H;
+    tail_add(q, g, w.tpart);
+    g.b_idx = w.s.rchild + M0;
+    g.C = dW + H;
+    tail_add(q, g, w.tpart + tail_part_floats(H, H));
+    q.src = w.dAp + int64_t(M0) * w.ldh;
+    q.ld = w.ldh;
+    q.rows = Nint;
+    q.cols = H;
+    q.sum_part = w.tsum;
+    q.sum_out = db;
+    q.demb = demb;
+    q.demb_n = int64_t(d.V) * H;
+    q.dx = w.dx;
+    q.ldx = H;
+    q.E = H;
+    q.leaves = M0;
+    q.nseg = nseg;
+    q.seg = w.s.seg;
+    return tail_run(q, "treernn_bwd_tail", st);
 }
 
 }  // namespace
@@ -995,8 +1012,8 @@ extern "C" janus_status janus_treernn_fwd(const janus_treernn_desc* d, const jan
     janus_status e = prepare_rnn(d, t, ws, ws_bytes, s, w);
     if (e != JANUS_OK) return e;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const RnnPlan plan = rnn_plan(*d);
-    if (rnn_persist_fits(plan, *d, s.N)) return treernn_fwd_persistent_call(*d, t, s, w, plan, emb, W, b, h_root, st);
+    const RnnXcdPlan xp = rnn_xcd_plan(*d, t, s);
+    if (xp.on) return treernn_fwd_xcd_call(*d, t, s, w, xp, emb, W, b, h_root, st);
     if ((e = upload_tree(t, s, w.s, st)) != JANUS_OK) return e;
     const int H = d->H;
     const int M0 = s.level_offsets[1];
@@ -1036,9 +1053,8 @@ extern "C" janus_status janus_treernn_bwd(const janus_treernn_desc* d, const jan
     if (e != JANUS_OK) return e;
     const int M0 = s.level_offsets[1];
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const RnnPlan plan = rnn_plan(*d);
-    if (rnn_persist_fits(plan, *d, s.N))
-        return treernn_bwd_persistent_call(*d, t, s, w, plan, W, dh_root, demb, dW, db, st);
+    const RnnXcdPlan xp = rnn_xcd_plan(*d, t, s);
+    if (xp.on) return treernn_bwd_xcd_call(*d, t, s, w, xp, W, dh_root, demb, dW, db, st);
     TreeHost host;
     if ((e = upload_tree(t, s, w.s, st, &host)) != JANUS_OK) return e;
     const int H = d->H, N = s.N;

@@ -505,6 +505,258 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
     }
 }
 
+// ----------------------------------------------------------------- TreeRNN
+// h = tanh(W [h_L; h_R] + b) of the internal nodes; a leaf's h is its word
+// vector, which the set-up kernel puts in its row of hx, so only the tiles of
+// internal nodes run.
+struct RnnFwd {
+    int H, M0;
+    int groups, nu, force_remote;
+    const Group* group;
+    const Tile* tile;
+    const int32_t* lchild;
+    const int32_t* rchild;
+    const int32_t* rootk;
+    const float* W;            // [H x 2H]
+    const float* b;
+    float* hx;                 // [N x ldh]
+    int64_t ldh;
+    uint32_t hx_bytes;
+    float* h_root;
+    TreeSync* sync;
+};
+// Set-up of the forward: leaf rows of hx (and of h_root for a leaf that is a
+// root), empty rows of the internal nodes, counters and error flag zero.
+static __global__ __launch_bounds__(256) void rnn_fwd_init_kernel(int N, int M0, int H, const int32_t* lword,
+                                                                  const int32_t* rootk, const float* emb, float* hx,
+                                                                  int64_t ldh, float* h_root, TreeSync* s) {
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    zero_counters(s, i0, stride);
+    if (i0 == 0) s->error = 0u;
+    fill_empty(hx, ldh, M0, N - M0, H, i0, stride);
+    for (int64_t i = i0; i < int64_t(M0) * ldh; i += stride) {
+        const int p = int(i / ldh), j = int(i % ldh);
+        const float v = j < H ? emb[int64_t(lword[p]) * H + j] : 0.f;
+        hx[i] = v;
+        if (j < H && rootk[p] >= 0) h_root[int64_t(rootk[p]) * H + j] = v;
+    }
+}
+
+constexpr int kRnnU = 16;      // units of a forward workgroup: one row tile
+constexpr int kRnnJ = 8;       // k-groups of a wave at most: H up to 512
+constexpr int kRnnFwdLds = 2 * kWaves * 256 * 4;
+
+static __global__ __launch_bounds__(kThreads) void treernn_fwd_xcd(RnnFwd a) {
+    extern __shared__ __align__(16) float sm[];
+    constexpr int U = kRnnU, J = kRnnJ;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    const int H = a.H, v0 = m * U, KH = (H + 15) / 16;
+    const int kw0 = wave * 2 * KH / kWaves, nj = (wave + 1) * 2 * KH / kWaves - kw0;
+    uint4 w[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int kg = kw0 + j, side = kg >= KH, k = 16 * (kg - side * KH) + 4 * lq;
+        w[j] = j < nj ? weight4(a.W + side * H, 2 * H, v0 + lr < H ? v0 + lr : -1, k, H) : make_uint4(0, 0, 0, 0);
+    }
+    // cells: thread (unit cu, node cn)
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    const float bias = cell_thread ? a.b[cj] : 0.f;
+    bool dead = false;
+    unsigned phase = 0;
+    const int t0 = gr.t0 + gr.leaf_tiles;
+    if (t0 >= gr.t1) return;
+    TileWindow win;
+    win.init(a.tile, gr.t1, t0);
+    struct Links {
+        int ql, qr, rk;
+    };
+    auto links = [&](int t) {
+        const Tile tl = win.at(t);
+        Links k;
+        const int q = tl.p0 + min(lr, tile_rows(tl) - 1), p = tl.p0 + min(cn, tile_rows(tl) - 1);
+        k.ql = a.lchild[q];
+        k.qr = a.rchild[q];
+        k.rk = a.rootk[p];
+        return k;
+    };
+    Links next = links(t0);
+    for (int t = t0; t < gr.t1; ++t) {
+        const Tile tl = win.at(t);
+        const int rows = tile_rows(tl);
+        const Links k = next;
+        if (!local && t > t0) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+        const auto rs = make_rsrc(a.hx, a.hx_bytes);
+        const uint32_t ol = uint32_t(k.ql) * uint32_t(a.ldh), orr = uint32_t(k.qr) * uint32_t(a.ldh);
+        uint4 f[J];
+        xcd::load_operand<float>(f, rs, [&](int j) {
+            const int kg = kw0 + j;
+            const uint32_t o = kg < KH ? ol + uint32_t(16 * kg) : orr + uint32_t(16 * (kg - KH));
+            return lr < rows && j < nj ? (o + uint32_t(4 * lq)) * 4u : kOutOfRange;
+        }, local, a.sync, dead);
+        if (t + 1 < gr.t1) next = links(t + 1);
+        f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (j < nj) acc = xcd::mma(w[j], f[j], acc, static_cast<const float*>(nullptr));
+        float* red = sm + (t & 1) * kWaves * 256;
+        reinterpret_cast<f32x4_t*>(red)[wave * 64 + lane] = acc;
+        __syncthreads();
+        if (cell_thread && cn < rows) {
+            const int p = tl.p0 + cn;
+            const float h = tanhf_(bias + sum_waves<1>(red, cu, cn));
+            xcd::store_b32(rs, (uint32_t(p) * uint32_t(a.ldh) + uint32_t(cj)) * 4u, not_empty(__float_as_uint(h)));
+            if (k.rk >= 0) a.h_root[int64_t(k.rk) * H + cj] = h;
+        }
+    }
+}
+
+struct RnnBwd {
+    int H, M0;
+    int groups, nu, force_remote;
+    const Group* group;
+    const Tile* tile;
+    const int32_t* lchild;
+    const int32_t* rchild;
+    const int32_t* rootk;
+    const float* W;
+    const float* hx;
+    int64_t ldh;
+    const float* dh_root;
+    float* dA;                 // [N x ldh], internal rows
+    uint32_t dA_bytes;
+    float* dx;                 // [M0 x H] gradient of the leaves' word vectors
+    TreeSync* sync;
+};
+// Set-up of the backward: empty rows of dA, the gradient of a leaf that is a
+// root, counters zero.
+static __global__ __launch_bounds__(256) void rnn_bwd_init_kernel(int N, int M0, int H, const int32_t* rootpos,
+                                                                  int trees, const float* dh_root, float* dA,
+                                                                  int64_t ldh, float* dx, TreeSync* s) {
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    zero_counters(s, i0, stride);
+    fill_empty(dA, ldh, M0, N - M0, H, i0, stride);
+    for (int64_t i = i0; i < int64_t(trees) * H; i += stride) {
+        const int p = rootpos[i / H];
+        if (p < M0) dx[int64_t(p) * H + i % H] = dh_root[i];
+    }
+}
+
+// MT row tiles hold [dh_L; dh_R] of 8 MT units; K = H, at most 4 k-groups a wave.
+template <int MT>
+struct RnnBwdCfg {
+    static constexpr int U = 8 * MT, J = 4;
+    static constexpr int RED = kWaves * MT * 256;
+    static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
+};
+template <int MT>
+__global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
+    using C = RnnBwdCfg<MT>;
+    constexpr int U = C::U, J = C::J;
+    extern __shared__ __align__(16) float sm[];
+    float* dhl = sm + 2 * C::RED;   // [internal nodes][U]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    const int first = gr.t0 + gr.leaf_tiles;
+    if (first >= gr.t1) return;
+    const int H = a.H, v0 = m * U, nk = (H + 15) / 16;
+    const int kw0 = wave * nk / kWaves, nj = (wave + 1) * nk / kWaves - kw0;
+    uint4 w[MT][J];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int r = 16 * i + lr, u = v0 + (r >> 1), k = 16 * (kw0 + j) + 4 * lq;
+            float tmp[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                tmp[e] = u < H && j < nj && k + e < H ? a.W[int64_t(k + e) * 2 * H + (r & 1) * H + u] : 0.f;
+            w[i][j] = make_uint4(__float_as_uint(tmp[0]), __float_as_uint(tmp[1]), __float_as_uint(tmp[2]),
+                                 __float_as_uint(tmp[3]));
+        }
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    const auto rs = make_rsrc(a.dA, a.dA_bytes);
+    struct In {
+        int p, rk, ch;
+        float h, dhr;
+    } in;
+    TileWindow win;
+    win.init(a.tile, gr.t1, max(gr.t1 - 64, gr.t0));
+    auto fetch = [&](int t, In& x) {
+        const Tile tl = win.at(t, true);
+        const int q = tl.p0 + min(cn, tile_rows(tl) - 1);
+        x.ch = (tid >> 4 & 1) ? a.rchild[q] : a.lchild[q];
+        x.p = cell_thread && cn < tile_rows(tl) ? q : -1;
+        const int j = cell_thread ? cj : 0;
+        x.rk = a.rootk[q];
+        x.h = a.hx[int64_t(q) * a.ldh + j];
+        x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+    };
+    auto cells = [&](const In& x) {
+        if (x.p < 0) return;
+        const float dh = x.rk >= 0 ? x.dhr : dhl[(x.p - gr.int0) * U + cu];
+        xcd::store_b32(rs, (uint32_t(x.p) * uint32_t(a.ldh) + uint32_t(cj)) * 4u,
+                       not_empty(__float_as_uint(dh * (1.f - x.h * x.h))));
+    };
+    bool dead = false;
+    unsigned phase = 0;
+    int t = gr.t1 - 1;
+    fetch(t, in);
+    cells(in);
+    for (; t >= first; --t) {
+        const Tile tl = win.at(t, true);
+        const int rows = tile_rows(tl);
+        const bool more = t - 1 >= first;
+        const bool same = more && tile_level(win.at(t - 1, true)) == tile_level(tl);
+        In nx = in;
+        if (more) fetch(t - 1, nx);
+        if (same) cells(nx);   // a tile of the same level needs nothing of this one
+        if (!local) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+        uint4 f[J];
+        xcd::load_operand<float>(f, rs, [&](int j) {
+            return lr < rows && j < nj
+                       ? (uint32_t(tl.p0 + lr) * uint32_t(a.ldh) + uint32_t(16 * (kw0 + j) + 4 * lq)) * 4u
+                       : kOutOfRange;
+        }, local, a.sync, dead);
+        f32x4_t acc[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (j < nj) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i] = xcd::mma(w[i][j], f[j], acc[i], static_cast<const float*>(nullptr));
+            }
+        float* red = sm + (t & 1) * C::RED;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) reinterpret_cast<f32x4_t*>(red)[(wave * MT + i) * 64 + lane] = acc[i];
+        __syncthreads();
+        {
+            const int r = tid >> 4, n = tid & 15, u = r >> 1;
+            if (r < 2 * U && n < rows && v0 + u < H) {
+                const float v = sum_waves<MT>(red, r, n);
+                if (in.ch < a.M0) a.dx[int64_t(in.ch) * H + v0 + u] = v;
+                else dhl[(in.ch - gr.int0) * U + u] = v;
+            }
+        }
+        __syncthreads();   // the children's dh
+        if (more && !same) cells(nx);
+        in = nx;
+    }
+}
+
 // ------------------------------------------------------------- host side
 constexpr int kMaxGroups = 64;        // groups of one launch
 constexpr int kMaxParts = 16;         // launches of a batch at most
@@ -522,6 +774,15 @@ struct Cut {
     std::vector<int32_t> pos;          // node -> position
 };
 
+// Nodes a group may have: the most whose LDS (bytes(n)) a CU holds.
+template <class F>
+int node_capacity(size_t lds, F bytes) {
+    int n = 0;
+    for (int step = 1 << 16; step > 0; step >>= 1)
+        if (bytes(n + step) + 1024 <= lds) n += step;
+    return n;
+}
+
 // level_nodes: node ids by (level, id); level_offsets: their levels; tree[n]:
 // the tree of node n.  `capacity`: nodes a group may have (what its cells'
 // LDS holds).  False when the batch does not fit kMaxParts launches of groups
@@ -532,7 +793,7 @@ inline bool cut_batch(int num_trees, int N, const std::vector<int32_t>& level_no
     const tpersist::TreeDev dev = tpersist::tree_dev();
     const int xccs = dev.xccs > 0 && dev.xccs <= persist::kMaxXcds ? dev.xccs : 1;
     const int per_xcd = dev.cus / xccs;
-    if (per_xcd < nu) return false;
+    if (per_xcd < nu || capacity <= 0) return false;
     c.nu = nu;
     c.groups = std::min({num_trees, xccs * (per_xcd / nu), kMaxGroups});
     c.blocks = xccs * nu * ((c.groups + xccs - 1) / xccs);

@@ -52,3 +52,39 @@ def test_treelstm_without_shared_l2(H, monkeypatch):
     g1 = _treelstm(w)
     for k in ("h_root", "dW", "dU", "db", "demb"):
         assert np.array_equal(g0[k], g1[k]), k
+
+
+def _treernn(w):
+    from paper_1812_01329_amd import janus as J
+    J.janus_trace_begin()
+    step, g = _run(w)
+    labels = {r["label"] for r in J.janus_trace_end()}
+    assert {"treernn_fwd_persistent", "treernn_bwd_persistent", "treernn_bwd_tail"} <= labels, labels
+    assert J.janus_treernn_device_report(step.desc, w.trees, step.ws) == 0
+    r = oracle_steps.treernn_step(w)
+    t = TOL["f32"]
+    check("h_root", g["h_root"], r["h_root"], t["out"])
+    for k in ("dh_root", "dWs", "dbs", "dW", "db", "demb"):
+        check(k, g[k], r[k], t["grad"])
+    return g
+
+
+@pytest.mark.parametrize("H,n_trees", [(1, 3), (5, 1), (16, 70), (17, 9), (255, 9), (256, 20), (257, 20), (512, 6)])
+def test_treernn_widths(H, n_trees):
+    print(f"[rnn-xcd] H={H} trees={n_trees}", flush=True)
+    _treernn(wl.sst_treernn(n_trees=n_trees, H=H, V=60, seed=H))
+
+
+def test_treernn_several_launches():
+    print("[rnn-xcd] parts", flush=True)
+    _treernn(wl.sst_treernn(n_trees=500, H=300, V=100, min_leaves=35, max_leaves=41, seed=14))
+
+
+def test_treernn_without_shared_l2(monkeypatch):
+    w = wl.sst_treernn(n_trees=30, H=100, V=50, seed=5)
+    g0 = _treernn(w)
+    monkeypatch.setenv("JANUS_XCD_REMOTE", "1")
+    print("[rnn-xcd-remote]", flush=True)
+    g1 = _treernn(w)
+    for k in ("h_root", "dW", "db", "demb"):
+        assert np.array_equal(g0[k], g1[k]), k
