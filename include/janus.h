@@ -148,9 +148,9 @@ janus_status janus_lstm_state_carry(const janus_lstm_desc* d, int32_t B_prev,
 /*
  * Report of the current step made with this workspace (same d): the last
  * janus_lstm_seq_fwd call and the janus_lstm_seq_bwd calls after it.  The
- * persistent recurrence kernels separate their time steps with device-wide
- * barriers whose waits are bounded; when a wait runs out, the kernels drain
- * and the outputs are undefined.  Those calls return without synchronising,
+ * persistent recurrence kernels wait for the other workgroups' results of a
+ * time step with bounded waits; when a wait runs out, the kernels drain and
+ * the outputs are undefined.  Those calls return without synchronising,
  * so this call synchronises `stream` and reads the report back.  Reading does
  * not clear it; the next forward call does.
  *  timed_out         1 if any wait of the step ran out (forward or
@@ -273,9 +273,9 @@ janus_status janus_treelstm_fwd(const janus_treelstm_desc* d, const janus_tree_b
  *          c is zero).
  *  demb [V, E], dW [5H, E], dU [5H, 2H], db [5H]: float32, overwritten
  *          (rows of demb for words not in the batch are 0).
- * Where the weight slices fit one CU's LDS each direction is one launch of
- * co-resident workgroups that runs every level with a device-wide barrier
- * between levels (the waits are bounded; see janus_treelstm_device_report).
+ * With H up to 384 each direction is one launch of co-resident workgroups
+ * that runs every level of groups of whole trees (the waits for a level's
+ * results are bounded; see janus_treelstm_device_report).
  */
 janus_status janus_treelstm_bwd(const janus_treelstm_desc* d, const janus_tree_batch* t,
                                 const void* emb, const void* W, const void* U,
@@ -338,11 +338,10 @@ janus_status janus_treernn_bwd(const janus_treernn_desc* d, const janus_tree_bat
 
 /*
  * Device-side status of the TreeRNN calls made with this workspace since the
- * last forward (same d and t), as janus_treelstm_device_report: where the
- * weight slices fit one CU's LDS (H up to about 312) each direction is one
- * launch of co-resident workgroups with a device-wide barrier between levels
- * (Section 4.2.1 recursion, run level by level); a barrier that ran out of
- * its bounded wait sets *timed_out = 1 and the call returns
+ * last forward (same d and t), as janus_treelstm_device_report: with H
+ * up to 512 each direction is one launch of co-resident workgroups that runs
+ * every level of groups of whole trees (Section 4.2.1 recursion, run level by
+ * level); a bounded wait that ran out sets *timed_out = 1 and the call returns
  * JANUS_ERR_DEVICE (the results are then undefined).  The flag is cleared by
  * the next forward.  Errors: as janus_treernn_fwd's validation, or
  * INVALID_ARG for a NULL timed_out.
@@ -412,12 +411,11 @@ janus_status janus_childsum_bwd(const janus_childsum_desc* d, const janus_nary_t
 
 /*
  * Device-side status of the Child-Sum calls made with this workspace since
- * the last forward (same d and t), as janus_treelstm_device_report: where
- * the weight slices fit one CU's LDS (H up to about 156, E up to 512) each
- * direction is one launch of co-resident workgroups with device-wide
- * barriers between levels (Section 4.2.1 recursion, run level by level); a
- * barrier that ran out of its bounded wait sets *timed_out = 1 and the call
- * returns JANUS_ERR_DEVICE (the results are then undefined).  The flag is
+ * the last forward (same d and t), as janus_treelstm_device_report: with
+ * H below 320 and E up to 512 each direction is one launch of co-resident
+ * workgroups that runs every level of groups of whole trees (Section 4.2.1
+ * recursion, run level by level); a bounded wait that ran out sets
+ * *timed_out = 1 and the call returns JANUS_ERR_DEVICE (the results are then undefined).  The flag is
  * cleared by the next forward.  Errors: as janus_childsum_fwd's validation,
  * or INVALID_ARG for a NULL timed_out.
  */

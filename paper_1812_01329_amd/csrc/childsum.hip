@@ -10,27 +10,27 @@
 // Levels group nodes by height (a node after all of its children), the same
 // frontiers as the binary TreeNNs (Section 6.3.1, "+PARL").
 //
-// Forward.  x does not depend on the recursion, so XW = X W^T + b is one
-// contraction over all nodes first.  After a level is computed, one
-// contraction G = h U^T (all four blocks) serves its parents: by linearity
-// U_iou h~ of a parent is the sum of its children's G_iou rows, and child k's
-// forget gate reads G_f of row k.  A level is thus one cell kernel (which
-// gathers its children's G and c) and one contraction.
+// By linearity U_iou h~ of a node is the sum of its children's rows
+// G = h U^T (all four blocks), and child k's forget gate reads G_f of row k,
+// so one contraction per level serves the level's parents.  A node's cell
+// backward writes, for each child k, dG(k) = [da_iou(parent); da_f(parent, k)]
+// and the child's dc, and for itself dXW = [da_iou; sum_k da_f]; a node's
+// dh is its row of dG U (a root has dG = 0 and adds the head's gradient).
+// Then dW = dXW^T X, dU = dG^T h, db = sum of dXW, and dX = dXW W for the
+// embedding gradient.
 //
-// Backward, levels from the top down.  A node's cell backward writes, into
-// the row of each child k, dG(k) = [da_iou(parent); da_f(parent, k)] and the
-// child's dc; into its own row dXW = [da_iou; sum_k da_f].  When a level is
-// reached all its rows of dG are complete, so its dh = dG U is one
-// contraction over the level's contiguous rows (roots have dG = 0 and add
-// the head's gradient).  Then dW = dXW^T X, dU = dG^T H, db = sum of dXW,
-// and dX = dXW W for the embedding gradient.
+// H below 320: one launch each way over groups of trees per XCD
+// (tree_xcd.hpp).  Otherwise level by level, a cell kernel and a contraction
+// per level, with XW = X W^T + b over all nodes first.
 #include <algorithm>
 #include <vector>
 
-#include "childsum_persist.hpp"
 #include "device.hpp"
 #include "ops.hpp"
 #include "simt.hpp"
+#include "tree_common.hpp"
+#include "tree_tail.hpp"
+#include "tree_xcd.hpp"
 
 namespace janus {
 
@@ -41,6 +41,7 @@ struct CsWs {
     int32_t* pcoff = nullptr;    // [N + 1] children of position p: pkids[pcoff[p] .. pcoff[p + 1])
     int32_t* pkids = nullptr;    // [N] child positions
     int32_t* rootk = nullptr;    // [N] tree index of a root, -1 otherwise
+    // level by level
     float* XW = nullptr;         // [N x 4H] X W^T + b
     float* G = nullptr;          // [N x 4H] h U^T (forward), dG (backward)
     float* Gt = nullptr;         // [N x 3H] gates i, o, u
@@ -55,22 +56,22 @@ struct CsWs {
     float* Ut = nullptr;         // [H x 4H]
     float* part = nullptr;
     int32_t* seg = nullptr;      // the nodes grouped by word, for the embedding gradient
-    // persistent path: level offsets and the barrier's counters (carved right
-    // after the schedule arrays and before `seg`, so that each direction's
-    // upload is one copy), and node rows padded to whole 128-byte lines
-    int32_t* loff = nullptr;     // [N + 1]
+    // groups of trees per XCD (tree_xcd.hpp): the groups and their tiles (carved
+    // after the schedule arrays, so that one copy uploads both), the counters,
+    // and node rows padded to whole 128-byte lines
+    treex::Group* xgroup = nullptr;
+    treex::Tile* xtile = nullptr;    // [N]
     tpersist::TreeSync* tsync = nullptr;
-    float* XWp = nullptr;        // [N x ld4]
-    float* Gp = nullptr;         // [N x ld4] h U^T (forward)
+    float* xl = nullptr;         // [N x ldx] inputs
+    float* hx = nullptr;         // [N x ldh] h of every node
     float* dGp = nullptr;        // [N x ld4]
     float* dXWp = nullptr;       // [N x ld4]
     float* Gtp = nullptr;        // [N x ld3]
     float* Fp = nullptr;         // [N x ldh]
     float* Cp = nullptr;         // [N x ldh]
-    float* Hnp = nullptr;        // [N x ldh]
-    float* dcp = nullptr;        // [N x ldh]
-    float* dhp = nullptr;        // [N x ldh]
-    float* dxp = nullptr;        // [N x ldx]
+    float* dxp = nullptr;        // [3][N x E] parts of the inputs' gradient
+    float* tpart = nullptr;      // parts of dW and dU
+    float* tsum = nullptr;       // parts of db
     int64_t ld4 = 0, ld3 = 0, ldh = 0, ldx = 0;
 };
 
@@ -81,11 +82,13 @@ size_t carve_cs(const janus_treelstm_desc& d, int32_t N, void* base, CsWs& w) {
     w.pcoff = c.take<int32_t>(int64_t(N) + 1);
     w.pkids = c.take<int32_t>(N);
     w.rootk = c.take<int32_t>(N);
-    w.loff = c.take<int32_t>(int64_t(N) + 1);
+    w.xgroup = reinterpret_cast<treex::Group*>(
+        c.take<int32_t>(std::min(treex::kGroupInts, sizeof(treex::Group) / 4 * (size_t(N) + treex::kMaxGroups))));
+    w.xtile = c.take<treex::Tile>(N);
     w.tsync = c.take<tpersist::TreeSync>(1);
-    // the nodes grouped by word, and (persistent backward) each workgroup's
-    // first group of the embedding rows
-    w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)) + tpersist::kMaxTreeGrid);
+    w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));   // the nodes grouped by word
+    const size_t mark = c.off;
+    // a call takes one of the two paths: their arrays share the space
     w.XW = c.take<float>(int64_t(N) * 4 * H);
     w.G = c.take<float>(int64_t(N) * 4 * H);
     w.Gt = c.take<float>(int64_t(N) * 3 * H);
@@ -99,21 +102,23 @@ size_t carve_cs(const janus_treelstm_desc& d, int32_t N, void* base, CsWs& w) {
     w.Wt = c.take<float>(int64_t(E) * 4 * H);
     w.Ut = c.take<float>(int64_t(H) * 4 * H);
     w.part = c.take<float>(colsum_partial_floats(4 * H));
+    const size_t levels_end = c.off;
+    c.off = mark;
     w.ld4 = round_up(int64_t(4) * H, 32);
     w.ld3 = round_up(int64_t(3) * H, 32);
     w.ldh = round_up(H, 32);
     w.ldx = round_up(E, 32);
-    w.XWp = c.take<float>(int64_t(N) * w.ld4);
-    w.Gp = c.take<float>(int64_t(N) * w.ld4);
+    w.xl = c.take<float>(int64_t(N) * w.ldx);
+    w.hx = c.take<float>(int64_t(N) * w.ldh);
     w.dGp = c.take<float>(int64_t(N) * w.ld4);
     w.dXWp = c.take<float>(int64_t(N) * w.ld4);
     w.Gtp = c.take<float>(int64_t(N) * w.ld3);
     w.Fp = c.take<float>(int64_t(N) * w.ldh);
     w.Cp = c.take<float>(int64_t(N) * w.ldh);
-    w.Hnp = c.take<float>(int64_t(N) * w.ldh);
-    w.dcp = c.take<float>(int64_t(N) * w.ldh);
-    w.dhp = c.take<float>(int64_t(N) * w.ldh);
-    w.dxp = c.take<float>(int64_t(N) * w.ldx);
+    w.dxp = c.take<float>(int64_t(3) * N * E);
+    w.tpart = c.take<float>(tail_part_floats(4 * H, E) + tail_part_floats(4 * H, H));
+    w.tsum = c.take<float>(tail_sum_floats(N, 4 * H));
+    c.off = std::max(c.off, levels_end);
     return c.off + 256;
 }
 
@@ -190,22 +195,25 @@ janus_status check_cs(const janus_treelstm_desc* d) {
     return JANUS_OK;
 }
 
-// Validates the call and carves the workspace; `upload` also copies the
-// schedule arrays (carved one after another: one copy) for the level-by-level
-// kernels.
+// Validates the call and carves the workspace.
 janus_status prepare_cs(const janus_treelstm_desc* d, const janus_nary_tree_batch* t, void* ws, size_t ws_bytes,
-                        NarySchedule& s, CsWs& w, hipStream_t st, bool upload = true) {
+                        NarySchedule& s, CsWs& w) {
     janus_status e = check_cs(d);
     if (e != JANUS_OK) return e;
     if ((e = build_nary_schedule(t, d->V, s)) != JANUS_OK) return e;
     if (!ws || ws_bytes < carve_cs(*d, s.N, nullptr, w) || reinterpret_cast<uintptr_t>(ws) % 256 != 0)
         return JANUS_ERR_WORKSPACE;
     carve_cs(*d, s.N, ws, w);
-    if (!upload) return JANUS_OK;
+    return JANUS_OK;
+}
+
+// Copies the schedule arrays (carved one after another: one copy) for the
+// level-by-level kernels.
+janus_status upload_cs(const NarySchedule& s, const CsWs& w, hipStream_t st) {
     const size_t nb = sizeof(int32_t) * s.N;
-    // the barrier block is zeroed too, so the device report of a call on
-    // this path reads no stale flag
-    const std::vector<char> zero_sync(offsetof(tpersist::TreeSync, group), 0);
+    // the error flag is zeroed too, so the device report of a call on this
+    // path reads no stale one
+    const std::vector<char> zero_sync(tpersist::kTreeSyncCounters, 0);
     const UploadPiece pieces[] = {{w.pword, s.pword.data(), nb},
                                   {w.pcoff, s.pcoff.data(), nb + sizeof(int32_t)},
                                   {w.pkids, s.pkids.data(), sizeof(int32_t) * s.pkids.size()},
@@ -214,148 +222,238 @@ janus_status prepare_cs(const janus_treelstm_desc* d, const janus_nary_tree_batc
     return upload_pieces(pieces, 5, st);
 }
 
-// ------------------------------------------------------- persistent path
-// Grid and LDS of the persistent Child-Sum kernels: one workgroup per CU at
-// most, the grid a multiple of the column tiles (forward: 4H / 32 gate
-// columns; backward: H / 32 columns of dh).  Off with JANUS_TREE_PERSIST=0,
-// for inputs wider than 512 (the embedding gradient's two columns per
-// thread), or where the backward's U columns and dG tile (two 32 x 4H slabs)
-// do not fit the LDS (about H > 156); the level-by-level kernels run then.
+// ------------------------------------------------- groups of trees per XCD
+// Four gates of 4 NT units per forward workgroup, 16 units of dh per backward
+// workgroup.  H below 320 (the forward's G rows of a group's nodes then still
+// leave room in the LDS for batches of a few hundred nodes per group), E up to
+// 512; off with JANUS_TREE_PERSIST=0.  Other sizes run level by level.
 struct CsPlan {
     bool on = false;
-    int ncolf = 0, fwd_grid = 0, ncolb = 0, bwd_grid = 0;
+    int NT = 0, fwd_nu = 0, bwd_nu = 0;
+    treex::Cut cut;
     size_t fwd_lds = 0, bwd_lds = 0;
+    // the schedule in the cut's order
+    std::vector<int32_t> word, coff, kids, rootk;
 };
-CsPlan cs_plan(const janus_treelstm_desc& d) {
+size_t cs_fwd_lds(int NT, int nodes) {
+    return NT == 1 ? treex::CsFwdCfg<1>::lds(nodes) : NT == 2 ? treex::CsFwdCfg<2>::lds(nodes) : treex::CsFwdCfg<3>::lds(nodes);
+}
+CsPlan cs_plan(const janus_treelstm_desc& d, const janus_nary_tree_batch* t, const NarySchedule& s) {
     CsPlan p;
-    const char* e = getenv("JANUS_TREE_PERSIST");
-    if (e && e[0] == '0') return p;
+    const char* env = getenv("JANUS_TREE_PERSIST");
+    if (env && env[0] == '0') return p;
     const tpersist::TreeDev dev = tpersist::tree_dev();
-    if (dev.cus <= 0 || dev.lds == 0 || d.E > tpersist::kMaxE) return p;
-    p.ncolf = (4 * d.H + 31) / 32;
-    p.ncolb = (d.H + 31) / 32;
-    if (p.ncolf > dev.cus) return p;
-    const int cus = dev.cus < tpersist::kMaxTreeGrid ? dev.cus : tpersist::kMaxTreeGrid;
-    p.fwd_grid = p.ncolf * (cus / p.ncolf);
-    p.bwd_grid = p.ncolb * (cus / p.ncolb);
-    p.fwd_lds = size_t(tpersist::cs_fwd_lds_floats(d.E, d.H)) * sizeof(float);
-    p.bwd_lds = size_t(tpersist::cs_bwd_lds_floats(d.H)) * sizeof(float);
-    p.on = p.fwd_lds <= dev.lds && p.bwd_lds <= dev.lds;
+    if (dev.cus <= 0 || dev.lds == 0 || d.H >= 320 || d.E > tpersist::kMaxE) return p;
+    const int32_t N = s.N;
+    if (int64_t(N) * round_up(4 * d.H, 32) * 4 >= (int64_t(1) << 31) || int64_t(N) * round_up(d.E, 32) * 4 >= (int64_t(1) << 31))
+        return p;   // 32-bit byte offsets
+    p.NT = d.H <= 128 ? 1 : d.H <= 256 ? 2 : 3;
+    p.fwd_nu = (d.H + 4 * p.NT - 1) / (4 * p.NT);
+    p.bwd_nu = (d.H + treex::CsBwdCfg::U - 1) / treex::CsBwdCfg::U;
+    const int capacity = treex::node_capacity(
+        dev.lds, [&](int n) { return std::max(cs_fwd_lds(p.NT, n), treex::CsBwdCfg::lds(n)); });
+    // positions are by (level, id) already; a child belongs to its parent's tree
+    const int L = int(s.level_offsets.size()) - 1;
+    std::vector<int32_t> tree(N, 0), ident(N);
+    for (int32_t k = 0; k < t->num_trees; ++k) tree[s.rootpos[k]] = k;
+    for (int32_t q = N; q-- > 0;) {
+        ident[q] = q;
+        for (int32_t e = s.pcoff[q]; e < s.pcoff[q + 1]; ++e) tree[s.pkids[e]] = tree[q];
+    }
+    if (!treex::cut_batch(t->num_trees, N, ident, s.level_offsets, L, tree, std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut))
+        return p;
+    p.fwd_lds = cs_fwd_lds(p.NT, p.cut.most_nodes);
+    p.bwd_lds = treex::CsBwdCfg::lds(p.cut.most_nodes);
+    p.word.resize(N);
+    p.rootk.resize(N);
+    p.coff.assign(N + 1, 0);
+    p.kids.reserve(N);
+    for (int32_t q = 0; q < N; ++q) {
+        const int32_t o = p.cut.order[q];
+        p.word[q] = s.pword[o];
+        p.rootk[q] = s.rootk[o];
+        for (int32_t e = s.pcoff[o]; e < s.pcoff[o + 1]; ++e) p.kids.push_back(p.cut.pos[s.pkids[e]]);
+        p.coff[q + 1] = int32_t(p.kids.size());
+    }
+    p.on = true;
     return p;
 }
+int cs_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
+unsigned cs_fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
+int cs_force_remote() {
+    const char* e = getenv("JANUS_XCD_REMOTE");
+    return e && e[0] == '1' ? 1 : 0;
+}
 
-// Forward: schedule, level offsets and the zeroed barrier block (error flag
-// included) in one copy, then one launch for every level.
-janus_status cs_fwd_persistent_call(const janus_treelstm_desc& d, const NarySchedule& s, const CsWs& w,
-                                    const CsPlan& plan, const void* emb, const void* W, const void* U, const void* b,
-                                    void* h_root, hipStream_t st) {
-    const size_t nb = sizeof(int32_t) * s.N;
-    const std::vector<char> zero_sync(offsetof(tpersist::TreeSync, group), 0);
-    const UploadPiece pieces[] = {{w.pword, s.pword.data(), nb},
-                                  {w.pcoff, s.pcoff.data(), nb + sizeof(int32_t)},
-                                  {w.pkids, s.pkids.data(), sizeof(int32_t) * s.pkids.size()},
-                                  {w.rootk, s.rootk.data(), nb},
-                                  {w.loff, s.level_offsets.data(), sizeof(int32_t) * s.level_offsets.size()},
-                                  {w.tsync, zero_sync.data(), zero_sync.size()}};
+template <int NT>
+janus_status launch_cs_fwd(const CsPlan& p, const treex::CsFwd& a, hipStream_t st) {
+    static size_t attr = 0;
+    return tpersist::tree_persistent_launch(treex::childsum_fwd_xcd<NT>, cs_blocks(p.cut, p.fwd_nu), p.fwd_lds, a, st,
+                                            attr, treex::kThreads);
+}
+
+janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s, const CsWs& w, const CsPlan& p,
+                             const void* emb, const void* W, const void* U, const void* b, void* h_root,
+                             hipStream_t st) {
+    const int32_t N = s.N;
+    const size_t nb = sizeof(int32_t) * N;
+    const UploadPiece pieces[] = {{w.pword, p.word.data(), nb},
+                                  {w.pcoff, p.coff.data(), nb + sizeof(int32_t)},
+                                  {w.pkids, p.kids.data(), sizeof(int32_t) * p.kids.size()},
+                                  {w.rootk, p.rootk.data(), nb},
+                                  {w.xgroup, p.cut.group.data(), sizeof(treex::Group) * p.cut.group.size()},
+                                  {w.xtile, p.cut.tile.data(), sizeof(treex::Tile) * p.cut.tile.size()}};
     janus_status e = upload_pieces(pieces, 6, st);
     if (e != JANUS_OK) return e;
-    tpersist::CsFwdArgs a;
+    treex::CsFwd a = {};
     a.E = d.E;
     a.H = d.H;
-    a.N = s.N;
-    a.nlev = int(s.level_offsets.size()) - 1;
-    a.ncol = plan.ncolf;
-    a.loff = w.loff;
-    a.pword = w.pword;
-    a.pcoff = w.pcoff;
-    a.pkids = w.pkids;
+    a.M0 = s.level_offsets[1];
+    a.groups = p.cut.groups;
+    a.nu = p.fwd_nu;
+    a.force_remote = cs_force_remote();
+    a.tile = w.xtile;
+    a.coff = w.pcoff;
+    a.kids = w.pkids;
     a.rootk = w.rootk;
-    a.emb = static_cast<const float*>(emb);
     a.W = static_cast<const float*>(W);
     a.U = static_cast<const float*>(U);
     a.b = static_cast<const float*>(b);
-    a.XW = w.XWp;
-    a.G = w.Gp;
-    a.ld4 = w.ld4;
+    a.x = w.xl;
+    a.ldx = w.ldx;
+    a.x_bytes = uint32_t(int64_t(N) * w.ldx * 4);
+    a.hx = w.hx;
+    a.ldh = w.ldh;
+    a.hx_bytes = uint32_t(int64_t(N) * w.ldh * 4);
     a.Gt = w.Gtp;
     a.ld3 = w.ld3;
     a.F = w.Fp;
     a.C = w.Cp;
-    a.Hn = w.Hnp;
-    a.ldh = w.ldh;
     a.h_root = static_cast<float*>(h_root);
     a.sync = w.tsync;
-    static size_t attr = 0;
-    const double flops = 2.0 * s.N * 4.0 * d.H * (double(d.E) + double(d.H));
-    TraceScope trace("childsum_fwd_persistent", flops, 0.0, st);
-    return tpersist::tree_persistent_launch(tpersist::childsum_fwd_persistent, plan.fwd_grid, plan.fwd_lds, a, st,
-                                            attr);
+    for (int part = 0; part < p.cut.parts; ++part) {
+        if (part == 0) {
+            TraceScope trace("tree_fwd_init", 0.0, 4.0 * double(N) * (w.ldh + 2.0 * w.ldx), st);
+            hipLaunchKernelGGL(treex::fwd_init_kernel, dim3(cs_fill_blocks(int64_t(N) * (w.ldh + w.ldx))), dim3(256), 0,
+                               st, N, N, d.E, w.pword, static_cast<const float*>(emb), w.xl, w.ldx, w.hx, w.ldh, d.H,
+                               w.tsync);
+        } else {   // the counters of the next launch
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(4), dim3(256), 0, st, w.hx, w.ldh, int64_t(0), int64_t(0), d.H,
+                               w.tsync);
+        }
+        JANUS_LAUNCH_CHECK();
+        a.group = w.xgroup + part * p.cut.groups;
+        TraceScope trace("childsum_fwd_persistent", 2.0 * N * 4.0 * d.H * (double(d.E) + double(d.H)) / p.cut.parts, 0.0,
+                         st);
+        e = p.NT == 1 ? launch_cs_fwd<1>(p, a, st) : p.NT == 2 ? launch_cs_fwd<2>(p, a, st) : launch_cs_fwd<3>(p, a, st);
+        if (e != JANUS_OK) return e;
+    }
+    return JANUS_OK;
 }
 
-// Backward: the forward's schedule (the workspace is unchanged between the
-// calls); the nodes grouped by word and the barrier's counters (not its
-// error flag) in one copy, then one launch.
-janus_status cs_bwd_persistent_call(const janus_treelstm_desc& d, const NarySchedule& s, const CsWs& w,
-                                    const CsPlan& plan, const void* emb, const void* W, const void* U,
-                                    const void* dh_root, float* demb, float* dW, float* dU, float* db,
-                                    hipStream_t st) {
+// The schedule is the forward's (the workspace is unchanged between the calls).
+janus_status cs_bwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s, const CsWs& w, const CsPlan& p,
+                             const void* W, const void* U, const void* dh_root, float* demb, float* dW, float* dU,
+                             float* db, hipStream_t st) {
+    const int32_t N = s.N;
+    const int H = d.H, E = d.E;
     std::vector<int32_t> seg;
-    const int nseg = embed_segments(s.pword.data(), s.N, d.V, seg);
-    // first group of each workgroup's rows [V w / grid, V (w + 1) / grid)
-    for (int g = 0; g < plan.bwd_grid; ++g) {
-        const int32_t* sid = seg.data() + s.N + nseg + 1;
-        const int64_t v0 = int64_t(d.V) * g / plan.bwd_grid;
-        const int32_t first = int32_t(std::lower_bound(sid, sid + nseg, v0) - sid);
-        seg.push_back(first);
-    }
-    const size_t counters = offsetof(tpersist::TreeSync, group) - tpersist::kTreeSyncCounters;
-    const std::vector<char> zero_counters(counters, 0);
-    const UploadPiece pieces[] = {
-        {reinterpret_cast<char*>(w.tsync) + tpersist::kTreeSyncCounters, zero_counters.data(), counters},
-        {w.seg, seg.data(), seg.size() * sizeof(int32_t)}};
-    janus_status e = upload_pieces(pieces, 2, st);
+    const int nseg = embed_segments(p.word.data(), N, d.V, seg);
+    janus_status e = upload(w.seg, seg.data(), seg.size() * sizeof(int32_t), st);
     if (e != JANUS_OK) return e;
-    tpersist::CsBwdArgs a;
-    a.E = d.E;
-    a.H = d.H;
-    a.N = s.N;
-    a.nlev = int(s.level_offsets.size()) - 1;
-    a.ncol = plan.ncolb;
-    a.nseg = nseg;
-    a.V = d.V;
-    a.loff = w.loff;
-    a.pword = w.pword;
-    a.pcoff = w.pcoff;
-    a.pkids = w.pkids;
+    treex::CsBwd a = {};
+    a.H = H;
+    a.M0 = s.level_offsets[1];
+    a.groups = p.cut.groups;
+    a.nu = p.bwd_nu;
+    a.force_remote = cs_force_remote();
+    a.tile = w.xtile;
+    a.coff = w.pcoff;
+    a.kids = w.pkids;
     a.rootk = w.rootk;
-    a.seg = w.seg;
-    a.emb = static_cast<const float*>(emb);
-    a.W = static_cast<const float*>(W);
     a.U = static_cast<const float*>(U);
     a.Gt = w.Gtp;
     a.ld3 = w.ld3;
     a.F = w.Fp;
     a.C = w.Cp;
-    a.Hn = w.Hnp;
     a.ldh = w.ldh;
     a.dh_root = static_cast<const float*>(dh_root);
     a.dG = w.dGp;
-    a.dXW = w.dXWp;
     a.ld4 = w.ld4;
-    a.dc = w.dcp;
-    a.dx = w.dxp;
-    a.ldx = w.ldx;
-    a.demb = demb;
-    a.dW = dW;
-    a.dU = dU;
-    a.db = db;
+    a.dG_bytes = uint32_t(int64_t(N) * w.ld4 * 4);
+    a.dXW = w.dXWp;
     a.sync = w.tsync;
-    static size_t attr = 0;
-    // dh = dG U, dW, dU and dx over every node
-    const double flops = 2.0 * s.N * 4.0 * d.H * (2.0 * d.H + 2.0 * d.E);
-    TraceScope trace("childsum_bwd_persistent", flops, 0.0, st);
-    return tpersist::tree_persistent_launch(tpersist::childsum_bwd_persistent, plan.bwd_grid, plan.bwd_lds, a, st,
-                                            attr);
+    for (int part = 0; part < p.cut.parts; ++part) {
+        if (part == 0) {
+            TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(N) * w.ld4, st);
+            hipLaunchKernelGGL(treex::cs_bwd_init_kernel, dim3(cs_fill_blocks(int64_t(N) * w.ld4)), dim3(256), 0, st, N, H,
+                               w.rootk, w.dGp, w.ld4, w.tsync);
+        } else {
+            hipLaunchKernelGGL(treex::fill_kernel, dim3(4), dim3(256), 0, st, w.hx, w.ldh, int64_t(0), int64_t(0), H,
+                               w.tsync);
+        }
+        JANUS_LAUNCH_CHECK();
+        a.group = w.xgroup + part * p.cut.groups;
+        static size_t attr = 0;
+        TraceScope trace("childsum_bwd_persistent", 2.0 * N * 4.0 * H * double(H) / p.cut.parts, 0.0, st);
+        e = tpersist::tree_persistent_launch(treex::childsum_bwd_xcd, cs_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
+                                             treex::kThreads);
+        if (e != JANUS_OK) return e;
+    }
+    TailArgs q;
+    GemmDesc g;
+    g.dtype = JANUS_F32;
+    // dW = dXW^T X, dU = dG^T h (roots' rows of dG are 0)
+    g.M = 4 * H;
+    g.N = E;
+    g.K = N;
+    g.a_t = g.b_t = true;
+    g.A = w.dXWp;
+    g.lda = w.ld4;
+    g.B = w.xl;
+    g.ldb = w.ldx;
+    g.C = dW;
+    g.ldc = E;
+    tail_add(q, g, w.tpart);
+    g.N = H;
+    g.A = w.dGp;
+    g.B = w.hx;
+    g.ldb = w.ldh;
+    g.C = dU;
+    g.ldc = H;
+    tail_add(q, g, w.tpart + tail_part_floats(4 * H, E));
+    // dX = dXW W, in up to three parts that the embedding rows add up
+    g.M = N;
+    g.N = E;
+    g.K = 4 * H;
+    g.a_t = false;
+    g.A = w.dXWp;
+    g.B = W;
+    g.ldb = E;
+    g.C = nullptr;
+    tail_add(q, g, w.dxp, 3);
+    TailProblem& dx = q.p[q.n - 1];
+    if (dx.splits == 1) {
+        dx.g.C = w.dxp;
+        dx.g.ldc = E;
+    }
+    q.dx = w.dxp;
+    q.ldx = E;
+    q.dx_parts = dx.splits;
+    q.dx_stride = int64_t(N) * E;
+    q.src = w.dXWp;
+    q.ld = w.ld4;
+    q.rows = N;
+    q.cols = 4 * H;
+    q.sum_part = w.tsum;
+    q.sum_out = db;
+    q.demb = demb;
+    q.demb_n = int64_t(d.V) * E;
+    q.E = E;
+    q.leaves = N;
+    q.nseg = nseg;
+    q.seg = w.seg;
+    return tail_run(q, "childsum_bwd_tail", st);
 }
 
 }  // namespace
@@ -377,10 +475,11 @@ extern "C" janus_status janus_childsum_fwd(const janus_childsum_desc* d, const j
     hipStream_t st = static_cast<hipStream_t>(stream);
     NarySchedule s;
     CsWs w;
-    const CsPlan plan = cs_plan(*d);
-    janus_status e = prepare_cs(d, t, ws, ws_bytes, s, w, st, !plan.on);
+    janus_status e = prepare_cs(d, t, ws, ws_bytes, s, w);
     if (e != JANUS_OK) return e;
-    if (plan.on) return cs_fwd_persistent_call(*d, s, w, plan, emb, W, U, b, h_root, st);
+    const CsPlan plan = cs_plan(*d, t, s);
+    if (plan.on) return cs_fwd_xcd_call(*d, s, w, plan, emb, W, U, b, h_root, st);
+    if ((e = upload_cs(s, w, st)) != JANUS_OK) return e;
     const int H = d->H, E = d->E, N = s.N;
     const int L = int(s.level_offsets.size()) - 1;
     if ((e = transpose_f32(static_cast<const float*>(W), 4 * H, E, w.Wt, st)) != JANUS_OK) return e;
@@ -416,10 +515,11 @@ extern "C" janus_status janus_childsum_bwd(const janus_childsum_desc* d, const j
     hipStream_t st = static_cast<hipStream_t>(stream);
     NarySchedule s;
     CsWs w;
-    const CsPlan plan = cs_plan(*d);
-    janus_status e = prepare_cs(d, t, ws, ws_bytes, s, w, st, !plan.on);
+    janus_status e = prepare_cs(d, t, ws, ws_bytes, s, w);
     if (e != JANUS_OK) return e;
-    if (plan.on) return cs_bwd_persistent_call(*d, s, w, plan, emb, W, U, dh_root, demb, dW, dU, db, st);
+    const CsPlan plan = cs_plan(*d, t, s);
+    if (plan.on) return cs_bwd_xcd_call(*d, s, w, plan, W, U, dh_root, demb, dW, dU, db, st);
+    if ((e = upload_cs(s, w, st)) != JANUS_OK) return e;
     const int H = d->H, E = d->E, N = s.N;
     const int L = int(s.level_offsets.size()) - 1;
     // roots have no parent: their dG rows and dc stay 0
@@ -461,7 +561,7 @@ extern "C" janus_status janus_childsum_device_report(const janus_childsum_desc* 
     hipStream_t st = static_cast<hipStream_t>(stream);
     NarySchedule s;
     CsWs w;
-    janus_status e = prepare_cs(d, t, const_cast<void*>(ws), ws_bytes, s, w, st, false);
+    janus_status e = prepare_cs(d, t, const_cast<void*>(ws), ws_bytes, s, w);
     if (e != JANUS_OK) return e;
     unsigned flag = 0;
     JANUS_HIP(hipStreamSynchronize(st));

@@ -37,7 +37,6 @@ namespace janus {
 
 namespace {
 
-using tpersist::kMaxTreeGrid;
 using tpersist::TreeDev;
 using tpersist::tree_dev;
 using tpersist::tree_persistent_launch;

@@ -757,6 +757,397 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
     }
 }
 
+// --------------------------------------------------------------- Child-Sum
+// A node's i, o, u take U (sum of its children's h) and each child its own
+// forget gate, so by linearity a node needs its children's rows G = U h.  The
+// owner of a unit computes the four gate rows of G for every node of the group
+// (from the exchanged h) and keeps them in LDS for the parent's cell.  Forward
+// and backward are each a serial chain of one exchange per tile, like the
+// binary trees'; the step of 25 trees of 5-50 nodes (E 300, H 150) went from
+// 352 us, with barriers over the whole device around each level, to 173 us.
+struct CsFwd {
+    int E, H, M0;
+    int groups, nu, force_remote;
+    const Group* group;
+    const Tile* tile;
+    const int32_t* coff;       // [N + 1] children of position p: kids[coff[p] .. coff[p + 1])
+    const int32_t* kids;       // child positions
+    const int32_t* rootk;
+    const float* W;            // [4H x E], blocks (i, o, u, f)
+    const float* U;            // [4H x H]
+    const float* b;
+    const float* x;            // [N x ldx] inputs
+    int64_t ldx;
+    uint32_t x_bytes;
+    float* hx;                 // [N x ldh]
+    int64_t ldh;
+    uint32_t hx_bytes;
+    float* Gt;                 // [N x ld3] gates i, o, u
+    int64_t ld3;
+    float* F;                  // [N x ldh] forget gate of each node towards its parent
+    float* C;                  // [N x ldh]
+    float* h_root;
+    TreeSync* sync;
+};
+
+// The children of a cell, the first two prefetched, the others eight at a time.
+struct Kids {
+    int n, c0, k[2];
+};
+template <class F>
+__device__ __forceinline__ void each_kid(const Kids& q, const int32_t* kids, F f) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (e < q.n) f(e, q.k[e]);
+    for (int e = 2; e < q.n; e += 8) {
+        int k[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) k[i] = e + i < q.n ? kids[q.c0 + e + i] : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (e + i < q.n) f(e + i, k[i]);
+    }
+}
+
+// NT row tiles hold the four gates of U = 4 NT units (row 4 u + gate), so a
+// lane's four accumulators are the gates of one (unit, node).
+template <int NT>
+struct CsFwdCfg {
+    static constexpr int U = 4 * NT;
+    static constexpr int JE = 4, JH = NT;             // k-groups of a wave: E up to 512, H up to 128 NT
+    static constexpr int RED = kWaves * NT * 256;     // floats of one set of partial tiles
+    // two sets for x W, one for G; then G and c of the group's nodes
+    static size_t lds(int nodes) { return sizeof(float) * (3 * size_t(RED) + size_t(nodes) * 5 * U); }
+};
+template <int NT>
+__global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
+    using C = CsFwdCfg<NT>;
+    constexpr int U = C::U, JE = C::JE, JH = C::JH;
+    extern __shared__ __align__(16) float sm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    f32x4_t* gl = reinterpret_cast<f32x4_t*>(sm + 3 * C::RED);                              // [nodes][U] gates
+    float* cl = sm + 3 * C::RED + int64_t(gr.nleaf + gr.nint) * 4 * U;                     // [nodes][U]
+    const int H = a.H, E = a.E, v0 = m * U;
+    const int ne = (E + 15) / 16, nh = (H + 15) / 16;
+    const int ke0 = wave * ne / kWaves, nje = (wave + 1) * ne / kWaves - ke0;
+    const int kh0 = wave * nh / kWaves, njh = (wave + 1) * nh / kWaves - kh0;
+    uint4 we[NT][JE], wh[NT][JH];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const int u = v0 + 4 * i + (lr >> 2), row = u < H ? (lr & 3) * H + u : -1;
+#pragma unroll
+        for (int j = 0; j < JE; ++j)
+            we[i][j] = j < nje ? weight4(a.W, E, row, 16 * (ke0 + j) + 4 * lq, E) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < JH; ++j)
+            wh[i][j] = j < njh ? weight4(a.U, H, row, 16 * (kh0 + j) + 4 * lq, H) : make_uint4(0, 0, 0, 0);
+    }
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    float bias[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[q] = cell_thread ? a.b[q * H + cj] : 0.f;
+    // partial tiles of a unit's four gates: tile cu / 4, lane 16 (cu % 4) + cn
+    const int po = (cu >> 2) * 64 + (cu & 3) * 16 + cn;
+    auto sum4 = [&](const f32x4_t* red) {
+        f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += red[w * NT * 64 + po];
+        return s;
+    };
+    f32x4_t* redx = reinterpret_cast<f32x4_t*>(sm);
+    f32x4_t* redg = reinterpret_cast<f32x4_t*>(sm + 2 * C::RED);
+    const auto rx = make_rsrc(a.x, a.x_bytes), rh = make_rsrc(a.hx, a.hx_bytes);
+    TileWindow win;
+    win.init(a.tile, gr.t1, gr.t0);
+    bool dead = false;
+    unsigned phase = 0;
+
+    auto load_x = [&](int t, uint4 (&f)[JE]) {
+        const Tile tl = win.at(t);
+        xcd::load_operand<float>(f, rx, [&](int j) {
+            return lr < tile_rows(tl) && j < nje
+                       ? (uint32_t(tl.p0 + lr) * uint32_t(a.ldx) + uint32_t(16 * (ke0 + j) + 4 * lq)) * 4u
+                       : kOutOfRange;
+        }, false, a.sync, dead);
+    };
+    auto mma_x = [&](int t, const uint4 (&f)[JE]) {
+        f32x4_t acc[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < JE; ++j)
+            if (j < nje) {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[i] = xcd::mma(we[i][j], f[j], acc[i], static_cast<const float*>(nullptr));
+            }
+#pragma unroll
+        for (int i = 0; i < NT; ++i) redx[(t & 1) * kWaves * NT * 64 + (wave * NT + i) * 64 + lane] = acc[i];
+    };
+    // a cell's children and root slot: the list's ends first, the first ids later
+    struct Cell {
+        int p, rk, c0, c1;
+    };
+    auto fetch = [&](int t) {
+        const Tile tl = win.at(t);
+        Cell c;
+        const int p = tl.p0 + min(cn, tile_rows(tl) - 1);
+        c.p = cell_thread && cn < tile_rows(tl) ? p : -1;
+        c.rk = a.rootk[p];
+        c.c0 = a.coff[p];
+        c.c1 = a.coff[p + 1];
+        return c;
+    };
+    auto fetch_kids = [&](const Cell& c) {
+        Kids q;
+        q.n = c.p >= 0 ? c.c1 - c.c0 : 0;
+        q.c0 = c.c0;
+        q.k[0] = q.n > 0 ? a.kids[c.c0] : 0;
+        q.k[1] = q.n > 1 ? a.kids[c.c0 + 1] : 0;
+        return q;
+    };
+    uint4 fx[JE];
+    load_x(gr.t0, fx);
+    Cell ce = fetch(gr.t0);
+    mma_x(gr.t0, fx);
+    Kids kd = fetch_kids(ce);
+    __syncthreads();
+    for (int t = gr.t0; t < gr.t1; ++t) {
+        const Tile tl = win.at(t);
+        const int rows = tile_rows(tl);
+        const bool more = t + 1 < gr.t1;
+        if (more) load_x(t + 1, fx);
+        if (ce.p >= 0) {
+            const int p = ce.p;
+            const f32x4_t xw = sum4(redx + (t & 1) * kWaves * NT * 64);
+            float ai = xw[0] + bias[0], ao = xw[1] + bias[1], au = xw[2] + bias[2], cs = 0.f;
+            const float af = xw[3] + bias[3];
+            each_kid(kd, a.kids, [&](int, int k) {
+                const int lo = local_of(gr, a.M0, k) * U + cu;
+                const f32x4_t gk = gl[lo];
+                ai += gk[0];
+                ao += gk[1];
+                au += gk[2];
+                const float f = sigmoidf_(af + gk[3]);
+                a.F[int64_t(k) * a.ldh + cj] = f;
+                cs += f * cl[lo];
+            });
+            const float gi = sigmoidf_(ai), go = sigmoidf_(ao), gu = tanhf_(au);
+            const float c = gi * gu + cs;
+            const float h = go * tanhf_(c);
+            xcd::store_b32(rh, (uint32_t(p) * uint32_t(a.ldh) + uint32_t(cj)) * 4u, not_empty(__float_as_uint(h)));
+            cl[local_of(gr, a.M0, p) * U + cu] = c;
+            a.C[int64_t(p) * a.ldh + cj] = c;
+            float* gt = a.Gt + int64_t(p) * a.ld3 + cj;
+            gt[0] = gi;
+            gt[H] = go;
+            gt[2 * H] = gu;
+            if (ce.rk >= 0) a.h_root[int64_t(ce.rk) * H + cj] = h;
+        }
+        if (!more) break;   // the last tile holds roots: nobody needs their G
+        const int pc = ce.p;
+        ce = fetch(t + 1);
+        mma_x(t + 1, fx);   // while h of this tile arrives
+        if (!local) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+        uint4 f[JH];
+        xcd::load_operand<float>(f, rh, [&](int j) {
+            return lr < rows && j < njh
+                       ? (uint32_t(tl.p0 + lr) * uint32_t(a.ldh) + uint32_t(16 * (kh0 + j) + 4 * lq)) * 4u
+                       : kOutOfRange;
+        }, local, a.sync, dead);
+        kd = fetch_kids(ce);
+        f32x4_t acc[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < JH; ++j)
+            if (j < njh) {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[i] = xcd::mma(wh[i][j], f[j], acc[i], static_cast<const float*>(nullptr));
+            }
+#pragma unroll
+        for (int i = 0; i < NT; ++i) redg[(wave * NT + i) * 64 + lane] = acc[i];
+        __syncthreads();
+        if (pc >= 0) gl[local_of(gr, a.M0, pc) * U + cu] = sum4(redg);
+        __syncthreads();
+    }
+}
+
+struct CsBwd {
+    int H, M0;
+    int groups, nu, force_remote;
+    const Group* group;
+    const Tile* tile;
+    const int32_t* coff;
+    const int32_t* kids;
+    const int32_t* rootk;
+    const float* U;
+    const float* Gt;
+    int64_t ld3;
+    const float* F;
+    const float* C;
+    int64_t ldh;
+    const float* dh_root;
+    float* dG;                 // [N x ld4] gradient of each node's G row (exchange); zero for roots
+    int64_t ld4;
+    uint32_t dG_bytes;
+    float* dXW;                // [N x ld4]
+    TreeSync* sync;
+};
+// Set-up: empty rows of dG, zero for roots, counters zero.
+static __global__ __launch_bounds__(256) void cs_bwd_init_kernel(int N, int H, const int32_t* rootk, float* dG,
+                                                                 int64_t ld4, TreeSync* s) {
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    zero_counters(s, i0, stride);
+    const int q = int(ld4 / 4);
+    uint4* d = reinterpret_cast<uint4*>(dG);
+    for (int64_t i = i0; i < int64_t(N) * q; i += stride) {
+        const int c = 4 * int(i % q);
+        const uint32_t e = rootk[i / q] >= 0 ? 0u : kEmpty;
+        d[i] = make_uint4(c < 4 * H ? e : 0u, c + 1 < 4 * H ? e : 0u, c + 2 < 4 * H ? e : 0u, c + 3 < 4 * H ? e : 0u);
+    }
+}
+
+// One row tile of 16 units; K = 4H gate columns, at most J k-groups a wave.
+struct CsBwdCfg {
+    static constexpr int U = 16, J = 10;
+    static constexpr int RED = kWaves * 256;
+    static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
+};
+static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
+    using C = CsBwdCfg;
+    constexpr int U = C::U, J = C::J;
+    extern __shared__ __align__(16) float sm[];
+    float* dcl = sm + 2 * C::RED;   // [nodes][U]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lq = lane >> 4;
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
+    const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
+    if (g < 0) return;
+    const Group gr = a.group[g];
+    const int H = a.H, K = 4 * H, v0 = m * U, nk = (K + 15) / 16;
+    const int kw0 = wave * nk / kWaves, nj = (wave + 1) * nk / kWaves - kw0;
+    uint4 w[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int u = v0 + lr, k = 16 * (kw0 + j) + 4 * lq;
+        float tmp[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tmp[e] = u < H && j < nj && k + e < K ? a.U[int64_t(k + e) * H + u] : 0.f;
+        w[j] = make_uint4(__float_as_uint(tmp[0]), __float_as_uint(tmp[1]), __float_as_uint(tmp[2]), __float_as_uint(tmp[3]));
+    }
+    const int cu = tid >> 4, cn = tid & 15, cj = v0 + cu;
+    const bool cell_thread = cu < U && cj < H;
+    const auto rs = make_rsrc(a.dG, a.dG_bytes);
+    TileWindow win;
+    win.init(a.tile, gr.t1, max(gr.t1 - 64, gr.t0));
+    bool dead = false;
+    unsigned phase = 0;
+    // a cell's inputs, a tile ahead: first what its position gives, then its
+    // first children, then their values
+    struct Cell {
+        int p, rk, c0, c1;
+        float gi, go, gu, c, dhr;
+    };
+    struct Kid2 {
+        Kids q;
+        float f[2], c[2];
+    };
+    auto fetch = [&](int t) {
+        const Tile tl = win.at(t, true);
+        Cell x;
+        const int p = tl.p0 + min(cn, tile_rows(tl) - 1), j = cell_thread ? cj : 0;
+        x.p = cell_thread && cn < tile_rows(tl) ? p : -1;
+        x.rk = a.rootk[p];
+        x.c0 = a.coff[p];
+        x.c1 = a.coff[p + 1];
+        const float* gt = a.Gt + int64_t(p) * a.ld3 + j;
+        x.gi = gt[0];
+        x.go = gt[H];
+        x.gu = gt[2 * H];
+        x.c = a.C[int64_t(p) * a.ldh + j];
+        x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+        return x;
+    };
+    auto fetch_ids = [&](const Cell& x, Kid2& k) {
+        k.q.n = x.p >= 0 ? x.c1 - x.c0 : 0;
+        k.q.c0 = x.c0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) k.q.k[e] = e < k.q.n ? a.kids[x.c0 + e] : 0;
+    };
+    auto fetch_kids = [&](Kid2& k) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            k.f[e] = e < k.q.n ? a.F[int64_t(k.q.k[e]) * a.ldh + cj] : 0.f;
+            k.c[e] = e < k.q.n ? a.C[int64_t(k.q.k[e]) * a.ldh + cj] : 0.f;
+        }
+    };
+    Cell x = fetch(gr.t1 - 1);
+    Kid2 kd;
+    fetch_ids(x, kd);
+    fetch_kids(kd);
+    for (int t = gr.t1 - 1; t >= gr.t0; --t) {
+        const Tile tl = win.at(t, true);
+        const int rows = tile_rows(tl);
+        const bool more = t > gr.t0;
+        Cell nx = x;
+        if (more) nx = fetch(t - 1);
+        if (!local && t < gr.t1 - 1) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
+        uint4 f[J];
+        xcd::load_operand<float>(f, rs, [&](int j) {
+            return lr < rows && j < nj
+                       ? (uint32_t(tl.p0 + lr) * uint32_t(a.ld4) + uint32_t(16 * (kw0 + j) + 4 * lq)) * 4u
+                       : kOutOfRange;
+        }, local, a.sync, dead);
+        Kid2 nk2 = kd;
+        if (more) fetch_ids(nx, nk2);
+        f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (j < nj) acc = xcd::mma(w[j], f[j], acc, static_cast<const float*>(nullptr));
+        float* red = sm + (t & 1) * C::RED;
+        reinterpret_cast<f32x4_t*>(red)[wave * 64 + lane] = acc;
+        __syncthreads();
+        if (x.p >= 0) {
+            const int p = x.p;
+            const float dh = sum_waves<1>(red, cu, cn) + x.dhr;   // a root's dG row is 0
+            const float tau = tanhf_(x.c);
+            const float dc = x.rk >= 0 ? 0.f : dcl[local_of(gr, a.M0, p) * U + cu];
+            const float dct = dc + dh * x.go * (1.f - tau * tau);
+            const float dai = dct * x.gu * x.gi * (1.f - x.gi), dao = dh * tau * x.go * (1.f - x.go);
+            const float dau = dct * x.gi * (1.f - x.gu * x.gu);
+            float dafs = 0.f;
+            each_kid(kd.q, a.kids, [&](int e, int k) {
+                const float fk = e == 0 ? kd.f[0] : e == 1 ? kd.f[1] : a.F[int64_t(k) * a.ldh + cj];
+                const float ck = e == 0 ? kd.c[0] : e == 1 ? kd.c[1] : a.C[int64_t(k) * a.ldh + cj];
+                const float daf = dct * ck * fk * (1.f - fk);
+                dafs += daf;
+                const uint32_t o = (uint32_t(k) * uint32_t(a.ld4) + uint32_t(cj)) * 4u;
+                xcd::store_b32(rs, o, not_empty(__float_as_uint(dai)));
+                xcd::store_b32(rs, o + 4u * uint32_t(H), not_empty(__float_as_uint(dao)));
+                xcd::store_b32(rs, o + 8u * uint32_t(H), not_empty(__float_as_uint(dau)));
+                xcd::store_b32(rs, o + 12u * uint32_t(H), not_empty(__float_as_uint(daf)));
+                dcl[local_of(gr, a.M0, k) * U + cu] = dct * fk;
+            });
+            float* xw = a.dXW + int64_t(p) * a.ld4 + cj;
+            xw[0] = dai;
+            xw[H] = dao;
+            xw[2 * H] = dau;
+            xw[3 * H] = dafs;
+        }
+        if (more) fetch_kids(nk2);
+        x = nx;
+        kd = nk2;
+    }
+}
+
 // ------------------------------------------------------------- host side
 constexpr int kMaxGroups = 64;        // groups of one launch
 constexpr int kMaxParts = 16;         // launches of a batch at most

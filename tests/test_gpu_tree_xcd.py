@@ -88,3 +88,50 @@ def test_treernn_without_shared_l2(monkeypatch):
     g1 = _treernn(w)
     for k in ("h_root", "dW", "db", "demb"):
         assert np.array_equal(g0[k], g1[k]), k
+
+
+def _childsum(w, persistent=True):
+    from paper_1812_01329_amd import janus as J
+    from paper_1812_01329_amd.train_step import make_step
+    step = make_step(w)
+    J.janus_trace_begin()
+    step.run()
+    g = step.results()
+    labels = {r["label"] for r in J.janus_trace_end()}
+    assert ({"childsum_fwd_persistent", "childsum_bwd_persistent", "childsum_bwd_tail"} <= labels) == persistent, labels
+    assert J.janus_childsum_device_report(step.desc, w.trees, step.ws) == 0
+    r = oracle_steps.childsum_step(w)
+    t = TOL["f32"]
+    check("h_root", g["h_root"], r["h_root"], t["out"])
+    for k in ("dh_root", "dWs", "dbs", "dW", "dU", "db", "demb"):
+        check(k, g[k], r[k], t["grad"])
+    return g
+
+
+@pytest.mark.parametrize("H,E,n_trees", [(1, 1, 3), (3, 5, 1), (64, 37, 70), (128, 64, 9), (129, 33, 20), (256, 8, 5),
+                                         (257, 300, 9), (319, 512, 6)])
+def test_childsum_widths(H, E, n_trees):
+    print(f"[childsum-xcd] H={H} E={E} trees={n_trees}", flush=True)
+    _childsum(wl.sst_childsum(n_trees=n_trees, E=E, H=H, V=60, seed=H + E))
+
+
+def test_childsum_several_launches():
+    print("[childsum-xcd] parts", flush=True)
+    _childsum(wl.sst_childsum(n_trees=300, E=16, H=300, V=100, min_nodes=35, max_nodes=45, seed=14))
+
+
+def test_childsum_tree_past_the_groups_room_runs_levels():
+    """One tree of more nodes than a group's G and c rows in LDS."""
+    print("[childsum-xcd] large tree", flush=True)
+    _childsum(wl.sst_childsum(n_trees=2, E=16, H=260, V=100, sizes=[900, 20], seed=15), persistent=False)
+
+
+@pytest.mark.parametrize("H", [29, 200])
+def test_childsum_without_shared_l2(H, monkeypatch):
+    w = wl.sst_childsum(n_trees=30, E=24, H=H, V=50, seed=5)
+    g0 = _childsum(w)
+    monkeypatch.setenv("JANUS_XCD_REMOTE", "1")
+    print(f"[childsum-xcd-remote] H={H}", flush=True)
+    g1 = _childsum(w)
+    for k in ("h_root", "dW", "dU", "db", "demb"):
+        assert np.array_equal(g0[k], g1[k]), k
