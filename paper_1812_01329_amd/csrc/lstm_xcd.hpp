@@ -19,11 +19,23 @@
 // Four slots are used in turn, so the exchange stays in the L2; see the slot
 // argument below.
 //
+// Memory operations complete in issue order for a wave that waits for its
+// loads, so nothing a poll need not wait for stands between a publication and
+// the next poll: the loads of the next step's own operands, and the forward's
+// results for later kernels (gates, c, h), are issued once the operand of the
+// exchange has arrived, and complete while it is multiplied.  (The backward's
+// only results, dG, follow their publication: 3% better in float32 than after
+// the poll, the same in bf16.)  (Forward per step,
+// stores and loads issued right after the publication: H 1024 2.9 us, H 656
+// 2.5, H 512 1.9; issued after the poll: 2.2, 1.6, 1.5.)
+//
 // Measured per time step against the kernels with a device-wide barrier:
-// H 1024, B 128 (lengths 1..200): forward 2.9 against 5.9 us, backward 3.4
-// against 7.7; H 656, B 20: 2.5 against 4.5 and 3.3 against 6.5; H 512, B 33:
-// forward 1.9 against 4.1.  float32, H 256, B 32, against one launch per step:
-// 1.9 against 9.7 us and 2.6 against 53.
+// H 1024, B 128: forward 2.2 against 5.9 us, backward 3.2 against 7.7; H 656,
+// B 20: 1.6 against 4.5 and 2.2 against 6.5; H 512, B 33: forward 1.5 against
+// 4.1.  float32, H 256, B 32, against one launch per step: 1.6 against 9.7 us
+// and 2.4 against 53.  A launch adds 17-40 us before its first step (placement
+// and weights).  The backward's step is longer by its operand, four times the
+// forward's: every workgroup reads all gate columns of its rows from the L2.
 //
 // Inside a workgroup the eight waves split the contraction's k range (each
 // loads only its share of the operand, once), add their partial tiles through
@@ -36,9 +48,9 @@
 // one: its owner refills its own pieces of that slot with the pattern, after
 // storing its result.  The slot is written again two steps later and read the
 // step after.  Each thread waits for its earlier stores (the refill among
-// them) before it stores a result, so whoever has read a thread's result of
-// one step finds the pattern or the new value in the pieces that thread
-// refilled before, never the old value.
+// them) between its poll and its next result, so whoever has read a thread's
+// result of one step finds the pattern or the new value in the pieces that
+// thread refilled before, never the old value.
 #pragma once
 
 #include "device.hpp"
@@ -423,34 +435,81 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
         so[c] = uint32_t(L::index(g * RT + (wave + 8 * c) / NT, a.nkg, lr, cu[c])) * uint32_t(sizeof(T));
     unsigned phase = 0;
     bool dead = false;
-    // the schedule, carried: rows of steps t and t + 1, packed offset of step
-    // t; the row count of step t + 2 is loaded a step before it is needed
-    int act = act_at(a.active, a.fixed, a.B, 0, a.t_eff), act_raw = act_at(a.active, a.fixed, a.B, 1, a.t_eff);
+    // the schedule, carried: rows of steps t - 1, t and t + 1, packed offset of
+    // step t; the row count of step t + 2 is loaded a step before it is needed
+    int act_prev = 0, act = act_at(a.active, a.fixed, a.B, 0, a.t_eff);
+    int act_next = act_at(a.active, a.fixed, a.B, 1, a.t_eff), act_raw = 0;
     int64_t off_t = 0;
     prefetch(act, 0);
 
+    // a step's results, stored for later kernels while the next step's products
+    // run: between a result's publication and the poll for the others' no store
+    // and no load from memory is issued that the poll would have to wait for
+    float hn[CPW];
+    Gates<T> gs[CPW];
+    uint32_t hw[CPW][2];   // bf16: h of the four units of lanes lr, lr + 16, ..
+    auto store_results = [&](int t, int64_t off, int rows, int rows_next) {
+        const int64_t nrow = int64_t(a.B) + off;
+        const auto rgs = make_rsrc(a.Gs + off * a.ldg, uint32_t(rows) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) {
+            if (!(own[c] && cr[c] < rows)) continue;
+            const int u = cu[c], r = cr[c];
+            a.Cs[(nrow + r) * a.ldh + u] = creg[c];
+            gs[c].store(rgs, (uint32_t(r) * uint32_t(a.ldg) + 4u * uint32_t(u)) * uint32_t(sizeof(T)));
+            T* ydst = a.y ? a.y + (int64_t(t) * a.B + cb[c]) * H + u : nullptr;
+            if constexpr (L::EPL == 8) {
+                if (lq == 0) {   // H is a multiple of 8, so the four units are cells
+                    const uint2 v = make_uint2(hw[c][0], hw[c][1]);
+                    if (a.Hs) *reinterpret_cast<uint2*>(a.Hs + (nrow + r) * a.ldh + u) = v;
+                    if (ydst) *reinterpret_cast<uint2*>(ydst) = v;
+                }
+                if (a.HT) a.HT[int64_t(u) * a.ldht + nrow + r] = f2bf(hn[c]);
+            } else {
+                if (a.Hs) a.Hs[(nrow + r) * a.ldh + u] = hn[c];
+                if (ydst) *ydst = hn[c];
+            }
+            if (r >= rows_next) {   // last step of this sequence
+                if (a.hT) a.hT[int64_t(cb[c]) * H + u] = hn[c];
+                if (a.cT) a.cT[int64_t(cb[c]) * H + u] = creg[c];
+            }
+        }
+    };
+
     for (int t = 0; t < steps; ++t) {
-        const int act_next = __builtin_amdgcn_readfirstlane(act_raw);
         const bool more = t + 1 < steps;
         if (!local && t > 0) remote_barrier(a.sync, g, phase, unsigned(a.nu));
         f32x4_t acc[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) acc[p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        uint4 f[RT * J];
         {
             const auto rs = make_rsrc(a.ring + (t & 3) * slot, slot_bytes);
-            uint4 f[RT * J];
             load_operand<T>(f, rs, [&](int i) {
                 const int rt = i / J, j = i % J;
                 const bool ok = row0 + 16 * rt + lr < act && (wave * J + j) * L::KG + L::EPL * lq < kv;
                 return ok ? fo + uint32_t(rt) * fstep + uint32_t(j) * 1024u : kOutOfRange;
             }, local, a.sync, dead);
+        }
+        // whatever this wave stored in the step before, the refill of its slot
+        // pieces among it, is complete
+        wait_own_stores();
+        Gates<T> x4[CPW];
 #pragma unroll
-            for (int j = 0; j < J; ++j)
+        for (int c = 0; c < CPW; ++c) x4[c] = xg[c];
+        if (t > 0) act_next = __builtin_amdgcn_readfirstlane(act_raw);
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
+        for (int j = 0; j < J; ++j)
 #pragma unroll
-                    for (int i = 0; i < NT; ++i)
-                        acc[rt * NT + i] = mma(w[i][j], f[rt * J + j], acc[rt * NT + i], static_cast<const T*>(nullptr));
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+                    acc[rt * NT + i] = mma(w[i][j], f[rt * J + j], acc[rt * NT + i], static_cast<const T*>(nullptr));
+        if (t > 0) store_results(t - 1, off_t - act_prev, act_prev, act);
+        act_raw = t + 2 < a.t_eff ? a.B : 0;
+        if (more) {
+            prefetch(act_next, off_t + act);
+            if (!a.fixed) act_raw = a.active[min(t + 2, a.t_eff)];
         }
         // sum over the waves, in wave order
         f32x4_t* buf = red + (C::DB ? (t & 1) * kWaves * NP * 64 : 0);
@@ -467,12 +526,10 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
                 for (int q = 0; q < kWaves; ++q) sum[c] += buf[(q * NP + wave + 8 * c) * 64 + lane];
             }
         }
-        float hn[CPW];
-        Gates<T> gs[CPW];
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
             float x[4], ga[4];
-            xg[c].get(x);
+            x4[c].get(x);
             ga[0] = sigmoidf_(sum[c][0] + x[0]);
             ga[1] = sigmoidf_(sum[c][1] + x[1]);
             ga[2] = tanhf_(sum[c][2] + x[2]);
@@ -484,8 +541,6 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
             gs[c].set(ga);
         }
         // h_t for the next step: the only values the other members read
-        wait_own_stores();
-        uint32_t hw[CPW][2];   // bf16: the four units of lanes lr, lr + 16, .. (held by lanes < 16)
         {
             const auto rn = make_rsrc(a.ring + ((t + 1) & 3) * slot, slot_bytes);
             const auto rp = make_rsrc(a.ring + ((t + 3) & 3) * slot, slot_bytes);
@@ -506,41 +561,11 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
                 }
             }
         }
-        // results for later kernels and the next step's operands
-        const int64_t nrow = int64_t(a.B) + off_t;
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            if (!(own[c] && cr[c] < act)) continue;
-            const int u = cu[c], r = cr[c];
-            a.Cs[(nrow + r) * a.ldh + u] = creg[c];
-            const auto rgs = make_rsrc(a.Gs + off_t * a.ldg, uint32_t(act) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
-            gs[c].store(rgs, (uint32_t(r) * uint32_t(a.ldg) + 4u * uint32_t(u)) * uint32_t(sizeof(T)));
-            T* ydst = a.y ? a.y + (int64_t(t) * a.B + cb[c]) * H + u : nullptr;
-            if constexpr (L::EPL == 8) {
-                if (lq == 0) {   // H is a multiple of 8, so the four units are cells
-                    const uint2 v = make_uint2(hw[c][0], hw[c][1]);
-                    if (a.Hs) *reinterpret_cast<uint2*>(a.Hs + (nrow + r) * a.ldh + u) = v;
-                    if (ydst) *reinterpret_cast<uint2*>(ydst) = v;
-                }
-                if (a.HT) a.HT[int64_t(u) * a.ldht + nrow + r] = f2bf(hn[c]);
-            } else {
-                if (a.Hs) a.Hs[(nrow + r) * a.ldh + u] = hn[c];
-                if (ydst) *ydst = hn[c];
-            }
-            if (r >= act_next) {   // last step of this sequence
-                if (a.hT) a.hT[int64_t(cb[c]) * H + u] = hn[c];
-                if (a.cT) a.cT[int64_t(cb[c]) * H + u] = creg[c];
-            }
-        }
-        int act_later = t + 2 < a.t_eff ? a.B : 0;
-        if (more) {
-            prefetch(act_next, off_t + act);
-            if (!a.fixed) act_later = a.active[min(t + 2, a.t_eff)];
-        }
         off_t += act;
+        act_prev = act;
         act = act_next;
-        act_raw = act_later;
     }
+    if (steps > 0) store_results(steps - 1, off_t - act_prev, act_prev, act);
 }
 
 // ---------------------------------------------------------------- backward
@@ -606,19 +631,69 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
 
     // weights: Wh^T, rows = units v0 + 16 i + lr, k = interleaved gate columns
     uint4 w[MT][J];
+    if constexpr (L::EPL == 8) {
+        // Rows of Wh (one k each) hold the workgroup's U units in 2 U bytes: a
+        // wave loads each k-group's 32 rows in 16-byte pieces, then turns them
+        // through its part of the LDS.  Against 2-byte loads of each element
+        // (8 times as many instructions): H 1024, time before the first step
+        // 67 -> 34 us; H 656, 36 -> 24.
+        constexpr int PR = C::U / 8, PIECES = 32 * PR, PPL = (PIECES + 63) / 64;   // pieces of a row, a k-group, a lane
+        constexpr int LD = 16 * MT + 2;                                            // row pitch (elements)
+        static_assert(32 * LD * 2 * kWaves <= C::SMEM, "a k-group per wave in LDS");
+        uint32_t* sw = reinterpret_cast<uint32_t*>(smem_raw) + wave * 16 * LD;
+        uint4 raw[J][PPL];
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int q = 0; q < PPL; ++q) {
+                const int e = lane + 64 * q, k = (wave * J + j) * 32 + e / PR, u = v0 + 8 * (e % PR);
+                const int uu = k >> 2, ga = k & 3;
+                raw[j][q] = e < PIECES && u < vend && uu < H
+                                ? *reinterpret_cast<const uint4*>(a.Wh + (int64_t(ga) * H + uu) * H + u)
+                                : make_uint4(0, 0, 0, 0);
+            }
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const int u = v0 + 16 * i + lr, k = (wave * J + j) * L::KG + L::EPL * lq;
-            T tmp[L::EPL];
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int e = 0; e < L::EPL; ++e) {
-                const int uu = (k + e) >> 2, ga = e & 3;
-                tmp[e] = (u < vend && uu < H) ? a.Wh[(int64_t(ga) * H + uu) * H + u] : T(0);
+            for (int q = 0; q < PPL; ++q) {
+                const int e = lane + 64 * q;
+                if (e < PIECES) {
+                    uint32_t* d = sw + ((e / PR) * LD + 8 * (e % PR)) / 2;
+                    d[0] = raw[j][q].x;
+                    d[1] = raw[j][q].y;
+                    d[2] = raw[j][q].z;
+                    d[3] = raw[j][q].w;
+                }
             }
-            __builtin_memcpy(&w[i][j], tmp, 16);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const bf16_t* sr = reinterpret_cast<const bf16_t*>(sw);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                bf16_t tmp[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) tmp[e] = 16 * i + lr < C::U ? sr[(8 * lq + e) * LD + 16 * i + lr] : bf16_t(0);
+                __builtin_memcpy(&w[i][j], tmp, 16);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
+        __syncthreads();   // the sums over the waves use this LDS
+    } else {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int u = v0 + 16 * i + lr, k = (wave * J + j) * L::KG + L::EPL * lq;
+                T tmp[L::EPL];
+#pragma unroll
+                for (int e = 0; e < L::EPL; ++e) {
+                    const int uu = (k + e) >> 2, ga = e & 3;
+                    tmp[e] = (u < vend && uu < H) ? a.Wh[(int64_t(ga) * H + uu) * H + u] : T(0);
+                }
+                __builtin_memcpy(&w[i][j], tmp, 16);
+            }
+    }
 
     // cells: entry q = tid + 512 c of the pairs' 16 x 16 tiles
     int cu[CPT], cr[CPT], cb[CPT];
@@ -685,9 +760,9 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
         float dh[CPT];
 #pragma unroll
         for (int c = 0; c < CPT; ++c) dh[c] = dhp[c];
+        f32x4_t acc[NP];
         if (!first) {
             if (!local) remote_barrier(a.sync, g, phase, unsigned(a.nu));
-            f32x4_t acc[NP];
 #pragma unroll
             for (int p = 0; p < NP; ++p) acc[p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             const auto rs = make_rsrc(a.ring + ((t + 1) & 3) * slot, slot_bytes);
@@ -704,6 +779,23 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
                     for (int i = 0; i < MT; ++i)
                         acc[rt * MT + i] = mma(w[i][j], f[j], acc[rt * MT + i], static_cast<const T*>(nullptr));
             }
+        }
+        // whatever this wave stored in the step before, the refill of its slot
+        // pieces among it, is complete, and this step's operands are here
+        wait_own_stores();
+        Gates<T> g4[CPT];
+        float cp[CPT], cl[CPT], dyc[CPT];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            g4[c] = gt_[c];
+            cp[c] = cpv[c];
+            cl[c] = cnv[c];
+            dyc[c] = dyv[c];
+        }
+        const int m2 = __builtin_amdgcn_readfirstlane(act_m2);
+        if (t > 0) prefetch(t - 1, act_m1, act, m2, off_t - act_m1);
+        act_m2 = t < 3 ? 0 : a.fixed ? a.B : a.active[t - 3];
+        if (!first) {
             f32x4_t* buf = red + (t & 1) * kWaves * NP * 64;
 #pragma unroll
             for (int p = 0; p < NP; ++p) buf[(wave * NP + p) * 64 + lane] = acc[p];
@@ -733,25 +825,24 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
         for (int c = 0; c < CPT; ++c) {
             const bool cell = own[c] && cr[c] < act;
             float ga[4];
-            gt_[c].get(ga);
-            if (cell && cr[c] >= act_next) cnx[c] = cnv[c];
-            const float dhv = dh[c] + dyv[c];
+            g4[c].get(ga);
+            if (cell && cr[c] >= act_next) cnx[c] = cl[c];
+            const float dhv = dh[c] + dyc[c];
             const float gi = ga[0], gf = ga[1], gg = ga[2], go = ga[3];
             const float tau = tanhf_(cnx[c]);
             const float d_o = dhv * tau;
             const float dct = dcr[c] + dhv * go * (1.f - tau * tau);
-            const float d4[4] = {dct * gg * gi * (1.f - gi), dct * cpv[c] * gf * (1.f - gf), dct * gi * (1.f - gg * gg),
+            const float d4[4] = {dct * gg * gi * (1.f - gi), dct * cp[c] * gf * (1.f - gf), dct * gi * (1.f - gg * gg),
                                  d_o * go * (1.f - go)};
             dg[c].set(d4);
             if (cell) {
                 dcr[c] = dct * gf;
-                cnx[c] = cpv[c];
+                cnx[c] = cp[c];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) dbs[c][e] += d4[e];
             }
         }
         // dG_t for the next (earlier) step: the only values the other members read
-        wait_own_stores();
         {
             const auto rn = make_rsrc(a.ring + (t & 3) * slot, slot_bytes);
             const auto rp = make_rsrc(a.ring + ((t + 2) & 3) * slot, slot_bytes);
@@ -779,13 +870,10 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
                 }
             }
         }
-        const int m2 = __builtin_amdgcn_readfirstlane(act_m2);
-        if (t > 0) prefetch(t - 1, act_m1, act, m2, off_t - act_m1);
         act_next = act;
         act = t > 0 ? act_m1 : a.B;
         off_t -= act_m1;
         act_m1 = m2;
-        act_m2 = t < 3 ? 0 : a.fixed ? a.B : a.active[t - 3];
     }
 
     // bias gradient of this group's rows: per unit and gate, rows in order
