@@ -280,9 +280,9 @@ CsPlan cs_plan(const janus_treelstm_desc& d, const janus_nary_tree_batch* t, con
 }
 int cs_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
 unsigned cs_fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
-int cs_force_remote() {
+int cs_xccs(const treex::Cut& c) {
     const char* e = getenv("JANUS_XCD_REMOTE");
-    return e && e[0] == '1' ? 1 : 0;
+    return e && e[0] == '1' ? 0 : c.xccs;
 }
 
 template <int NT>
@@ -311,7 +311,7 @@ janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
     a.M0 = s.level_offsets[1];
     a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
-    a.force_remote = cs_force_remote();
+    a.xccs = cs_xccs(p.cut);
     a.tile = w.xtile;
     a.coff = w.pcoff;
     a.kids = w.pkids;
@@ -366,7 +366,7 @@ janus_status cs_bwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
     a.M0 = s.level_offsets[1];
     a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
-    a.force_remote = cs_force_remote();
+    a.xccs = cs_xccs(p.cut);
     a.tile = w.xtile;
     a.coff = w.pcoff;
     a.kids = w.pkids;

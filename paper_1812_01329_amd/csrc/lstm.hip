@@ -139,7 +139,7 @@ int64_t persist_fwd_part_floats(const janus_lstm_desc& d, int ns) {
 int xcd_max_h(janus_dtype dt) { return dt == JANUS_BF16 ? 1024 : 512; }
 
 struct XcdPlan {
-    int Q = 0, RT = 0, nu = 0, blocks = 0;   // Q == 0: does not fit
+    int Q = 0, RT = 0, nu = 0, blocks = 0, xccs = 0;   // Q == 0: does not fit
 };
 
 // One launch works `rows` rows (at most 256) in groups of 16 RT.  A group is
@@ -153,6 +153,7 @@ XcdPlan xcd_plan(const janus_lstm_desc& d, int rows) {
     if (d.H > xcd_max_h(d.dtype) || (d.dtype == JANUS_BF16 && d.H % 8 != 0)) return p;
     const int Q = (d.H + 255) / 256;
     p.nu = (d.H + 8 * Q - 1) / (8 * Q);
+    p.xccs = xccs;
     if (per_xcd < p.nu) return p;
     const int room = xccs * (per_xcd / p.nu);
     const int tiles = (rows + 15) / 16;
@@ -1191,7 +1192,6 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
         a.t_eff = s.t_eff;
         a.fixed = s.fixed ? 1 : 0;
         a.nkg = int((H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
-        a.force_remote = env_is("JANUS_XCD_REMOTE", '1') ? 1 : 0;
         a.active = w.act_dev;
         a.offsets = w.off_dev;
         a.perm = perm;
@@ -1216,6 +1216,7 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
             const XcdPlan p = xcd_plan(d, rows);
             a.rbase = rb;
             a.nu = p.nu;
+            a.xccs = env_is("JANUS_XCD_REMOTE", '1') ? 0 : p.xccs;
             a.groups = xcd_groups(rows, p.RT);
             xcd_steps(s, rb, p.RT, a.groups, a.steps);
             const double work = part_rows(s, rb);
@@ -1427,7 +1428,6 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
             a.t_eff = s.t_eff;
             a.fixed = s.fixed ? 1 : 0;
             a.nkg = int((4 * H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
-            a.force_remote = env_is("JANUS_XCD_REMOTE", '1') ? 1 : 0;
             a.active = w.act_dev;
             a.offsets = w.off_dev;
             a.perm = perm;
@@ -1455,6 +1455,7 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
                 const XcdPlan p = xcd_plan(d, rows);
                 a.rbase = rb;
                 a.nu = p.nu;
+                a.xccs = env_is("JANUS_XCD_REMOTE", '1') ? 0 : p.xccs;
                 a.groups = xcd_groups(rows, p.RT);
                 xcd_steps(s, rb, p.RT, a.groups, a.steps);
                 {

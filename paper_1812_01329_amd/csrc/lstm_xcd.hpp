@@ -33,8 +33,8 @@
 // H 1024, B 128: forward 2.2 against 5.9 us, backward 3.2 against 7.7; H 656,
 // B 20: 1.6 against 4.5 and 2.2 against 6.5; H 512, B 33: forward 1.5 against
 // 4.1.  float32, H 256, B 32, against one launch per step: 1.6 against 9.7 us
-// and 2.4 against 53.  A launch adds 17-40 us before its first step (placement
-// and weights).  The backward's step is longer by its operand, four times the
+// and 2.3 against 53.  A launch adds 5-22 us before its first step (mostly its
+// weights).  The backward's step is longer by its operand, four times the
 // forward's: every workgroup reads all gate columns of its rows from the L2.
 //
 // Inside a workgroup the eight waves split the contraction's k range (each
@@ -128,43 +128,78 @@ __device__ __forceinline__ void wait_own_stores() {
 }
 
 // Place of a workgroup: member m of row group g, or g = -1 for a workgroup
-// that has nothing to do.  The census counts the workgroups of every XCD; an
-// XCD with c of them holds c / nu groups, dealt to the XCDs in turn.  When
-// they do not hold all `groups` (an uneven placement), the groups are
-// consecutive ranks over all XCDs instead and `local` is 0: the steps are
-// then separated by a barrier of the group with device-scope fences.
+// that has nothing to do.  A launch has the same number of workgroups for
+// every XCD, a multiple of nu, and they count themselves on their XCD.  The
+// i-th of XCD x belongs to its turn i / nu, group (i / nu) xccs + x; once the
+// turn's nu workgroups have arrived (all on one XCD, `local`) it starts,
+// without waiting for the rest of the device.  Where the placement was
+// uneven, a turn stays incomplete: when every workgroup of the launch has been
+// counted, those of incomplete turns and those past their XCD's last turn are
+// ranked over all XCDs and serve the groups left in consecutive nu; the steps
+// of such a group are separated by a barrier of its own with device-scope
+// fences (with xccs 0, all groups).  All of them derive the same ranks from
+// the final counts.
+// (Waiting for the whole launch on one counter took 12 us of a launch of 256;
+// a turn is complete after 1.4.)
 struct Place {
     int g, m, local;
 };
 template <class S>
-__device__ __forceinline__ Place take_place(S* s, int nu, int groups, int force_remote) {
+__device__ __forceinline__ unsigned census_at(S* s, int q) {
+    return __hip_atomic_load(&s->census[q][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class S>
+__device__ __forceinline__ Place take_place(S* s, int nu, int groups, int xccs) {
     __shared__ int place[3];
     if (threadIdx.x == 0) {
-        const unsigned x = persist::xcc_id();
-        const unsigned xidx = __hip_atomic_fetch_add(&s->census[x][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(&s->count, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        const bool ok = persist::spin_until(s, &s->count, gridDim.x);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int x = int(persist::xcc_id());
+        const int i =
+            int(__hip_atomic_fetch_add(&s->census[x][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        // turns of XCD q: the groups q, q + xccs, .. below `groups`
+        auto turns = [&](int q) { return q < xccs ? (groups - q + xccs - 1) / xccs : 0; };
+        const int turn = i / nu;
+        int g = -1, m = i % nu, local = 0;
         unsigned c[persist::kMaxXcds];
+        for (int spins = 0;; ++spins) {
+            if (turn < turns(x) && int(census_at(s, x)) >= (turn + 1) * nu) {
+                g = turn * xccs + x;
+                local = 1;
+                break;
+            }
+            unsigned all = 0;
+            if (turn >= turns(x) || (spins & 15) == 15) {
 #pragma unroll
-        for (int q = 0; q < persist::kMaxXcds; ++q)
-            c[q] = __hip_atomic_load(&s->census[q][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int turn = int(xidx) / nu;
-        int room = 0, before = 0, first = 0;
+                for (int q = 0; q < persist::kMaxXcds; ++q) c[q] = census_at(s, q);
 #pragma unroll
-        for (int q = 0; q < persist::kMaxXcds; ++q) {
-            const int n = int(c[q]) / nu;
-            room += n;
-            before += min(n, turn) + (q < int(x) && n > turn ? 1 : 0);
-            first += q < int(x) ? int(c[q]) : 0;
+                for (int q = 0; q < persist::kMaxXcds; ++q) all += c[q];
+            }
+            if (all == gridDim.x) {
+                const int full = min(turns(x), int(c[x]) / nu);
+                if (turn < full) continue;   // the turn was completed meanwhile
+                // rank among the workgroups outside complete turns, and the
+                // group of that rank among those no complete turn works
+                int rank = i - full * nu;
+                for (int q = 0; q < x; ++q) rank += int(c[q]) - min(turns(q), int(c[q]) / nu) * nu;
+                int left = rank / nu;
+                m = rank % nu;
+                for (int k = 0; k < groups && g < 0; ++k) {
+                    bool worked = false;
+                    if (xccs > 0) worked = k / xccs < int(census_at(s, k % xccs)) / nu;
+                    if (!worked && left-- == 0) g = k;
+                }
+                break;
+            }
+            if (turn >= turns(x)) __builtin_amdgcn_s_sleep(16);
+            if ((spins & 63) == 63 && __hip_atomic_load(&s->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+                break;
+            if (spins > persist::kSpinLimit) {
+                __hip_atomic_store(&s->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
         }
-        const bool local = room >= groups && !force_remote;
-        const int rank = first + int(xidx);
-        int g = local ? before : rank / nu;
-        if (local && turn >= int(c[x]) / nu) g = -1;   // left over on its XCD
-        place[0] = (!ok || g >= groups) ? -1 : g;
-        place[1] = local ? int(xidx) % nu : rank % nu;
-        place[2] = local ? 1 : 0;
+        place[0] = g;
+        place[1] = m;
+        place[2] = local;
     }
     __syncthreads();
     return Place{place[0], place[1], place[2]};
@@ -330,7 +365,7 @@ struct FwdArgs {
     int H, B, t_eff, fixed;
     int rbase;                 // first sorted row of this launch
     int groups, nu, nkg;       // row groups, workgroups of a group, k-groups of the operand
-    int force_remote;
+    int xccs;                  // XCDs the groups are dealt to (0: no group shares an L2)
     int steps[kMaxGroups];     // steps each group runs (length of its first row)
     const int32_t* active;
     const int32_t* offsets;
@@ -370,7 +405,7 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     f32x4_t* red = reinterpret_cast<f32x4_t*>(smem_raw);   // [buffer][wave][pair][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Place pl = take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const Place pl = take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -574,7 +609,7 @@ struct BwdArgs {
     int H, B, t_eff, fixed;
     int rbase;
     int groups, nu, nkg;       // nkg: k-groups of the 4H interleaved gate columns
-    int force_remote;
+    int xccs;                  // XCDs the groups are dealt to (0: no group shares an L2)
     int gbase;                 // row groups of the earlier launches (rows of db_part)
     int steps[kMaxGroups];
     const int32_t* active;
@@ -617,7 +652,7 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     f32x4_t* red = reinterpret_cast<f32x4_t*>(smem_raw);   // [buffer][wave][pair][64]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Place pl = take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const Place pl = take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -636,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
         // wave loads each k-group's 32 rows in 16-byte pieces, then turns them
         // through its part of the LDS.  Against 2-byte loads of each element
         // (8 times as many instructions): H 1024, time before the first step
-        // 67 -> 34 us; H 656, 36 -> 24.
+        // 33 us less; H 656, 12 us less.
         constexpr int PR = C::U / 8, PIECES = 32 * PR, PPL = (PIECES + 63) / 64;   // pieces of a row, a k-group, a lane
         constexpr int LD = 16 * MT + 2;                                            // row pitch (elements)
         static_assert(32 * LD * 2 * kWaves <= C::SMEM, "a k-group per wave in LDS");

@@ -449,7 +449,7 @@ janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
     a.M0 = M0;
     a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
-    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
     a.tile = w.xtile;
     a.lchild = w.lchild;
     a.rchild = w.rchild;
@@ -504,7 +504,7 @@ janus_status treelstm_bwd_xcd_levels(const janus_treelstm_desc& d, const TreeSch
     a.M0 = M0;
     a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
-    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
     a.tile = w.xtile;
     a.lchild = w.lchild;
     a.rchild = w.rchild;
@@ -876,7 +876,7 @@ janus_status treernn_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
     a.M0 = M0;
     a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
-    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
     a.tile = w.s.xtile;
     a.lchild = w.s.lchild;
     a.rchild = w.s.rchild;
@@ -930,7 +930,7 @@ janus_status treernn_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
     a.M0 = M0;
     a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
-    a.force_remote = tree_env("JANUS_XCD_REMOTE", '1') ? 1 : 0;
+    a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
     a.tile = w.s.xtile;
     a.lchild = w.s.lchild;
     a.rchild = w.s.rchild;

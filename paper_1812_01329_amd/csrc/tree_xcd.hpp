@@ -155,7 +155,7 @@ __device__ __forceinline__ uint4 weight4(const float* W, int64_t ld, int r, int 
 // ------------------------------------------------------- TreeLSTM, forward
 struct LstmFwd {
     int E, H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;        // of this launch
     const Tile* tile;
     const int32_t* lchild;
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
     float* cl = sm + 2 * C::RED;   // [nodes][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
 // ------------------------------------------------------ TreeLSTM, backward
 struct LstmBwd {
     int H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;
     const Tile* tile;          // the forward's tiles, walked backwards
     const int32_t* lchild;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
     extern __shared__ __align__(16) float sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
 // internal nodes run.
 struct RnnFwd {
     int H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;
     const Tile* tile;
     const int32_t* lchild;
@@ -551,7 +551,7 @@ static __global__ __launch_bounds__(kThreads) void treernn_fwd_xcd(RnnFwd a) {
     constexpr int U = kRnnU, J = kRnnJ;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -619,7 +619,7 @@ static __global__ __launch_bounds__(kThreads) void treernn_fwd_xcd(RnnFwd a) {
 
 struct RnnBwd {
     int H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;
     const Tile* tile;
     const int32_t* lchild;
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
     float* dhl = sm + 2 * C::RED;   // [internal nodes][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
 // 352 us, with barriers over the whole device around each level, to 173 us.
 struct CsFwd {
     int E, H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;
     const Tile* tile;
     const int32_t* coff;       // [N + 1] children of position p: kids[coff[p] .. coff[p + 1])
@@ -826,7 +826,7 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
     extern __shared__ __align__(16) float sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -981,7 +981,7 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
 
 struct CsBwd {
     int H, M0;
-    int groups, nu, force_remote;
+    int groups, nu, xccs;
     const Group* group;
     const Tile* tile;
     const int32_t* coff;
@@ -1027,7 +1027,7 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
     float* dcl = sm + 2 * C::RED;   // [nodes][U]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lq = lane >> 4;
-    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.force_remote);
+    const xcd::Place pl = xcd::take_place(a.sync, a.nu, a.groups, a.xccs);
     const int g = __builtin_amdgcn_readfirstlane(pl.g), m = __builtin_amdgcn_readfirstlane(pl.m);
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
@@ -1157,7 +1157,7 @@ constexpr size_t kGroupInts = size_t(kMaxGroups) * kMaxParts * (sizeof(Group) / 
 // order lists the nodes by position: all leaves, then all internal nodes, in
 // each by (group, level, id).
 struct Cut {
-    int groups = 0, parts = 0, blocks = 0, nu = 0;
+    int groups = 0, parts = 0, blocks = 0, nu = 0, xccs = 0;
     int most_nodes = 0;                // nodes of the largest group
     std::vector<Group> group;          // [parts * groups]
     std::vector<Tile> tile;
@@ -1186,6 +1186,7 @@ inline bool cut_batch(int num_trees, int N, const std::vector<int32_t>& level_no
     const int per_xcd = dev.cus / xccs;
     if (per_xcd < nu || capacity <= 0) return false;
     c.nu = nu;
+    c.xccs = xccs;
     c.groups = std::min({num_trees, xccs * (per_xcd / nu), kMaxGroups});
     c.blocks = xccs * nu * ((c.groups + xccs - 1) / xccs);
     std::vector<int32_t> size(num_trees, 0), by(num_trees);
