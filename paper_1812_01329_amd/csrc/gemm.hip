@@ -711,12 +711,24 @@ __global__ __launch_bounds__(kColTile) void colsum_final_kernel(const float* par
     out[out_idx ? out_idx[c] : c] = s;
 }
 
-__global__ void zero_kernel(unsigned char* p, size_t head, uint4* mid, size_t n16, unsigned char* tail, size_t ntail) {
-    size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+struct ZeroOp {
+    unsigned char* head;
+    uint4* mid;
+    unsigned char* tail;
+    size_t n16;
+    unsigned nhead, ntail;
+};
+struct ZeroOps {
+    ZeroOp op[kMaxZeroRanges];
+};
+// blockIdx.y selects the range
+__global__ void zero_kernel(ZeroOps z) {
+    const ZeroOp& o = z.op[blockIdx.y];
     const size_t stride = size_t(gridDim.x) * blockDim.x;
-    for (; i < n16; i += stride) mid[i] = make_uint4(0, 0, 0, 0);
-    if (blockIdx.x == 0 && threadIdx.x < head) p[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
+    for (size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x; i < o.n16; i += stride)
+        o.mid[i] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x == 0 && threadIdx.x < o.nhead) o.head[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < o.ntail) o.tail[threadIdx.x] = 0;
 }
 
 }  // namespace
@@ -1148,19 +1160,33 @@ janus_status colsum(janus_dtype dt, const void* in, int64_t R, int C, int64_t ld
     return JANUS_OK;
 }
 
-janus_status zero_fill(void* p, size_t bytes, hipStream_t stream) {
-    if (bytes == 0) return JANUS_OK;
-    unsigned char* b = static_cast<unsigned char*>(p);
-    size_t head = (16 - reinterpret_cast<uintptr_t>(b) % 16) % 16;
-    if (head > bytes) head = bytes;
-    const size_t n16 = (bytes - head) / 16;
-    const size_t nt = bytes - head - n16 * 16;
-    unsigned blocks = unsigned(n16 / 256 + 1 < 4096 ? n16 / 256 + 1 : 4096);
-    TraceScope trace("zero_fill", 0.0, double(bytes), stream);
-    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, stream, b, head,
-                       reinterpret_cast<uint4*>(b + head), n16, b + head + n16 * 16, nt);
+janus_status zero_fill(const ZeroRange* r, int n, hipStream_t stream) {
+    ZeroOps z{};
+    int m = 0;
+    size_t most = 0;
+    double total = 0;
+    for (int i = 0; i < n; ++i) {
+        if (r[i].bytes == 0) continue;
+        if (m == kMaxZeroRanges) return JANUS_ERR_INVALID_ARG;
+        unsigned char* b = static_cast<unsigned char*>(r[i].p);
+        size_t head = (16 - reinterpret_cast<uintptr_t>(b) % 16) % 16;
+        if (head > r[i].bytes) head = r[i].bytes;
+        const size_t n16 = (r[i].bytes - head) / 16;
+        z.op[m++] = ZeroOp{b, reinterpret_cast<uint4*>(b + head), b + head + n16 * 16, n16, unsigned(head),
+                           unsigned(r[i].bytes - head - n16 * 16)};
+        most = std::max(most, n16);
+        total += double(r[i].bytes);
+    }
+    if (m == 0) return JANUS_OK;
+    const unsigned blocks = unsigned(std::min<size_t>(most / 256 + 1, 4096));
+    TraceScope trace("zero_fill", 0.0, total, stream);
+    hipLaunchKernelGGL(zero_kernel, dim3(blocks, unsigned(m)), dim3(256), 0, stream, z);
     JANUS_LAUNCH_CHECK();
     return JANUS_OK;
+}
+janus_status zero_fill(void* p, size_t bytes, hipStream_t stream) {
+    const ZeroRange r{p, bytes};
+    return zero_fill(&r, 1, stream);
 }
 
 }  // namespace janus

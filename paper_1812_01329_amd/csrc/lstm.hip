@@ -210,9 +210,11 @@ size_t carve(const janus_lstm_desc& d, void* base, LstmWs& w) {
     // rows padded to whole 128-byte lines (see the persistent kernels' barrier)
     w.ldh = round_up(d.H, 64);
     w.ldg = round_up(int64_t(4) * d.H, 64);
+    // the schedule, in one piece (place_rows sets prevrow)
     w.perm = c.take<int32_t>(d.B);
-    w.xrow = c.take<int32_t>(TB);
-    w.prevrow = c.take<int32_t>(TB);
+    w.act_dev = c.take<int32_t>(int64_t(d.T) + 1);
+    w.off_dev = c.take<int32_t>(int64_t(d.T) + 2);
+    w.xrow = c.take<int32_t>(2 * TB + 64);
     w.Hs.assign(d.L, nullptr);
     w.Cs.assign(d.L, nullptr);
     w.Gs.assign(d.L, nullptr);
@@ -234,8 +236,6 @@ size_t carve(const janus_lstm_desc& d, void* base, LstmWs& w) {
         w.bi[l] = c.take<char>(int64_t(4) * d.H * es);
     }
     w.perm4 = c.take<int32_t>(int64_t(4) * d.H);
-    w.act_dev = c.take<int32_t>(int64_t(d.T) + 1);
-    w.off_dev = c.take<int32_t>(int64_t(d.T) + 2);
     w.sync = c.take<persist::Sync>(1);
     if (d.H <= xcd_max_h(d.dtype)) {
         // rows of the largest launch, rounded up to two 16-row tiles
@@ -262,6 +262,9 @@ size_t carve(const janus_lstm_desc& d, void* base, LstmWs& w) {
     w.gs = c.take<char>(int64_t(w.gs_bytes));
     return c.off + 256;
 }
+
+// The running rows' lists lie together, whatever their number.
+void place_rows(const SeqSchedule& s, LstmWs& w) { w.prevrow = w.xrow + round_up(s.packed, 64); }
 
 int persist_kw(int B) { return B <= 32 ? 8 : B <= 64 ? 4 : B <= 128 ? 2 : 1; }
 
@@ -372,15 +375,6 @@ bool use_xcd_bwd(const janus_lstm_desc& d) {
 __global__ void perm4_kernel(int H, int32_t* perm4) {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n < 4 * H) perm4[n] = (n & 3) * H + (n >> 2);
-}
-
-// dst row n (interleaved) = src row (n % 4) * H + n / 4, rows of `cols` elements
-template <typename T>
-__global__ void interleave_rows_kernel(const T* src, T* dst, int H, int cols) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= int64_t(4) * H * cols) return;
-    const int n = int(i / cols), k = int(i % cols);
-    dst[i] = src[(int64_t(n & 3) * H + (n >> 2)) * cols + k];
 }
 
 // ------------------------------------------------------------ init kernels
@@ -1125,20 +1119,36 @@ void xcd_steps(const SeqSchedule& s, int rbase, int rt, int groups, int32_t* ste
 }
 int xcd_groups(int rows, int rt) { return (rows + 16 * rt - 1) / (16 * rt); }
 
-// Initial state and operand slots of the row-group forward for rows rb + [0, kMaxB).
+template <typename T>
+xcd::Interleave<T> interleaved(const LstmWs& w, int l, const void* Wx, const void* b, int H, int Il) {
+    return {static_cast<const T*>(Wx), static_cast<T*>(w.Wxi[l]), static_cast<const T*>(b), static_cast<T*>(w.bi[l]), H,
+            Il};
+}
+template <typename T>
+unsigned interleave_blocks(int H, int Il) {   // 16 bytes a thread
+    const int64_t n = int64_t(4) * H * Il * int64_t(sizeof(T));
+    return unsigned(std::min<int64_t>((n + 4095) / 4096, 16384));
+}
+
+// Initial state and operand slots of the row-group forward for rows rb + [0, kMaxB),
+// and (with Wx) the layer's interleaved weights.
 template <typename T>
 janus_status fwd_init_xcd(const janus_lstm_desc& d, const SeqSchedule& s, const LstmWs& w, int l, int rb,
-                          const int32_t* perm, const float* h0, const float* c0, float* hT, float* cT, hipStream_t st) {
+                          const int32_t* perm, const float* h0, const float* c0, float* hT, float* cT, const void* Wx,
+                          const void* b, hipStream_t st) {
     const int rows = std::min(d.B - rb, persist::kMaxB);
     const XcdPlan p = xcd_plan(d, rows);
     const int tiles = p.RT * xcd_groups(rows, p.RT);
     const int nkg = int((d.H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
     const int64_t n = int64_t(tiles) * 16 * nkg * xcd::Lay<T>::KG;
-    TraceScope trace("lstm_fwd_init", 0.0, double(rows) * d.H * (8.0 + 4.0 + sizeof(T)), st);
-    hipLaunchKernelGGL(xcd::fwd_init_kernel<T>, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 1024))), dim3(256), 0,
-                       st, d.B, d.H, w.ldh, rb, tiles, nkg, perm, h0, c0, static_cast<T*>(w.Hs[l]), w.Cs[l],
+    const int Il = l == 0 ? d.I : d.H;
+    const unsigned wblocks = Wx ? interleave_blocks<T>(d.H, Il) : 0;
+    TraceScope trace("lstm_fwd_init", 0.0, double(rows) * d.H * (8.0 + 4.0 + sizeof(T)) +
+                     (Wx ? 2.0 * sizeof(T) * double(int64_t(4) * d.H * (Il + 1)) : 0.0), st);
+    hipLaunchKernelGGL(xcd::fwd_init_kernel<T>, dim3(wblocks + unsigned(std::min<int64_t>((n + 255) / 256, 1024))),
+                       dim3(256), 0, st, d.B, d.H, w.ldh, rb, tiles, nkg, perm, h0, c0, static_cast<T*>(w.Hs[l]), w.Cs[l],
                        s.active[0], hT, cT, use_ht(d, s, true) ? reinterpret_cast<T*>(w.HT[l]) : nullptr, w.ldht,
-                       static_cast<T*>(w.ring), w.sync);
+                       static_cast<T*>(w.ring), w.sync, interleaved<T>(w, l, Wx, b, d.H, Il), int(wblocks));
     JANUS_LAUNCH_CHECK();
     return JANUS_OK;
 }
@@ -1151,14 +1161,10 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
                                   hipStream_t st) {
     const int H = d.H, B = d.B;
     const int Il = l == 0 ? d.I : H;
-    const int64_t rows4 = int64_t(4) * H * Il;
-    {
-        TraceScope trace("interleave_weights", 0.0, 2.0 * sizeof(T) * double(rows4 + 4 * H), st);
-        hipLaunchKernelGGL(interleave_rows_kernel<T>, dim3(unsigned((rows4 + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const T*>(Wx), static_cast<T*>(w.Wxi[l]), H, Il);
-        JANUS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(interleave_rows_kernel<T>, dim3(unsigned((4 * H + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const T*>(b), static_cast<T*>(w.bi[l]), H, 1);
+    if (!use_xcd_fwd(d)) {   // (there the set-up kernel does it)
+        TraceScope trace("interleave_weights", 0.0, 2.0 * sizeof(T) * double(int64_t(4) * H * (Il + 1)), st);
+        hipLaunchKernelGGL(xcd::interleave_kernel<T>, dim3(interleave_blocks<T>(H, Il)), dim3(256), 0, st,
+                           interleaved<T>(w, l, Wx, b, H, Il));
         JANUS_LAUNCH_CHECK();
     }
     GemmDesc g;
@@ -1211,7 +1217,7 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
         a.ring = static_cast<T*>(w.ring);
         a.sync = w.sync;
         for (int rb = 0; rb < B; rb += persist::kMaxB) {
-            if (rb > 0 && (e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0, c0, hT, cT, st)) != JANUS_OK) return e;
+            if (rb > 0 && (e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0, c0, hT, cT, nullptr, nullptr, st)) != JANUS_OK) return e;
             const int rows = std::min(B - rb, persist::kMaxB);
             const XcdPlan p = xcd_plan(d, rows);
             a.rbase = rb;
@@ -1283,8 +1289,11 @@ janus_status lstm_fwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     const int64_t TB = int64_t(d.T) * B;
     const int32_t* perm = s.fixed ? nullptr : w.perm;
     const int32_t* xrow = s.fixed ? nullptr : w.xrow;
-    if (!s.fixed) {
-        janus_status e = zero_fill(y, size_t(TB) * H * sizeof(T), st);
+    {
+        // a step starts: the report, timeout flag included, covers this call
+        // and the backward calls after it
+        const ZeroRange z[] = {{w.sync, sizeof(persist::Sync)}, {y, s.fixed ? 0 : size_t(TB) * H * sizeof(T)}};
+        janus_status e = zero_fill(z, 2, st);
         if (e != JANUS_OK) return e;
     }
     const bool al = weight_aligned(d);
@@ -1303,7 +1312,8 @@ janus_status lstm_fwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
         if (in_xcds) {
             // (with nothing to run, the later parts' rows are set here too)
             for (int rb = 0; rb < (s.packed == 0 ? B : 1); rb += persist::kMaxB) {
-                janus_status e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0l, c0l, hTl, cTl, st);
+                janus_status e = fwd_init_xcd<T>(d, s, w, l, rb, perm, h0l, c0l, hTl, cTl,
+                                                  s.packed > 0 ? Wx[l] : nullptr, b[l], st);
                 if (e != JANUS_OK) return e;
             }
         } else {
@@ -1408,13 +1418,20 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     const int32_t* xrow = s.fixed ? nullptr : w.xrow;
     const int32_t* prevrow = s.fixed ? nullptr : w.prevrow;
     const bool al = weight_aligned(d);
-    if (dx && !s.fixed) {
-        janus_status e = zero_fill(dx, size_t(TB) * d.I * sizeof(T), st);
+    {
+        // The backward's own report fields start at zero; the timeout flag and
+        // the forward's fields stay as the forward left them, so a wait that
+        // ran out in the forward is still reported after the backward (and the
+        // backward's kernels drain at once instead of computing on its garbage).
+        const ZeroRange z[] = {{w.sync, persist::kSyncCounterBytes},
+                               {&w.sync->groups, 2 * sizeof(unsigned)},
+                               {dx, dx && !s.fixed ? size_t(TB) * d.I * sizeof(T) : 0}};
+        janus_status e = zero_fill(z, 3, st);
         if (e != JANUS_OK) return e;
     }
     const int64_t bh = int64_t(B) * H;
     const bool persistent = use_persistent(d);
-    if (persistent) {
+    if (persistent && !use_xcd_bwd(d)) {
         TraceScope trace("perm4", 0.0, 16.0 * H, st);
         hipLaunchKernelGGL(perm4_kernel, dim3(unsigned((4 * H + 255) / 256)), dim3(256), 0, st, H, w.perm4);
         JANUS_LAUNCH_CHECK();
@@ -1462,7 +1479,8 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
                     const int64_t n16 = int64_t(xcd::kSlots) * a.groups * p.RT * a.nkg * 64;
                     TraceScope trace("lstm_bwd_init", 0.0, 16.0 * double(n16), st);
                     hipLaunchKernelGGL(xcd::bwd_init_kernel, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 1024))),
-                                       dim3(256), 0, st, reinterpret_cast<uint4*>(w.ring), n16, w.sync);
+                                       dim3(256), 0, st, reinterpret_cast<uint4*>(w.ring), n16, w.sync, H,
+                                       top && rb == 0 ? w.perm4 : nullptr);
                     JANUS_LAUNCH_CHECK();
                 }
                 const double work = part_rows(s, rb);
@@ -1708,19 +1726,16 @@ janus_status lstm_bwd_impl(const janus_lstm_desc& d, const SeqSchedule& s, const
     return JANUS_OK;
 }
 
+// One copy: the running rows' two lists lie one after the other.
 janus_status upload_schedule(const SeqSchedule& s, const LstmWs& w, hipStream_t st) {
     if (s.fixed) return JANUS_OK;
-    janus_status e = upload(w.perm, s.perm.data(), sizeof(int32_t) * s.B, st);
-    if (e != JANUS_OK) return e;
-    if (s.packed > 0) {
-        e = upload(w.xrow, s.xrow.data(), sizeof(int32_t) * s.packed, st);
-        if (e != JANUS_OK) return e;
-        e = upload(w.prevrow, s.prevrow.data(), sizeof(int32_t) * s.packed, st);
-        if (e != JANUS_OK) return e;
-    }
-    e = upload(w.act_dev, s.active.data(), sizeof(int32_t) * (s.T + 1), st);
-    if (e != JANUS_OK) return e;
-    return upload(w.off_dev, s.offsets.data(), sizeof(int32_t) * (s.T + 2), st);
+    const size_t rows = sizeof(int32_t) * s.packed;
+    const UploadPiece pieces[] = {{w.perm, s.perm.data(), sizeof(int32_t) * s.B},
+                                  {w.act_dev, s.active.data(), sizeof(int32_t) * (s.T + 1)},
+                                  {w.off_dev, s.offsets.data(), sizeof(int32_t) * (s.T + 2)},
+                                  {w.xrow, s.xrow.data(), rows},
+                                  {w.prevrow, s.prevrow.data(), rows}};
+    return upload_pieces(pieces, s.packed > 0 ? 5 : 3, st);
 }
 
 // ------------------------------------------------------- padded problems
@@ -1790,7 +1805,8 @@ size_t carve_pad(const janus_lstm_desc& d, void* base, PadWs& w) {
 //   dst[r, c] (r < rows, c < cols) = src[sr, c] for c < scols, else 0,
 // where the source row sr is r (gate_dH == 0) or, for gate-major parameter
 // rows, gate g = r / gate_dH, unit u = r % gate_dH, sr = g * gate_sH + u (no
-// source row, i.e. 0, when u >= gate_sH).  Elements are es = 2 or 4 bytes.
+// source row, i.e. 0, when u >= gate_sH).  Columns and strides count units of es
+// bytes (2 to 16), one or more elements.
 // blockIdx.y selects the copy; blocks stride over its elements.
 constexpr int kMaxRemaps = 16;
 struct RemapOp {
@@ -1803,27 +1819,49 @@ struct RemapBatch {
     RemapOp op[kMaxRemaps];
 };
 
+// Units of sizeof(T) bytes: an element, or as many as divide a row's lengths
+// and whose addresses are aligned (then scols, cols and the strides count
+// units).  Four loads in flight per thread (one, on four times the workgroups:
+// 10.4 us), 32-bit divisions where the copy allows them.  H 650 (units of 4
+// and 8 bytes), against elements and 64-bit divisions: 12.3 -> 9.2 us a launch.
 template <typename T>
-__device__ __forceinline__ void remap_one(const RemapOp& o, int64_t i) {
-    const int64_t r = i / o.cols;
-    const int c = int(i % o.cols);
-    int64_t sr = r;
-    bool ok = c < o.scols;
-    if (o.gate_dH > 0) {
-        const int64_t g = r / o.gate_dH, u = r % o.gate_dH;
-        ok = ok && u < o.gate_sH;
-        sr = g * o.gate_sH + u;
+__device__ __forceinline__ void remap_units(const RemapOp& o, int64_t i0, int64_t stride) {
+    constexpr int NB = 4;
+    const int64_t n = o.rows * o.cols;
+    const bool small = n < (int64_t(1) << 31);
+    for (int64_t i = i0; i < n; i += NB * stride) {
+        T v[NB];
+        int64_t at[NB];
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const int64_t k = i + e * stride;
+            const int64_t r = small ? int64_t(unsigned(k) / unsigned(o.cols)) : k / o.cols;
+            const int c = int(k - r * o.cols);
+            int64_t sr = r;
+            bool ok = k < n && c < o.scols;
+            if (o.gate_dH > 0) {
+                const int64_t g = small ? int64_t(unsigned(r) / unsigned(o.gate_dH)) : r / o.gate_dH;
+                const int64_t u = r - g * o.gate_dH;
+                ok = ok && u < o.gate_sH;
+                sr = g * o.gate_sH + u;
+            }
+            v[e] = T{};
+            if (ok) v[e] = static_cast<const T*>(o.src)[sr * o.sld + c];
+            at[e] = k < n ? r * o.dld + c : -1;
+        }
+#pragma unroll
+        for (int e = 0; e < NB; ++e)
+            if (at[e] >= 0) static_cast<T*>(o.dst)[at[e]] = v[e];
     }
-    static_cast<T*>(o.dst)[r * o.dld + c] = ok ? static_cast<const T*>(o.src)[sr * o.sld + c] : T(0);
 }
 
 __global__ __launch_bounds__(256) void remap_batch_kernel(RemapBatch b) {
     const RemapOp& o = b.op[blockIdx.y];
-    const int64_t n = o.rows * o.cols;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-        if (o.es == 2) remap_one<uint16_t>(o, i);
-        else remap_one<uint32_t>(o, i);
-    }
+    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+    if (o.es == 16) remap_units<uint4>(o, i0, stride);
+    else if (o.es == 8) remap_units<uint2>(o, i0, stride);
+    else if (o.es == 4) remap_units<uint32_t>(o, i0, stride);
+    else remap_units<uint16_t>(o, i0, stride);
 }
 
 // Collects copies and launches them together (in groups of kMaxRemaps).
@@ -1839,8 +1877,13 @@ struct RemapList {
             janus_status e = launch(st);
             if (e != JANUS_OK) return e;
         }
-        b.op[n++] = RemapOp{src, dst, sld, dld, rows, scols, cols, gate_sH, gate_dH, int(sizeof(T))};
-        most = std::max(most, rows * cols);
+        int v = 16 / int(sizeof(T));   // elements of a unit
+        while (v > 1 && (scols % v || cols % v || sld % v || dld % v ||
+                         (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % (v * sizeof(T))))
+            v /= 2;
+        b.op[n++] = RemapOp{src, dst, sld / v, dld / v, rows, scols / v, cols / v, gate_sH, gate_dH,
+                            v * int(sizeof(T))};
+        most = std::max(most, rows * (cols / v));
         return JANUS_OK;
     }
     janus_status launch(hipStream_t st) {
@@ -1848,7 +1891,7 @@ struct RemapList {
         double bytes = 0;
         for (int i = 0; i < n; ++i) bytes += 2.0 * double(b.op[i].rows) * b.op[i].cols * b.op[i].es;
         TraceScope trace("pad_copy", 0.0, bytes, st);
-        const unsigned gx = unsigned(std::min<int64_t>((most + 255) / 256, 1024));
+        const unsigned gx = unsigned(std::min<int64_t>((most + 1023) / 1024, 1024));
         hipLaunchKernelGGL(remap_batch_kernel, dim3(gx, unsigned(n)), dim3(256), 0, st, b);
         JANUS_LAUNCH_CHECK();
         n = 0;
@@ -1892,6 +1935,7 @@ janus_status lstm_fwd_padded(const janus_lstm_desc& d, const SeqSchedule& s, voi
     carve_pad(d, ws, w);
     LstmWs inner;
     carve(p, ws, inner);
+    place_rows(s, inner);
     RemapList q;
     janus_status e = pad_params(d, p, w, x, Wx, Wh, b, q, st);
     if (e != JANUS_OK) return e;
@@ -1918,6 +1962,7 @@ janus_status lstm_bwd_padded(const janus_lstm_desc& d, const SeqSchedule& s, voi
     carve_pad(d, ws, w);
     LstmWs inner;
     carve(p, ws, inner);
+    place_rows(s, inner);
     // the padded Wx, Wh and x are still in the workspace from the forward call
     (void)x;
     (void)Wx;
@@ -1982,12 +2027,10 @@ extern "C" janus_status janus_lstm_seq_fwd(const janus_lstm_desc* d, const void*
     const bool pad = needs_padding(*d);
     LstmWs w;
     carve(pad ? padded_desc(*d) : *d, ws, w);
+    place_rows(s, w);
     hipStream_t st = static_cast<hipStream_t>(stream);
     e = upload_schedule(s, w, st);
     if (e != JANUS_OK) return e;
-    // a step starts: the report, timeout flag included, covers this call and
-    // the backward calls after it
-    if ((e = zero_fill(w.sync, sizeof(persist::Sync), st)) != JANUS_OK) return e;
     if (pad) return lstm_fwd_padded(*d, s, ws, x, Wx, Wh, b, h0, c0, y, hT, cT, st);
     if (d->dtype == JANUS_BF16)
         return lstm_fwd_impl<bf16_t, StepBF16>(*d, s, w, x, Wx, Wh, b, h0, c0, y, hT, cT, st);
@@ -2015,15 +2058,10 @@ extern "C" janus_status janus_lstm_seq_bwd(const janus_lstm_desc* d, const void*
     const bool pad = needs_padding(*d);
     LstmWs w;
     carve(pad ? padded_desc(*d) : *d, ws, w);
+    place_rows(s, w);
     hipStream_t st = static_cast<hipStream_t>(stream);
     e = upload_schedule(s, w, st);
     if (e != JANUS_OK) return e;
-    // The backward's own report fields start at zero; the timeout flag and
-    // the forward's fields stay as the forward left them, so a wait that ran
-    // out in the forward is still reported after the backward (and the
-    // backward's kernels drain at once instead of computing on its garbage).
-    if ((e = zero_fill(w.sync, persist::kSyncCounterBytes, st)) != JANUS_OK) return e;
-    if ((e = zero_fill(&w.sync->groups, 2 * sizeof(unsigned), st)) != JANUS_OK) return e;
     if (pad) return lstm_bwd_padded(*d, s, ws, x, Wx, Wh, dy, dhT, dcT, dx, dh0, dc0, dWx, dWh, db, st);
     if (d->dtype == JANUS_BF16)
         return lstm_bwd_impl<bf16_t, StepBF16>(*d, s, w, x, Wx, Wh, dy, dhT, dcT, dx, dh0, dc0, dWx, dWh, db, st);

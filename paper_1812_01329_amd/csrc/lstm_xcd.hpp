@@ -53,6 +53,8 @@
 // thread refilled before, never the old value.
 #pragma once
 
+#include <type_traits>
+
 #include "device.hpp"
 #include "lstm_persist.hpp"
 
@@ -300,18 +302,58 @@ template <> struct Gates<float> {
 };
 
 // ------------------------------------------------------------------ set-up
+// Gate-interleaved copies of a layer's Wx and b: row n of the copy is row
+// (n % 4) H + n / 4, in 16-byte pieces where the rows are whole pieces, one a
+// thread (H 656, with the set-up of the forward: 5 us; four pieces a thread on a
+// quarter of the workgroups: 17).
+template <typename T>
+struct Interleave {
+    const T* W;
+    T* Wi;
+    const T* b;
+    T* bi;
+    int H, cols;
+};
+template <typename T>
+__device__ __forceinline__ void interleave(const Interleave<T>& a, int64_t i0, int64_t stride) {
+    const int H = a.H;
+    auto copy = [&](auto* d, const auto* s, int per_row) {
+        const int64_t n = int64_t(4) * H * per_row;
+        for (int64_t i = i0; i < n; i += stride) {
+            const int r = int(n <= 0xffffffffll ? int64_t(unsigned(i) / unsigned(per_row)) : i / per_row);
+            d[i] = s[(int64_t(r & 3) * H + (r >> 2)) * per_row + (i - int64_t(r) * per_row)];
+        }
+    };
+    constexpr int P = 16 / int(sizeof(T));
+    if (a.cols % P == 0 && ((reinterpret_cast<uintptr_t>(a.W) | reinterpret_cast<uintptr_t>(a.Wi)) & 15) == 0)
+        copy(reinterpret_cast<uint4*>(a.Wi), reinterpret_cast<const uint4*>(a.W), a.cols / P);
+    else
+        copy(a.Wi, a.W, a.cols);
+    copy(a.bi, a.b, 1);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void interleave_kernel(Interleave<T> a) {
+    interleave(a, int64_t(blockIdx.x) * 256 + threadIdx.x, int64_t(gridDim.x) * 256);
+}
+
 // Forward: slot 0 = h0 of rows rbase + [0, 16 tiles) (zero past the batch and
 // past H), the other slots empty, the barrier counters zero, and the initial
 // state in the activation store (Hs, Cs rows [0, B), columns [0, B) of HT);
-// a length-0 sequence ends in its initial state.
+// a length-0 sequence ends in its initial state.  The first wblocks workgroups
+// interleave the layer's weights instead.
 template <typename T>
 __global__ __launch_bounds__(256) void fwd_init_kernel(int B, int H, int64_t ldh, int rbase, int tiles, int nkg,
                                                        const int32_t* perm, const float* h0, const float* c0, T* Hs,
                                                        float* Cs, int active0, float* hT, float* cT, T* HT, int64_t ldht,
-                                                       T* ring, Sync* sync) {
+                                                       T* ring, Sync* sync, Interleave<T> weights, int wblocks) {
     using L = Lay<T>;
+    if (int(blockIdx.x) < wblocks) {
+        interleave(weights, int64_t(blockIdx.x) * 256 + threadIdx.x, int64_t(wblocks) * 256);
+        return;
+    }
     const int64_t n = int64_t(tiles) * nkg * 64 * L::EPL;   // elements of a slot
-    const int64_t stride = int64_t(gridDim.x) * 256, i0 = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t stride = int64_t(gridDim.x - wblocks) * 256,
+                  i0 = int64_t(blockIdx.x - wblocks) * 256 + threadIdx.x;
     uint4* rest = reinterpret_cast<uint4*>(ring + n);
     for (int64_t i = i0; i < (kSlots - 1) * n / L::EPL; i += stride)
         rest[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
@@ -342,12 +384,16 @@ __global__ __launch_bounds__(256) void fwd_init_kernel(int B, int H, int64_t ldh
     }
 }
 
-// Backward: every slot empty, the barrier counters zero.
-static __global__ __launch_bounds__(256) void bwd_init_kernel(uint4* ring, int64_t n16, Sync* sync) {
+// Backward: every slot empty, the barrier counters zero, and the map of the
+// interleaved gate rows to gate-major rows (perm4, may be NULL).
+static __global__ __launch_bounds__(256) void bwd_init_kernel(uint4* ring, int64_t n16, Sync* sync, int H,
+                                                              int32_t* perm4) {
     const int64_t stride = int64_t(gridDim.x) * 256, i0 = int64_t(blockIdx.x) * 256 + threadIdx.x;
     for (int64_t i = i0; i < n16; i += stride) ring[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(sync);
     for (int64_t i = i0; i < int64_t(persist::kSyncCounterBytes / 4); i += stride) cnt[i] = 0u;
+    if (perm4)
+        for (int64_t i = i0; i < 4 * H; i += stride) perm4[i] = int(i & 3) * H + int(i >> 2);
 }
 
 // db[g * H + u] = sum over the row groups of their sums, in group order

@@ -77,6 +77,13 @@ janus_status colsum(janus_dtype dt, const void* in, int64_t R, int C, int64_t ld
 
 // clear `bytes` bytes of device memory (a kernel, so it may be captured)
 janus_status zero_fill(void* p, size_t bytes, hipStream_t stream);
+// several ranges (at most kMaxZeroRanges that are not empty) in one launch
+constexpr int kMaxZeroRanges = 4;
+struct ZeroRange {
+    void* p;
+    size_t bytes;
+};
+janus_status zero_fill(const ZeroRange* r, int n, hipStream_t stream);
 
 // dE [V, H] float32 = 0, then dE[ids[r]] = sum of dx[r] over the rows with
 // that id, in ascending r (deterministic, no atomics).  The rows are grouped
