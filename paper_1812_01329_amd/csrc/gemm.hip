@@ -571,6 +571,136 @@ void gemm_nt_fast_kernel(NtArgs p, GemmDesc g) {
     }
 }
 
+// The same contraction in 128 x 128 x 64 tiles for grids of few tiles: four
+// waves of 64 x 64, four LDS stages.  A 256 x 256 tile alone on its CU takes
+// 1.5 us per K block, the round trip of a load (one block in flight); here
+// three blocks are in flight (0.65 us per block) and a grid has four times the
+// tiles.
+struct MidCfg {
+    static constexpr int BM = 128, BN = 128, BK = 64, NT = 256;
+    static constexpr int LOADS = 8;                      // 1 KB loads per wave and stage
+    static constexpr int STAGE = (BM + BN) * BK;         // bf16 elements
+};
+template <typename OutT, bool SCATTER, int EPI>
+__global__ __launch_bounds__(MidCfg::NT) void gemm_nt_mid_kernel(NtArgs p, GemmDesc g) {
+    using C_ = MidCfg;
+    // separate objects, so that reading one does not wait for the loads that
+    // fill the others
+    __shared__ __align__(16) bf16_t stage0[C_::STAGE];
+    __shared__ __align__(16) bf16_t stage1[C_::STAGE];
+    __shared__ __align__(16) bf16_t stage2[C_::STAGE];
+    __shared__ __align__(16) bf16_t stage3[C_::STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // block -> (split, tile), as above
+    int vb = blockIdx.x;
+    if (gridDim.x % 8 == 0) vb = (vb % 8) * int(gridDim.x / 8) + vb / 8;
+    const int tiles = p.mt * p.nt, split = vb / tiles, t = vb % tiles;
+    constexpr int GM = 4;
+    const int first_m = t / (GM * p.nt) * GM, gsz = min(p.mt - first_m, GM);
+    const int m0 = (first_m + t % (GM * p.nt) % gsz) * C_::BM, n0 = t % (GM * p.nt) / gsz * C_::BN;
+    const int kt0 = split * p.ktiles_per_split;
+    const int nk = max(0, min(p.ktiles_per_split, (p.K + C_::BK - 1) / C_::BK - kt0));
+
+    // loads: waves 0-1 fill the A tile, 2-3 the B tile; load j of wave w covers
+    // tile rows 64 (w % 2) + 8 j + lane / 8, chunks swizzled by row as above
+    const bool isA = wave < 2;
+    const int lw = wave & 1;
+    const int rows = isA ? p.M : p.N, row0 = isA ? m0 : n0;
+    const int64_t ld = isA ? p.lda : p.ldb;
+    const int32_t* idx = isA ? p.a_idx : p.b_idx;
+    const bf16_t* src = isA ? p.A : p.B;
+    const int kchunk = ((lane & 7) ^ (lane >> 3)) * 8;
+    uint32_t rowoff[C_::LOADS];
+#pragma unroll
+    for (int j = 0; j < C_::LOADS; ++j) {
+        const int r = lw * 64 + j * 8 + (lane >> 3), gr = row0 + r;
+        const int64_t src_row = idx ? int64_t(idx[min(gr, rows - 1)]) : int64_t(r);
+        rowoff[j] = gr < rows ? uint32_t(src_row * ld * 2) : kNtOutOfRange;
+    }
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(idx ? src : src + int64_t(row0) * ld), (short)0,
+                                                      0x7fffffff, 0x00020000);
+    const int lds_op = (isA ? 0 : C_::BM * C_::BK) + lw * 64 * C_::BK;
+    auto issue = [&](int kt, bf16_t* stage) {
+        const int k = (kt0 + kt) * C_::BK + kchunk;
+        const uint32_t kbad = k < p.K ? 0u : kNtOutOfRange;
+#pragma unroll
+        for (int j = 0; j < C_::LOADS; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(stage + lds_op + j * 8 * C_::BK), 16,
+                                                     (rowoff[j] + uint32_t(k) * 2u) | kbad, 0, 0, 0);
+    };
+    const int wr0 = (wave >> 1) * 64, wc0 = (wave & 1) * 64, sw = lane & 7, kq = lane >> 4;
+    const int ar = (wr0 + (lane & 15)) * C_::BK, br = C_::BM * C_::BK + (wc0 + (lane & 15)) * C_::BK;
+    f32x4_t acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // block `it` of the walk, in stage `cur`; block it + 3 goes to `free`, which
+    // every wave has read out by the barrier
+    auto step = [&](int it, const bf16_t* cur, bf16_t* free) {
+        __builtin_amdgcn_sched_barrier(0);
+        // this block's loads are the oldest of at most three blocks'; own LDS reads are done
+        if (it + 2 < nk) __builtin_amdgcn_s_waitcnt(0x4070);        // vmcnt(16) lgkmcnt(0)
+        else if (it + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8)
+        else __builtin_amdgcn_s_waitcnt(0x0070);                    // vmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        if (it + 3 < nk) issue(it + 3, free);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < C_::BK / 32; ++ks) {
+            const int c = ((4 * ks + kq) ^ sw) << 3;
+            uint4 fa[4], fb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                fa[i] = *reinterpret_cast<const uint4*>(cur + ar + i * 16 * C_::BK + c);
+                fb[i] = *reinterpret_cast<const uint4*>(cur + br + i * 16 * C_::BK + c);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
+                                                                        __builtin_bit_cast(bf16x8_t, fb[j]), acc[i][j],
+                                                                        0, 0, 0);
+        }
+    };
+    if (nk > 0) issue(0, stage0);
+    if (nk > 1) issue(1, stage1);
+    if (nk > 2) issue(2, stage2);
+    for (int it = 0; it < nk; it += 4) {
+        step(it, stage0, stage3);
+        if (it + 1 < nk) step(it + 1, stage1, stage0);
+        if (it + 2 < nk) step(it + 2, stage2, stage1);
+        if (it + 3 < nk) step(it + 3, stage3, stage2);
+    }
+    // element v of acc[i][j]: row 16 i + 4 (lane / 16) + v, column 16 j + lane % 16
+    const bf16_t* bias = static_cast<const bf16_t*>(g.bias);
+    float bv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + wc0 + 16 * j + (lane & 15);
+        bv[j] = EPI == kEpiStore && bias && col < p.N ? bf2f(bias[col]) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = m0 + wr0 + 16 * i + 4 * kq + v;
+            if (row >= p.M) continue;
+            int64_t crow = row;
+            if constexpr (SCATTER) crow = g.c_idx[row];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int col = n0 + wc0 + 16 * j + (lane & 15);
+                if (col >= p.N) continue;
+                if constexpr (EPI == kEpiPartial)
+                    p.partial[(int64_t(split) * p.M + row) * p.N + col] = acc[i][j][v];
+                else
+                    static_cast<OutT*>(g.C)[crow * g.ldc + col] = from_f<OutT>(g.alpha * acc[i][j][v] + bv[j]);
+            }
+        }
+}
+
 // C = alpha * (sum over splits of the partials, in split order) + bias
 template <typename OutT, typename BiasT = bf16_t>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* partial, int splits, int M, int N,
@@ -750,6 +880,7 @@ struct NtPlan {
     int64_t ldt = 0;                 // leading dimension of copies (K rounded to 64)
     int amode = kInPlace, bmode = kInPlace;
     int splits = 1, ktiles_per_split = 0;
+    bool mid = false;                // 128 x 128 tiles
     size_t a_off = 0, b_off = 0, p_off = 0, bytes = 0;
 };
 
@@ -773,6 +904,32 @@ int nt_splits(int tiles, int ktiles, int M, int N) {
         }
     }
     return best;
+}
+
+// Whether 128 x 128 tiles are expected to be faster, with how many splits (at
+// most those of the 256 x 256 tiles, whose scratch the caller has).  A K block
+// takes about 0.65 us while the grid is one round of the chip, and a further
+// round costs another 2.5 us to start.  (2624 x 656 outputs over K = 700: 24 us
+// in 33 tiles of 256, 14 in 126 of 128; over 700 rows and K = 656 27 and 16.5;
+// 700 x 10000 over K = 650, two rounds: 26 and 28; 4096 x 512 over K = 13000: 88
+// with splits, 127 in 128 tiles without.)
+bool nt_mid(int tiles, int ktiles, int M, int N, int& splits) {
+    if (tiles >= 160) return false;
+    auto sum = [&](int n) { return n > 1 ? 5.0 + 2e-6 * n * double(M) * N : 0.0; };
+    double least = 1.5 * ((ktiles + splits - 1) / splits) + sum(splits);
+    const int64_t small = int64_t((M + MidCfg::BM - 1) / MidCfg::BM) * ((N + MidCfg::BN - 1) / MidCfg::BN);
+    int best = 0;
+    for (int n = 1; n <= splits; ++n) {
+        const double rounds = double((small * n + 255) / 256);
+        const double us = 0.65 * ((ktiles + n - 1) / n) * rounds + 2.5 * (rounds - 1) + sum(n);
+        if (us < least) {
+            least = us;
+            best = n;
+        }
+    }
+    if (best == 0) return false;
+    splits = best;
+    return true;
 }
 
 // The fast path takes every bf16 contraction with at least 16 rows and
@@ -799,7 +956,8 @@ NtPlan plan_nt(const GemmDesc& g) {
     if (int64_t(NtCfg::BM) * p.ldt * 2 >= kMaxOff) return p;
     const int tiles = ((g.M + NtCfg::BM - 1) / NtCfg::BM) * ((g.N + NtCfg::BN - 1) / NtCfg::BN);
     const int ktiles = (g.K + NtCfg::BK - 1) / NtCfg::BK;
-    const int splits = nt_splits(tiles, ktiles, g.M, g.N);
+    int splits = nt_splits(tiles, ktiles, g.M, g.N);
+    p.mid = nt_mid(tiles, ktiles, g.M, g.N, splits);
     p.ktiles_per_split = (ktiles + splits - 1) / splits;
     p.splits = (ktiles + p.ktiles_per_split - 1) / p.ktiles_per_split;
     size_t off = 0;
@@ -832,6 +990,17 @@ int device_cus() {
         return 0;
     }
     return v;
+}
+
+template <typename OutT, bool SCATTER, int EPI>
+janus_status launch_nt_mid(const NtArgs& a, const GemmDesc& g, hipStream_t s) {
+    const double out_bytes = EPI == kEpiPartial ? 4.0 * a.splits : double(sizeof(OutT));
+    TraceScope trace(nt_label(sizeof(OutT) == 4, SCATTER, EPI == kEpiPartial), 2.0 * g.M * g.N * double(g.K),
+                     (double(g.M) * g.K + double(g.N) * g.K) * 2.0 + double(g.M) * g.N * out_bytes, s);
+    hipLaunchKernelGGL((gemm_nt_mid_kernel<OutT, SCATTER, EPI>), dim3(unsigned(a.mt * a.nt * a.splits)),
+                       dim3(MidCfg::NT), 0, s, a, g);
+    JANUS_LAUNCH_CHECK();
+    return JANUS_OK;
 }
 
 template <typename OutT, bool SCATTER, int EPI>
@@ -922,13 +1091,15 @@ janus_status gemm_fast(const GemmDesc& g, const NtPlan& p, hipStream_t s) {
     };
     if ((e = prepare(p.amode, g.A, g.lda, g.a_idx, g.M, p.a_off, a.A, a.lda, a.a_idx)) != JANUS_OK) return e;
     if ((e = prepare(p.bmode, g.B, g.ldb, g.b_idx, g.N, p.b_off, a.B, a.ldb, a.b_idx)) != JANUS_OK) return e;
-    a.mt = (g.M + NtCfg::BM - 1) / NtCfg::BM;
-    a.nt = (g.N + NtCfg::BN - 1) / NtCfg::BN;
+    const int bm = p.mid ? MidCfg::BM : NtCfg::BM, bn = p.mid ? MidCfg::BN : NtCfg::BN;
+    a.mt = (g.M + bm - 1) / bm;
+    a.nt = (g.N + bn - 1) / bn;
     a.splits = p.splits;
     a.ktiles_per_split = p.ktiles_per_split;
     if (p.splits > 1) {
         a.partial = reinterpret_cast<float*>(scratch + p.p_off);
-        if ((e = launch_nt<float, false, kEpiPartial>(a, g, s)) != JANUS_OK) return e;
+        e = p.mid ? launch_nt_mid<float, false, kEpiPartial>(a, g, s) : launch_nt<float, false, kEpiPartial>(a, g, s);
+        if (e != JANUS_OK) return e;
         const int64_t n = int64_t(g.M) * g.N;
         TraceScope trace("splitk_reduce", 0.0, 4.0 * n * p.splits + n * (g.c_f32 ? 4.0 : 2.0), s);
         if (g.c_f32)
@@ -939,6 +1110,13 @@ janus_status gemm_fast(const GemmDesc& g, const NtPlan& p, hipStream_t s) {
                                a.partial, p.splits, g.M, g.N, g);
         JANUS_LAUNCH_CHECK();
         return JANUS_OK;
+    }
+    if (p.mid) {
+        if (g.c_f32)
+            return g.c_idx ? launch_nt_mid<float, true, kEpiStore>(a, g, s)
+                           : launch_nt_mid<float, false, kEpiStore>(a, g, s);
+        return g.c_idx ? launch_nt_mid<bf16_t, true, kEpiStore>(a, g, s)
+                       : launch_nt_mid<bf16_t, false, kEpiStore>(a, g, s);
     }
     if (g.c_f32) return g.c_idx ? launch_nt<float, true, kEpiStore>(a, g, s) : launch_nt<float, false, kEpiStore>(a, g, s);
     return g.c_idx ? launch_nt<bf16_t, true, kEpiStore>(a, g, s) : launch_nt<bf16_t, false, kEpiStore>(a, g, s);

@@ -30,3 +30,11 @@ def test_float32(rows, H, P):
 @pytest.mark.parametrize("V,H,rows", [(3001, 37, 20), (130, 1, 9)])
 def test_float32_softmax(V, H, rows, monkeypatch):
     _softmax("f32", V, H, rows, "1", "random", monkeypatch)
+
+
+@pytest.mark.parametrize("V,H,rows", [(300, 64, 130), (129, 128, 600), (1000, 192, 129), (260, 256, 257),
+                                      (640, 320, 200), (127, 584, 700)])
+def test_few_tiles_bf16(V, H, rows, monkeypatch):
+    """128 x 128 tiles: partial tiles either way, one to more K blocks than
+    there are LDS stages."""
+    _softmax("bf16", V, H, rows, "1", "random", monkeypatch)
