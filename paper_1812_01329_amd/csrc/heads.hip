@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <mutex>
 #include <cstdlib>
+#include <utility>
 #include <vector>
 
 #include "device.hpp"
@@ -545,48 +546,67 @@ janus_status embed_backward(janus_dtype dt, const void* dx, const int32_t* ids_h
 // ------------------------------------------------------- small softmax head
 // The whole softmax cross-entropy head of a small problem (a few hundred
 // rows, at most 64 classes, e.g. the 5-class sentiment head at the tree
-// roots) in one workgroup: h and Wout in LDS, the logits, per-row
-// log-sum-exp, loss, dz = (softmax - onehot) / rows, dh = dz Wout,
-// dWout = dz^T h and dbout = column sums of dz, each summed in a fixed
-// order.  One launch instead of three contractions, two reductions and
-// the column sums.
+// roots) in one launch: h and Wout in LDS, the logits, per-row log-sum-exp,
+// loss, dz = (softmax - onehot) / rows, dh = dz Wout, dWout = dz^T h and
+// dbout = column sums of dz, each summed in a fixed order.
+//
+// It is bound by its chain of LDS sums, not by bytes.  Up to 16 workgroups
+// each stage h and Wout and form all logits and dz (nothing is exchanged),
+// and share out the elements of dh, dWout and dbout, whose sums were two
+// thirds of the time of one workgroup; each logit is summed by four lanes.
+// Measured per call against one workgroup of 256 threads: 25 rows, 5 classes,
+// H 150 14.4 -> 10.4 us, H 300 21.9 -> 10.1; 60 rows, 64 classes, H 100 92.5
+// -> 33.1.  Past 64 KB, against the contractions: 100 rows, 5 classes, H 300
+// 34.1 -> 16.5; 97 rows, 18 classes, H 150 36.2 -> 24.9.
 constexpr int kXentSmallV = 64;
+constexpr int kXentSmallThreads = 512;
+constexpr int kXentSmallLanes = 4;      // lanes of one logit
+constexpr int kXentSmallBlocks = 16;
 constexpr size_t kXentSmallLds = 64 * 1024;
+constexpr size_t kXentWideLds = 152 * 1024;
+constexpr int64_t kXentWideLogits = int64_t(1) << 18;
 
 size_t xent_small_lds(const janus_xent_desc& d) {
     return sizeof(float) * (size_t(d.rows) * d.H + size_t(d.V) * d.H + size_t(d.rows) * d.V + size_t(d.rows));
 }
+// Past 64 KB of operands a workgroup fills a CU by itself and every one
+// repeats the staging and the logits, so there the launch is taken only while
+// those stay short: up to 2^18 products (rows V H), where it still takes two
+// thirds of the contractions' time (24.9 against 36.2 us).
 bool xent_small_fits(const janus_xent_desc& d) {
     const char* e = getenv("JANUS_XENT_SMALL");
     if (e && e[0] == '0') return false;
-    return d.V <= kXentSmallV && xent_small_lds(d) <= kXentSmallLds;
+    if (d.V > kXentSmallV) return false;
+    const size_t lds = xent_small_lds(d);
+    return lds <= kXentSmallLds || (lds <= kXentWideLds && int64_t(d.rows) * d.V * d.H <= kXentWideLogits);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void xent_small_kernel(const T* h, const T* W, const T* b, const int32_t* tgt,
-                                                         int rows, int V, int H, T* dh, float* dW, float* db,
-                                                         float* loss) {
+__global__ __launch_bounds__(kXentSmallThreads) void xent_small_kernel(const T* h, const T* W, const T* b,
+                                                                       const int32_t* tgt, int rows, int V, int H,
+                                                                       T* dh, float* dW, float* db, float* loss) {
     extern __shared__ float xs[];
     float* hs = xs;                    // [rows][H]
     float* wsm = hs + rows * H;        // [V][H]
     float* zs = wsm + V * H;           // [rows][V]: logits, then dz
     float* ls = zs + rows * V;         // [rows] loss of each row
+    constexpr int NT = kXentSmallThreads, S = kXentSmallLanes;
     const int tid = threadIdx.x;
     // h and W into LDS, NB elements in flight per thread: the raw values are
     // loaded first and converted only after the last load of the batch is
     // issued, so a batch costs one memory round trip, not one per element
     auto stage = [&](float* dst, const T* src, int n) {
         constexpr int NB = 32;
-        for (int base = tid; base < n; base += 256 * NB) {
+        for (int base = tid; base < n; base += NT * NB) {
             T v[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                const int idx = base + i * 256;
+                const int idx = base + i * NT;
                 v[i] = idx < n ? src[idx] : T(0);
             }
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-                const int idx = base + i * 256;
+                const int idx = base + i * NT;
                 if (idx < n) dst[idx] = to_f(v[i]);
             }
         }
@@ -594,15 +614,20 @@ __global__ __launch_bounds__(256) void xent_small_kernel(const T* h, const T* W,
     stage(hs, h, rows * H);
     stage(wsm, W, V * H);
     __syncthreads();
-    for (int i = tid; i < rows * V; i += blockDim.x) {
+    // lane q of a logit takes k = q (mod S); whole waves run the loop
+    for (int i0 = 0; i0 < rows * V * S; i0 += NT) {
+        const int i = min((i0 + tid) / S, rows * V - 1), q = tid & (S - 1);
         const int r = i / V, v = i - r * V;
-        float s = to_f(b[v]);
-        for (int k = 0; k < H; ++k) s += hs[r * H + k] * wsm[v * H + k];
-        zs[i] = s;
+        float s = 0.f;
+#pragma unroll 8
+        for (int k = q; k < H; k += S) s += hs[r * H + k] * wsm[v * H + k];
+#pragma unroll
+        for (int m = 1; m < S; m <<= 1) s += __shfl_xor(s, m);
+        if (q == 0 && i0 + tid < rows * V * S) zs[i] = s + to_f(b[v]);
     }
     __syncthreads();
     const float inv = 1.f / float(rows);
-    for (int r = tid; r < rows; r += blockDim.x) {
+    for (int r = tid; r < rows; r += NT) {
         float* z = zs + r * V;
         float m = -INFINITY;
         for (int v = 0; v < V; ++v) m = fmaxf(m, z[v]);
@@ -614,27 +639,33 @@ __global__ __launch_bounds__(256) void xent_small_kernel(const T* h, const T* W,
         for (int v = 0; v < V; ++v) z[v] = (__expf(z[v] - m) * rs - (v == t ? 1.f : 0.f)) * inv;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (blockIdx.x == 0 && tid < 64) {
         float s = 0.f;
-        for (int r = 0; r < rows; ++r) s += ls[r];
-        *loss = s * inv;
+        for (int r = tid; r < rows; r += 64) s += ls[r];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+        if (tid == 0) *loss = s * inv;
     }
-    for (int i = tid; i < rows * H; i += blockDim.x) {
+    // dWout and dbout from the last thread of the grid on, dh from the first
+    const int n = int(gridDim.x) * NT, t = int(blockIdx.x) * NT + tid;
+    for (int i = n - 1 - t; i < V * H + V; i += n) {
+        float s = 0.f;
+        if (i < V * H) {
+            const int v = i / H, k = i - v * H;
+#pragma unroll 4
+            for (int r = 0; r < rows; ++r) s += zs[r * V + v] * hs[r * H + k];
+            dW[i] = s;
+        } else {
+            const int v = i - V * H;
+            for (int r = 0; r < rows; ++r) s += zs[r * V + v];
+            db[v] = s;
+        }
+    }
+    for (int i = t; i < rows * H; i += n) {
         const int r = i / H, k = i - r * H;
         float s = 0.f;
         for (int v = 0; v < V; ++v) s += zs[r * V + v] * wsm[v * H + k];
         dh[i] = from_f<T>(s);
-    }
-    for (int i = tid; i < V * H; i += blockDim.x) {
-        const int v = i / H, k = i - v * H;
-        float s = 0.f;
-        for (int r = 0; r < rows; ++r) s += zs[r * V + v] * hs[r * H + k];
-        dW[i] = s;
-    }
-    for (int v = tid; v < V; v += blockDim.x) {
-        float s = 0.f;
-        for (int r = 0; r < rows; ++r) s += zs[r * V + v];
-        db[v] = s;
     }
 }
 
@@ -652,11 +683,27 @@ janus_status xent_small(const janus_xent_desc& d, const int32_t* ids_dev, const 
             attr = smem;
         }
     }
+    // A result that lies on an operand is written after every read of it only
+    // in a launch of one workgroup.
+    const size_t es = dtype_size(d.dtype), nh = size_t(d.rows) * d.H, nw = size_t(d.V) * d.H;
+    const std::pair<const void*, size_t> in[] = {
+        {h, nh * es}, {Wout, nw * es}, {bout, d.V * es}, {ids_dev, d.rows * sizeof(int32_t)}};
+    const std::pair<const void*, size_t> out[] = {
+        {dh, nh * es}, {dWout, nw * sizeof(float)}, {dbout, d.V * sizeof(float)}, {loss, sizeof(float)}};
+    bool overlap = false;
+    for (const auto& a : in)
+        for (const auto& b : out) {
+            const uintptr_t x = reinterpret_cast<uintptr_t>(a.first), y = reinterpret_cast<uintptr_t>(b.first);
+            overlap = overlap || (x < y + b.second && y < x + a.second);
+        }
+    // one element of the results per thread, as far as kXentSmallBlocks go
+    const int blocks =
+        overlap ? 1 : int(std::min<size_t>(kXentSmallBlocks, (nh + nw + kXentSmallThreads - 1) / kXentSmallThreads));
     TraceScope trace("xent_small", 2.0 * 3.0 * d.rows * double(d.V) * d.H,
-                     double(dtype_size(d.dtype)) * (2.0 * d.rows * d.H + double(d.V) * d.H), st);
-    hipLaunchKernelGGL(xent_small_kernel<T>, dim3(1), dim3(256), smem, st, static_cast<const T*>(h),
-                       static_cast<const T*>(Wout), static_cast<const T*>(bout), ids_dev, d.rows, d.V, d.H,
-                       static_cast<T*>(dh), dWout, dbout, loss);
+                     double(es) * (2.0 * d.rows * d.H + double(d.V) * d.H), st);
+    hipLaunchKernelGGL(xent_small_kernel<T>, dim3(unsigned(blocks)), dim3(kXentSmallThreads), smem, st,
+                       static_cast<const T*>(h), static_cast<const T*>(Wout), static_cast<const T*>(bout), ids_dev,
+                       d.rows, d.V, d.H, static_cast<T*>(dh), dWout, dbout, loss);
     JANUS_LAUNCH_CHECK();
     return JANUS_OK;
 }

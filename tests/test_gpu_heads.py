@@ -149,6 +149,43 @@ def test_softmax_cross_entropy(dtype, V, Hd, rows, small, kind, monkeypatch):
     check("dbout", db.cpu().numpy(), rdb, t["grad"])
 
 
+@pytest.mark.parametrize("dtype,V,Hd,rows,one_launch", [
+    ("f32", 1, 1, 1, True), ("f32", 64, 1, 65, True), ("bf16", 2, 3, 1000, True), ("f32", 5, 300, 49, True),
+    ("f32", 5, 300, 100, True), ("bf16", 5, 301, 101, True), ("f32", 5, 300, 130, False),
+    ("f32", 18, 150, 97, True), ("f32", 19, 150, 97, False)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_softmax_head_in_one_launch(dtype, V, Hd, rows, one_launch, in_place):
+    """The one-launch head at the edges of its rule (operands of 64 KB and of
+    152 KB, 2^18 logit products), with one and with sixteen workgroups; dh
+    written over h, which a launch of one workgroup serves."""
+    import torch
+    from paper_1812_01329_amd import janus as J
+    rng = np.random.default_rng(V + Hd + rows)
+    tgt = rng.integers(0, V, rows).astype(np.int32)
+    print(f"[xent-one] {dtype} V={V} H={Hd} rows={rows} in_place={in_place}", flush=True)
+    W, b, h = _vals(rng, (V, Hd), 0.5, dtype), _vals(rng, (V,), 0.5, dtype), _vals(rng, (rows, Hd), 1.0, dtype)
+    dt = J.BF16 if dtype == "bf16" else J.F32
+    ws = torch.empty(J.janus_xent_workspace_bytes(V, Hd, rows, dt, J.XENT_FWD_BWD), dtype=torch.uint8, device="cuda:0")
+    hd = _dev(h, dtype)
+    dh = hd if in_place and one_launch else torch.empty_like(hd)
+    dW, db, loss = (torch.empty(s, dtype=torch.float32, device="cuda:0") for s in ((V, Hd), (V,), (1,)))
+    J.janus_trace_begin()
+    J.janus_embed_softmax_xent(J.XentDesc(V, Hd, rows, dt), J.XENT_FWD_BWD, tgt, torch.from_numpy(tgt).to("cuda:0"),
+                               table=_dev(W, dtype), bias=_dev(b, dtype), inp=hd, out=dh, dtable=dW, dbias=db,
+                               loss=loss, ws=ws)
+    assert ("xent_small" in {r["label"] for r in J.janus_trace_end()}) == one_launch
+    rl, rdh, rdW, rdb, _ = H_.softmax_xent(h, W, b, tgt)
+    t = TOL[dtype]
+    if V > 1:   # one class: loss and gradients are 0
+        check("loss", np.array([loss.item()]), np.array([rl]), t["out"])
+        check("dh", _host(dh), rdh, t["grad"])
+        check("dWout", dW.cpu().numpy(), rdW, t["grad"])
+        check("dbout", db.cpu().numpy(), rdb, t["grad"])
+    else:
+        for v in (loss, dh, dW, db):
+            assert float(v.float().abs().max()) <= 1e-6
+
+
 @pytest.mark.parametrize("dtype,rows,Hd,P", [("f32", 77, 36, 20), ("bf16", 300, 128, 72), ("bf16", 520, 256, 256)])
 def test_linear_mse(dtype, rows, Hd, P):
     """Projection + MSE on ragged float32 shapes and on bf16 shapes that take
