@@ -339,15 +339,26 @@ int persist_bwd_slices(const janus_lstm_desc& d) {
 
 // The persistent path: for bf16, H a multiple of 8, one co-resident workgroup
 // per slice and the weight slice in LDS; for float32, what runs in row groups
-// per XCD and is not small enough for the one-workgroup kernels.  A batch of
+// per XCD and is not faster in the one-workgroup kernels.  A batch of
 // more than 256 rows runs in parts of 256 sorted rows, one launch each.  It
 // can be switched off with JANUS_PERSIST=0 (the per-step kernels then run).
 bool use_small(const janus_lstm_desc& d);
+// float32 problems that fit one workgroup and are faster there than in row
+// groups per XCD.  A step of one workgroup grows with its B H H products, one
+// CU's LDS reads, while a step of the row groups stays an exchange through
+// the L2.  One layer, forward and backward, one workgroup against row groups:
+// H 16, B 4, T 64 216 and 276 us; at 4096 products H 32, B 4, T 16 96 and
+// 100, H 64, B 1, T 16 103 and 101; then H 33, B 5, T 40 225 and 199; H 64, B
+// 4, T 16 140 and 104; H 16, B 64, T 64 451 and 289; H 64, B 32, T 100 2963
+// and 427.
+constexpr int64_t kSmallProducts = 4096;
+bool small_pays(const janus_lstm_desc& d) { return int64_t(d.B) * d.H * d.H <= kSmallProducts; }
 bool use_persistent(const janus_lstm_desc& d) {
     if (env_is("JANUS_PERSIST", '0')) return false;
     const DeviceInfo info = device_info();
     if (info.cus <= 0) return false;
-    if (d.dtype == JANUS_F32) return !use_small(d) && xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
+    if (d.dtype == JANUS_F32)
+        return !(use_small(d) && small_pays(d)) && xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
     if (d.dtype != JANUS_BF16 || d.H % 8 != 0) return false;
     return persist_fwd_slices(d) > 0 && persist_bwd_slices(d) > 0;
 }
@@ -881,8 +892,8 @@ size_t small_bwd_lds(const janus_lstm_desc& d) {
     return sizeof(float) * (size_t(d.H) * (4 * d.H + small_bwd_split(d)) + size_t(11) * d.B * d.H);
 }
 
-// The one-workgroup recurrence replaces the per-step kernels (it is never
-// taken where the persistent path applies) when every cell has a thread
+// The one-workgroup recurrence replaces the per-step kernels, and the
+// persistent path where small_pays says so, when every cell has a thread
 // slot and Wh (float32), the state and dG fit one workgroup's LDS.
 // JANUS_SMALL=0 switches it off.
 bool use_small(const janus_lstm_desc& d) {

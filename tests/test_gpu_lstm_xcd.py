@@ -82,6 +82,25 @@ def test_nan_rows_do_not_stall(dtype):
     assert np.array_equal(g["y"][:, rest], clean["y"][:, rest])
 
 
+@pytest.mark.parametrize("H,B,groups", [(16, 16, False), (64, 1, False), (65, 1, True), (16, 17, True), (1, 2048, False),
+                                        (3, 700, True), (64, 40, True)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_small_float32_on_both_sides_of_the_rule(H, B, groups, ragged):
+    """float32 problems of up to 4096 products per step run in one workgroup,
+    larger ones that would fit one too in row groups."""
+    from paper_1812_01329_amd import janus as J
+    w = _lstm("mse", "f32", L=2, I=24, H=H, B=B, T=7, lengths=_ragged(B, 7, H + B) if ragged else None, seed=H, h0=True,
+              P=16)
+    print(f"[xcd-small] H={H} B={B} ragged={ragged}", flush=True)
+    J.janus_trace_begin()
+    step, g = _run(w)
+    labels = {r["label"] for r in J.janus_trace_end()}
+    assert ("lstm_fwd_small" in labels, "lstm_bwd_small" in labels) == (not groups, not groups), labels
+    rep = _report(step)
+    assert rep["timed_out"] == 0 and (rep["bwd_groups"] > 0) == groups
+    compare_lstm(g, oracle_steps.lstm_step(w), "f32")
+
+
 def test_two_threads_on_two_streams():
     """Kernels whose workgroups wait for each other take turns across
     streams: two host threads, each on its own stream, give the bits of the
