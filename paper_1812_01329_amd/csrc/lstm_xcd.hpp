@@ -495,13 +495,19 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
         cb[c] = own[c] && a.perm ? a.perm[cr[c]] : cr[c];
         creg[c] = own[c] ? a.Cs[int64_t(cr[c]) * a.ldh + cu[c]] : 0.f;
     }
+    // Gate rows of a step are addressed from the group's first row on, so that
+    // their 32-bit offsets hold for any batch: the bytes of this group's rows
+    // among the first `act`, and a cell's offset in them.
+    auto gate_rows_bytes = [&](int act) {
+        return uint32_t(min(max(act - row0, 0), 16 * RT)) * uint32_t(a.ldg) * uint32_t(sizeof(T));
+    };
+    auto gate_off = [&](int c) {
+        return (uint32_t(cr[c] - row0) * uint32_t(a.ldg) + 4u * uint32_t(cu[c])) * uint32_t(sizeof(T));
+    };
     auto prefetch = [&](int act, int64_t off) {
-        const auto rs = make_rsrc(a.XG + off * a.ldg, uint32_t(act) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
+        const auto rs = make_rsrc(a.XG + (off + row0) * a.ldg, gate_rows_bytes(act));
 #pragma unroll
-        for (int c = 0; c < CPW; ++c)
-            xg[c].load(rs, own[c] && cr[c] < act
-                               ? (uint32_t(cr[c]) * uint32_t(a.ldg) + 4u * uint32_t(cu[c])) * uint32_t(sizeof(T))
-                               : kOutOfRange);
+        for (int c = 0; c < CPW; ++c) xg[c].load(rs, own[c] && cr[c] < act ? gate_off(c) : kOutOfRange);
     };
     const int steps = a.steps[g];
     const int ntiles = a.groups * RT;
@@ -531,13 +537,13 @@ __global__ __launch_bounds__(kThreads) void lstm_fwd_xcd(FwdArgs<T> a) {
     uint32_t hw[CPW][2];   // bf16: h of the four units of lanes lr, lr + 16, ..
     auto store_results = [&](int t, int64_t off, int rows, int rows_next) {
         const int64_t nrow = int64_t(a.B) + off;
-        const auto rgs = make_rsrc(a.Gs + off * a.ldg, uint32_t(rows) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
+        const auto rgs = make_rsrc(a.Gs + (off + row0) * a.ldg, gate_rows_bytes(rows));
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
             if (!(own[c] && cr[c] < rows)) continue;
             const int u = cu[c], r = cr[c];
             a.Cs[(nrow + r) * a.ldh + u] = creg[c];
-            gs[c].store(rgs, (uint32_t(r) * uint32_t(a.ldg) + 4u * uint32_t(u)) * uint32_t(sizeof(T)));
+            gs[c].store(rgs, gate_off(c));
             T* ydst = a.y ? a.y + (int64_t(t) * a.B + cb[c]) * H + u : nullptr;
             if constexpr (L::EPL == 8) {
                 if (lq == 0) {   // H is a multiple of 8, so the four units are cells
@@ -795,17 +801,23 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
         for (int e = 0; e < 4; ++e) dbs[c][e] = 0.f;
         so[c] = uint32_t(L::index(g * RT + p / MT, a.nkg, ln & 15, 4 * cu[c])) * uint32_t(sizeof(T));
     }
+    // gate rows from the group's first row on, as in the forward
+    auto gate_rows_bytes = [&](int act) {
+        return uint32_t(min(max(act - row0, 0), 16 * RT)) * uint32_t(a.ldg) * uint32_t(sizeof(T));
+    };
+    auto gate_off = [&](int c) {
+        return (uint32_t(cr[c] - row0) * uint32_t(a.ldg) + 4u * uint32_t(cu[c])) * uint32_t(sizeof(T));
+    };
     // operands of the cells that do not depend on dh, one step ahead
     Gates<T> gt_[CPT];
     float cpv[CPT], cnv[CPT], dyv[CPT];
     auto prefetch = [&](int t, int act, int act_next, int act_prev, int64_t off_t) {
         const int64_t prev_base = t == 0 ? 0 : int64_t(a.B) + off_t - act_prev;
-        const auto rgs = make_rsrc(a.Gs + off_t * a.ldg, uint32_t(act) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
+        const auto rgs = make_rsrc(a.Gs + (off_t + row0) * a.ldg, gate_rows_bytes(act));
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
             const bool cell = own[c] && cr[c] < act;
-            gt_[c].load(rgs, cell ? (uint32_t(cr[c]) * uint32_t(a.ldg) + 4u * uint32_t(cu[c])) * uint32_t(sizeof(T))
-                                  : kOutOfRange);
+            gt_[c].load(rgs, cell ? gate_off(c) : kOutOfRange);
             cpv[c] = cell ? a.Cs[(prev_base + cr[c]) * a.ldh + cu[c]] : 0.f;
             // c_t is carried from the later step where the row ran there
             cnv[c] = cell && cr[c] >= act_next ? a.Cs[(a.B + off_t + cr[c]) * a.ldh + cu[c]] : 0.f;
@@ -938,8 +950,8 @@ __global__ __launch_bounds__(kThreads) void lstm_bwd_xcd(BwdArgs<T> a) {
             if (!(own[c] && cr[c] < act)) continue;
             const int u = cu[c], r = cr[c];
             if (a.G) {
-                const auto rg = make_rsrc(a.G + off_t * a.ldg, uint32_t(act) * uint32_t(a.ldg) * uint32_t(sizeof(T)));
-                dg[c].store(rg, (uint32_t(r) * uint32_t(a.ldg) + 4u * uint32_t(u)) * uint32_t(sizeof(T)));
+                const auto rg = make_rsrc(a.G + (off_t + row0) * a.ldg, gate_rows_bytes(act));
+                dg[c].store(rg, gate_off(c));
             }
             if constexpr (L::EPL == 8) {
                 if (a.GT) {

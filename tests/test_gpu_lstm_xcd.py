@@ -11,7 +11,7 @@ import pytest
 
 from oracle import steps as oracle_steps
 from paper_1812_01329_amd import workloads as wl
-from tests.parity import compare_lstm
+from tests.parity import TOL, compare_lstm
 from tests.test_gpu_parity import _lstm, _run
 
 pytestmark = pytest.mark.gpu
@@ -99,6 +99,57 @@ def test_small_float32_on_both_sides_of_the_rule(H, B, groups, ragged):
     rep = _report(step)
     assert rep["timed_out"] == 0 and (rep["bwd_groups"] > 0) == groups
     compare_lstm(g, oracle_steps.lstm_step(w), "f32")
+
+
+@pytest.mark.parametrize("dtype,B", [("f32", (1 << 19) + 17)])
+def test_step_of_more_than_4_gib_of_gate_rows(dtype, B):
+    """One step of a batch whose gate rows (B x 4H) pass 4 GiB, every row
+    against the same step in float64."""
+    import torch
+
+    from paper_1812_01329_amd import janus as J
+    H, I = 512, 8
+    dt, cdt = (torch.float32, J.F32) if dtype == "f32" else (torch.bfloat16, J.BF16)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    rnd = lambda *s, k=1.0: (torch.randn(*s, generator=g, device="cuda") * k).to(dt)
+    x, dy = rnd(1, B, I), rnd(1, B, H)
+    Wx, Wh, b = rnd(4 * H, I, k=0.3), rnd(4 * H, H, k=0.04), rnd(4 * H, k=0.1)
+    h0 = rnd(1, B, H, k=0.5).float()
+    y, dx = torch.zeros_like(dy), torch.zeros_like(x)
+    dh0 = torch.zeros_like(h0)
+    dWx, dWh, db = (torch.zeros(t.shape, device="cuda") for t in (Wx, Wh, b))
+    d = J.LstmDesc(1, I, H, B, 1, cdt)
+    ws = torch.empty(J.janus_lstm_workspace_bytes(1, I, H, B, 1, cdt), dtype=torch.uint8, device="cuda")
+    print(f"[xcd-4gib] {dtype} B={B} ws={ws.numel() >> 20} MiB", flush=True)
+    J.janus_lstm_seq_fwd(d, x, None, [Wx], [Wh], [b], h0, None, y, None, None, ws)
+    J.janus_lstm_seq_bwd(d, x, None, [Wx], [Wh], ws, dy, None, None, dx, dh0, None, [dWx], [dWh], [db])
+    assert J.janus_lstm_device_report(d, ws)["timed_out"] == 0
+    t = TOL[dtype]
+
+    def near(name, a, ref, tol):
+        e = float((a.double() - ref).abs().max() / ref.abs().max())
+        assert e <= tol, f"{name}: relative error {e:.3e} > {tol:.1e}"
+
+    X, H0, U, V = x.double()[0], h0[0], Wx.double(), Wh.double()
+    sWx, sWh, sb = torch.zeros_like(U), torch.zeros_like(V), torch.zeros(4 * H, dtype=torch.float64, device="cuda")
+    for r in range(0, B, 1 << 16):
+        q = slice(r, min(r + (1 << 16), B))
+        hp = H0[q].double()
+        i, f, gg, o = (X[q] @ U.T + hp @ V.T + b.double()).chunk(4, 1)
+        i, gg, o = i.sigmoid(), gg.tanh(), o.sigmoid()
+        c = i * gg
+        tau = c.tanh()
+        near(f"y[{r}]", y[0, q], o * tau, t["out"])
+        dh = dy[0, q].double()
+        dc = dh * o * (1 - tau * tau)
+        da = torch.cat([dc * gg * i * (1 - i), torch.zeros_like(dc), dc * i * (1 - gg * gg), dh * tau * o * (1 - o)], 1)
+        near(f"dx[{r}]", dx[0, q], da @ U, t["grad"])
+        near(f"dh0[{r}]", dh0[0, q], da @ V, t["grad"])
+        sWx += da.T @ X[q]
+        sWh += da.T @ hp
+        sb += da.sum(0)
+    for k, a, ref in (("dWx", dWx, sWx), ("dWh", dWh, sWh), ("db", db, sb)):
+        near(k, a, ref, t["grad"])
 
 
 def test_two_threads_on_two_streams():
