@@ -526,7 +526,9 @@ struct RnnFwd {
     TreeSync* sync;
 };
 // Set-up of the forward: leaf rows of hx (and of h_root for a leaf that is a
-// root), empty rows of the internal nodes, counters and error flag zero.
+// root), empty rows of the internal nodes, counters and error flag zero.  A
+// word vector's NaN of the pattern's bits is stored as another NaN, so that no
+// wait takes the leaf for one not stored yet.
 static __global__ __launch_bounds__(256) void rnn_fwd_init_kernel(int N, int M0, int H, const int32_t* lword,
                                                                   const int32_t* rootk, const float* emb, float* hx,
                                                                   int64_t ldh, float* h_root, TreeSync* s) {
@@ -537,7 +539,7 @@ static __global__ __launch_bounds__(256) void rnn_fwd_init_kernel(int N, int M0,
     for (int64_t i = i0; i < int64_t(M0) * ldh; i += stride) {
         const int p = int(i / ldh), j = int(i % ldh);
         const float v = j < H ? emb[int64_t(lword[p]) * H + j] : 0.f;
-        hx[i] = v;
+        hx[i] = __uint_as_float(not_empty(__float_as_uint(v)));
         if (j < H && rootk[p] >= 0) h_root[int64_t(rootk[p]) * H + j] = v;
     }
 }

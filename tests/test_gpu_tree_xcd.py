@@ -135,3 +135,34 @@ def test_childsum_without_shared_l2(H, monkeypatch):
     g1 = _childsum(w)
     for k in ("h_root", "dW", "dU", "db", "demb"):
         assert np.array_equal(g0[k], g1[k]), k
+
+
+@pytest.mark.parametrize("model", ["treelstm", "treernn", "childsum"])
+def test_nan_word_vectors_do_not_stall(model):
+    """A word vector holding a NaN of the bit pattern that marks a row not yet
+    stored: its tree's root is NaN, the other trees keep their bits."""
+    from paper_1812_01329_amd import janus as J
+    make = {"treelstm": lambda: wl.sst_treelstm(n_trees=9, E=20, H=72, V=40, seed=3),
+            "treernn": lambda: wl.sst_treernn(n_trees=9, H=72, V=40, seed=3),
+            "childsum": lambda: wl.sst_childsum(n_trees=9, E=20, H=72, V=40, seed=3)}[model]
+    report = {"treelstm": J.janus_treelstm_device_report, "treernn": J.janus_treernn_device_report,
+              "childsum": J.janus_childsum_device_report}[model]
+    w = make()
+    word = w.trees.word
+    word[word == 39] = 0
+    n = int(w.trees.root[2])
+    if model == "childsum":
+        while w.trees.child_offsets[n] < w.trees.child_offsets[n + 1]:
+            n = int(w.trees.children[w.trees.child_offsets[n]])
+    else:
+        while w.trees.left[n] >= 0:
+            n = int(w.trees.left[n])
+    word[n] = 39
+    _, clean = _run(w)
+    w.emb.view(np.uint32)[39, 5] = 0xffffffff
+    print(f"[tree-xcd-nan] {model}", flush=True)
+    step, g = _run(w)
+    assert report(step.desc, w.trees, step.ws) == 0
+    assert np.isnan(g["h_root"][2]).all()
+    rest = [k for k in range(9) if k != 2]
+    assert np.array_equal(g["h_root"][rest], clean["h_root"][rest])
