@@ -45,7 +45,8 @@ constexpr int kRows = 16;        // nodes of a tile
 
 // One group's part of the launch: nodes by position (leaves first, then the
 // internal nodes; both contiguous per group), its tiles in order.  The tiles
-// [t0, t1) start with the `leaf_tiles` tiles of leaves.
+// [t0, t1) start with the `leaf_tiles` tiles of leaves.  A batch of a few large
+// trees in several launches leaves groups without trees (t0 == t1).
 struct Group {
     int leaf0, nleaf, int0, nint;
     int t0, t1, leaf_tiles, pad;
@@ -206,6 +207,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     const int H = a.H, E = a.E, v0 = m * U;
     const int KH = (H + 15) / 16;   // k-groups of one child
 
@@ -377,6 +379,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     float* dhl = sm + 2 * C::RED;                          // [nodes][U]
     float* dcl = dhl + int64_t(gr.nleaf + gr.nint) * U;    // [nodes][U]
     const int H = a.H, K = 5 * H, v0 = m * U;
@@ -558,6 +561,7 @@ static __global__ __launch_bounds__(kThreads) void treernn_fwd_xcd(RnnFwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     const int H = a.H, v0 = m * U, KH = (H + 15) / 16;
     const int kw0 = wave * 2 * KH / kWaves, nj = (wave + 1) * 2 * KH / kWaves - kw0;
     uint4 w[J];
@@ -670,6 +674,7 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     const int first = gr.t0 + gr.leaf_tiles;
     if (first >= gr.t1) return;
     const int H = a.H, v0 = m * U, nk = (H + 15) / 16;
@@ -833,6 +838,7 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     f32x4_t* gl = reinterpret_cast<f32x4_t*>(sm + 3 * C::RED);                              // [nodes][U] gates
     float* cl = sm + 3 * C::RED + int64_t(gr.nleaf + gr.nint) * 4 * U;                     // [nodes][U]
     const int H = a.H, E = a.E, v0 = m * U;
@@ -1034,6 +1040,7 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
     const bool local = __builtin_amdgcn_readfirstlane(pl.local) != 0;
     if (g < 0) return;
     const Group gr = a.group[g];
+    if (gr.t0 >= gr.t1) return;   // a group without trees
     const int H = a.H, K = 4 * H, v0 = m * U, nk = (K + 15) / 16;
     const int kw0 = wave * nk / kWaves, nj = (wave + 1) * nk / kWaves - kw0;
     uint4 w[J];

@@ -13,12 +13,18 @@ from tests.test_gpu_parity import _run
 pytestmark = pytest.mark.gpu
 
 
-def _treelstm(w):
+def _launches(recs, model):
+    """Launches of the forward's and the backward's level program."""
+    n = {r["label"]: r["launches"] for r in recs}
+    assert f"{model}_bwd_tail" in n, n
+    return n[f"{model}_fwd_persistent"], n[f"{model}_bwd_persistent"]
+
+
+def _treelstm(w, parts=1):
     from paper_1812_01329_amd import janus as J
     J.janus_trace_begin()
     step, g = _run(w)
-    labels = {r["label"] for r in J.janus_trace_end()}
-    assert {"treelstm_fwd_persistent", "treelstm_bwd_persistent", "treelstm_bwd_tail"} <= labels, labels
+    assert _launches(J.janus_trace_end(), "treelstm") == (parts, parts)
     assert J.janus_treelstm_device_report(step.desc, w.trees, step.ws) == 0
     r = oracle_steps.tree_step(w)
     t = TOL["f32"]
@@ -40,7 +46,7 @@ def test_treelstm_several_launches():
     """A group's cells keep dh and dc of every node in LDS, so a large batch
     runs in parts."""
     print("[tree-xcd] parts", flush=True)
-    _treelstm(wl.sst_treelstm(n_trees=300, E=16, H=260, V=100, min_leaves=25, max_leaves=31, seed=14))
+    _treelstm(wl.sst_treelstm(n_trees=300, E=16, H=260, V=100, min_leaves=25, max_leaves=31, seed=14), parts=3)
 
 
 @pytest.mark.parametrize("H", [29, 200])
@@ -54,12 +60,11 @@ def test_treelstm_without_shared_l2(H, monkeypatch):
         assert np.array_equal(g0[k], g1[k]), k
 
 
-def _treernn(w):
+def _treernn(w, parts=1):
     from paper_1812_01329_amd import janus as J
     J.janus_trace_begin()
     step, g = _run(w)
-    labels = {r["label"] for r in J.janus_trace_end()}
-    assert {"treernn_fwd_persistent", "treernn_bwd_persistent", "treernn_bwd_tail"} <= labels, labels
+    assert _launches(J.janus_trace_end(), "treernn") == (parts, parts)
     assert J.janus_treernn_device_report(step.desc, w.trees, step.ws) == 0
     r = oracle_steps.treernn_step(w)
     t = TOL["f32"]
@@ -77,7 +82,7 @@ def test_treernn_widths(H, n_trees):
 
 def test_treernn_several_launches():
     print("[rnn-xcd] parts", flush=True)
-    _treernn(wl.sst_treernn(n_trees=500, H=300, V=100, min_leaves=35, max_leaves=41, seed=14))
+    _treernn(wl.sst_treernn(n_trees=500, H=300, V=100, min_leaves=35, max_leaves=41, seed=14), parts=3)
 
 
 def test_treernn_without_shared_l2(monkeypatch):
@@ -90,15 +95,18 @@ def test_treernn_without_shared_l2(monkeypatch):
         assert np.array_equal(g0[k], g1[k]), k
 
 
-def _childsum(w, persistent=True):
+def _childsum(w, persistent=True, parts=1):
     from paper_1812_01329_amd import janus as J
     from paper_1812_01329_amd.train_step import make_step
     step = make_step(w)
     J.janus_trace_begin()
     step.run()
     g = step.results()
-    labels = {r["label"] for r in J.janus_trace_end()}
-    assert ({"childsum_fwd_persistent", "childsum_bwd_persistent", "childsum_bwd_tail"} <= labels) == persistent, labels
+    recs = J.janus_trace_end()
+    if persistent:
+        assert _launches(recs, "childsum") == (parts, parts)
+    else:
+        assert not any(r["label"].endswith("_persistent") for r in recs), recs
     assert J.janus_childsum_device_report(step.desc, w.trees, step.ws) == 0
     r = oracle_steps.childsum_step(w)
     t = TOL["f32"]
@@ -117,7 +125,7 @@ def test_childsum_widths(H, E, n_trees):
 
 def test_childsum_several_launches():
     print("[childsum-xcd] parts", flush=True)
-    _childsum(wl.sst_childsum(n_trees=300, E=16, H=300, V=100, min_nodes=35, max_nodes=45, seed=14))
+    _childsum(wl.sst_childsum(n_trees=300, E=16, H=300, V=100, min_nodes=35, max_nodes=45, seed=14), parts=5)
 
 
 def test_childsum_tree_past_the_groups_room_runs_levels():
@@ -135,6 +143,19 @@ def test_childsum_without_shared_l2(H, monkeypatch):
     g1 = _childsum(w)
     for k in ("h_root", "dW", "dU", "db", "demb"):
         assert np.array_equal(g0[k], g1[k]), k
+
+
+@pytest.mark.parametrize("model", ["treelstm", "treernn", "childsum"])
+def test_groups_without_trees(model):
+    """Nine trees of which no two fit one group, eight groups a launch: two
+    launches, seven groups of them without a tree."""
+    print(f"[tree-xcd-empty] {model}", flush=True)
+    if model == "treelstm":
+        _treelstm(wl.sst_treelstm(n_trees=9, E=16, H=300, V=50, sizes=[300] * 9, seed=6), parts=2)
+    elif model == "treernn":
+        _treernn(wl.sst_treernn(n_trees=9, H=300, V=50, sizes=[600] * 9, seed=6), parts=2)
+    else:
+        _childsum(wl.sst_childsum(n_trees=9, E=16, H=300, V=50, sizes=[200] * 9, seed=6), parts=2)
 
 
 @pytest.mark.parametrize("model", ["treelstm", "treernn", "childsum"])
