@@ -20,6 +20,17 @@
  *    stream) and returns without synchronising; device faults surface at the
  *    caller's next synchronisation.  Calls are re-entrant given distinct
  *    workspaces.
+ *  - The LSTM and tree calls launch kernels whose workgroups wait for each
+ *    other's results, so all of a kernel's workgroups (up to one per CU) must
+ *    run at once.  The waits are bounded (a tenth of a second and more); one
+ *    that runs out makes the kernels drain, leaves the outputs undefined and
+ *    is reported by the call's *_device_report.  Launches of direct calls on
+ *    several streams of a device are ordered by the library where they do not
+ *    fit the device together.  What it cannot order: calls replayed from
+ *    captured graphs (do not replay two graphs with such calls, or one beside
+ *    direct calls on another stream, at the same time on one device) and the
+ *    caller's own kernels (one that holds CUs for longer than the bound while
+ *    such a kernel waits for them makes it run out).
  *  - Workspaces are caller-allocated device memory of at least the size
  *    returned by the matching *_workspace_bytes function, 256-byte aligned.
  *    The forward call stores the values its backward needs there; the

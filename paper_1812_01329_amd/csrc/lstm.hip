@@ -991,10 +991,8 @@ janus_status persistent_launch(K kernel, int blocks, size_t smem, const A& args,
     JANUS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel),
                                                            persist::kThreads, smem));
     if (per_cu < 1 || int64_t(per_cu) * info.cus < blocks) return JANUS_ERR_UNSUPPORTED;
-    ResidentTurn turn(st);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(persist::kThreads), smem, st, args);
-    JANUS_LAUNCH_CHECK();
-    return JANUS_OK;
+    void* argv[] = {const_cast<A*>(&args)};
+    return resident_launch(reinterpret_cast<const void*>(kernel), blocks, persist::kThreads, smem, argv, st, info.cus);
 }
 
 janus_status launch_fwd_persistent(const janus_lstm_desc& d, int ns, persist::FwdArgs& a, double flops,

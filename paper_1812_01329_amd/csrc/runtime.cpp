@@ -1,6 +1,8 @@
 // Host runtime: pinned staging ring for schedule uploads, status strings.
 #include "runtime.hpp"
 
+#include <hip/hip_ext.h>
+
 #include <cstdio>
 #include <cstring>
 #include <deque>
@@ -127,19 +129,23 @@ janus_status upload_pieces(const UploadPiece* pieces, int n, hipStream_t stream)
 // ------------------------------------------------- kernels that need the chip
 namespace {
 
-struct Turn {
-    std::mutex mu;               // held from the wait to the record
-    bool used = false;           // `last` is set
-    bool shared = false;         // more than one stream has been seen
-    hipStream_t last = nullptr;
-    hipEvent_t ev = nullptr;     // after the last launch (once shared)
+// The resident launches of a stream.
+struct Resident {
+    const void* key = nullptr;   // the stream
+    hipEvent_t ev = nullptr;     // completion of the latest launch
+    int blocks = 0;              // most workgroups of its launches not known to be complete
+    bool waited = false;         // the launch being placed is ordered after it
+};
+struct ResidentDevice {
+    std::mutex mu;               // held from the wait to the launch
+    bool shared = false;         // a second stream has been seen: every launch has its event
+    hipStream_t first = nullptr; // the only stream so far
+    std::vector<Resident> used;
 };
 
 constexpr int kMaxDevices = 64;
-Turn& turn(int dev) {
-    static Turn t[kMaxDevices];
-    return t[dev];
-}
+constexpr unsigned kResidentEvent = hipEventDisableTiming | hipEventDisableSystemFence;   // orders, publishes nothing
+constexpr size_t kMaxResident = 32;   // streams kept before complete ones are dropped
 
 bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -150,38 +156,103 @@ bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-}  // namespace
+// Event calls made while another thread captures a stream in the global mode
+// would end that capture; in this scope they are this thread's own affair.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture() {
+        if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
 
-ResidentTurn::ResidentTurn(hipStream_t stream) : stream_(stream) {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices || capturing(stream)) {
-        (void)hipGetLastError();
-        return;
-    }
-    Turn& t = turn(dev);
-    t.mu.lock();
-    dev_ = dev;
-    bool ok = true;
-    if (t.used && t.last != stream) {
-        if (!t.shared) {
-            // first sight of a second stream: mark the end of the first one's work
-            ok = hipEventCreateWithFlags(&t.ev, hipEventDisableTiming) == hipSuccess;
-            t.shared = ok;
-            if (ok && !capturing(t.last)) ok = hipEventRecord(t.ev, t.last) == hipSuccess;
-        }
-        if (ok) ok = hipStreamWaitEvent(stream, t.ev, 0) == hipSuccess;
-    }
-    // a stream that is gone has nothing left to wait for
-    if (!ok) (void)hipGetLastError();
-    t.used = true;
-    t.last = stream;
+// hipStreamPerThread names another stream on each thread
+const void* stream_key(hipStream_t s) {
+    static thread_local char own;
+    return s == hipStreamPerThread ? static_cast<const void*>(&own) : static_cast<const void*>(s);
 }
 
-ResidentTurn::~ResidentTurn() {
-    if (dev_ < 0) return;
-    Turn& t = turn(dev_);
-    if (t.shared && hipEventRecord(t.ev, stream_) != hipSuccess) (void)hipGetLastError();
-    t.mu.unlock();
+}  // namespace
+
+janus_status resident_launch(const void* kernel, int blocks, int threads, size_t smem, void** args, hipStream_t stream,
+                             int cus) {
+    static ResidentDevice devices[kMaxDevices];
+    int dev = -1;
+    JANUS_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= kMaxDevices || capturing(stream)) {
+        JANUS_HIP(hipLaunchKernel(kernel, dim3(blocks), dim3(threads), args, smem, stream));
+        return JANUS_OK;
+    }
+    ResidentDevice& d = devices[dev];
+    std::lock_guard<std::mutex> lock(d.mu);
+    const RelaxedCapture relaxed;
+    const void* key = stream_key(stream);
+    if (!d.shared) {
+        if (stream != hipStreamPerThread && (d.used.empty() || d.used[0].key == key)) {
+            if (d.used.empty()) {
+                d.used.push_back(Resident());
+                d.used[0].key = key;
+                d.first = stream;
+            }
+            d.used[0].blocks = cus;
+            JANUS_HIP(hipLaunchKernel(kernel, dim3(blocks), dim3(threads), args, smem, stream));
+            return JANUS_OK;
+        }
+        if (!d.used.empty()) {   // mark the end of the first stream's work
+            Resident& r = d.used[0];
+            JANUS_HIP(hipEventCreateWithFlags(&r.ev, kResidentEvent));
+            if (capturing(d.first) || hipEventRecord(r.ev, d.first) != hipSuccess) {
+                (void)hipGetLastError();   // gone, or now a capture
+                r.blocks = 0;
+            }
+        }
+        d.shared = true;
+    }
+    // The dispatcher deals workgroups to the 8 XCDs in turn, so a launch takes
+    // as many CUs of each: counted in whole rounds.
+    const int need = (blocks + 7) / 8 * 8;
+    int self = -1, together = need;
+    for (int i = 0; i < int(d.used.size()); ++i) {
+        d.used[i].waited = false;
+        if (d.used[i].key == key) self = i;
+        else together += d.used[i].blocks;
+    }
+    // what does not fit beside this launch is complete or waited for, the largest first
+    while (together > cus) {
+        Resident* most = nullptr;
+        for (int i = 0; i < int(d.used.size()); ++i) {
+            Resident& r = d.used[i];
+            if (i != self && !r.waited && r.blocks > 0 && (!most || r.blocks > most->blocks)) most = &r;
+        }
+        if (!most) break;
+        together -= most->blocks;
+        if (hipEventQuery(most->ev) == hipSuccess) {
+            most->blocks = 0;
+            continue;
+        }
+        (void)hipGetLastError();
+        JANUS_HIP(hipStreamWaitEvent(stream, most->ev, 0));
+        most->waited = true;   // (it may still run beside launches of a third stream)
+    }
+    if (self < 0) {
+        // a stream of a launch that is complete gives its place to this one
+        for (int i = 0; i < int(d.used.size()) && self < 0; ++i)
+            if (d.used[i].blocks == 0 || (d.used.size() >= kMaxResident && hipEventQuery(d.used[i].ev) == hipSuccess))
+                self = i;
+        (void)hipGetLastError();
+        if (self < 0) {
+            Resident r;
+            JANUS_HIP(hipEventCreateWithFlags(&r.ev, kResidentEvent));
+            d.used.push_back(r);
+            self = int(d.used.size()) - 1;
+        }
+        d.used[self].key = key;
+        d.used[self].blocks = 0;
+    }
+    Resident& r = d.used[self];
+    JANUS_HIP(hipExtLaunchKernel(kernel, dim3(blocks), dim3(threads), args, smem, stream, nullptr, r.ev, 0));
+    r.blocks = r.blocks > need ? r.blocks : need;
+    return JANUS_OK;
 }
 
 // ------------------------------------------------------------------ tracing

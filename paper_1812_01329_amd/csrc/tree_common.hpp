@@ -75,10 +75,8 @@ inline janus_status tree_persistent_launch(K kernel, int blocks, size_t smem, co
     JANUS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel),
                                                            threads, smem));
     if (per_cu < 1 || int64_t(per_cu) * tree_dev().cus < blocks) return JANUS_ERR_UNSUPPORTED;
-    ResidentTurn turn(st);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), smem, st, args);
-    JANUS_LAUNCH_CHECK();
-    return JANUS_OK;
+    void* argv[] = {const_cast<A*>(&args)};
+    return resident_launch(reinterpret_cast<const void*>(kernel), blocks, threads, smem, argv, st, tree_dev().cus);
 }
 
 }  // namespace tpersist

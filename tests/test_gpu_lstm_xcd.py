@@ -187,3 +187,41 @@ def test_two_threads_on_two_streams():
         assert np.array_equal(s.results()[k], a), k
     for s in steps[:2]:
         assert _report(s)["timed_out"] == 0
+
+
+def test_many_streams_come_and_go():
+    """Streams that are destroyed right after a step, and more of them than
+    the library keeps in mind: small steps that fit the chip together, and
+    some that need it whole, all with the bits of the first run."""
+    import ctypes
+
+    import torch
+    from paper_1812_01329_amd.train_step import make_step
+    hip = ctypes.CDLL("libamdhip64.so")
+    ws = [_lstm("mse", "f32", L=1, I=24, H=72, B=9, T=5, seed=31, P=16),
+          _lstm("mse", "bf16", L=1, I=24, H=1024, B=128, T=5, seed=32, P=16),
+          wl.sst_treernn(n_trees=20, H=64, V=50, seed=33)]
+    steps = [make_step(w) for w in ws]
+    keys = ["y", "y", "h_root"]
+    for s in steps:
+        s.run()
+    want = [s.results()[k] for s, k in zip(steps, keys)]
+    print("[xcd-streams]", flush=True)
+    last = [None] * len(steps)   # a step's runs follow each other
+    for i in range(60):
+        j = 0 if i % 4 else 1 + i // 4 % 2
+        h = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(h), 1) == 0
+        st = torch.cuda.ExternalStream(h.value)
+        if last[j] is not None:
+            st.wait_event(last[j])
+        with torch.cuda.stream(st):
+            steps[j].run()
+        last[j] = torch.cuda.Event()
+        last[j].record(st)
+        assert hip.hipStreamDestroy(h) == 0
+    torch.cuda.synchronize()
+    for s, k, a in zip(steps, keys, want):
+        assert np.array_equal(s.results()[k], a), k
+    for s in steps[:2]:
+        assert _report(s)["timed_out"] == 0
