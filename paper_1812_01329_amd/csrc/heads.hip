@@ -13,6 +13,7 @@
 
 #include "device.hpp"
 #include "gemm_f32.hpp"
+#include "gemm_plan.hpp"
 #include "ops.hpp"
 
 namespace janus {
@@ -274,12 +275,12 @@ size_t head_gemm_scratch(janus_dtype dt, int rows, int H, int V) {
     g.dtype = dt;
     g.M = rows; g.N = V; g.K = H;
     g.lda = g.ldb = H;           // rows of no whole 16-byte chunks are copied
-    size_t m = gemm_scratch_bound(g);
+    size_t m = gemm_scratch_bound(g, GemmSize::kExact);
     g.N = H; g.K = V; g.b_t = true;
     g.lda = V; g.ldb = H;
-    m = std::max(m, gemm_scratch_bound(g));
+    m = std::max(m, gemm_scratch_bound(g, GemmSize::kExact));
     g.M = V; g.N = H; g.K = rows; g.a_t = true;
-    return std::max(m, gemm_scratch_bound(g));
+    return std::max(m, gemm_scratch_bound(g, GemmSize::kExact));
 }
 
 size_t carve_xent(const janus_xent_desc& d, janus_xent_op op, void* base, XentWs& w) {

@@ -35,6 +35,7 @@
 #include <vector>
 
 #include "device.hpp"
+#include "gemm_plan.hpp"
 #include "lstm_persist.hpp"
 #include "lstm_xcd.hpp"
 #include "ops.hpp"
@@ -185,20 +186,20 @@ size_t lstm_gemm_scratch(const janus_lstm_desc& d) {
         g.dtype = d.dtype;
         g.M = int(TB); g.N = 4 * d.H; g.K = Il;            // input projection
         g.a_idx = reinterpret_cast<const int32_t*>(16);
-        m = std::max(m, gemm_scratch_bound(g, true));
+        m = std::max(m, gemm_scratch_bound(g, GemmSize::kUpToM));
         g = GemmDesc();
         g.dtype = d.dtype;
         g.M = 4 * d.H; g.N = Il; g.K = int(TB);             // dWx, dWh (dG^T in place, rows transposed)
         g.a_zero_pad = true;
         g.b_t = true;
-        m = std::max(m, gemm_scratch_bound(g));
+        m = std::max(m, gemm_scratch_bound(g, GemmSize::kUpToK));
         g.N = d.H;
-        m = std::max(m, gemm_scratch_bound(g));
+        m = std::max(m, gemm_scratch_bound(g, GemmSize::kUpToK));
         g = GemmDesc();
         g.dtype = d.dtype;
         g.M = int(TB); g.N = Il; g.K = 4 * d.H;             // dX = dG Wx
         g.b_t = true;
-        m = std::max(m, gemm_scratch_bound(g, true));
+        m = std::max(m, gemm_scratch_bound(g, GemmSize::kUpToM));
     }
     return m;
 }

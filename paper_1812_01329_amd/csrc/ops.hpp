@@ -38,19 +38,18 @@ struct GemmDesc {
     // (a_t / b_t false only) rows of A / B hold zeros from K up to the next
     // multiple of 8, so they may be read in whole 16-byte chunks
     bool a_zero_pad = false, b_zero_pad = false;
-    // device scratch for transposed operand copies and split-K partials,
-    // gemm_scratch_bytes(g) bytes; with less, a slower path that needs none
-    // is taken
+    // device scratch for transposed operand copies and split-K partials
+    // (gemm_scratch_bound); with less, a slower path that needs none is taken
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
 };
 
 janus_status gemm(const GemmDesc& g, hipStream_t stream);
-size_t gemm_scratch_bytes(const GemmDesc& g);
-// scratch enough for the contraction with any K up to g.K and any
-// gathered-row count (for sizing workspaces in advance); `fewer_rows`: also
-// with any M up to g.M
-size_t gemm_scratch_bound(const GemmDesc& g, bool fewer_rows = false);
+// What is known of a contraction when its scratch is reserved: its size, its
+// size with any K up to g.K (operands stored k-major, or with rows zero-padded
+// past K), or with any M up to g.M.  gemm_scratch_bound(g, size) bytes are
+// enough, with any gathered-row count.
+enum class GemmSize { kExact, kUpToK, kUpToM };
 
 // Projection + MSE in one pass (bf16, K-contiguous h [M, K] and W [N, K]):
 // d = h W^T + bias - tgt, dY = scale d (bf16, [M, N]), part[0, mt * nt) =
