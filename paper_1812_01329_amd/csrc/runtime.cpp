@@ -32,7 +32,9 @@ class PinnedRing {
   public:
     static constexpr size_t kCapacity = size_t(64) << 20;
 
-    janus_status put(void* dst, const void* src, size_t bytes, hipStream_t stream) {
+    // `fill(p)` writes the `bytes` bytes to copy to dst
+    template <class F>
+    janus_status put(void* dst, size_t bytes, hipStream_t stream, F fill) {
         std::lock_guard<std::mutex> lock(mu_);
         if (!base_) {
             const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&base_), kCapacity, hipHostMallocDefault);
@@ -55,7 +57,7 @@ class PinnedRing {
                 ++it;
             }
         }
-        std::memcpy(base_ + head_, src, bytes);
+        fill(base_ + head_);
         JANUS_HIP(hipMemcpyAsync(dst, base_ + head_, bytes, hipMemcpyHostToDevice, stream));
         hipEvent_t ev;
         if (!free_events_.empty()) {
@@ -96,7 +98,7 @@ PinnedRing& ring() {
 
 janus_status upload(void* dst_dev, const void* src_host, size_t bytes, hipStream_t stream) {
     if (bytes == 0) return JANUS_OK;
-    return ring().put(dst_dev, src_host, bytes, stream);
+    return ring().put(dst_dev, bytes, stream, [&](char* p) { std::memcpy(p, src_host, bytes); });
 }
 
 janus_status upload_pieces(const UploadPiece* pieces, int n, hipStream_t stream) {
@@ -119,11 +121,18 @@ janus_status upload_pieces(const UploadPiece* pieces, int n, hipStream_t stream)
         }
         return JANUS_OK;
     }
-    std::vector<char> image(span, 0);
-    for (int i = 0; i < n; ++i)
-        if (pieces[i].bytes) std::memcpy(image.data() + (static_cast<char*>(pieces[i].dst) - base), pieces[i].src,
-                                         pieces[i].bytes);
-    return upload(base, image.data(), span, stream);
+    if (span == 0) return JANUS_OK;
+    return ring().put(base, span, stream, [&](char* p) {
+        size_t at = 0;
+        for (int i = 0; i < n; ++i) {
+            if (!pieces[i].bytes) continue;
+            const size_t off = size_t(static_cast<char*>(pieces[i].dst) - base);
+            std::memset(p + at, 0, off - at);
+            std::memcpy(p + off, pieces[i].src, pieces[i].bytes);
+            at = off + pieces[i].bytes;
+        }
+        std::memset(p + at, 0, span - at);
+    });
 }
 
 // ------------------------------------------------- kernels that need the chip
