@@ -284,9 +284,13 @@ janus_status janus_treelstm_fwd(const janus_treelstm_desc* d, const janus_tree_b
  *          c is zero).
  *  demb [V, E], dW [5H, E], dU [5H, 2H], db [5H]: float32, overwritten
  *          (rows of demb for words not in the batch are 0).
- * With H up to 384 each direction is one launch of co-resident workgroups
- * that runs every level of groups of whole trees (the waits for a level's
- * results are bounded; see janus_treelstm_device_report).
+ * With H up to 384 and E up to 512 each direction is one launch of co-resident
+ * workgroups that runs every level of groups of whole trees (the waits for a
+ * level's results are bounded; see janus_treelstm_device_report).  Batches of
+ * more nodes than the groups hold, and trees so large that the other groups
+ * would wait for them, take a few such launches (at most 16; the trees then run
+ * in pieces, subtrees first); wider models and larger batches run one level at a
+ * time.
  */
 janus_status janus_treelstm_bwd(const janus_treelstm_desc* d, const janus_tree_batch* t,
                                 const void* emb, const void* W, const void* U,
@@ -352,8 +356,8 @@ janus_status janus_treernn_bwd(const janus_treernn_desc* d, const janus_tree_bat
  * last forward (same d and t), as janus_treelstm_device_report: with H
  * up to 512 each direction is one launch of co-resident workgroups that runs
  * every level of groups of whole trees (Section 4.2.1 recursion, run level by
- * level); a bounded wait that ran out sets *timed_out = 1 and the call returns
- * JANUS_ERR_DEVICE (the results are then undefined).  The flag is cleared by
+ * level), or a few as for the TreeLSTM; a bounded wait that ran out sets
+ * *timed_out = 1 and the call returns JANUS_ERR_DEVICE (the results are then undefined).  The flag is cleared by
  * the next forward.  Errors: as janus_treernn_fwd's validation, or
  * INVALID_ARG for a NULL timed_out.
  */
@@ -425,9 +429,9 @@ janus_status janus_childsum_bwd(const janus_childsum_desc* d, const janus_nary_t
  * the last forward (same d and t), as janus_treelstm_device_report: with
  * H below 320 and E up to 512 each direction is one launch of co-resident
  * workgroups that runs every level of groups of whole trees (Section 4.2.1
- * recursion, run level by level); a bounded wait that ran out sets
- * *timed_out = 1 and the call returns JANUS_ERR_DEVICE (the results are then undefined).  The flag is
- * cleared by the next forward.  Errors: as janus_childsum_fwd's validation,
+ * recursion, run level by level), or a few as for the TreeLSTM; a bounded wait
+ * that ran out sets *timed_out = 1 and the call returns JANUS_ERR_DEVICE (the
+ * results are then undefined).  The flag is cleared by the next forward.  Errors: as janus_childsum_fwd's validation,
  * or INVALID_ARG for a NULL timed_out.
  */
 janus_status janus_childsum_device_report(const janus_childsum_desc* d, const janus_nary_tree_batch* t,

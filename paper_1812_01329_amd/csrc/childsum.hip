@@ -20,7 +20,7 @@
 // embedding gradient.
 //
 // H below 320: one launch each way over groups of trees per XCD
-// (tree_xcd.hpp).  Otherwise level by level, a cell kernel and a contraction
+// (tree_xcd.hpp), a few for large trees and batches.  Otherwise level by level, a cell kernel and a contraction
 // per level, with XW = X W^T + b over all nodes first.
 #include <algorithm>
 #include <vector>
@@ -56,11 +56,10 @@ struct CsWs {
     float* Ut = nullptr;         // [H x 4H]
     float* part = nullptr;
     int32_t* seg = nullptr;      // the nodes grouped by word, for the embedding gradient
-    // groups of trees per XCD (tree_xcd.hpp): the groups and their tiles (carved
-    // after the schedule arrays, so that one copy uploads both), the counters,
-    // and node rows padded to whole 128-byte lines
-    treex::Group* xgroup = nullptr;
-    treex::Tile* xtile = nullptr;    // [N]
+    // groups of trees per XCD (tree_xcd.hpp): the groups, followed by their
+    // tiles (carved after the schedule arrays, so that one copy uploads both),
+    // the counters, and node rows padded to whole 128-byte lines
+    treex::Group* xgroup = nullptr;  // the groups of every launch, then up to N tiles
     tpersist::TreeSync* tsync = nullptr;
     float* xl = nullptr;         // [N x ldx] inputs
     float* hx = nullptr;         // [N x ldh] h of every node
@@ -69,6 +68,7 @@ struct CsWs {
     float* Gtp = nullptr;        // [N x ld3]
     float* Fp = nullptr;         // [N x ldh]
     float* Cp = nullptr;         // [N x ldh]
+    float* dcx = nullptr;        // [N x ldh] dc of the roots of pieces of trees
     float* dxp = nullptr;        // [3][N x E] parts of the inputs' gradient
     float* tpart = nullptr;      // parts of dW and dU
     float* tsum = nullptr;       // parts of db
@@ -82,9 +82,7 @@ size_t carve_cs(const janus_treelstm_desc& d, int32_t N, void* base, CsWs& w) {
     w.pcoff = c.take<int32_t>(int64_t(N) + 1);
     w.pkids = c.take<int32_t>(N);
     w.rootk = c.take<int32_t>(N);
-    w.xgroup = reinterpret_cast<treex::Group*>(
-        c.take<int32_t>(std::min(treex::kGroupInts, sizeof(treex::Group) / 4 * (size_t(N) + treex::kMaxGroups))));
-    w.xtile = c.take<treex::Tile>(N);
+    w.xgroup = reinterpret_cast<treex::Group*>(c.take<char>(treex::kGroupBytes + size_t(N) * sizeof(treex::Tile)));
     w.tsync = c.take<tpersist::TreeSync>(1);
     w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));   // the nodes grouped by word
     const size_t mark = c.off;
@@ -115,6 +113,7 @@ size_t carve_cs(const janus_treelstm_desc& d, int32_t N, void* base, CsWs& w) {
     w.Gtp = c.take<float>(int64_t(N) * w.ld3);
     w.Fp = c.take<float>(int64_t(N) * w.ldh);
     w.Cp = c.take<float>(int64_t(N) * w.ldh);
+    w.dcx = c.take<float>(int64_t(N) * w.ldh);
     w.dxp = c.take<float>(int64_t(3) * N * E);
     w.tpart = c.take<float>(tail_part_floats(4 * H, E) + tail_part_floats(4 * H, H));
     w.tsum = c.take<float>(tail_sum_floats(N, 4 * H));
@@ -225,15 +224,16 @@ janus_status upload_cs(const NarySchedule& s, const CsWs& w, hipStream_t st) {
 // ------------------------------------------------- groups of trees per XCD
 // Four gates of 4 NT units per forward workgroup, 16 units of dh per backward
 // workgroup.  H below 320 (the forward's G rows of a group's nodes then still
-// leave room in the LDS for batches of a few hundred nodes per group), E up to
-// 512; off with JANUS_TREE_PERSIST=0.  Other sizes run level by level.
+// leave room in the LDS for a few hundred nodes per group; larger trees run in
+// pieces), E up to 512; off with JANUS_TREE_PERSIST=0.  Other sizes run level by level.
 struct CsPlan {
     bool on = false;
     int NT = 0, fwd_nu = 0, bwd_nu = 0;
     treex::Cut cut;
     size_t fwd_lds = 0, bwd_lds = 0;
-    // the schedule in the cut's order
-    std::vector<int32_t> word, coff, kids, rootk;
+    // the schedule in the cut's order (in cut.more)
+    int32_t *word = nullptr, *coff = nullptr, *kids = nullptr, *rootk = nullptr;
+    size_t nkids = 0;
 };
 size_t cs_fwd_lds(int NT, int nodes) {
     return NT == 1 ? treex::CsFwdCfg<1>::lds(nodes) : NT == 2 ? treex::CsFwdCfg<2>::lds(nodes) : treex::CsFwdCfg<3>::lds(nodes);
@@ -252,44 +252,54 @@ CsPlan cs_plan(const janus_treelstm_desc& d, const janus_nary_tree_batch* t, con
     p.bwd_nu = (d.H + treex::CsBwdCfg::U - 1) / treex::CsBwdCfg::U;
     const int capacity = treex::node_capacity(
         dev.lds, [&](int n) { return std::max(cs_fwd_lds(p.NT, n), treex::CsBwdCfg::lds(n)); });
-    // positions are by (level, id) already; a child belongs to its parent's tree
-    const int L = int(s.level_offsets.size()) - 1;
-    std::vector<int32_t> tree(N, 0), ident(N);
-    for (int32_t k = 0; k < t->num_trees; ++k) tree[s.rootpos[k]] = k;
-    for (int32_t q = N; q-- > 0;) {
-        ident[q] = q;
-        for (int32_t e = s.pcoff[q]; e < s.pcoff[q + 1]; ++e) tree[s.pkids[e]] = tree[q];
-    }
-    if (!treex::cut_batch(t->num_trees, N, ident, s.level_offsets, L, tree, std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut))
+    p.cut.take(N, size_t(4) * N + 1);
+    std::fill(p.cut.parent, p.cut.parent + N, -1);
+    for (int32_t q = 0; q < N; ++q)
+        for (int32_t e = s.pcoff[q]; e < s.pcoff[q + 1]; ++e) p.cut.parent[s.pkids[e]] = q;
+    if (!treex::cut_batch(N, s.level_offsets, int(s.level_offsets.size()) - 1,
+                          treex::cut_shape(dev, std::max(p.fwd_nu, p.bwd_nu), capacity), p.cut))
         return p;
     p.fwd_lds = cs_fwd_lds(p.NT, p.cut.most_nodes);
     p.bwd_lds = treex::CsBwdCfg::lds(p.cut.most_nodes);
-    p.word.resize(N);
-    p.rootk.resize(N);
-    p.coff.assign(N + 1, 0);
-    p.kids.reserve(N);
+    p.word = p.cut.more;
+    p.rootk = p.word + N;
+    p.kids = p.rootk + N;
+    p.coff = p.kids + N;
+    p.coff[0] = 0;
     for (int32_t q = 0; q < N; ++q) {
         const int32_t o = p.cut.order[q];
         p.word[q] = s.pword[o];
-        p.rootk[q] = s.rootk[o];
-        for (int32_t e = s.pcoff[o]; e < s.pcoff[o + 1]; ++e) p.kids.push_back(p.cut.pos[s.pkids[e]]);
-        p.coff[q + 1] = int32_t(p.kids.size());
+        p.rootk[q] = p.cut.split && p.cut.piece[o] ? treex::kPieceRoot : s.rootk[o];
+        for (int32_t e = s.pcoff[o]; e < s.pcoff[o + 1]; ++e) p.kids[p.nkids++] = p.cut.pos[s.pkids[e]];
+        p.coff[q + 1] = int32_t(p.nkids);
     }
     p.on = true;
     return p;
 }
-int cs_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
+treex::Tile* cs_tiles(const CsWs& w, const treex::Cut& c) {
+    return reinterpret_cast<treex::Tile*>(w.xgroup + c.group.size());
+}
 unsigned cs_fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
 int cs_xccs(const treex::Cut& c) {
     const char* e = getenv("JANUS_XCD_REMOTE");
     return e && e[0] == '1' ? 0 : c.xccs;
 }
 
-template <int NT>
-janus_status launch_cs_fwd(const CsPlan& p, const treex::CsFwd& a, hipStream_t st) {
+template <int NT, bool PIECES>
+janus_status launch_cs_fwd(int blocks, size_t lds, const treex::CsFwd& a, hipStream_t st) {
     static size_t attr = 0;
-    return tpersist::tree_persistent_launch(treex::childsum_fwd_xcd<NT>, cs_blocks(p.cut, p.fwd_nu), p.fwd_lds, a, st,
-                                            attr, treex::kThreads);
+    return tpersist::tree_persistent_launch(treex::childsum_fwd_xcd<NT, PIECES>, blocks, lds, a, st, attr,
+                                            treex::kThreads);
+}
+template <int NT>
+janus_status launch_cs_fwd(const CsPlan& p, int blocks, const treex::CsFwd& a, hipStream_t st) {
+    return p.cut.split ? launch_cs_fwd<NT, true>(blocks, p.fwd_lds, a, st)
+                       : launch_cs_fwd<NT, false>(blocks, p.fwd_lds, a, st);
+}
+template <bool PIECES>
+janus_status launch_cs_bwd(int blocks, size_t lds, const treex::CsBwd& a, hipStream_t st) {
+    static size_t attr = 0;
+    return tpersist::tree_persistent_launch(treex::childsum_bwd_xcd<PIECES>, blocks, lds, a, st, attr, treex::kThreads);
 }
 
 janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s, const CsWs& w, const CsPlan& p,
@@ -297,22 +307,21 @@ janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
                              hipStream_t st) {
     const int32_t N = s.N;
     const size_t nb = sizeof(int32_t) * N;
-    const UploadPiece pieces[] = {{w.pword, p.word.data(), nb},
-                                  {w.pcoff, p.coff.data(), nb + sizeof(int32_t)},
-                                  {w.pkids, p.kids.data(), sizeof(int32_t) * p.kids.size()},
-                                  {w.rootk, p.rootk.data(), nb},
+    const UploadPiece pieces[] = {{w.pword, p.word, nb},
+                                  {w.pcoff, p.coff, nb + sizeof(int32_t)},
+                                  {w.pkids, p.kids, sizeof(int32_t) * p.nkids},
+                                  {w.rootk, p.rootk, nb},
                                   {w.xgroup, p.cut.group.data(), sizeof(treex::Group) * p.cut.group.size()},
-                                  {w.xtile, p.cut.tile.data(), sizeof(treex::Tile) * p.cut.tile.size()}};
+                                  {cs_tiles(w, p.cut), p.cut.tile.data(), sizeof(treex::Tile) * p.cut.tile.size()}};
     janus_status e = upload_pieces(pieces, 6, st);
     if (e != JANUS_OK) return e;
     treex::CsFwd a = {};
     a.E = d.E;
     a.H = d.H;
     a.M0 = s.level_offsets[1];
-    a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
     a.xccs = cs_xccs(p.cut);
-    a.tile = w.xtile;
+    a.tile = cs_tiles(w, p.cut);
     a.coff = w.pcoff;
     a.kids = w.pkids;
     a.rootk = w.rootk;
@@ -329,9 +338,12 @@ janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
     a.ld3 = w.ld3;
     a.F = w.Fp;
     a.C = w.Cp;
+    a.Gx = w.dGp;   // free until the backward
+    a.ld4 = w.ld4;
     a.h_root = static_cast<float*>(h_root);
     a.sync = w.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
+    const int parts = int(p.cut.launch.size());
+    for (int part = 0; part < parts; ++part) {
         if (part == 0) {
             TraceScope trace("tree_fwd_init", 0.0, 4.0 * double(N) * (w.ldh + 2.0 * w.ldx), st);
             hipLaunchKernelGGL(treex::fwd_init_kernel, dim3(cs_fill_blocks(int64_t(N) * (w.ldh + w.ldx))), dim3(256), 0,
@@ -342,10 +354,14 @@ janus_status cs_fwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
                                w.tsync);
         }
         JANUS_LAUNCH_CHECK();
-        a.group = w.xgroup + part * p.cut.groups;
-        TraceScope trace("childsum_fwd_persistent", 2.0 * N * 4.0 * d.H * (double(d.E) + double(d.H)) / p.cut.parts, 0.0,
-                         st);
-        e = p.NT == 1 ? launch_cs_fwd<1>(p, a, st) : p.NT == 2 ? launch_cs_fwd<2>(p, a, st) : launch_cs_fwd<3>(p, a, st);
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.xgroup + l.first;
+        a.groups = l.groups;
+        const int blocks = p.cut.blocks(l, p.fwd_nu);
+        TraceScope trace("childsum_fwd_persistent", 2.0 * N * 4.0 * d.H * (double(d.E) + double(d.H)) / parts, 0.0, st);
+        e = p.NT == 1   ? launch_cs_fwd<1>(p, blocks, a, st)
+            : p.NT == 2 ? launch_cs_fwd<2>(p, blocks, a, st)
+                        : launch_cs_fwd<3>(p, blocks, a, st);
         if (e != JANUS_OK) return e;
     }
     return JANUS_OK;
@@ -358,16 +374,15 @@ janus_status cs_bwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
     const int32_t N = s.N;
     const int H = d.H, E = d.E;
     std::vector<int32_t> seg;
-    const int nseg = embed_segments(p.word.data(), N, d.V, seg);
+    const int nseg = embed_segments(p.word, N, d.V, seg);
     janus_status e = upload(w.seg, seg.data(), seg.size() * sizeof(int32_t), st);
     if (e != JANUS_OK) return e;
     treex::CsBwd a = {};
     a.H = H;
     a.M0 = s.level_offsets[1];
-    a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
     a.xccs = cs_xccs(p.cut);
-    a.tile = w.xtile;
+    a.tile = cs_tiles(w, p.cut);
     a.coff = w.pcoff;
     a.kids = w.pkids;
     a.rootk = w.rootk;
@@ -382,9 +397,11 @@ janus_status cs_bwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
     a.ld4 = w.ld4;
     a.dG_bytes = uint32_t(int64_t(N) * w.ld4 * 4);
     a.dXW = w.dXWp;
+    a.dcx = w.dcx;
     a.sync = w.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
-        if (part == 0) {
+    const int parts = int(p.cut.launch.size());
+    for (int part = parts; part-- > 0;) {   // parents before the pieces below them
+        if (part == parts - 1) {
             TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(N) * w.ld4, st);
             hipLaunchKernelGGL(treex::cs_bwd_init_kernel, dim3(cs_fill_blocks(int64_t(N) * w.ld4)), dim3(256), 0, st, N, H,
                                w.rootk, w.dGp, w.ld4, w.tsync);
@@ -393,11 +410,12 @@ janus_status cs_bwd_xcd_call(const janus_treelstm_desc& d, const NarySchedule& s
                                w.tsync);
         }
         JANUS_LAUNCH_CHECK();
-        a.group = w.xgroup + part * p.cut.groups;
-        static size_t attr = 0;
-        TraceScope trace("childsum_bwd_persistent", 2.0 * N * 4.0 * H * double(H) / p.cut.parts, 0.0, st);
-        e = tpersist::tree_persistent_launch(treex::childsum_bwd_xcd, cs_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
-                                             treex::kThreads);
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.xgroup + l.first;
+        a.groups = l.groups;
+        const int blocks = p.cut.blocks(l, p.bwd_nu);
+        TraceScope trace("childsum_bwd_persistent", 2.0 * N * 4.0 * H * double(H) / parts, 0.0, st);
+        e = p.cut.split ? launch_cs_bwd<true>(blocks, p.bwd_lds, a, st) : launch_cs_bwd<false>(blocks, p.bwd_lds, a, st);
         if (e != JANUS_OK) return e;
     }
     TailArgs q;

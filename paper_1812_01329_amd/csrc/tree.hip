@@ -61,12 +61,11 @@ struct TreeWs {
     float* part = nullptr;
     int32_t* seg = nullptr;      // the leaves grouped by word, for the embedding gradient
     int64_t ld5 = 0;
-    // groups of trees per XCD (tree_xcd.hpp): the groups and their tiles (carved
-    // after the schedule arrays, so that one copy uploads both), the counters,
-    // and node rows padded to whole 128-byte lines
+    // groups of trees per XCD (tree_xcd.hpp): the groups, followed by their
+    // tiles (carved after the schedule arrays, so that one copy uploads both),
+    // the counters, and node rows padded to whole 128-byte lines
     tpersist::TreeSync* tsync = nullptr;
-    treex::Group* xgroup = nullptr;
-    treex::Tile* xtile = nullptr;    // [N]
+    treex::Group* xgroup = nullptr;  // the groups of every launch, then up to N tiles
     float* xl = nullptr;         // [N x ldx] leaf inputs
     float* hx = nullptr;         // [N x ldc] h of every node
     float* Gp = nullptr;         // [N x ldg] gates
@@ -79,9 +78,9 @@ struct TreeWs {
     int64_t ldg = 0, ldc = 0, ldl = 0, lda = 0, ldx = 0;
 };
 
-// room for the groups of every launch of a batch of K trees
-size_t xgroup_ints(int32_t K) {
-    return std::min(treex::kGroupInts, sizeof(treex::Group) / 4 * (size_t(K) + treex::kMaxGroups));
+// the groups of every launch and the tiles of N nodes
+treex::Group* take_cut(Carver& c, int32_t N) {
+    return reinterpret_cast<treex::Group*>(c.take<char>(treex::kGroupBytes + size_t(N) * sizeof(treex::Tile)));
 }
 
 size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, TreeWs& w) {
@@ -94,8 +93,7 @@ size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, Tre
     w.parent = c.take<int32_t>(N);
     w.rootk = c.take<int32_t>(N);
     w.rootpos = c.take<int32_t>(K);
-    w.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(xgroup_ints(K)));
-    w.xtile = c.take<treex::Tile>(N);
+    w.xgroup = take_cut(c, N);
     w.tsync = c.take<tpersist::TreeSync>(1);
     w.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));   // the leaves grouped by word
     w.A = c.take<float>(int64_t(N) * w.ld5);
@@ -124,39 +122,32 @@ size_t carve(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base, Tre
     return c.off + 256;
 }
 
-// one schedule array set per call, in level order
+// one schedule array set per call, in level order or in that of a cut
 struct TreeHost {
-    std::vector<int32_t> lword, lchild, rchild, parent, rootk, rootpos;
+    int32_t *lword, *lchild, *rchild, *parent, *rootk, *rootpos;
+    static size_t ints(int32_t N, int32_t K) { return size_t(5) * N + K; }
+    TreeHost(int32_t* store, int32_t N)
+        : lword(store), lchild(lword + N), rchild(lchild + N), parent(rchild + N), rootk(parent + N), rootpos(rootk + N) {}
 };
 
-void build_host(const janus_tree_batch* t, int32_t N, const std::vector<int32_t>& order,
-                const std::vector<int32_t>& pos, TreeHost& h) {
-    h.lword.assign(N, -1);
-    h.lchild.assign(N, -1);
-    h.rchild.assign(N, -1);
-    h.parent.assign(N, -1);
-    h.rootk.assign(N, -1);
-    h.rootpos.assign(t->num_trees, 0);
-    for (int32_t p = 0; p < N; ++p) {
-        const int32_t n = order[p];
-        if (t->left[n] < 0) {
-            h.lword[p] = t->word[n];
-        } else {
-            const int32_t pl = pos[t->left[n]], pr = pos[t->right[n]];
-            h.lchild[p] = pl;
-            h.rchild[p] = pr;
-            h.parent[pl] = 2 * p;
-            h.parent[pr] = 2 * p + 1;
-        }
+// The schedule's arrays; pos: where each of its positions goes (NULL: it stays).
+void build_host(const janus_tree_batch* t, const TreeSchedule& s, const int32_t* pos, const TreeHost& h) {
+    const int32_t N = s.N, M0 = s.level_offsets[1];
+    std::fill(h.lword, h.lword + size_t(5) * N, -1);
+    auto at = [&](int32_t n) { return pos ? pos[s.pos[n]] : s.pos[n]; };
+    for (int32_t i = 0; i < M0; ++i) h.lword[pos ? pos[i] : i] = t->word[s.level_nodes[i]];
+    for (int32_t i = M0; i < N; ++i) {
+        const int32_t n = s.level_nodes[i], p = pos ? pos[i] : i, l = at(t->left[n]), r = at(t->right[n]);
+        h.lchild[p] = l;
+        h.rchild[p] = r;
+        h.parent[l] = 2 * p;
+        h.parent[r] = 2 * p + 1;
     }
     for (int32_t k = 0; k < t->num_trees; ++k) {
-        const int32_t p = pos[t->root[k]];
+        const int32_t p = at(t->root[k]);
         h.rootk[p] = k;
         h.rootpos[k] = p;
     }
-}
-void build_host(const janus_tree_batch* t, const TreeSchedule& s, TreeHost& h) {
-    build_host(t, s.N, s.level_nodes, s.pos, h);
 }
 
 __device__ __forceinline__ float sig(float x) { return sigmoidf_(x); }
@@ -304,21 +295,21 @@ janus_status check(const janus_treelstm_desc* d) {
     return JANUS_OK;
 }
 
-// `keep`: receives the host arrays (the backward groups the leaves by word
-// from them)
+// `words`: receives the leaves' words (the backward groups the leaves by them)
 janus_status upload_tree(const janus_tree_batch* t, const TreeSchedule& s, const TreeWs& w, hipStream_t st,
-                         TreeHost* keep = nullptr) {
-    TreeHost local;
-    TreeHost& h = keep ? *keep : local;
-    build_host(t, s, h);
+                         std::vector<int32_t>* words = nullptr) {
+    std::vector<int32_t> store(TreeHost::ints(s.N, t->num_trees));
+    const TreeHost h(store.data(), s.N);
+    build_host(t, s, nullptr, h);
+    if (words) words->assign(h.lword, h.lword + s.level_offsets[1]);
     const size_t nb = sizeof(int32_t) * s.N;
     // The error flag is zeroed too, so the device report of a call on this
     // path reads no stale one.
     const std::vector<char> zero_sync(tpersist::kTreeSyncCounters, 0);
-    const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},   {w.lchild, h.lchild.data(), nb},
-                                  {w.rchild, h.rchild.data(), nb}, {w.parent, h.parent.data(), nb},
-                                  {w.rootk, h.rootk.data(), nb},
-                                  {w.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
+    const UploadPiece pieces[] = {{w.lword, h.lword, nb},   {w.lchild, h.lchild, nb},
+                                  {w.rchild, h.rchild, nb}, {w.parent, h.parent, nb},
+                                  {w.rootk, h.rootk, nb},
+                                  {w.rootpos, h.rootpos, sizeof(int32_t) * t->num_trees},
                                   {w.tsync, zero_sync.data(), zero_sync.size()}};
     return upload_pieces(pieces, 7, st);
 }
@@ -344,15 +335,14 @@ bool tree_env(const char* name, char v) {
     return e && e[0] == v;
 }
 
-// The tree of every node (a child belongs to its parent's).
-std::vector<int32_t> tree_of_nodes(const janus_tree_batch* t, const TreeSchedule& s) {
-    std::vector<int32_t> tree(s.N, 0);
-    for (int32_t k = 0; k < t->num_trees; ++k) tree[t->root[k]] = k;
-    for (int32_t i = s.N; i-- > 0;) {
+bool cut_trees(const janus_tree_batch* t, const TreeSchedule& s, const treex::CutShape& shape, treex::Cut& c) {
+    c.take(s.N, TreeHost::ints(s.N, t->num_trees));
+    std::fill(c.parent, c.parent + s.N, -1);
+    for (int32_t i = s.level_offsets[1]; i < s.N; ++i) {
         const int32_t n = s.level_nodes[i];
-        if (t->left[n] >= 0) tree[t->left[n]] = tree[t->right[n]] = tree[n];
+        c.parent[s.pos[t->left[n]]] = c.parent[s.pos[t->right[n]]] = i;
     }
-    return tree;
+    return treex::cut_batch(s.N, s.level_offsets, s.num_levels, shape, c);
 }
 
 // The binary TreeLSTM in groups of trees per XCD: row tiles of the forward
@@ -391,66 +381,79 @@ TreeXcdPlan tree_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* 
     p.bwd_nu = (d.H + bu - 1) / bu;
     const int capacity = treex::node_capacity(
         dev.lds, [&](int n) { return std::max(tree_xcd_fwd_lds(p.NT, n), tree_xcd_bwd_lds(p.MT, n)); });
-    p.on = treex::cut_batch(t->num_trees, s.N, s.level_nodes, s.level_offsets, s.num_levels, tree_of_nodes(t, s),
-                            std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut);
+    p.on = cut_trees(t, s, treex::cut_shape(dev, std::max(p.fwd_nu, p.bwd_nu), capacity), p.cut);
     p.fwd_lds = tree_xcd_fwd_lds(p.NT, p.cut.most_nodes);
     p.bwd_lds = tree_xcd_bwd_lds(p.MT, p.cut.most_nodes);
     return p;
 }
-// workgroups of a launch whose groups have nu members
-int tree_xcd_blocks(const treex::Cut& c, int nu) { return c.blocks / c.nu * nu; }
+treex::Tile* cut_tiles(const TreeWs& w, const treex::Cut& c) {
+    return reinterpret_cast<treex::Tile*>(w.xgroup + c.group.size());
+}
 
 // The schedule in the order of a cut, with its groups and tiles: one copy.
-janus_status upload_cut(const janus_tree_batch* t, int32_t N, const TreeWs& w, const treex::Cut& c, hipStream_t st) {
-    TreeHost h;
-    build_host(t, N, c.order, c.pos, h);
-    const size_t nb = sizeof(int32_t) * N;
-    const UploadPiece pieces[] = {{w.lword, h.lword.data(), nb},
-                                  {w.lchild, h.lchild.data(), nb},
-                                  {w.rchild, h.rchild.data(), nb},
-                                  {w.parent, h.parent.data(), nb},
-                                  {w.rootk, h.rootk.data(), nb},
-                                  {w.rootpos, h.rootpos.data(), sizeof(int32_t) * t->num_trees},
+janus_status upload_cut(const janus_tree_batch* t, const TreeSchedule& s, const TreeWs& w, const treex::Cut& c,
+                        hipStream_t st) {
+    const TreeHost h(c.more, s.N);
+    build_host(t, s, c.pos, h);
+    if (c.split)
+        for (int32_t i = 0; i < s.N; ++i)
+            if (c.piece[i]) h.rootk[c.pos[i]] = treex::kPieceRoot;
+    const size_t nb = sizeof(int32_t) * s.N;
+    const UploadPiece pieces[] = {{w.lword, h.lword, nb},
+                                  {w.lchild, h.lchild, nb},
+                                  {w.rchild, h.rchild, nb},
+                                  {w.parent, h.parent, nb},
+                                  {w.rootk, h.rootk, nb},
+                                  {w.rootpos, h.rootpos, sizeof(int32_t) * t->num_trees},
                                   {w.xgroup, c.group.data(), sizeof(treex::Group) * c.group.size()},
-                                  {w.xtile, c.tile.data(), sizeof(treex::Tile) * c.tile.size()}};
+                                  {cut_tiles(w, c), c.tile.data(), sizeof(treex::Tile) * c.tile.size()}};
     return upload_pieces(pieces, 8, st);
 }
 // The leaves grouped by word, in the order of a cut.
-int leaf_segments(const janus_tree_batch* t, int32_t M0, int32_t V, const treex::Cut& c, std::vector<int32_t>& seg) {
-    std::vector<int32_t> word(M0);
-    for (int32_t i = 0; i < M0; ++i) word[i] = t->word[c.order[i]];
-    return embed_segments(word.data(), M0, V, seg);
+int leaf_segments(const janus_tree_batch* t, const TreeSchedule& s, int32_t V, const treex::Cut& c,
+                  std::vector<int32_t>& seg) {
+    const int32_t M0 = s.level_offsets[1];
+    int32_t* word = c.more;
+    for (int32_t i = 0; i < M0; ++i) word[i] = t->word[s.level_nodes[c.order[i]]];
+    return embed_segments(word, M0, V, seg);
 }
 
 unsigned fill_blocks(int64_t n) { return unsigned(std::min<int64_t>((n + 1023) / 1024, 1024)); }
 
-template <int NT>
-janus_status launch_tree_fwd(const TreeXcdPlan& p, const treex::LstmFwd& a, hipStream_t st) {
+template <int NT, bool PIECES>
+janus_status launch_tree_fwd(int blocks, size_t lds, const treex::LstmFwd& a, hipStream_t st) {
     static size_t attr = 0;
-    return tree_persistent_launch(treex::treelstm_fwd_xcd<NT>, tree_xcd_blocks(p.cut, p.fwd_nu), p.fwd_lds, a, st, attr,
-                                  treex::kThreads);
+    return tree_persistent_launch(treex::treelstm_fwd_xcd<NT, PIECES>, blocks, lds, a, st, attr, treex::kThreads);
+}
+template <int NT>
+janus_status launch_tree_fwd(const TreeXcdPlan& p, int blocks, const treex::LstmFwd& a, hipStream_t st) {
+    return p.cut.split ? launch_tree_fwd<NT, true>(blocks, p.fwd_lds, a, st)
+                       : launch_tree_fwd<NT, false>(blocks, p.fwd_lds, a, st);
+}
+template <int MT, bool PIECES>
+janus_status launch_tree_bwd(int blocks, size_t lds, const treex::LstmBwd& a, hipStream_t st) {
+    static size_t attr = 0;
+    return tree_persistent_launch(treex::treelstm_bwd_xcd<MT, PIECES>, blocks, lds, a, st, attr, treex::kThreads);
 }
 template <int MT>
-janus_status launch_tree_bwd(const TreeXcdPlan& p, const treex::LstmBwd& a, hipStream_t st) {
-    static size_t attr = 0;
-    return tree_persistent_launch(treex::treelstm_bwd_xcd<MT>, tree_xcd_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
-                                  treex::kThreads);
+janus_status launch_tree_bwd(const TreeXcdPlan& p, int blocks, const treex::LstmBwd& a, hipStream_t st) {
+    return p.cut.split ? launch_tree_bwd<MT, true>(blocks, p.bwd_lds, a, st)
+                       : launch_tree_bwd<MT, false>(blocks, p.bwd_lds, a, st);
 }
 
 janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
                                    const TreeWs& w, const TreeXcdPlan& p, const void* emb, const void* W, const void* U,
                                    const void* b, void* h_root, hipStream_t st) {
-    janus_status e = upload_cut(t, s.N, w, p.cut, st);
+    janus_status e = upload_cut(t, s, w, p.cut, st);
     if (e != JANUS_OK) return e;
     const int M0 = s.level_offsets[1];
     treex::LstmFwd a = {};
     a.E = d.E;
     a.H = d.H;
     a.M0 = M0;
-    a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
     a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
-    a.tile = w.xtile;
+    a.tile = cut_tiles(w, p.cut);
     a.lchild = w.lchild;
     a.rchild = w.rchild;
     a.parent = w.parent;
@@ -472,7 +475,8 @@ janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
     a.ldl = w.ldl;
     a.h_root = static_cast<float*>(h_root);
     a.sync = w.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
+    const int parts = int(p.cut.launch.size());
+    for (int part = 0; part < parts; ++part) {
         if (part == 0) {
             TraceScope trace("tree_fwd_init", 0.0, 4.0 * (double(s.N) * w.ldc + 2.0 * M0 * w.ldx), st);
             hipLaunchKernelGGL(treex::fwd_init_kernel, dim3(fill_blocks(int64_t(s.N) * w.ldc + int64_t(M0) * w.ldx)),
@@ -483,13 +487,16 @@ janus_status treelstm_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
                                w.tsync);
         }
         JANUS_LAUNCH_CHECK();
-        a.group = w.xgroup + part * p.cut.groups;
-        const double flops = 2.0 * 5.0 * d.H * (double(M0) * d.E + double(s.N - M0) * 2.0 * d.H) / p.cut.parts;
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.xgroup + l.first;
+        a.groups = l.groups;
+        const int blocks = p.cut.blocks(l, p.fwd_nu);
+        const double flops = 2.0 * 5.0 * d.H * (double(M0) * d.E + double(s.N - M0) * 2.0 * d.H) / parts;
         TraceScope trace("treelstm_fwd_persistent", flops, 0.0, st);
-        e = p.NT == 1   ? launch_tree_fwd<1>(p, a, st)
-            : p.NT == 2 ? launch_tree_fwd<2>(p, a, st)
-            : p.NT == 3 ? launch_tree_fwd<3>(p, a, st)
-                        : launch_tree_fwd<4>(p, a, st);
+        e = p.NT == 1   ? launch_tree_fwd<1>(p, blocks, a, st)
+            : p.NT == 2 ? launch_tree_fwd<2>(p, blocks, a, st)
+            : p.NT == 3 ? launch_tree_fwd<3>(p, blocks, a, st)
+                        : launch_tree_fwd<4>(p, blocks, a, st);
         if (e != JANUS_OK) return e;
     }
     return JANUS_OK;
@@ -502,10 +509,9 @@ janus_status treelstm_bwd_xcd_levels(const janus_treelstm_desc& d, const TreeSch
     treex::LstmBwd a = {};
     a.H = d.H;
     a.M0 = M0;
-    a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
     a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
-    a.tile = w.xtile;
+    a.tile = cut_tiles(w, p.cut);
     a.lchild = w.lchild;
     a.rchild = w.rchild;
     a.rootk = w.rootk;
@@ -515,21 +521,27 @@ janus_status treelstm_bwd_xcd_levels(const janus_treelstm_desc& d, const TreeSch
     a.C = w.Cp;
     a.ldc = w.ldc;
     a.dh_root = static_cast<const float*>(dh_root);
+    a.dhx = w.dh;
+    a.dcx = w.dc;
     a.dA = w.dAp;
     a.lda = w.lda;
     a.dA_bytes = uint32_t(int64_t(s.N) * w.lda * 4);
     a.sync = w.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
-        const int64_t rows = part == 0 ? s.N - M0 : 0;
+    const int parts = int(p.cut.launch.size());
+    for (int part = parts; part-- > 0;) {   // parents before the pieces below them
+        const int64_t rows = part == parts - 1 ? s.N - M0 : 0;
         {
             TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(rows) * w.lda, st);
             hipLaunchKernelGGL(treex::fill_kernel, dim3(fill_blocks(rows * w.lda + 4096)), dim3(256), 0, st, w.dAp, w.lda,
                                int64_t(M0), rows, 5 * d.H, w.tsync);
             JANUS_LAUNCH_CHECK();
         }
-        a.group = w.xgroup + part * p.cut.groups;
-        TraceScope trace("treelstm_bwd_persistent", 2.0 * 5.0 * d.H * double(s.N - M0) * 2.0 * d.H / p.cut.parts, 0.0, st);
-        const janus_status e = p.MT == 1 ? launch_tree_bwd<1>(p, a, st) : launch_tree_bwd<2>(p, a, st);
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.xgroup + l.first;
+        a.groups = l.groups;
+        const int blocks = p.cut.blocks(l, p.bwd_nu);
+        TraceScope trace("treelstm_bwd_persistent", 2.0 * 5.0 * d.H * double(s.N - M0) * 2.0 * d.H / parts, 0.0, st);
+        const janus_status e = p.MT == 1 ? launch_tree_bwd<1>(p, blocks, a, st) : launch_tree_bwd<2>(p, blocks, a, st);
         if (e != JANUS_OK) return e;
     }
     return JANUS_OK;
@@ -543,7 +555,7 @@ janus_status treelstm_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
                                    const void* dh_root, float* demb, float* dW, float* dU, float* db, hipStream_t st) {
     const int M0 = s.level_offsets[1], Nint = s.N - M0, H = d.H, E = d.E;
     std::vector<int32_t> seg;
-    const int nseg = leaf_segments(t, M0, d.V, p.cut, seg);
+    const int nseg = leaf_segments(t, s, d.V, p.cut, seg);
     janus_status e;
     if ((e = upload(w.seg, seg.data(), seg.size() * sizeof(int32_t), st)) != JANUS_OK) return e;
     if ((e = treelstm_bwd_xcd_levels(d, s, w, p, U, dh_root, st)) != JANUS_OK) return e;
@@ -615,7 +627,7 @@ janus_status treelstm_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tre
 // db = column sums of da over the internal nodes, and the leaves' dh is the
 // gradient of their word vectors.
 struct TreeRnnWs {
-    TreeWs s;                    // schedule arrays (lword .. rootpos, xgroup, xtile, tsync, seg) only
+    TreeWs s;                    // schedule arrays (lword .. rootpos, xgroup, tsync, seg) only
     float* A = nullptr;          // [N x H] pre-activations (forward), da (backward)
     float* Hn = nullptr;         // [N x H] h of every node
     float* HLR = nullptr;        // [N - M0 x 2H] children's h of internal nodes
@@ -640,8 +652,7 @@ size_t carve_rnn(const janus_treelstm_desc& d, int32_t N, int32_t K, void* base,
     w.s.parent = c.take<int32_t>(N);
     w.s.rootk = c.take<int32_t>(N);
     w.s.rootpos = c.take<int32_t>(K);
-    w.s.xgroup = reinterpret_cast<treex::Group*>(c.take<int32_t>(xgroup_ints(K)));
-    w.s.xtile = c.take<treex::Tile>(N);
+    w.s.xgroup = take_cut(c, N);
     w.s.tsync = c.take<tpersist::TreeSync>(1);
     w.s.seg = c.take<int32_t>(int64_t(embed_seg_ints(N)));
     w.A = c.take<float>(int64_t(N) * H);
@@ -761,8 +772,8 @@ extern "C" janus_status janus_treelstm_bwd(const janus_treelstm_desc* d, const j
     hipStream_t st = static_cast<hipStream_t>(stream);
     const TreeXcdPlan xp = tree_xcd_plan(*d, t, s);
     if (xp.on) return treelstm_bwd_xcd_call(*d, t, s, w, xp, W, U, dh_root, demb, dW, dU, db, st);
-    TreeHost host;
-    if ((e = upload_tree(t, s, w, st, &host)) != JANUS_OK) return e;
+    std::vector<int32_t> words;
+    if ((e = upload_tree(t, s, w, st, &words)) != JANUS_OK) return e;
     const int H = d->H, E = d->E, N = s.N;
     const int64_t kh = int64_t(t->num_trees) * H;
     {
@@ -816,7 +827,7 @@ extern "C" janus_status janus_treelstm_bwd(const janus_treelstm_desc* d, const j
     e = simt_gemm<false, kSimtStore>("tree_dx_gemm", M0, E, 5 * H, w.A, w.ld5, nullptr, static_cast<const float*>(W), E,
                                      nullptr, nullptr, w.dxl, E, st);
     if (e != JANUS_OK) return e;
-    return embed_backward(JANUS_F32, w.dxl, host.lword.data(), M0, E, demb, d->V, w.seg, st);
+    return embed_backward(JANUS_F32, w.dxl, words.data(), M0, E, demb, d->V, w.seg, st);
 }
 
 extern "C" janus_status janus_treelstm_device_report(const janus_treelstm_desc* d, const janus_tree_batch* t,
@@ -859,8 +870,7 @@ RnnXcdPlan rnn_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* t,
     p.fwd_nu = (d.H + treex::kRnnU - 1) / treex::kRnnU;
     p.bwd_nu = (d.H + 8 * p.MT - 1) / (8 * p.MT);
     const int capacity = treex::node_capacity(dev.lds, [&](int n) { return rnn_bwd_lds(p.MT, n); });
-    p.on = treex::cut_batch(t->num_trees, s.N, s.level_nodes, s.level_offsets, s.num_levels, tree_of_nodes(t, s),
-                            std::max(p.fwd_nu, p.bwd_nu), capacity, p.cut);
+    p.on = cut_trees(t, s, treex::cut_shape(dev, std::max(p.fwd_nu, p.bwd_nu), capacity, false), p.cut);
     p.bwd_lds = rnn_bwd_lds(p.MT, p.cut.most_nodes);
     return p;
 }
@@ -868,16 +878,15 @@ RnnXcdPlan rnn_xcd_plan(const janus_treelstm_desc& d, const janus_tree_batch* t,
 janus_status treernn_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree_batch* t, const TreeSchedule& s,
                                   const TreeRnnWs& w, const RnnXcdPlan& p, const void* emb, const void* W,
                                   const void* b, void* h_root, hipStream_t st) {
-    janus_status e = upload_cut(t, s.N, w.s, p.cut, st);
+    janus_status e = upload_cut(t, s, w.s, p.cut, st);
     if (e != JANUS_OK) return e;
     const int M0 = s.level_offsets[1];
     treex::RnnFwd a = {};
     a.H = d.H;
     a.M0 = M0;
-    a.groups = p.cut.groups;
     a.nu = p.fwd_nu;
     a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
-    a.tile = w.s.xtile;
+    a.tile = cut_tiles(w.s, p.cut);
     a.lchild = w.s.lchild;
     a.rchild = w.s.rchild;
     a.rootk = w.s.rootk;
@@ -888,7 +897,8 @@ janus_status treernn_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
     a.hx_bytes = uint32_t(int64_t(s.N) * w.ldh * 4);
     a.h_root = static_cast<float*>(h_root);
     a.sync = w.s.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
+    const int parts = int(p.cut.launch.size());
+    for (int part = 0; part < parts; ++part) {
         if (part == 0) {
             TraceScope trace("tree_fwd_init", 0.0, 4.0 * double(s.N + M0) * w.ldh, st);
             hipLaunchKernelGGL(treex::rnn_fwd_init_kernel, dim3(fill_blocks(int64_t(s.N) * w.ldh)), dim3(256), 0, st,
@@ -899,21 +909,27 @@ janus_status treernn_fwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
                                w.s.tsync);
         }
         JANUS_LAUNCH_CHECK();
-        a.group = w.s.xgroup + part * p.cut.groups;
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.s.xgroup + l.first;
+        a.groups = l.groups;
         static size_t attr = 0;
-        TraceScope trace("treernn_fwd_persistent", 2.0 * d.H * 2.0 * d.H * double(s.N - M0) / p.cut.parts, 0.0, st);
-        e = tree_persistent_launch(treex::treernn_fwd_xcd, tree_xcd_blocks(p.cut, p.fwd_nu), treex::kRnnFwdLds, a, st,
-                                   attr, treex::kThreads);
+        TraceScope trace("treernn_fwd_persistent", 2.0 * d.H * 2.0 * d.H * double(s.N - M0) / parts, 0.0, st);
+        e = tree_persistent_launch(treex::treernn_fwd_xcd, p.cut.blocks(l, p.fwd_nu), treex::kRnnFwdLds, a, st, attr,
+                                   treex::kThreads);
         if (e != JANUS_OK) return e;
     }
     return JANUS_OK;
 }
 
-template <int MT>
-janus_status launch_rnn_bwd(const RnnXcdPlan& p, const treex::RnnBwd& a, hipStream_t st) {
+template <int MT, bool PIECES>
+janus_status launch_rnn_bwd(int blocks, size_t lds, const treex::RnnBwd& a, hipStream_t st) {
     static size_t attr = 0;
-    return tree_persistent_launch(treex::treernn_bwd_xcd<MT>, tree_xcd_blocks(p.cut, p.bwd_nu), p.bwd_lds, a, st, attr,
-                                  treex::kThreads);
+    return tree_persistent_launch(treex::treernn_bwd_xcd<MT, PIECES>, blocks, lds, a, st, attr, treex::kThreads);
+}
+template <int MT>
+janus_status launch_rnn_bwd(const RnnXcdPlan& p, int blocks, const treex::RnnBwd& a, hipStream_t st) {
+    return p.cut.split ? launch_rnn_bwd<MT, true>(blocks, p.bwd_lds, a, st)
+                       : launch_rnn_bwd<MT, false>(blocks, p.bwd_lds, a, st);
 }
 
 // The schedule is the forward's (the workspace is unchanged between the calls).
@@ -922,16 +938,15 @@ janus_status treernn_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
                                   float* demb, float* dW, float* db, hipStream_t st) {
     const int M0 = s.level_offsets[1], Nint = s.N - M0, H = d.H;
     std::vector<int32_t> seg;
-    const int nseg = leaf_segments(t, M0, d.V, p.cut, seg);
+    const int nseg = leaf_segments(t, s, d.V, p.cut, seg);
     janus_status e = upload(w.s.seg, seg.data(), seg.size() * sizeof(int32_t), st);
     if (e != JANUS_OK) return e;
     treex::RnnBwd a = {};
     a.H = H;
     a.M0 = M0;
-    a.groups = p.cut.groups;
     a.nu = p.bwd_nu;
     a.xccs = tree_env("JANUS_XCD_REMOTE", '1') ? 0 : p.cut.xccs;
-    a.tile = w.s.xtile;
+    a.tile = cut_tiles(w.s, p.cut);
     a.lchild = w.s.lchild;
     a.rchild = w.s.rchild;
     a.rootk = w.s.rootk;
@@ -939,12 +954,14 @@ janus_status treernn_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
     a.hx = w.hx;
     a.ldh = w.ldh;
     a.dh_root = static_cast<const float*>(dh_root);
+    a.dhx = w.dh;
     a.dA = w.dAp;
     a.dA_bytes = uint32_t(int64_t(s.N) * w.ldh * 4);
     a.dx = w.dx;
     a.sync = w.s.tsync;
-    for (int part = 0; part < p.cut.parts; ++part) {
-        if (part == 0) {
+    const int parts = int(p.cut.launch.size());
+    for (int part = parts; part-- > 0;) {   // parents before the pieces below them
+        if (part == parts - 1) {
             TraceScope trace("tree_bwd_init", 0.0, 4.0 * double(Nint) * w.ldh, st);
             hipLaunchKernelGGL(treex::rnn_bwd_init_kernel, dim3(fill_blocks(int64_t(Nint) * w.ldh + 4096)), dim3(256), 0,
                                st, s.N, M0, H, w.s.rootpos, t->num_trees, a.dh_root, w.dAp, w.ldh, w.dx, w.s.tsync);
@@ -953,9 +970,12 @@ janus_status treernn_bwd_xcd_call(const janus_treelstm_desc& d, const janus_tree
                                w.s.tsync);
         }
         JANUS_LAUNCH_CHECK();
-        a.group = w.s.xgroup + part * p.cut.groups;
-        TraceScope trace("treernn_bwd_persistent", 2.0 * H * 2.0 * H * double(Nint) / p.cut.parts, 0.0, st);
-        e = p.MT == 1 ? launch_rnn_bwd<1>(p, a, st) : launch_rnn_bwd<2>(p, a, st);
+        const treex::CutLaunch& l = p.cut.launch[part];
+        a.group = w.s.xgroup + l.first;
+        a.groups = l.groups;
+        const int blocks = p.cut.blocks(l, p.bwd_nu);
+        TraceScope trace("treernn_bwd_persistent", 2.0 * H * 2.0 * H * double(Nint) / parts, 0.0, st);
+        e = p.MT == 1 ? launch_rnn_bwd<1>(p, blocks, a, st) : launch_rnn_bwd<2>(p, blocks, a, st);
         if (e != JANUS_OK) return e;
     }
     // dW = dA_int^T [h_L; h_R], the children's rows gathered; db; demb
@@ -1054,8 +1074,8 @@ extern "C" janus_status janus_treernn_bwd(const janus_treernn_desc* d, const jan
     hipStream_t st = static_cast<hipStream_t>(stream);
     const RnnXcdPlan xp = rnn_xcd_plan(*d, t, s);
     if (xp.on) return treernn_bwd_xcd_call(*d, t, s, w, xp, W, dh_root, demb, dW, db, st);
-    TreeHost host;
-    if ((e = upload_tree(t, s, w.s, st, &host)) != JANUS_OK) return e;
+    std::vector<int32_t> words;
+    if ((e = upload_tree(t, s, w.s, st, &words)) != JANUS_OK) return e;
     const int H = d->H, N = s.N;
     const int64_t kh = int64_t(t->num_trees) * H;
     {
@@ -1088,7 +1108,7 @@ extern "C" janus_status janus_treernn_bwd(const janus_treernn_desc* d, const jan
         return e;
     }
     // the leaves' dh is the gradient of their word vectors
-    return embed_backward(JANUS_F32, w.dh, host.lword.data(), M0, H, demb, d->V, w.s.seg, st);
+    return embed_backward(JANUS_F32, w.dh, words.data(), M0, H, demb, d->V, w.s.seg, st);
 }
 
 extern "C" janus_status janus_treernn_device_report(const janus_treernn_desc* d, const janus_tree_batch* t,

@@ -17,17 +17,25 @@
 // from its children or parent (c, dc, dh of the owned units) stays in the LDS
 // of the workgroup that owns the unit.
 //
+// A tree that is larger than a group may be, or so large that the other XCDs
+// would wait for it, runs in pieces (tree_cut.hpp): subtrees in one launch, what
+// is above them in the next, the backward in the opposite order.  At the cuts a
+// node's values go through memory (`PIECES`): c, and G of the Child-Sum, up; dh
+// and dc down.  Step of one tree, whole (level by level where it fits no
+// group), and in pieces, against the kernels with a device-wide barrier:
+// TreeLSTM H 150, 600 leaves 531 and 249 against 435 us, 1200 leaves 778 and
+// 333 against 567; TreeRNN H 300, 1200 leaves 635 and 215 against 401;
+// Child-Sum H 150, 1200 nodes 677 and 289 against 506.
+//
 // Measured, forward and backward levels of the binary TreeLSTM against the
 // kernels with a device-wide barrier per level: 25 trees of 5-50 leaves, H
 // 150: 61 and 58 us against 116 and about 120; 100 trees, H 300, against one
 // launch per level: 282 and 252 us against 950 and 720.
 #pragma once
 
-#include <algorithm>
-#include <vector>
-
 #include "lstm_xcd.hpp"
 #include "tree_common.hpp"
+#include "tree_cut.hpp"
 
 namespace janus {
 namespace treex {
@@ -41,20 +49,8 @@ using xcd::not_empty;
 
 constexpr int kThreads = xcd::kThreads;
 constexpr int kWaves = xcd::kWaves;
-constexpr int kRows = 16;        // nodes of a tile
+constexpr int kPieceRoot = -2;   // in place of a root's tree index: the parent runs in another launch
 
-// One group's part of the launch: nodes by position (leaves first, then the
-// internal nodes; both contiguous per group), its tiles in order.  The tiles
-// [t0, t1) start with the `leaf_tiles` tiles of leaves.  A batch of a few large
-// trees in several launches leaves groups without trees (t0 == t1).
-struct Group {
-    int leaf0, nleaf, int0, nint;
-    int t0, t1, leaf_tiles, pad;
-};
-// A tile: first position and (rows | level << 8).
-struct Tile {
-    int p0, rows_level;
-};
 __device__ __forceinline__ int tile_rows(Tile t) { return t.rows_level & 0xff; }
 __device__ __forceinline__ int tile_level(Tile t) { return t.rows_level >> 8; }
 // The tiles of a group, read 64 at a time into one register of the wave, so
@@ -83,6 +79,11 @@ struct TileWindow {
         return r;
     }
 };
+// Whether a position is one of the group's nodes (in a launch of pieces of
+// trees a child or parent may have run, or run later, in another one).
+__device__ __forceinline__ bool inside(const Group& g, int M0, int p) {
+    return p < M0 ? unsigned(p - g.leaf0) < unsigned(g.nleaf) : unsigned(p - g.int0) < unsigned(g.nint);
+}
 // index of a position among its group's nodes
 __device__ __forceinline__ int local_of(const Group& g, int M0, int p) {
     return p < M0 ? p - g.leaf0 : g.nleaf + p - g.int0;
@@ -194,7 +195,7 @@ struct LstmFwdCfg {
     static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
 };
 
-template <int NT>
+template <int NT, bool PIECES>
 __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
     using C = LstmFwdCfg<NT>;
     constexpr int U = C::U, J = C::J;
@@ -280,6 +281,12 @@ __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
         f32x4_t acc[NT];
 #pragma unroll
         for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // c of children that an earlier launch worked
+        float xl = 0.f, xr = 0.f;
+        if (PIECES && cell && !leaf) {
+            if (!inside(gr, a.M0, k.lc)) xl = a.C[int64_t(k.lc) * a.ldc + cj];
+            if (!inside(gr, a.M0, k.rc)) xr = a.C[int64_t(k.rc) * a.ldc + cj];
+        }
         uint4 f[J];
         if (leaf) {
             const auto rs = make_rsrc(a.x, a.x_bytes);
@@ -315,7 +322,11 @@ __global__ __launch_bounds__(kThreads) void treelstm_fwd_xcd(LstmFwd a) {
             const float gi = sigmoidf_(z[0]), gl = sigmoidf_(z[1]), gr_ = sigmoidf_(z[2]), go = sigmoidf_(z[3]);
             const float gu = tanhf_(z[4]);
             float c = gi * gu;
-            if (!leaf) c += gl * cl[local_of(gr, a.M0, k.lc) * U + cu] + gr_ * cl[local_of(gr, a.M0, k.rc) * U + cu];
+            if (!leaf) {
+                if (!PIECES || inside(gr, a.M0, k.lc)) xl = cl[local_of(gr, a.M0, k.lc) * U + cu];
+                if (!PIECES || inside(gr, a.M0, k.rc)) xr = cl[local_of(gr, a.M0, k.rc) * U + cu];
+                c += gl * xl + gr_ * xr;
+            }
             const float h = go * tanhf_(c);
             // published for the tiles above
             if (k.par >= 0)
@@ -350,6 +361,8 @@ struct LstmBwd {
     const float* C;
     int64_t ldc;
     const float* dh_root;
+    float* dhx;                // [N x H] dh and dc of the roots of pieces, from the parents' launch
+    float* dcx;
     float* dA;                 // [N x lda] gate-major; internal rows are the exchange
     int64_t lda;
     uint32_t dA_bytes;
@@ -367,7 +380,7 @@ struct LstmBwdCfg {
     static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + 2 * size_t(nodes) * U); }
 };
 
-template <int MT>
+template <int MT, bool PIECES>
 __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
     using C = LstmBwdCfg<MT>;
     constexpr int U = C::U, J = C::J;
@@ -406,7 +419,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
     struct In {
         int p, lc, rc, rk;
         int ch;                          // child of this thread's element of [dh_L; dh_R]
-        float g[5], c, cl, cr, dhr;
+        float g[5], c, cl, cr, dhr, dcr;
     } in;
     TileWindow win;
     win.init(a.tile, gr.t1, max(gr.t1 - 64, gr.t0));
@@ -429,6 +442,11 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
         x.cl = a.C[int64_t(x.lc >= 0 ? x.lc : p) * a.ldc + j];
         x.cr = a.C[int64_t(x.rc >= 0 ? x.rc : p) * a.ldc + j];
         x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+        x.dcr = 0.f;
+        if (PIECES && x.rk == kPieceRoot) {
+            x.dhr = a.dhx[int64_t(p) * H + j];
+            x.dcr = a.dcx[int64_t(p) * H + j];
+        }
     };
     // cell backward of a tile: dA published (internal) or stored (leaves),
     // the children's dc into LDS
@@ -436,7 +454,7 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
         if (x.p < 0) return;
         const int lo = local_of(gr, a.M0, x.p) * U + cu;
         const bool leaf = x.p < a.M0;
-        const float dh = x.rk >= 0 ? x.dhr : dhl[lo], dc = x.rk >= 0 ? 0.f : dcl[lo];
+        const float dh = x.rk != -1 ? x.dhr : dhl[lo], dc = x.rk != -1 ? x.dcr : dcl[lo];
         const float gi = x.g[0], gl = x.g[1], gr_ = x.g[2], go = x.g[3], gu = x.g[4];
         const float tau = tanhf_(x.c);
         const float d_o = dh * tau;
@@ -453,8 +471,10 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
         for (int q = 0; q < 5; ++q)
             xcd::store_b32(rs, o + uint32_t(q) * uint32_t(H) * 4u, not_empty(__float_as_uint(da[q])));
         if (!leaf) {
-            dcl[local_of(gr, a.M0, x.lc) * U + cu] = dct * gl;
-            dcl[local_of(gr, a.M0, x.rc) * U + cu] = dct * gr_;
+            if (!PIECES || inside(gr, a.M0, x.lc)) dcl[local_of(gr, a.M0, x.lc) * U + cu] = dct * gl;
+            else a.dcx[int64_t(x.lc) * H + cj] = dct * gl;
+            if (!PIECES || inside(gr, a.M0, x.rc)) dcl[local_of(gr, a.M0, x.rc) * U + cu] = dct * gr_;
+            else a.dcx[int64_t(x.rc) * H + cj] = dct * gr_;
         }
     };
     static_assert(2 * U * 16 <= kThreads, "one element of a tile's [dh_L; dh_R] per thread: row 2 u + side, node");
@@ -494,8 +514,11 @@ __global__ __launch_bounds__(kThreads) void treelstm_bwd_xcd(LstmBwd a) {
         __syncthreads();
         {
             const int r = tid >> 4, n = tid & 15;
-            if (r < 2 * U && n < rows && v0 + (r >> 1) < H)
-                dhl[local_of(gr, a.M0, in.ch) * U + (r >> 1)] = sum_waves<MT>(red, r, n);
+            if (r < 2 * U && n < rows && v0 + (r >> 1) < H) {
+                const float v = sum_waves<MT>(red, r, n);
+                if (!PIECES || inside(gr, a.M0, in.ch)) dhl[local_of(gr, a.M0, in.ch) * U + (r >> 1)] = v;
+                else a.dhx[int64_t(in.ch) * H + v0 + (r >> 1)] = v;
+            }
         }
         __syncthreads();   // the children's dh and dc
         if (more && !same) cells(nx);
@@ -635,6 +658,7 @@ struct RnnBwd {
     const float* hx;
     int64_t ldh;
     const float* dh_root;
+    float* dhx;                // [N x H] dh of the roots of pieces, from the parents' launch
     float* dA;                 // [N x ldh], internal rows
     uint32_t dA_bytes;
     float* dx;                 // [M0 x H] gradient of the leaves' word vectors
@@ -661,7 +685,7 @@ struct RnnBwdCfg {
     static constexpr int RED = kWaves * MT * 256;
     static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
 };
-template <int MT>
+template <int MT, bool PIECES>
 __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
     using C = RnnBwdCfg<MT>;
     constexpr int U = C::U, J = C::J;
@@ -710,10 +734,11 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
         x.rk = a.rootk[q];
         x.h = a.hx[int64_t(q) * a.ldh + j];
         x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+        if (PIECES && x.rk == kPieceRoot) x.dhr = a.dhx[int64_t(q) * H + j];
     };
     auto cells = [&](const In& x) {
         if (x.p < 0) return;
-        const float dh = x.rk >= 0 ? x.dhr : dhl[(x.p - gr.int0) * U + cu];
+        const float dh = x.rk != -1 ? x.dhr : dhl[(x.p - gr.int0) * U + cu];
         xcd::store_b32(rs, (uint32_t(x.p) * uint32_t(a.ldh) + uint32_t(cj)) * 4u,
                        not_empty(__float_as_uint(dh * (1.f - x.h * x.h))));
     };
@@ -755,7 +780,8 @@ __global__ __launch_bounds__(kThreads) void treernn_bwd_xcd(RnnBwd a) {
             if (r < 2 * U && n < rows && v0 + u < H) {
                 const float v = sum_waves<MT>(red, r, n);
                 if (in.ch < a.M0) a.dx[int64_t(in.ch) * H + v0 + u] = v;
-                else dhl[(in.ch - gr.int0) * U + u] = v;
+                else if (!PIECES || inside(gr, a.M0, in.ch)) dhl[(in.ch - gr.int0) * U + u] = v;
+                else a.dhx[int64_t(in.ch) * H + v0 + u] = v;
             }
         }
         __syncthreads();   // the children's dh
@@ -793,6 +819,8 @@ struct CsFwd {
     int64_t ld3;
     float* F;                  // [N x ldh] forget gate of each node towards its parent
     float* C;                  // [N x ldh]
+    float* Gx;                 // [N x ld4] G of the roots of pieces, [unit][gate]
+    int64_t ld4;
     float* h_root;
     TreeSync* sync;
 };
@@ -826,7 +854,7 @@ struct CsFwdCfg {
     // two sets for x W, one for G; then G and c of the group's nodes
     static size_t lds(int nodes) { return sizeof(float) * (3 * size_t(RED) + size_t(nodes) * 5 * U); }
 };
-template <int NT>
+template <int NT, bool PIECES>
 __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
     using C = CsFwdCfg<NT>;
     constexpr int U = C::U, JE = C::JE, JH = C::JH;
@@ -937,14 +965,22 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
             float ai = xw[0] + bias[0], ao = xw[1] + bias[1], au = xw[2] + bias[2], cs = 0.f;
             const float af = xw[3] + bias[3];
             each_kid(kd, a.kids, [&](int, int k) {
-                const int lo = local_of(gr, a.M0, k) * U + cu;
-                const f32x4_t gk = gl[lo];
+                f32x4_t gk;
+                float ck;
+                if (!PIECES || inside(gr, a.M0, k)) {
+                    const int lo = local_of(gr, a.M0, k) * U + cu;
+                    gk = gl[lo];
+                    ck = cl[lo];
+                } else {   // an earlier launch worked it
+                    gk = *reinterpret_cast<const f32x4_t*>(a.Gx + int64_t(k) * a.ld4 + 4 * cj);
+                    ck = a.C[int64_t(k) * a.ldh + cj];
+                }
                 ai += gk[0];
                 ao += gk[1];
                 au += gk[2];
                 const float f = sigmoidf_(af + gk[3]);
                 a.F[int64_t(k) * a.ldh + cj] = f;
-                cs += f * cl[lo];
+                cs += f * ck;
             });
             const float gi = sigmoidf_(ai), go = sigmoidf_(ao), gu = tanhf_(au);
             const float c = gi * gu + cs;
@@ -958,10 +994,14 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
             gt[2 * H] = gu;
             if (ce.rk >= 0) a.h_root[int64_t(ce.rk) * H + cj] = h;
         }
-        if (!more) break;   // the last tile holds roots: nobody needs their G
+        // the last tile holds roots: nobody needs their G, unless they are pieces'
+        if (!more && !(PIECES && gr.pieces)) break;
         const int pc = ce.p;
-        ce = fetch(t + 1);
-        mma_x(t + 1, fx);   // while h of this tile arrives
+        const bool keep = PIECES && ce.rk == kPieceRoot;
+        if (more) {
+            ce = fetch(t + 1);
+            mma_x(t + 1, fx);   // while h of this tile arrives
+        }
         if (!local) xcd::remote_barrier(a.sync, g, phase, unsigned(a.nu));
         uint4 f[JH];
         xcd::load_operand<float>(f, rh, [&](int j) {
@@ -969,7 +1009,7 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
                        ? (uint32_t(tl.p0 + lr) * uint32_t(a.ldh) + uint32_t(16 * (kh0 + j) + 4 * lq)) * 4u
                        : kOutOfRange;
         }, local, a.sync, dead);
-        kd = fetch_kids(ce);
+        if (more) kd = fetch_kids(ce);
         f32x4_t acc[NT];
 #pragma unroll
         for (int i = 0; i < NT; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -982,7 +1022,11 @@ __global__ __launch_bounds__(kThreads) void childsum_fwd_xcd(CsFwd a) {
 #pragma unroll
         for (int i = 0; i < NT; ++i) redg[(wave * NT + i) * 64 + lane] = acc[i];
         __syncthreads();
-        if (pc >= 0) gl[local_of(gr, a.M0, pc) * U + cu] = sum4(redg);
+        if (pc >= 0) {
+            const f32x4_t v = sum4(redg);
+            gl[local_of(gr, a.M0, pc) * U + cu] = v;
+            if (keep) *reinterpret_cast<f32x4_t*>(a.Gx + int64_t(pc) * a.ld4 + 4 * cj) = v;
+        }
         __syncthreads();
     }
 }
@@ -1006,6 +1050,7 @@ struct CsBwd {
     int64_t ld4;
     uint32_t dG_bytes;
     float* dXW;                // [N x ld4]
+    float* dcx;                // [N x ldh] dc of the roots of pieces, from the parents' launch
     TreeSync* sync;
 };
 // Set-up: empty rows of dG, zero for roots, counters zero.
@@ -1028,7 +1073,8 @@ struct CsBwdCfg {
     static constexpr int RED = kWaves * 256;
     static size_t lds(int nodes) { return sizeof(float) * (2 * size_t(RED) + size_t(nodes) * U); }
 };
-static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
+template <bool PIECES>
+__global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
     using C = CsBwdCfg;
     constexpr int U = C::U, J = C::J;
     extern __shared__ __align__(16) float sm[];
@@ -1063,7 +1109,7 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
     // first children, then their values
     struct Cell {
         int p, rk, c0, c1;
-        float gi, go, gu, c, dhr;
+        float gi, go, gu, c, dhr, dcr;
     };
     struct Kid2 {
         Kids q;
@@ -1083,6 +1129,7 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
         x.gu = gt[2 * H];
         x.c = a.C[int64_t(p) * a.ldh + j];
         x.dhr = x.rk >= 0 ? a.dh_root[int64_t(x.rk) * H + j] : 0.f;
+        x.dcr = PIECES && x.rk == kPieceRoot ? a.dcx[int64_t(p) * a.ldh + j] : 0.f;
         return x;
     };
     auto fetch_ids = [&](const Cell& x, Kid2& k) {
@@ -1128,7 +1175,7 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
             const int p = x.p;
             const float dh = sum_waves<1>(red, cu, cn) + x.dhr;   // a root's dG row is 0
             const float tau = tanhf_(x.c);
-            const float dc = x.rk >= 0 ? 0.f : dcl[local_of(gr, a.M0, p) * U + cu];
+            const float dc = x.rk != -1 ? x.dcr : dcl[local_of(gr, a.M0, p) * U + cu];
             const float dct = dc + dh * x.go * (1.f - tau * tau);
             const float dai = dct * x.gu * x.gi * (1.f - x.gi), dao = dh * tau * x.go * (1.f - x.go);
             const float dau = dct * x.gi * (1.f - x.gu * x.gu);
@@ -1143,7 +1190,8 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
                 xcd::store_b32(rs, o + 4u * uint32_t(H), not_empty(__float_as_uint(dao)));
                 xcd::store_b32(rs, o + 8u * uint32_t(H), not_empty(__float_as_uint(dau)));
                 xcd::store_b32(rs, o + 12u * uint32_t(H), not_empty(__float_as_uint(daf)));
-                dcl[local_of(gr, a.M0, k) * U + cu] = dct * fk;
+                if (!PIECES || inside(gr, a.M0, k)) dcl[local_of(gr, a.M0, k) * U + cu] = dct * fk;
+                else a.dcx[int64_t(k) * a.ldh + cj] = dct * fk;
             });
             float* xw = a.dXW + int64_t(p) * a.ld4 + cj;
             xw[0] = dai;
@@ -1158,22 +1206,6 @@ static __global__ __launch_bounds__(kThreads) void childsum_bwd_xcd(CsBwd a) {
 }
 
 // ------------------------------------------------------------- host side
-constexpr int kMaxGroups = 64;        // groups of one launch
-constexpr int kMaxParts = 16;         // launches of a batch at most
-constexpr size_t kGroupInts = size_t(kMaxGroups) * kMaxParts * (sizeof(Group) / 4);
-
-// Cut of a batch: its trees in parts (one launch each) of `groups` groups.
-// order lists the nodes by position: all leaves, then all internal nodes, in
-// each by (group, level, id).
-struct Cut {
-    int groups = 0, parts = 0, blocks = 0, nu = 0, xccs = 0;
-    int most_nodes = 0;                // nodes of the largest group
-    std::vector<Group> group;          // [parts * groups]
-    std::vector<Tile> tile;
-    std::vector<int32_t> order;        // position -> node
-    std::vector<int32_t> pos;          // node -> position
-};
-
 // Nodes a group may have: the most whose LDS (bytes(n)) a CU holds.
 template <class F>
 int node_capacity(size_t lds, F bytes) {
@@ -1182,99 +1214,15 @@ int node_capacity(size_t lds, F bytes) {
         if (bytes(n + step) + 1024 <= lds) n += step;
     return n;
 }
-
-// level_nodes: node ids by (level, id); level_offsets: their levels; tree[n]:
-// the tree of node n.  `capacity`: nodes a group may have (what its cells'
-// LDS holds).  False when the batch does not fit kMaxParts launches of groups
-// of nu workgroups each.
-inline bool cut_batch(int num_trees, int N, const std::vector<int32_t>& level_nodes,
-                      const std::vector<int32_t>& level_offsets, int num_levels, const std::vector<int32_t>& tree, int nu,
-                      int capacity, Cut& c) {
-    const tpersist::TreeDev dev = tpersist::tree_dev();
-    const int xccs = dev.xccs > 0 && dev.xccs <= persist::kMaxXcds ? dev.xccs : 1;
-    const int per_xcd = dev.cus / xccs;
-    if (per_xcd < nu || capacity <= 0) return false;
-    c.nu = nu;
-    c.xccs = xccs;
-    c.groups = std::min({num_trees, xccs * (per_xcd / nu), kMaxGroups});
-    c.blocks = xccs * nu * ((c.groups + xccs - 1) / xccs);
-    std::vector<int32_t> size(num_trees, 0), by(num_trees);
-    for (int n = 0; n < N; ++n) ++size[tree[n]];
-    // trees from the largest on, each to the group with the fewest nodes
-    for (int k = 0; k < num_trees; ++k) by[k] = k;
-    std::sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return size[x] != size[y] ? size[x] > size[y] : x < y; });
-    std::vector<int32_t> bin(num_trees);
-    std::vector<int64_t> load;
-    for (c.parts = int(std::max<int64_t>(1, (int64_t(N) + int64_t(capacity) * c.groups - 1) / (int64_t(capacity) * c.groups)));;
-         ++c.parts) {
-        const int bins = c.parts * c.groups;
-        if (c.parts > kMaxParts || bins > num_trees + c.groups) return false;
-        load.assign(bins, 0);
-        std::vector<std::pair<int64_t, int>> heap;   // (-load, -bin): the least loaded, lowest bin on top
-        for (int b = 0; b < bins; ++b) heap.push_back({0, -b});
-        std::make_heap(heap.begin(), heap.end());
-        for (int k : by) {
-            std::pop_heap(heap.begin(), heap.end());
-            auto& top = heap.back();
-            bin[k] = -top.second;
-            load[bin[k]] += size[k];
-            top.first = -load[bin[k]];
-            std::push_heap(heap.begin(), heap.end());
-        }
-        const int64_t most = *std::max_element(load.begin(), load.end());
-        if (most <= capacity) {
-            c.most_nodes = int(most);
-            break;
-        }
-    }
-    const int bins = c.parts * c.groups, M0 = level_offsets[1];
-    c.group.assign(bins, Group{});
-    for (int i = 0; i < N; ++i) {
-        Group& g = c.group[bin[tree[level_nodes[i]]]];
-        ++(i < M0 ? g.nleaf : g.nint);
-    }
-    int lo = 0, io = M0;
-    for (Group& g : c.group) {
-        g.leaf0 = lo;
-        g.int0 = io;
-        lo += g.nleaf;
-        io += g.nint;
-    }
-    c.order.resize(N);
-    c.pos.resize(N);
-    std::vector<int32_t> nl(bins), ni(bins);
-    for (int b = 0; b < bins; ++b) {
-        nl[b] = c.group[b].leaf0;
-        ni[b] = c.group[b].int0;
-    }
-    // internal nodes of a group by level: how many of each group per level
-    std::vector<std::vector<int32_t>> width(bins);
-    for (int L = 0; L < num_levels; ++L)
-        for (int i = level_offsets[L]; i < level_offsets[L + 1]; ++i) {
-            const int n = level_nodes[i], b = bin[tree[n]];
-            const int p = L == 0 ? nl[b]++ : ni[b]++;
-            c.order[p] = n;
-            c.pos[n] = p;
-            if (L > 0) {
-                if (int(width[b].size()) < L) width[b].resize(L, 0);
-                ++width[b][L - 1];
-            }
-        }
-    c.tile.clear();
-    for (int b = 0; b < bins; ++b) {
-        Group& g = c.group[b];
-        g.t0 = int(c.tile.size());
-        for (int p = 0; p < g.nleaf; p += kRows) c.tile.push_back({g.leaf0 + p, std::min(kRows, g.nleaf - p)});
-        g.leaf_tiles = int(c.tile.size()) - g.t0;
-        int p0 = g.int0;
-        for (int L = 1; L <= int(width[b].size()); ++L) {
-            for (int p = 0; p < width[b][L - 1]; p += kRows)
-                c.tile.push_back({p0 + p, std::min(kRows, width[b][L - 1] - p) | L << 8});
-            p0 += width[b][L - 1];
-        }
-        g.t1 = int(c.tile.size());
-    }
-    return true;
+// What the current device holds of groups of nu workgroups.
+inline CutShape cut_shape(const tpersist::TreeDev& dev, int nu, int capacity, bool leaves = true) {
+    CutShape s;
+    s.leaves = leaves;
+    s.nu = nu;
+    s.xccs = dev.xccs > 0 && dev.xccs <= persist::kMaxXcds ? dev.xccs : 1;
+    s.per_xcd = dev.cus / s.xccs;
+    s.capacity = capacity;
+    return s;
 }
 
 }  // namespace treex

@@ -128,10 +128,59 @@ def test_childsum_several_launches():
     _childsum(wl.sst_childsum(n_trees=300, E=16, H=300, V=100, min_nodes=35, max_nodes=45, seed=14), parts=5)
 
 
-def test_childsum_tree_past_the_groups_room_runs_levels():
-    """One tree of more nodes than a group's G and c rows in LDS."""
-    print("[childsum-xcd] large tree", flush=True)
-    _childsum(wl.sst_childsum(n_trees=2, E=16, H=260, V=100, sizes=[900, 20], seed=15), persistent=False)
+def test_childsum_past_the_groups_width_runs_levels():
+    print("[childsum-xcd] H 320", flush=True)
+    _childsum(wl.sst_childsum(n_trees=2, E=16, H=320, V=100, sizes=[90, 20], seed=15), persistent=False)
+
+
+# One tree that the other XCDs would wait for, and trees of more nodes than a
+# group's LDS holds, run in pieces: launches of the pieces, then of what is above.
+@pytest.mark.parametrize("H,E,sizes,parts", [(29, 24, [300], 2), (150, 16, [700, 5, 1], 2), (150, 300, [2600], 2),
+                                             (200, 40, [400, 300], 2), (300, 20, [500], 2), (384, 8, [900, 30], 2)])
+def test_treelstm_pieces(H, E, sizes, parts):
+    print(f"[tree-xcd-pieces] H={H} sizes={sizes}", flush=True)
+    _treelstm(wl.sst_treelstm(n_trees=len(sizes), E=E, H=H, V=60, sizes=sizes, seed=H), parts=parts)
+
+
+@pytest.mark.parametrize("H,sizes,parts", [(29, [400], 2), (150, [2600, 1], 2), (300, [700, 600], 2), (512, [900], 2)])
+def test_treernn_pieces(H, sizes, parts):
+    print(f"[rnn-xcd-pieces] H={H} sizes={sizes}", flush=True)
+    _treernn(wl.sst_treernn(n_trees=len(sizes), H=H, V=60, sizes=sizes, seed=H), parts=parts)
+
+
+@pytest.mark.parametrize("H,E,sizes,parts", [(29, 24, [500], 2), (128, 16, [900, 5], 2), (150, 300, [2400], 2),
+                                             (260, 16, [900, 20], 2), (319, 8, [600, 300], 2)])
+def test_childsum_pieces(H, E, sizes, parts):
+    print(f"[childsum-xcd-pieces] H={H} sizes={sizes}", flush=True)
+    _childsum(wl.sst_childsum(n_trees=len(sizes), E=E, H=H, V=60, sizes=sizes, seed=H), parts=parts)
+
+
+@pytest.mark.parametrize("shape", ["chain", "star"])
+def test_childsum_extreme_shapes_in_pieces(shape):
+    """A chain longer than a group's LDS holds (371 nodes; pieces one above the
+    other: 900 = 56 + 371 + 371 + 102), and a node of more children than that."""
+    w = wl.sst_childsum(n_trees=1, E=16, H=300, V=60, sizes=[900], chain=shape == "chain", seed=8)
+    if shape == "star":
+        t = w.trees
+        n = len(t.word)
+        t.children[:] = [i for i in range(n) if i != t.root[0]]
+        t.child_offsets[:] = [0 if i <= t.root[0] else n - 1 for i in range(n + 1)]
+    print(f"[childsum-xcd-pieces] {shape}", flush=True)
+    _childsum(w, parts=4 if shape == "chain" else 2)
+
+
+@pytest.mark.parametrize("model", ["treelstm", "treernn", "childsum"])
+def test_pieces_without_shared_l2(model, monkeypatch):
+    make, run = {"treelstm": (lambda: wl.sst_treelstm(n_trees=2, E=24, H=120, V=50, sizes=[400, 40], seed=5), _treelstm),
+                 "treernn": (lambda: wl.sst_treernn(n_trees=2, H=120, V=50, sizes=[400, 40], seed=5), _treernn),
+                 "childsum": (lambda: wl.sst_childsum(n_trees=2, E=24, H=120, V=50, sizes=[800, 40], seed=5), _childsum),
+                 }[model]
+    g0 = run(make(), parts=2)
+    monkeypatch.setenv("JANUS_XCD_REMOTE", "1")
+    print(f"[tree-xcd-pieces-remote] {model}", flush=True)
+    g1 = run(make(), parts=2)
+    for k in ("h_root", "dW", "db", "demb"):
+        assert np.array_equal(g0[k], g1[k]), k
 
 
 @pytest.mark.parametrize("H", [29, 200])
