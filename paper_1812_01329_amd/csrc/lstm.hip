@@ -380,8 +380,9 @@ bool use_xcd_fwd(const janus_lstm_desc& d) {
 bool use_xcd_bwd(const janus_lstm_desc& d) {
     if (d.dtype == JANUS_F32) return true;
     if (env_is("JANUS_XCD", '0') || getenv("JANUS_BWD_SLICES")) return false;
-    if (int64_t(d.B) * 4 * d.H * 2 >= (int64_t(2) << 20)) return false;
-    return xcd_plan(d, std::min(d.B, persist::kMaxB)).Q > 0;
+    const int rows = std::min(d.B, persist::kMaxB);
+    if (int64_t(rows) * 4 * d.H * 2 >= (int64_t(2) << 20)) return false;
+    return xcd_plan(d, rows).Q > 0;
 }
 
 __global__ void perm4_kernel(int H, int32_t* perm4) {

@@ -47,6 +47,18 @@ def test_row_groups(dtype, H, B, ragged):
     compare_lstm(g, oracle_steps.lstm_step(w), dtype)
 
 
+@pytest.mark.parametrize("H,B,groups", [(512, 513, 2 * 8 + 1), (256, 520, 2 * 8 + 1), (1024, 255, 8), (1024, 256, 0)])
+def test_backward_rule_looks_at_the_rows_of_a_launch(H, B, groups):
+    """Row groups in the backward, unless the 256 rows that a launch takes have
+    2 MB of dG a step (H 1024); the sliced kernels report other groups."""
+    w = _lstm("mse", "bf16", L=1, I=24, H=H, B=B, T=3, seed=H, P=16, scale=1.0 / np.sqrt(H))
+    print(f"[xcd-rule] H={H} B={B}", flush=True)
+    step, g = _run(w)
+    rep = _report(step)
+    assert rep["timed_out"] == 0 and (rep["bwd_groups"] == groups) == (groups > 0), rep
+    compare_lstm(g, oracle_steps.lstm_step(w), "bf16")
+
+
 @pytest.mark.parametrize("dtype,H,B", [("f32", 157, 50), ("bf16", 704, 100)])
 def test_row_groups_without_shared_l2(dtype, H, B, monkeypatch):
     """The same bits as with each group on one XCD, and none counted as local."""
@@ -101,7 +113,7 @@ def test_small_float32_on_both_sides_of_the_rule(H, B, groups, ragged):
     compare_lstm(g, oracle_steps.lstm_step(w), "f32")
 
 
-@pytest.mark.parametrize("dtype,B", [("f32", (1 << 19) + 17)])
+@pytest.mark.parametrize("dtype,B", [("f32", (1 << 19) + 17), ("bf16", (1 << 20) + 17)])
 def test_step_of_more_than_4_gib_of_gate_rows(dtype, B):
     """One step of a batch whose gate rows (B x 4H) pass 4 GiB, every row
     against the same step in float64."""
