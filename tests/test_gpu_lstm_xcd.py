@@ -44,6 +44,7 @@ def test_row_groups(dtype, H, B, ragged):
     rep = _report(step)
     print(f"[xcd] report {rep}", flush=True)
     assert rep["timed_out"] == 0 and rep["bwd_groups"] > 0
+    assert rep["bwd_local_groups"] > 0   # groups that exchanged through their XCD's L2
     compare_lstm(g, oracle_steps.lstm_step(w), dtype)
 
 
@@ -65,7 +66,8 @@ def test_row_groups_without_shared_l2(dtype, H, B, monkeypatch):
     T = 12
     w = _lstm("mse", dtype, L=1, I=24, H=H, B=B, T=T, lengths=_ragged(B, T, 3), seed=4, h0=True, P=16,
               scale=1.0 / np.sqrt(H))
-    _, g0 = _run(w)
+    step, g0 = _run(w)
+    assert _report(step)["bwd_local_groups"] > 0
     monkeypatch.setenv("JANUS_XCD_REMOTE", "1")
     print(f"[xcd-remote] {dtype} H={H} B={B}", flush=True)
     step, g1 = _run(w)
