@@ -1210,7 +1210,6 @@ janus_status fwd_layer_persistent(const janus_lstm_desc& d, const SeqSchedule& s
         a.fixed = s.fixed ? 1 : 0;
         a.nkg = int((H + xcd::Lay<T>::KG - 1) / xcd::Lay<T>::KG);
         a.active = w.act_dev;
-        a.offsets = w.off_dev;
         a.perm = perm;
         a.Wh = static_cast<const T*>(Wh);
         a.Hs = static_cast<T*>(w.Hs[l]);

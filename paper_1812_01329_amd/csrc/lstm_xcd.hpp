@@ -414,7 +414,6 @@ struct FwdArgs {
     int xccs;                  // XCDs the groups are dealt to (0: no group shares an L2)
     int steps[kMaxGroups];     // steps each group runs (length of its first row)
     const int32_t* active;
-    const int32_t* offsets;
     const int32_t* perm;
     const T* Wh;
     T* Hs;                     // may be NULL

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, Sgd
 constexpr int sgd_chunks(int n) { return (n + kSgdTable - 1) / kSgdTable; }
 
 constexpr size_t sgd_ws_bytes(int n) {
-    return ((size_t(sgd_chunks(n)) * kSgdBlocks * sizeof(double) + 255) / 256) * 256 + 256;
+    return (size_t(sgd_chunks(n)) * kSgdBlocks * sizeof(double) + 255) / 256 * 256;
 }
 
 // The allocation-free update keeps its block sums in this file-scope array

@@ -19,15 +19,10 @@ constexpr int kMaxE = 512;    // widest input row of the persistent Child-Sum
 struct TreeSync {
     unsigned error;
     unsigned pad_e[63];
-    unsigned count;
-    unsigned pad0[63];
-    unsigned xcd[16][64];
-    unsigned census[16][64];
+    unsigned census[16][64];    // workgroups that have arrived on each XCD
     unsigned group[64][64];     // arrivals of each tree group's workgroups (groups that share no L2)
 };
-constexpr size_t kTreeSyncCounters = offsetof(TreeSync, count);   // byte offset of the counters
-
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+constexpr size_t kTreeSyncCounters = offsetof(TreeSync, census);   // byte offset of the counters
 
 // ------------------------------------------------------------ host side
 struct TreeDev {

@@ -47,7 +47,7 @@ struct TailArgs {
     // embedding gradient: zeroed whole, then the rows of the words in the batch
     float* demb = nullptr;
     int64_t demb_n = 0;      // floats
-    int zero_first = 0, pieces = 0;
+    int zero_first = 0;
     // second launch
     const float* dx = nullptr;   // gradient of leaf r: row r (pitch ldx), dx_parts of them dx_stride apart
     int64_t ldx = 0, dx_stride = 0;
@@ -243,7 +243,6 @@ inline janus_status tail_run(TailArgs& a, const char* label, hipStream_t st) {
     a.reduce_n += a.cols;
     a.zero_first = items;
     items += int((a.demb_n + 4 * kTailZero - 1) / (4 * kTailZero));
-    a.pieces = items;
     {
         TraceScope trace(label, flops, 0.0, st);
         hipLaunchKernelGGL(tree_tail_kernel, dim3(unsigned(items)), dim3(F32Cfg::NT), 0, st, a);
