@@ -78,15 +78,15 @@ struct F32Operand {
     }
     __device__ __forceinline__ void load(int k0, int k1, int tid) {
         if constexpr (!T) {
-            if (k0 + F32Cfg::BK <= k1) {
+            const int n = k1 - (k0 + c4);   // k of this thread's pieces inside
+            if (n >= 4) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4_u*>(p[i] + k0 + c4);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float* q = p[i] + k0 + c4;
-                    const int n = k1 - (k0 + c4);
-                    v[i] = float4_u{n > 0 ? q[0] : 0.f, n > 1 ? q[1] : 0.f, n > 2 ? q[2] : 0.f, n > 3 ? q[3] : 0.f};
+                    v[i] = float4_u{n > 0 ? q[0] : 0.f, n > 1 ? q[1] : 0.f, n > 2 ? q[2] : 0.f, 0.f};
                 }
             }
         } else {
