@@ -566,6 +566,7 @@ constexpr int kXentSmallBlocks = 16;
 constexpr size_t kXentSmallLds = 64 * 1024;
 constexpr size_t kXentWideLds = 152 * 1024;
 constexpr int64_t kXentWideLogits = int64_t(1) << 18;
+constexpr int kXentWideV = 24;
 
 size_t xent_small_lds(const janus_xent_desc& d) {
     return sizeof(float) * (size_t(d.rows) * d.H + size_t(d.V) * d.H + size_t(d.rows) * d.V + size_t(d.rows));
@@ -573,13 +574,17 @@ size_t xent_small_lds(const janus_xent_desc& d) {
 // Past 64 KB of operands a workgroup fills a CU by itself and every one
 // repeats the staging and the logits, so there the launch is taken only while
 // those stay short: up to 2^18 products (rows V H), where it still takes two
-// thirds of the contractions' time (24.9 against 36.2 us).
+// thirds of the contractions' time (24.9 against 36.2 us), and up to 24 classes,
+// since a row's exponentials are one thread's chain (float32, H 16, against the
+// contractions: 600 rows of 24 classes 71 and 74 us, 400 rows of 32 76 and 61,
+// 200 rows of 64 73 and 46).
 bool xent_small_fits(const janus_xent_desc& d) {
     const char* e = getenv("JANUS_XENT_SMALL");
     if (e && e[0] == '0') return false;
     if (d.V > kXentSmallV) return false;
     const size_t lds = xent_small_lds(d);
-    return lds <= kXentSmallLds || (lds <= kXentWideLds && int64_t(d.rows) * d.V * d.H <= kXentWideLogits);
+    return lds <= kXentSmallLds || (lds <= kXentWideLds && d.V <= kXentWideV &&
+                                    int64_t(d.rows) * d.V * d.H <= kXentWideLogits);
 }
 
 template <typename T>

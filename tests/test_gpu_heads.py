@@ -152,11 +152,11 @@ def test_softmax_cross_entropy(dtype, V, Hd, rows, small, kind, monkeypatch):
 @pytest.mark.parametrize("dtype,V,Hd,rows,one_launch", [
     ("f32", 1, 1, 1, True), ("f32", 64, 1, 65, True), ("bf16", 2, 3, 1000, True), ("f32", 5, 300, 49, True),
     ("f32", 5, 300, 100, True), ("bf16", 5, 301, 101, True), ("f32", 5, 300, 130, False),
-    ("f32", 18, 150, 97, True), ("f32", 19, 150, 97, False)])
+    ("f32", 18, 150, 97, True), ("f32", 19, 150, 97, False), ("f32", 24, 16, 400, True), ("f32", 25, 16, 400, False)])
 @pytest.mark.parametrize("in_place", [False, True])
 def test_softmax_head_in_one_launch(dtype, V, Hd, rows, one_launch, in_place):
     """The one-launch head at the edges of its rule (operands of 64 KB and of
-    152 KB, 2^18 logit products), with one and with sixteen workgroups; dh
+    152 KB, 2^18 logit products, 24 classes), with one and with sixteen workgroups; dh
     written over h, which a launch of one workgroup serves."""
     import torch
     from paper_1812_01329_amd import janus as J
