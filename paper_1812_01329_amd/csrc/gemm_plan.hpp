@@ -84,11 +84,17 @@ inline bool nt_mid(int tiles, int ktiles, int M, int N, int& splits) {
     return true;
 }
 
-// The fast path takes every bf16 contraction with at least 16 rows and
-// columns and K of 64 and more.  Below 128 rows or columns most of a 256-wide
+// The fast path takes bf16 contractions with at least 16 rows and columns and
+// K of 64 and more.  Below 128 rows or columns most of a 256-wide
 // tile is padding, but such a contraction has few tiles and its K, when long,
 // is then split over the chip, which the general kernel's serial walk of K
-// cannot do (96 x 300 outputs over K = 15000: 3430 us there).
+// cannot do (96 x 300 outputs over K = 15000: 3430 us there).  Where B
+// alone is k-major, the rows are aligned and K is below 128, the general kernel's
+// one launch is faster than the copies of B, and of A where K is no multiple of
+// 8, if both are needed or both sides are short (softmax head of 60 rows, H 64:
+// dh over 65 classes 12 us there and 22 here, 17 rows over 80 classes 2 us less
+// there; over 128, 12 and 13; weight gradients of 256 x 16 over K = 64 1.2 us more
+// there; with unaligned rows, or A k-major too, 18 to 20 us more).
 inline NtPlan plan_nt(const GemmDesc& g) {
     NtPlan p;
     if (g.dtype != JANUS_BF16 || g.M < 16 || g.N < 16 || g.K < 64) return p;
@@ -104,6 +110,9 @@ inline NtPlan plan_nt(const GemmDesc& g) {
                     : in_place_ok(g.A, g.lda, g.a_idx, g.a_src_rows, g.a_zero_pad) ? kInPlace : kCopyRows;
     p.bmode = g.b_t ? kCopyTransposed
                     : in_place_ok(g.B, g.ldb, g.b_idx, g.b_src_rows, g.b_zero_pad) ? kInPlace : kCopyRows;
+    const int narrow = (g.M < 128) + (g.N < 128), copies = (p.amode != kInPlace) + (p.bmode != kInPlace);
+    if (g.K < 128 && !g.a_t && g.b_t && narrow + copies >= 3 && narrow > 0 && rows16(g.A, g.lda) && rows16(g.B, g.ldb))
+        return p;
     p.ldt = round_up(int64_t(g.K), 64);
     if (int64_t(kNtTile.BM) * p.ldt * 2 >= kMaxOff) return p;
     const int tiles = nt_tiles(g.M, g.N);

@@ -52,10 +52,10 @@ def test_ragged_batches_keep_the_split_contractions(I, H, B, T, rows):
     n = np.full(B, T, np.int64)
     for i in range(B * T - rows):
         n[i % B] -= 1
-    w = _lstm("mse", "bf16", L=1, I=I, H=H, B=B, T=T, lengths=[int(v) for v in n], seed=I, P=64)
+    w = _lstm("mse", "bf16", L=1, I=I, H=H, B=B, T=T, lengths=[int(v) for v in n], seed=I, P=128)
     print(f"[ragged-splits] I={I} H={H} B={B} T={T} rows={rows}", flush=True)
     J.janus_trace_begin()
     _, g = _run(w)
     labels = {r["label"] for r in J.janus_trace_end()}
-    assert not any(k.startswith(("gemm_tn", "gemm_nn")) for k in labels), labels
+    assert "gemm_nt_splitk" in labels and not any(k.startswith(("gemm_tn", "gemm_nn")) for k in labels), labels
     compare_lstm(g, oracle_steps.lstm_step(w), "bf16")
