@@ -600,7 +600,7 @@ janus_status janus_sgd_clip_update(const janus_sgd_desc* d, void* const* params,
  * code under stream capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, rule and results as janus_sgd_clip_update,
  * without ws / ws_bytes: the block sums of the norm and the control word live
- * in a fixed array of the library (one per device, 32 KB, room for
+ * in a fixed array of the library (one per device, 33 KB, room for
  * JANUS_SGD_NOALLOC_MAX_TENSORS tensors), whose device address the library
  * looks up at the first call on each device and keeps until the process
  * ends.  The call allocates nothing (no hipMalloc, no events, no tracing).

@@ -8,7 +8,8 @@
 // state changes all-or-nothing (Section 4.2.3): a non-finite norm leaves
 // every parameter as it was.
 //
-// Two launches, each bound by HBM traffic:
+// Two launches, each bound by HBM traffic (per 64 tensors; with more, a third
+// of one block forms the step between them):
 //   sgd_sumsq_kernel   block b of kSgdBlocks sums g^2 (in float64) over its
 //                      range of the concatenation of the tensors;
 //   sgd_update_kernel  forms the norm from the block sums, lr s and whether
@@ -37,6 +38,19 @@ struct SgdTable {
     void* p[kSgdTable];
 };
 
+// The tensor that holds element `at` of the concatenation (the last one that
+// starts there or before).  A block works few of a table's tensors: walking past
+// the others cost 7.5 us a launch with 64 of them.
+__device__ __forceinline__ int tensor_at(const SgdTable& t, int64_t at) {
+    int lo = 0, hi = t.n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (t.off[mid] <= at) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 // [lo, hi) of the concatenation for block b of nb
 __device__ __forceinline__ void block_range(int64_t total, int b, int nb, int64_t& lo, int64_t& hi) {
     const int64_t base = total / nb, rem = total % nb;
@@ -62,7 +76,7 @@ __global__ __launch_bounds__(kSgdThreads) void sgd_sumsq_kernel(SgdTable t, doub
     int64_t lo, hi;
     block_range(t.off[t.n], blockIdx.x, gridDim.x, lo, hi);
     double acc = 0.0;
-    for (int i = 0; i < t.n; ++i) {
+    for (int i = tensor_at(t, lo); i < t.n && t.off[i] < hi; ++i) {
         const int64_t s0 = lo > t.off[i] ? lo : t.off[i];
         const int64_t s1 = hi < t.off[i + 1] ? hi : t.off[i + 1];
         if (s0 >= s1) continue;
@@ -101,6 +115,7 @@ struct SgdStep {
     int n;
     const uint32_t* hold;
     float* stats;
+    float* ready;    // {lr s, 1 to update} formed by a launch of its own, or NULL
 };
 __device__ bool sgd_step(const SgdStep& a, bool report, float& ls) {
     __shared__ double red[kSgdThreads / 64];
@@ -127,6 +142,15 @@ __device__ bool sgd_step(const SgdStep& a, bool report, float& ls) {
     return out[1] != 0.f;
 }
 
+__global__ __launch_bounds__(kSgdThreads) void sgd_step_kernel(SgdStep a) {
+    float ls = 0.f;
+    const bool update = sgd_step(a, true, ls);
+    if (threadIdx.x == 0) {
+        a.ready[0] = ls;
+        a.ready[1] = update ? 1.f : 0.f;
+    }
+}
+
 // One vector of four parameters: p - ls g.
 template <typename T>
 __device__ __forceinline__ void sgd_apply4(T* q, float4 v, float ls) {
@@ -146,18 +170,26 @@ __device__ __forceinline__ void sgd_apply4(T* q, float4 v, float ls) {
     }
 }
 
-// Every block forms the step from the block sums itself (8 KB from the L2,
-// one launch less), then walks its range backwards: the pass over the
-// gradients just before read it forwards, so their last part is still in the
-// 256 MB cache in front of the HBM.
+// With one table of tensors every block forms the step from the block sums
+// itself (8 KB from the L2, one launch less); with more, whose block sums every
+// block of every launch would add up, a launch of one block does (256 tensors of
+// 100000, float32: 148 us a call without, 135 with it, 96 with tensor_at
+// besides).  A block then walks its range backwards: the pass over the gradients just before read it forwards, so their
+// last part is still in the 256 MB cache in front of the HBM.
 template <typename T>
 __global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, SgdStep st) {
     float ls = 0.f;
-    if (!sgd_step(st, blockIdx.x == 0, ls)) return;
+    if (st.ready) {
+        if (st.ready[1] == 0.f) return;
+        ls = st.ready[0];
+    } else if (!sgd_step(st, blockIdx.x == 0, ls)) {
+        return;
+    }
     const int tid = threadIdx.x;
     int64_t lo, hi;
     block_range(t.off[t.n], blockIdx.x, gridDim.x, lo, hi);
-    for (int i = t.n - 1; i >= 0; --i) {
+    if (lo >= hi) return;
+    for (int i = tensor_at(t, hi - 1); i >= 0 && t.off[i + 1] > lo; --i) {
         const int64_t s0 = lo > t.off[i] ? lo : t.off[i];
         const int64_t s1 = hi < t.off[i + 1] ? hi : t.off[i + 1];
         if (s0 >= s1) continue;
@@ -180,11 +212,11 @@ __global__ __launch_bounds__(kSgdThreads) void sgd_update_kernel(SgdTable t, Sgd
 
 constexpr int sgd_chunks(int n) { return (n + kSgdTable - 1) / kSgdTable; }
 
-constexpr size_t sgd_ws_bytes(int n) {
-    return (size_t(sgd_chunks(n)) * kSgdBlocks * sizeof(double) + 255) / 256 * 256;
-}
+// the block sums, then (with several tables) the step
+constexpr size_t sgd_sum_bytes(int n) { return (size_t(sgd_chunks(n)) * kSgdBlocks * sizeof(double) + 255) / 256 * 256; }
+constexpr size_t sgd_ws_bytes(int n) { return sgd_sum_bytes(n) + (sgd_chunks(n) > 1 ? 256 : 0); }
 
-// The allocation-free update keeps its block sums in this file-scope array
+// The allocation-free update keeps its block sums and the step in this file-scope array
 // (one copy per device, alive until the process ends) instead of a caller
 // workspace: room for kNoAllocMaxTensors tensors.  Every call writes all of
 // it that it reads (each block its sum), so nothing is cleared between calls.
@@ -256,7 +288,7 @@ janus_status sgd_check(const janus_sgd_desc* d, void* const* params, const float
     return JANUS_OK;
 }
 
-// The launches of the update on `ws` (the norm's block sums).  `traced`: record the
+// The launches of the update on `ws` (the norm's block sums and the step).  `traced`: record the
 // launches for janus_trace_end (which creates events, so the
 // allocation-free entry point passes false).
 janus_status sgd_run(const janus_sgd_desc* d, void* const* params, const float* const* grads, const int64_t* sizes,
@@ -271,7 +303,13 @@ janus_status sgd_run(const janus_sgd_desc* d, void* const* params, const float* 
                            partial + int64_t(c) * kSgdBlocks);
         JANUS_LAUNCH_CHECK();
     }
-    SgdStep step{d->lr, d->max_norm, partial, nc * kSgdBlocks, hold, stats};
+    SgdStep step{d->lr, d->max_norm, partial, nc * kSgdBlocks, hold, stats, nullptr};
+    if (nc > 1) {
+        step.ready = reinterpret_cast<float*>(static_cast<char*>(ws) + sgd_sum_bytes(d->n));
+        TraceScope trace(traced ? "sgd_step" : no_label, 0.0, 8.0 * nc * kSgdBlocks, st);
+        hipLaunchKernelGGL(sgd_step_kernel, dim3(1), dim3(kSgdThreads), 0, st, step);
+        JANUS_LAUNCH_CHECK();
+    }
     const size_t es = dtype_size(d->dtype);
     for (int c = 0; c < nc; ++c) {
         const SgdTable t = sgd_table(c, d->n, params, grads, sizes);
@@ -282,7 +320,6 @@ janus_status sgd_run(const janus_sgd_desc* d, void* const* params, const float* 
         else
             hipLaunchKernelGGL(sgd_update_kernel<float>, dim3(kSgdBlocks), dim3(kSgdThreads), 0, st, t, step);
         JANUS_LAUNCH_CHECK();
-        step.stats = nullptr;   // written by the first launch
     }
     return JANUS_OK;
 }

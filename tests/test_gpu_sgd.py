@@ -123,6 +123,38 @@ def test_non_finite_gradient_leaves_parameters(bad):
         assert np.array_equal(k.reshape(p.shape), p.astype(np.float64))
 
 
+@pytest.mark.parametrize("n", [64, 65, 200])
+def test_several_tables_non_finite_held_and_empty(n):
+    """The step formed once for several tables of 64 tensors: one NaN in the
+    last of them, a hold word, then an update; a run of empty tensors longer
+    than a table among them."""
+    import torch
+    from paper_1812_01329_amd import janus as J
+    shapes = [(0,) if n == 200 and 40 <= i < 140 else (1 + 37 * i % 301,) for i in range(n)]
+    params, grads = _inputs(48 + n, shapes, "f32")
+    nan = [g.copy() for g in grads]
+    nan[-1][0] = math.nan
+    new, stats = _run(params, nan, "f32", 0.1, 1.0)
+    assert math.isnan(stats[0]) and stats[1] == 0.0
+    for k, p in zip(new, params):
+        assert np.array_equal(k.reshape(p.shape), p.astype(np.float64))
+    P, G = [_dev(p, "f32") for p in params], [_dev(g, "f32") for g in grads]
+    d = J.SgdDesc(n, J.F32, 0.1, 1.0)
+    ws = torch.empty(J.sgd_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    st = torch.full((2,), -1.0, dtype=torch.float32, device="cuda")
+    hold = torch.ones(1, dtype=torch.int32, device="cuda")
+    for held in (1, 0):
+        hold.fill_(held)
+        J.janus_sgd_clip_update(d, P, G, stats=st, ws=ws, hold=hold.data_ptr())
+        if held:
+            assert _host(st)[1] == 0.0
+            for k, p in zip(P, params):
+                assert np.array_equal(_host(k), p.astype(np.float64))
+    ref, norm, s, applied = osgd.sgd_clip_update(params, grads, 0.1, 1.0)
+    assert applied and _host(st)[0] == pytest.approx(norm, rel=2e-7)
+    _check([_host(k) for k in P], ref, params, grads, "f32", 0.1, s)
+
+
 def test_repeated_calls_identical():
     P, G = _inputs(46, SHAPES, "f32", 3.0)
     a, sa = _run(P, G, "f32", 0.01, 1.0)
