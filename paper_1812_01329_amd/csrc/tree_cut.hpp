@@ -11,6 +11,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <memory>
+#include <numeric>
 #include <utility>
 #include <vector>
 
@@ -124,21 +125,26 @@ inline bool deal_units(const std::vector<int32_t>& size, int groups, int capacit
     }
 }
 
-// Whole trees; tree_size: nodes of each.
-inline bool plan_trees(int N, const int32_t* parent, const CutShape& s, CutPlan& p, std::vector<int32_t>& tree_size) {
-    // first the tree of each node, parents before children
-    for (int i = N; i-- > 0;) {
-        if (parent[i] >= 0) {
-            p.bin[i] = p.bin[parent[i]];
-        } else {
-            p.bin[i] = int32_t(tree_size.size());
-            tree_size.push_back(0);
-        }
-        ++tree_size[p.bin[i]];
+// Nodes of the subtree of each position, and an entry for the roots' missing
+// parent past the last; the roots, the first in order last.
+inline std::vector<int32_t> subtree_sizes(int N, const int32_t* parent, std::vector<int32_t>& root) {
+    std::vector<int32_t> size(size_t(N) + 1, 1);
+    for (int i = 0; i < N; ++i) {
+        if (parent[i] >= 0)
+            size[parent[i]] += size[i];
+        else
+            root.push_back(i);
     }
+    std::reverse(root.begin(), root.end());
+    return size;
+}
+
+// Whole trees of tree_size nodes: the groups of their roots.
+inline bool plan_trees(const std::vector<int32_t>& root, const std::vector<int32_t>& tree_size, const CutShape& s,
+                       CutPlan& p) {
     std::vector<int32_t> tree_bin;
-    if (!deal_units(tree_size, std::min(int(tree_size.size()), s.most_groups()), s.capacity, p, tree_bin)) return false;
-    for (int i = 0; i < N; ++i) p.bin[i] = tree_bin[p.bin[i]];
+    if (!deal_units(tree_size, std::min(int(root.size()), s.most_groups()), s.capacity, p, tree_bin)) return false;
+    for (size_t k = 0; k < root.size(); ++k) p.bin[root[k]] = tree_bin[k];
     return true;
 }
 
@@ -147,37 +153,46 @@ inline bool plan_trees(int N, const int32_t* parent, const CutShape& s, CutPlan&
 // round, whose launches find the pieces' results in memory.  The first round
 // makes pieces of a 2 G-th of the nodes, for balance; a second takes all that is
 // above them, unless a tree of that is still larger than a group.
-inline bool plan_pieces(int N, const int32_t* parent, const CutShape& s, CutPlan& p, std::vector<char>& piece) {
-    std::vector<int32_t> left, unit, unit_size, unit_bin;
-    std::fill(p.bin, p.bin + N, -1);
+// left: subtree_sizes.  One loop over all nodes finds the first round's pieces,
+// parents before children, the later rounds only visit what is left (9 trees of
+// 999 to 1399 nodes: 63 us with loops over all nodes for each round and their
+// tiles counted, 31 so).
+inline bool plan_pieces(int N, const int32_t* parent, std::vector<int32_t> left, const CutShape& s, CutPlan& p,
+                        std::vector<char>& piece) {
+    std::vector<int32_t> id(size_t(N) + 1, -1);   // unit of a node
+    std::vector<int32_t> rest, above, unit, unit_size, unit_bin, bin;
     piece.assign(N, 0);
-    for (int round = 0;; ++round) {
-        left.assign(N, 0);   // nodes left below (and with) a node that is left
-        int64_t total = 0;
-        for (int i = 0; i < N; ++i) {
-            if (p.bin[i] >= 0) continue;
-            ++total;
-            ++left[i];
-            if (parent[i] >= 0) left[parent[i]] += left[i];
+    int64_t most = std::min<int64_t>(s.capacity, std::max<int64_t>(kRows, N / (2 * s.most_groups())));
+    const auto visit = [&](int i) {
+        const int up = parent[i] < 0 ? N : parent[i];
+        id[i] = id[up];
+        if (id[up] >= 0) return;
+        if (left[i] <= most) {
+            id[i] = int32_t(bin.size() + unit.size());
+            piece[i] = up < N;
+            unit.push_back(i);
+            unit_size.push_back(left[i]);
+        } else {
+            above.push_back(i);
         }
-        if (total == 0) return true;
-        int64_t most = s.capacity;
-        if (round == 0) most = std::min<int64_t>(most, std::max<int64_t>(kRows, total / (2 * s.most_groups())));
+    };
+    for (int i = N; i-- > 0;) visit(i);
+    for (;;) {
+        if (!deal_units(unit_size, std::min(int(unit.size()), s.most_groups()), s.capacity, p, unit_bin)) return false;
+        bin.insert(bin.end(), unit_bin.begin(), unit_bin.end());
+        if (above.empty()) break;
+        rest.swap(above);
+        above.clear();
         unit.clear();
         unit_size.clear();
-        for (int i = 0; i < N; ++i)
-            if (p.bin[i] < 0 && left[i] <= most && (parent[i] < 0 || left[parent[i]] > most)) {
-                unit.push_back(i);
-                unit_size.push_back(left[i]);
-            }
-        if (!deal_units(unit_size, std::min(int(unit.size()), s.most_groups()), s.capacity, p, unit_bin)) return false;
-        for (size_t k = 0; k < unit.size(); ++k) {
-            p.bin[unit[k]] = unit_bin[k];
-            piece[unit[k]] = parent[unit[k]] >= 0;
-        }
-        for (int i = N; i-- > 0;)
-            if (p.bin[i] < 0 && parent[i] >= 0) p.bin[i] = p.bin[parent[i]];
+        most = s.capacity;
+        for (int i : rest) left[i] = 1;
+        for (size_t k = rest.size(); k-- > 0;)
+            if (parent[rest[k]] >= 0) left[parent[rest[k]]] += left[rest[k]];
+        for (int i : rest) visit(i);
     }
+    for (int i = 0; i < N; ++i) p.bin[i] = bin[id[i]];
+    return true;
 }
 
 // Calls node(i, group) for every position in order, and level(L, group, nodes)
@@ -203,9 +218,9 @@ inline void each_level(int num_levels, const std::vector<int32_t>& level_offsets
 // Nodes and tiles of each group of a plan, and what its launches take together in units
 // of a tile: each as long as its longest group, and a start worth kStart tiles.
 // (`leaves`: tiles of leaves are worked, too.)
+constexpr int kStart = 8;
 inline int64_t plan_cost(int num_levels, const std::vector<int32_t>& level_offsets, bool leaves, const CutPlan& p,
                          std::vector<Group>& group) {
-    constexpr int kStart = 8;
     group.assign(p.bins, Group{});
     each_level(num_levels, level_offsets, p, [](int, int) {}, [&](int L, int b, int rows) {
         Group& g = group[b];
@@ -226,35 +241,49 @@ inline int64_t plan_cost(int num_levels, const std::vector<int32_t>& level_offse
 // The cut of a batch (c.take and c.parent are the caller's): its trees whole, or in pieces where a tree is larger than
 // a group may be, or so large a part of the batch that the other XCDs would
 // wait for it and the pieces take less time (one tree of 1199 nodes of a
-// TreeLSTM of H 150, step: 531 us whole, 249 in pieces).  Trees up to
-// kWholeNodes nodes stay whole: their chain of levels is most of their time.
+// TreeLSTM of H 150, step: 531 us whole, 249 in pieces).  Pieces are only made
+// where the wait could hold a second start and the host's work for them, about
+// 3 ns a node, a tile of 16 taking 1.5 us and more (30 trees of 239 nodes
+// of a TreeRNN of H 64: step 270 us with pieces made and dropped, 214 without; 8 trees of 199
+// and one of 799, H 150: 192 us whole, 160 in pieces).
 // False when the batch does not fit kMaxParts launches.
-constexpr int kWholeNodes = 128;
 inline bool cut_batch(int N, const std::vector<int32_t>& level_offsets, int num_levels, const CutShape& s, Cut& c) {
     if (s.nu <= 0 || s.per_xcd < s.nu || s.xccs <= 0 || s.capacity <= 0) return false;
-    std::vector<int32_t> tree_size;
-    std::vector<Group> other;
-    CutPlan p;
-    p.bin = c.bin;
-    const bool whole = plan_trees(N, c.parent, s, p, tree_size);
+    std::vector<int32_t> root, tree_size;
+    const std::vector<int32_t> size = subtree_sizes(N, c.parent, root);
+    for (int32_t r : root) tree_size.push_back(size[r]);
     const int32_t largest = *std::max_element(tree_size.begin(), tree_size.end());
-    int64_t cost = 0;
-    if (whole) cost = plan_cost(num_levels, level_offsets, s.leaves, p, c.group);
-    c.split = false;
-    if (!whole || (largest > kWholeNodes && int64_t(largest) * s.most_groups() > N)) {
-        std::vector<int32_t> bin(N);
-        CutPlan q;
+    std::vector<int32_t> bin;
+    std::vector<Group> other;
+    CutPlan p, q;   // whole and in pieces
+    p.bin = c.bin;
+    const bool whole = plan_trees(root, tree_size, s, p);
+    // nodes whose tiles are worked, of n nodes (without leaves: of a binary tree)
+    const auto worked = [&](int64_t n) { return s.leaves ? n : n / 2; };
+    c.split = !whole;
+    int64_t cost = INT64_MAX;
+    // nodes of the longest groups above an even share
+    const int64_t above = int64_t(p.most_nodes) * int64_t(p.launch.size()) - N / s.most_groups();
+    if (!whole || worked(above) > kStart * kRows + N / 40) {
+        bin.resize(N);
         q.bin = bin.data();
-        if (plan_pieces(N, c.parent, s, q, c.piece) &&
-            (plan_cost(num_levels, level_offsets, s.leaves, q, other) < cost || !whole)) {
-            std::copy(bin.begin(), bin.end(), c.bin);
-            p = std::move(q);
-            p.bin = c.bin;
-            c.group.swap(other);
-            c.split = true;
-        } else if (!whole) {
+        if (plan_pieces(N, c.parent, size, s, q, c.piece))
+            cost = plan_cost(num_levels, level_offsets, s.leaves, q, other);
+        else if (!whole)
             return false;
-        }
+        // about what the largest tree alone takes whole, every other level with a tile that is not full
+        c.split |= cost < kStart + worked(largest) / kRows + num_levels / 2;
+    }
+    if (!c.split) {
+        for (int i = N; i-- > 0;)
+            if (c.parent[i] >= 0) c.bin[i] = c.bin[c.parent[i]];
+        c.split = cost < plan_cost(num_levels, level_offsets, s.leaves, p, c.group);
+    }
+    if (c.split) {
+        std::copy(bin.begin(), bin.end(), c.bin);
+        p = std::move(q);
+        p.bin = c.bin;
+        c.group.swap(other);
     }
     c.xccs = s.xccs;
     c.launch = std::move(p.launch);

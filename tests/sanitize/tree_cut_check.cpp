@@ -79,7 +79,48 @@ static Batch draw(int trees, int most, int kind) {
     return sorted(up);
 }
 
+// `count` trees of n leaves each, the first of `first` leaves
+Batch equal_trees(int count, int n, int first) {
+    std::vector<int32_t> up;
+    for (int k = 0; k < count; ++k) {
+        std::vector<int32_t> open;
+        for (int i = 0; i < (k == 0 ? first : n); ++i) {
+            open.push_back(int32_t(up.size()));
+            up.push_back(-1);
+        }
+        while (open.size() > 1) {
+            const int i = below(int(open.size()) - 1);
+            up[open[i]] = up[open[i + 1]] = int32_t(up.size());
+            open[i] = int32_t(up.size());
+            open.erase(open.begin() + i + 1);
+            up.push_back(-1);
+        }
+    }
+    return sorted(up);
+}
+bool cuts_trees(const Batch& b, int nu, bool leaves) {
+    CutShape s;
+    s.nu = nu;
+    s.per_xcd = 32;
+    s.xccs = 8;
+    s.leaves = leaves;
+    s.capacity = 4000;
+    Cut c;
+    c.take(b.N, 0);
+    std::copy(b.parent.begin(), b.parent.end(), c.parent);
+    NEED(cut_batch(b.N, b.level_offsets, b.levels, s, c));
+    NEED(c.split || c.piece.empty());   // none are made to be dropped
+    return c.split;
+}
+
 int main() {
+    // pieces only where one tree keeps the other groups waiting for more than they cost
+    for (bool leaves : {false, true}) {
+        NEED(!cuts_trees(equal_trees(30, 120, 120), 8, leaves));
+        NEED(!cuts_trees(equal_trees(25, 50, 50), 19, leaves));
+        NEED(cuts_trees(equal_trees(9, 100, 400), 19, leaves));
+        NEED(cuts_trees(equal_trees(1, 600, 600), 19, leaves));
+    }
     int pieces = 0;
     for (the_case = 0; the_case < 1500; ++the_case) {
         const int trees = the_case % 3 == 0 ? 1 + below(3) : 1 + below(300);
