@@ -256,6 +256,9 @@ CsPlan cs_plan(const janus_treelstm_desc& d, const janus_nary_tree_batch* t, con
     std::fill(p.cut.parent, p.cut.parent + N, -1);
     for (int32_t q = 0; q < N; ++q)
         for (int32_t e = s.pcoff[q]; e < s.pcoff[q + 1]; ++e) p.cut.parent[s.pkids[e]] = q;
+    p.cut.root.resize(t->num_trees);
+    for (int32_t q = 0; q < N; ++q)
+        if (s.rootk[q] >= 0) p.cut.root[s.rootk[q]] = q;
     if (!treex::cut_batch(N, s.level_offsets, int(s.level_offsets.size()) - 1,
                           treex::cut_shape(dev, std::max(p.fwd_nu, p.bwd_nu), capacity), p.cut))
         return p;

@@ -342,6 +342,7 @@ bool cut_trees(const janus_tree_batch* t, const TreeSchedule& s, const treex::Cu
         const int32_t n = s.level_nodes[i];
         c.parent[s.pos[t->left[n]]] = c.parent[s.pos[t->right[n]]] = i;
     }
+    for (int32_t k = 0; k < t->num_trees; ++k) c.root.push_back(s.pos[t->root[k]]);
     return treex::cut_batch(s.N, s.level_offsets, s.num_levels, shape, c);
 }
 

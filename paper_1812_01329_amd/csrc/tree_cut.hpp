@@ -55,6 +55,11 @@ struct Cut {
     int32_t* pos = nullptr;            // position in -> position out
     int32_t* bin = nullptr;            // position in -> group
     int32_t* more = nullptr;
+    // Positions in of the roots, set by the caller in the order of its trees:
+    // ties of the deal go by it.  (By height the tallest of equal trees would
+    // share a group: 25 trees of 50 leaves, TreeRNN of H 150, forward kernel 39.4
+    // us so, 42.3 by height, the mean of 12 batches.)
+    std::vector<int32_t> root;
     std::vector<CutLaunch> launch;     // in the order of the forward
     int xccs = 0;
     int most_nodes = 0;                // nodes of the largest group
@@ -125,17 +130,11 @@ inline bool deal_units(const std::vector<int32_t>& size, int groups, int capacit
     }
 }
 
-// Nodes of the subtree of each position, and an entry for the roots' missing
-// parent past the last; the roots, the first in order last.
-inline std::vector<int32_t> subtree_sizes(int N, const int32_t* parent, std::vector<int32_t>& root) {
-    std::vector<int32_t> size(size_t(N) + 1, 1);
-    for (int i = 0; i < N; ++i) {
-        if (parent[i] >= 0)
-            size[parent[i]] += size[i];
-        else
-            root.push_back(i);
-    }
-    std::reverse(root.begin(), root.end());
+// Nodes of the subtree of each position.
+inline std::vector<int32_t> subtree_sizes(int N, const int32_t* parent) {
+    std::vector<int32_t> size(N, 1);
+    for (int i = 0; i < N; ++i)
+        if (parent[i] >= 0) size[parent[i]] += size[i];
     return size;
 }
 
@@ -238,26 +237,27 @@ inline int64_t plan_cost(int num_levels, const std::vector<int32_t>& level_offse
     return cost;
 }
 
-// The cut of a batch (c.take and c.parent are the caller's): its trees whole, or in pieces where a tree is larger than
-// a group may be, or so large a part of the batch that the other XCDs would
-// wait for it and the pieces take less time (one tree of 1199 nodes of a
-// TreeLSTM of H 150, step: 531 us whole, 249 in pieces).  Pieces are only made
-// where the wait could hold a second start and the host's work for them, about
-// 3 ns a node, a tile of 16 taking 1.5 us and more (30 trees of 239 nodes
-// of a TreeRNN of H 64: step 270 us with pieces made and dropped, 214 without; 8 trees of 199
-// and one of 799, H 150: 192 us whole, 160 in pieces).
+// The cut of a batch (c.take, c.parent and c.root are the caller's): its trees
+// whole, or in pieces where a tree is larger than a group may be, or so large a
+// part of the batch that the other XCDs would wait for it and the pieces take
+// less time (one tree of 1199 nodes of a TreeLSTM of H 150, step: 531 us whole,
+// 249 in pieces).  Pieces are only made where the wait could hold a second start
+// and the host's work for them, about 3 ns a node, a tile of 16 taking 1.5 us
+// and more (30 trees of 239 nodes of a TreeRNN of H 64: step 270 us with pieces
+// made and dropped, 214 without; 8 trees of 199 and one of 799, H 150: 192 us
+// whole, 160 in pieces).
 // False when the batch does not fit kMaxParts launches.
 inline bool cut_batch(int N, const std::vector<int32_t>& level_offsets, int num_levels, const CutShape& s, Cut& c) {
     if (s.nu <= 0 || s.per_xcd < s.nu || s.xccs <= 0 || s.capacity <= 0) return false;
-    std::vector<int32_t> root, tree_size;
-    const std::vector<int32_t> size = subtree_sizes(N, c.parent, root);
-    for (int32_t r : root) tree_size.push_back(size[r]);
+    const std::vector<int32_t> size = subtree_sizes(N, c.parent);
+    std::vector<int32_t> tree_size;
+    for (int32_t r : c.root) tree_size.push_back(size[r]);
     const int32_t largest = *std::max_element(tree_size.begin(), tree_size.end());
     std::vector<int32_t> bin;
     std::vector<Group> other;
     CutPlan p, q;   // whole and in pieces
     p.bin = c.bin;
-    const bool whole = plan_trees(root, tree_size, s, p);
+    const bool whole = plan_trees(c.root, tree_size, s, p);
     // nodes whose tiles are worked, of n nodes (without leaves: of a binary tree)
     const auto worked = [&](int64_t n) { return s.leaves ? n : n / 2; };
     c.split = !whole;

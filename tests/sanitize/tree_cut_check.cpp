@@ -23,6 +23,7 @@ static int below(int n) { return int(rng() % unsigned(n)); }
 
 struct Batch {
     std::vector<int32_t> parent, level_offsets;   // by (level, id)
+    std::vector<int32_t> root;                    // by id
     int N = 0, levels = 0;
 };
 
@@ -49,7 +50,10 @@ static Batch sorted(const std::vector<int32_t>& up) {
     for (int n = 0; n < b.N; ++n) pos[n] = next[level[n]]++;
     b.parent.assign(b.N, -1);
     for (int n = 0; n < b.N; ++n)
-        if (up[n] >= 0) b.parent[pos[n]] = pos[up[n]];
+        if (up[n] >= 0)
+            b.parent[pos[n]] = pos[up[n]];
+        else
+            b.root.push_back(pos[n]);
     return b;
 }
 
@@ -98,6 +102,12 @@ Batch equal_trees(int count, int n, int first) {
     }
     return sorted(up);
 }
+std::vector<int32_t> sizes(const Batch& b) {
+    std::vector<int32_t> n(b.N, 1);
+    for (int i = 0; i < b.N; ++i)
+        if (b.parent[i] >= 0) n[b.parent[i]] += n[i];
+    return n;
+}
 bool cuts_trees(const Batch& b, int nu, bool leaves) {
     CutShape s;
     s.nu = nu;
@@ -108,8 +118,13 @@ bool cuts_trees(const Batch& b, int nu, bool leaves) {
     Cut c;
     c.take(b.N, 0);
     std::copy(b.parent.begin(), b.parent.end(), c.parent);
+    c.root = b.root;
     NEED(cut_batch(b.N, b.level_offsets, b.levels, s, c));
     NEED(c.split || c.piece.empty());   // none are made to be dropped
+    bool equal = !c.split;              // equal trees go to the groups in turn
+    for (size_t k = 1; k < b.root.size(); ++k) equal &= sizes(b)[b.root[k]] == sizes(b)[b.root[0]];
+    for (size_t k = 0; equal && k < b.root.size(); ++k)
+        NEED(c.bin[b.root[k]] == int(k) % std::min(int(b.root.size()), s.most_groups()));
     return c.split;
 }
 
@@ -134,6 +149,7 @@ int main() {
         Cut c;
         c.take(b.N, 0);
         std::copy(b.parent.begin(), b.parent.end(), c.parent);
+        c.root = b.root;
         if (!cut_batch(b.N, b.level_offsets, b.levels, s, c)) {
             NEED(b.N > s.capacity);   // a batch that fits one group is never refused
             continue;
